@@ -299,7 +299,7 @@ typedef struct fusco_segment {
  * Cumulative bytes of a descriptor list: d_cum[0] = 0, d_cum[i+1] = d_cum[i] + size of segment i
  * (d_cum has n + 1 entries).  The engine finds the segment of a stream position from this array.
  * Descriptors with an offset or size that is not a multiple of 16 are counted in *d_status and take
- * part with size 0.  n <= 2^26.  One launch, one workgroup.
+ * part with size 0.  n <= 2^26.  One launch for up to 8192 segments, two for longer lists.
  */
 int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum, int32_t *d_status, void *stream);
 

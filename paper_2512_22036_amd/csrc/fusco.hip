@@ -636,7 +636,14 @@ int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum,
 {
     if (n < 0 || n > ((int64_t)1 << 26) || !d_cum || !d_status || (n > 0 && !d_desc)) return FUSCO_ERR_INVALID_ARG;
     if (((uintptr_t)d_desc | (uintptr_t)d_cum) & 7u) return FUSCO_ERR_INVALID_ARG;
-    hipLaunchKernelGGL(segments_scan_kernel, dim3(1), dim3(kScanThreads), 0, (hipStream_t)stream, d_desc, n, d_cum, d_status);
+    hipStream_t s = (hipStream_t)stream;
+    if (n <= kScanSingleThreads * kScanItems) {
+        hipLaunchKernelGGL(segments_scan_kernel<true>, dim3(1), dim3(kScanSingleThreads), 0, s, d_desc, n, d_cum, d_status);
+    } else {
+        const dim3 chunks((unsigned)((n + kScanChunk - 1) / kScanChunk));
+        hipLaunchKernelGGL(segments_total_kernel, chunks, dim3(kScanThreads), 0, s, d_desc, n, d_cum, d_status);
+        hipLaunchKernelGGL(segments_scan_kernel<false>, chunks, dim3(kScanThreads), 0, s, d_desc, n, d_cum, d_status);
+    }
     return launch_status();
 }
 
@@ -665,8 +672,9 @@ int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segme
     a.cum = d_cum; a.n = n;
     a.src_bytes = src_bytes; a.dst_bytes = dst_bytes;
     a.slice_bytes = slice_bytes; a.slice_fill = d_slice_fill; a.status = d_status;
-    if (d_slice_fill) hipLaunchKernelGGL(segments_copy_kernel<true>, dim3((unsigned)blocks), dim3(kSegThreads), 0, s, a);
-    else hipLaunchKernelGGL(segments_copy_kernel<false>, dim3((unsigned)blocks), dim3(kSegThreads), 0, s, a);
+    const dim3 grid((unsigned)blocks);
+    if (d_slice_fill) hipLaunchKernelGGL(segments_copy_kernel<true>, grid, dim3(kSegThreads), 0, s, a);
+    else hipLaunchKernelGGL(segments_copy_kernel<false>, grid, dim3(kSegThreads), 0, s, a);
     return launch_status();
 }
 

@@ -12,47 +12,124 @@ namespace {
 // (offset, size) lists.  The active segment of a stream position is found from the cumulative
 // bytes, as in the paper's dense descriptor arrays.
 // ------------------------------------------------------------------------------------------
-constexpr int kScanThreads = 1024;
+constexpr int kScanThreads = 256;
+constexpr int kScanItems = 8;                            // descriptors per thread
+constexpr int kScanChunk = kScanThreads * kScanItems;    // descriptors per workgroup
+constexpr int kScanSingleThreads = 1024;                 // a list that one workgroup of this size covers takes one launch
 constexpr int kSegBlockBytes = 16384;   // stream bytes handled by one workgroup of the copy kernel
 constexpr int kSegThreads = 256;
-constexpr int kSegUnits = kSegBlockBytes / 16 / kSegThreads;   // 16-byte units per thread
+constexpr int kSegPieceBytes = 4096;    // stream bytes handled by one of its waves
+constexpr int kSegUnits = kSegPieceBytes / 16 / kWave;   // 16-byte units per thread
+constexpr int kSegRunBlocks = 8;        // consecutive blocks taken by one XCD
+
+// Sizes of the thread's kScanItems consecutive descriptors from index i0 on (0 beyond n, and for a descriptor whose
+// offset or size is not a multiple of 16, which is counted in bad); returns their sum.
+__device__ __forceinline__ uint64_t scan_load(const fusco_segment *desc, int64_t n, int64_t i0, uint64_t (&size)[kScanItems],
+                                              int &bad)
+{
+    uint64_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        size[q] = 0;
+        if (i0 + q >= n) continue;
+        const fusco_segment d = desc[i0 + q];
+        if ((d.offset | d.size) & 15u) ++bad;
+        else size[q] = d.size;
+        sum += size[q];
+    }
+    return sum;
+}
+
+// Cumulative bytes, first of two launches (left out when one workgroup covers the list): the bytes of every chunk of
+// kScanChunk descriptors are left at cum[end of the chunk] with bit 0 set.  All true cumulative values are
+// multiples of 16, so the second launch can tell such a chunk total from a finished entry.
+__global__ __launch_bounds__(kScanThreads) void segments_total_kernel(const fusco_segment *desc, int64_t n, uint64_t *cum,
+                                                                     int32_t *status)
+{
+    __shared__ uint64_t part[kScanThreads / kWave];
+    const int tid = threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk;
+    uint64_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        const int64_t i = c0 + q * kScanThreads + tid;
+        if (i >= n) continue;
+        const fusco_segment d = desc[i];
+        if (!((d.offset | d.size) & 15u)) sum += d.size;
+    }
+    for (int d = kWave / 2; d > 0; d >>= 1) sum += __shfl_down(sum, d, kWave);
+    if ((tid & (kWave - 1)) == 0) part[tid / kWave] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kScanThreads / kWave; ++w) sum += part[w];
+        const int64_t end = min(c0 + kScanChunk, n);
+        cum[end] = sum | 1u;
+        if (blockIdx.x == 0) *status = 0;
+    }
+}
 
 // cum[0] = 0, cum[i + 1] = cum[i] + size of segment i; a descriptor whose offset or size is not a
-// multiple of 16 is counted in *status and takes part with size 0.  One workgroup.
-__global__ __launch_bounds__(kScanThreads) void segments_scan_kernel(const fusco_segment *desc, int64_t n, uint64_t *cum,
-                                                                    int32_t *status)
+// multiple of 16 is counted in *status and takes part with size 0.  One workgroup per chunk of kScanChunk descriptors.
+// The bytes before the chunk come from the entries at the ends of the earlier chunks, each of which holds either that
+// chunk's own bytes (bit 0 set) or, once its workgroup has been there, the cumulative value; either will do, so
+// nobody waits: the workgroup takes the nearest finished entry and adds the totals between it and itself.
+// Bound by latency: one workgroup that walked the whole list took 69 us for 40000 descriptors and 385 us for 200000,
+// the two launches take 10 and 11 us.  SINGLE: one workgroup covers the list.
+template <bool SINGLE>
+__global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void segments_scan_kernel(const fusco_segment *desc,
+                                                                                                  int64_t n, uint64_t *cum,
+                                                                                                  int32_t *status)
 {
-    __shared__ uint64_t part[kScanThreads];
-    __shared__ int bad_total;
-    const int tid = threadIdx.x;
-    const int64_t per = (n + kScanThreads - 1) / kScanThreads;
-    const int64_t lo = min((int64_t)tid * per, n), hi = min(lo + per, n);
-    if (tid == 0) bad_total = 0;
-    __syncthreads();
-    uint64_t sum = 0;
+    __shared__ uint64_t part[(SINGLE ? kScanSingleThreads : kScanThreads) / kWave];
+    __shared__ unsigned long long before;
+    __shared__ int finished, bad_total;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk, i0 = c0 + (int64_t)tid * kScanItems;
+    if (tid == 0) {
+        before = 0;
+        finished = -1;
+        bad_total = 0;
+    }
+    uint64_t size[kScanItems];
     int bad = 0;
-    for (int64_t i = lo; i < hi; ++i) {
-        const fusco_segment d = desc[i];
-        if ((d.offset | d.size) & 15u) ++bad;
-        else sum += d.size;
+    const uint64_t sum = scan_load(desc, n, i0, size, bad);
+    uint64_t incl = sum;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint64_t up = __shfl_up(incl, d, kWave);
+        if (lane >= d) incl += up;
     }
-    part[tid] = sum;
-    if (bad) atomicAdd(&bad_total, bad);
+    if (lane == kWave - 1) part[wave] = incl;
     __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {   // inclusive scan of the per-thread sums
-        const uint64_t v = tid >= d ? part[tid - d] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
+    if (bad) atomicAdd(&bad_total, bad);
+    if constexpr (!SINGLE) {
+        // windows of the kScanThreads nearest earlier chunks, until a finished entry or the first chunk is in one
+        for (int64_t hi = blockIdx.x; hi > 0; hi -= kScanThreads) {
+            const int64_t j = hi - 1 - tid;   // thread 0 has the nearest chunk
+            uint64_t v = 0;
+            if (j >= 0) {
+                v = __hip_atomic_load(cum + (j + 1) * kScanChunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!(v & 1u)) atomicMax(&finished, kScanThreads - 1 - tid);
+            }
+            __syncthreads();
+            const int nearest = finished < 0 ? kScanThreads : kScanThreads - 1 - finished;
+            if (j >= 0 && tid <= nearest) atomicAdd(&before, (unsigned long long)(v & ~(uint64_t)1));
+            __syncthreads();
+            if (nearest < kScanThreads) break;
+        }
     }
-    uint64_t run = part[tid] - sum;
-    for (int64_t i = lo; i < hi; ++i) {
-        const fusco_segment d = desc[i];
-        cum[i] = run;
-        if (!((d.offset | d.size) & 15u)) run += d.size;
+    __syncthreads();
+    uint64_t run = before + incl - sum;
+    for (int w = 0; w < wave; ++w) run += part[w];
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        run += size[q];
+        if (i0 + q < n) __hip_atomic_store(cum + i0 + q + 1, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid == kScanThreads - 1) cum[n] = part[tid];
-    if (tid == 0) *status = bad_total;
+    if (blockIdx.x == 0 && tid == 0) cum[0] = 0;
+    if (tid == 0) {
+        if constexpr (SINGLE) *status = bad_total;
+        else if (bad_total) atomicAdd(status, bad_total);
+    }
 }
 
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v)
@@ -73,50 +150,106 @@ struct SegCopyArgs {
     int32_t *status;
 };
 
+// One workgroup per 16 KiB of the stream, one wave per 4 KiB of it: the wave finds the segment of its first byte by
+// probing 64 cumulative entries at a time (three dependent loads for 40000 segments, where halving takes
+// sixteen), then reads the next 64 segments' ends and offsets in one go and looks its units up in them.
+// An XCD takes runs of kSegRunBlocks neighbouring blocks: what it writes on a contiguous side are runs of 128 KiB.
+// Bound by memory once the search is short.  Measured, 287 MB in 40000 segments of 16 B to 14 KiB: pack 176 -> 106 us
+// (5.4 TB/s read and written), pack with 1 MiB slices 193 -> 124 us, unpack 178 -> 115 us.  A unit's load is issued as
+// soon as its segment is known: all four together take 119 and 125 us.  The rows are written with non-temporal
+// stores, which the L2 still merges into whole lines at the segments' ragged edges: unpack 115 us, against 124 us
+// with plain stores and 139 us with write-through ones; 8 KiB a wave 117 and 124 us, 2 KiB 117 us each.
 template <bool SLICES>
 __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs a)
 {
-    const uint64_t total = a.cum[a.n];
-    const uint64_t base = (uint64_t)blockIdx.x * kSegBlockBytes;
-    if (base >= total) return;
-    // segment of the workgroup's first byte: last i with cum[i] <= base (uniform, scalar loads)
-    int64_t lo = 0, hi = a.n;   // invariant: cum[lo] <= base < cum[hi]
-    while (hi - lo > 1) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (a.cum[mid] <= base) lo = mid;
-        else hi = mid;
+    __shared__ uint64_t s_src[kSegThreads], s_dst[kSegThreads];
+    __shared__ int s_end[kSegThreads], s_valid[kSegThreads];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    // workgroup b runs on XCD b mod 8; the blocks after the last whole round of runs are taken in order
+    constexpr uint32_t round = kXcds * kSegRunBlocks;
+    uint32_t block = blockIdx.x;
+    if (block < gridDim.x / round * round) {
+        const uint32_t in = block % round;
+        block += (in % kXcds) * kSegRunBlocks + in / kXcds - in;
     }
-    int64_t i = lo;
+    const uint64_t base = (uint64_t)block * kSegBlockBytes;
+    const uint64_t piece = base + (uint64_t)wave * kSegPieceBytes;
+    // the first probes of the search below are on their way together with the stream's size
+    int64_t lo = 0, hi = a.n, step = (a.n + kWave - 1) / kWave;
+    uint64_t probe = a.cum[min(lane * step, hi)];
+    const uint64_t total = a.cum[a.n];
+    if (base >= total) return;
+    uint64_t *src_at = s_src + wave * kWave, *dst_at = s_dst + wave * kWave;
+    int *end = s_end + wave * kWave, *valid = s_valid + wave * kWave;
     u32x4 v[kSegUnits];
-    uint64_t dst_at[kSegUnits];
+    uint64_t to[kSegUnits];
     bool ok[kSegUnits];
     int skipped = 0;
 #pragma unroll
-    for (int r = 0; r < kSegUnits; ++r) {
-        const uint64_t pos = base + ((uint64_t)r * kSegThreads + threadIdx.x) * 16;
-        ok[r] = false;
-        if (pos >= total) continue;
-        while (a.cum[i + 1] <= pos) ++i;            // i + 1 <= n because pos < cum[n]
-        const uint64_t intra = pos - a.cum[i];
-        const uint64_t so = a.src_desc ? a.src_desc[i].offset + intra : pos;
-        const uint64_t dofs = a.dst_desc ? a.dst_desc[i].offset + intra : pos;
-        // in range without any sum that could wrap: a unit fits iff its start is at most bytes - 16, and a
-        // start below `intra` means offset + intra wrapped around 2^64 (e.g. a negative offset)
-        const bool src_in = a.src_bytes >= 16 && so <= a.src_bytes - 16 && so >= intra;
-        const bool dst_in = a.dst_bytes >= 16 && dofs <= a.dst_bytes - 16 && dofs >= intra;
-        if (((so | dofs) & 15u) || !src_in || !dst_in) {
-            ++skipped;
-            continue;
+    for (int r = 0; r < kSegUnits; ++r) ok[r] = false;
+    if (piece < total) {
+        // 64 segments or fewer that hold the wave's first byte: cum[lo] <= piece < cum[hi]
+        while (hi - lo > kWave) {
+            const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lo + lane * step < hi && probe <= piece));
+            lo += (max(c, 1) - 1) * step;   // lane 0 probes cum[lo]: c >= 1 for cumulative entries that ascend
+            hi = min(lo + step, hi);
+            step = (hi - lo + kWave - 1) / kWave;
+            probe = a.cum[min(lo + lane * step, hi)];
         }
-        ok[r] = true;
-        dst_at[r] = dofs;
-        v[r] = *(const u32x4 *)(a.src + so);
+        // Windows of 64 segments [w, w + 64), the first one starting at byte `begin`; stream positions from here on
+        // are relative to the wave's piece.
+        const int bytes = (int)min((uint64_t)kSegPieceBytes, total - piece);
+        uint64_t begin = __shfl(probe, 0, kWave);
+        int first = 0;   // units below this position belong to an earlier window
+        for (int64_t w = lo;; w += kWave) {
+            const int64_t i = w + lane;
+            const uint64_t e = a.cum[min(i + 1, a.n)];
+            uint64_t b = __shfl_up(e, 1, kWave);
+            if (lane == 0) b = begin;
+            const int e_rel = e <= piece ? 0 : (int)min(e - piece, (uint64_t)kSegPieceBytes);
+            wave_lds_order();
+            end[lane] = e_rel;
+            if (i < a.n && e > piece && b < piece + bytes) {   // the wave's bytes touch this segment: its offsets are read
+                const uint64_t so = a.src_desc ? a.src_desc[i].offset : b, dofs = a.dst_desc ? a.dst_desc[i].offset : b;
+                // bytes of the segment, from its start, that lie inside both buffers; none for an offset that is
+                // misaligned or outside (nothing below can wrap: the offset is inside the buffer)
+                uint64_t room = 0;
+                if (!((so | dofs) & 15u) && a.src_bytes >= 16 && so <= a.src_bytes - 16 && a.dst_bytes >= 16 &&
+                    dofs <= a.dst_bytes - 16)
+                    room = min(min(a.src_bytes - so, a.dst_bytes - dofs) & ~(uint64_t)15, e - b);
+                const uint64_t good = b + room;
+                valid[lane] = good <= piece ? 0 : (int)min(good - piece, (uint64_t)kSegPieceBytes);
+                src_at[lane] = so - b + piece;
+                dst_at[lane] = dofs - b + piece;
+            }
+            wave_lds_order();
+            const int last = __shfl(e_rel, kWave - 1, kWave);
+#pragma unroll
+            for (int r = 0; r < kSegUnits; ++r) {
+                const int pos = (r * kWave + lane) * 16;
+                if (pos < first || pos >= last || pos >= bytes) continue;   // another window's, or beyond the stream
+                int q = 0;   // entries of `end` that are <= pos: at most 63, because pos < last
+#pragma unroll
+                for (int h = kWave / 2; h > 0; h >>= 1)
+                    if (end[q + h - 1] <= pos) q += h;
+                if (pos >= valid[q]) {
+                    ++skipped;
+                    continue;
+                }
+                ok[r] = true;
+                to[r] = dst_at[q] + (uint64_t)pos;
+                v[r] = load16_stream((const u32x4 *)(a.src + src_at[q] + (uint64_t)pos));
+            }
+            first = last;
+            begin = __shfl(e, kWave - 1, kWave);
+            if (last >= bytes || w + kWave >= a.n) break;
+        }
     }
 #pragma unroll
     for (int r = 0; r < kSegUnits; ++r) {
         if (!ok[r]) continue;
-        if constexpr (SLICES) store16_system((u32x4 *)(a.dst + dst_at[r]), v[r]);
-        else *(u32x4 *)(a.dst + dst_at[r]) = v[r];
+        if constexpr (SLICES) store16_system((u32x4 *)(a.dst + to[r]), v[r]);
+        else __builtin_nontemporal_store(v[r], (u32x4 *)(a.dst + to[r]));
     }
     if (skipped) atomicAdd(a.status, skipped);
     if constexpr (SLICES) {

@@ -193,3 +193,54 @@ def test_consumer_on_another_stream_sees_complete_slices_only(fusco, oracle):
         print("attempt %d: consumer had to wait for %d of %d slices" % (attempt, int((polls > 0).sum()), slices), flush=True)
     # over three runs the consumer was at least once ahead of the producer (it starts first): the two did overlap
     assert waited_total > 0
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 2049, 8191, 8192, 8193, 6 * 2048, 257 * 2048 + 1, 600 * 2048])
+def test_scan_and_copy_at_the_edges_of_their_windows(fusco, oracle, n):
+    """Lists around the scan's chunks of 2048 descriptors, its look-back windows of 256 chunks and the copy's windows of
+    64 segments, with runs of empty segments in them (a wave's 4 KiB of the stream then span several windows).  All
+    results are whole numbers and bytes: no tolerance."""
+    rng = np.random.default_rng(n)
+    size = rng.integers(0, 4, size=n).astype(np.int64) * 16
+    size[rng.random(n) < 0.02] = 4096 + 16
+    if n > 2000:
+        size[300:300 + 700] = 0                    # longer than ten windows of the copy
+    size[-1] = 16
+    order = rng.permutation(n)
+    off = np.zeros(n, dtype=np.int64)
+    off[order] = np.cumsum(size[order]) - size[order]
+    total = int(size.sum())
+    src = rng.integers(0, 256, size=total, dtype=np.uint8)
+    d_desc, d_src = desc_dev(off, size), dev(src)
+    cum, status = scan(fusco, d_desc)
+    assert int(status.item()) == 0
+    assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(size)]))
+    want = oracle.segments_copy(src, size, src_off=off)
+    packed = torch.full((total + 16,), 0xCD, dtype=torch.uint8, device="cuda")
+    fill = torch.zeros(((total + 16383) // 16384,), dtype=torch.int32, device="cuda")
+    for slices in (False, True):
+        packed.fill_(0xCD)
+        fusco.fusco_segments_copy(d_src, d_desc, packed, None, cum, total, status,
+                                  **(dict(slice_bytes=16384, slice_fill=fill) if slices else {}))
+        assert int(status.item()) == 0
+        assert np.array_equal(packed[:total].cpu().numpy(), want)
+        assert bool((packed[total:] == 0xCD).all())
+    assert int(fill.sum().item()) == total
+    back = torch.full((total,), 0xAB, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(packed, None, back, d_desc, cum, total, status)
+    assert int(status.item()) == 0 and torch.equal(back, d_src)
+    # scatter to scatter, the segments in another order at the destination
+    order = rng.permutation(n)
+    off2 = np.zeros(n, dtype=np.int64)
+    off2[order] = np.cumsum(size[order]) - size[order]
+    there = torch.full((total,), 0xAB, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(d_src, d_desc, there, desc_dev(off2, size), cum, total, status)
+    want2 = oracle.segments_copy(want, size, dst_off=off2, dst_bytes=total, fill_value=0xAB)
+    assert int(status.item()) == 0 and np.array_equal(there.cpu().numpy(), want2)
+    # descriptors that do not count: misaligned sizes spread over every chunk
+    bad = rng.choice(n, size=max(1, n // 50), replace=False)
+    size[bad] += 8
+    cum, status = scan(fusco, desc_dev(off, size))
+    valid = np.where(size % 16 == 0, size, 0)
+    assert int(status.item()) == len(bad)
+    assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(valid)]))
