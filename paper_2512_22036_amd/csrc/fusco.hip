@@ -111,6 +111,7 @@ static PlanArgs plan_args(const fusco_layout *L, const int32_t *d_topk_idx, void
     a.eloc_magic = ((1u << 20) + a.Eloc - 1) / a.Eloc;
     a.tpt = tokens_per_tile(L->k, rounds);
     a.n_tiles = num_tiles(L->N, L->k, rounds);
+    a.small_groups = a.n_tiles == 1 ? (L->P + kSmallPairs - 1) / kSmallPairs : 0;
     a.stride = L->E + L->D + 1;
     a.tile_hist = (int32_t *)d_scratch;   // unused (may be NULL) when the input is a single tile
     a.chunk_tiles = chunk_tiles_for(a.n_tiles, rounds);
@@ -134,13 +135,12 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
     const ArmedEvents ev;
     const dim3 block(kPlanThreads), tiles((unsigned)a.n_tiles);
     if (a.n_tiles == 1) {
-        if (rounds == 1) launch(plan_place_kernel<true, 1>, dim3(1), block, s, a, ev.start, ev.stop);
-        else launch(plan_place_kernel<true, 2>, dim3(1), block, s, a, ev.start, ev.stop);
+        launch(plan_small_kernel, dim3(1u + (unsigned)a.small_groups), dim3(kSmallThreads), s, a, ev.start, ev.stop);
     } else {
         // inputs of several tiles are always planned in tiles of two rounds (plan_rounds)
         launch(plan_count_kernel<kMaxRounds>, tiles, block, s, a, ev.start, nullptr);
         if (a.n_chunks > 0) launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks), block, s, a);
-        launch(plan_place_kernel<false, kMaxRounds>, tiles, block, s, a, nullptr, ev.stop);
+        launch(plan_place_kernel<kMaxRounds>, tiles, block, s, a, nullptr, ev.stop);
     }
     return launch_status();
 }
@@ -207,15 +207,8 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     m.C = (int32_t)(row_bytes / 16); m.Ca = (int32_t)(aux_row_bytes / 16);
     m.write_expert = 1; m.write_wire = 0;
     const ArmedEvents ev;
-    const dim3 grid((unsigned)(L->N > 0 ? L->N : 1)), block(kPlanThreads);
-    hipStream_t s = (hipStream_t)stream;
-    if (ev.start || ev.stop) {
-        if (rounds == 1) hipExtLaunchKernelGGL(plan_dispatch_kernel<1>, grid, block, 0, s, ev.start, ev.stop, 0, a, m);
-        else hipExtLaunchKernelGGL(plan_dispatch_kernel<2>, grid, block, 0, s, ev.start, ev.stop, 0, a, m);
-    } else {
-        if (rounds == 1) hipLaunchKernelGGL(plan_dispatch_kernel<1>, grid, block, 0, s, a, m);
-        else hipLaunchKernelGGL(plan_dispatch_kernel<2>, grid, block, 0, s, a, m);
-    }
+    const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N), block(kSmallThreads);
+    launch_args(plan_dispatch_kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, m);
     return launch_status();
 }
 

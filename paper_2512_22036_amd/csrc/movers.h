@@ -228,52 +228,61 @@ __global__ __launch_bounds__(256) void touch_kernel(const u32x4 *src, size_t n)
     asm volatile("" ::"v"(v));   // the value is not used: only the read matters
 }
 
-// Planner and dispatch in one launch for inputs of a single planner tile (decode-sized batches, where
-// three dependent launches cost more than the work): one workgroup per token, every workgroup works out the
-// whole plan in its own LDS (a few microseconds, all in parallel), workgroup 0 writes the descriptor
-// arrays, and each workgroup then moves its token's row to the slots it has just computed.  The row is
-// requested before the planning starts, so that its latency hides behind it.
+// Planner and dispatch in one launch for inputs of a single planner tile (decode-sized batches, where dependent
+// launches cost more than the work).  Workgroup 0 writes the counts, the next a.small_groups workgroups the
+// descriptors (plan_small_kernel's work), and one workgroup per token finds the slots of its own pairs and moves its
+// row there; none waits for another.  The row is requested before the slots are worked out, so that its latency hides
+// behind that.  Bound by the chain routing -> slots -> stores of one workgroup.  Kernel time, k = 8, 4 / 128 tokens of
+// 7392 B (two planes, D = 64) and 256 tokens of 4 KiB (D = 8): 5.0 / 6.6 / 7.3 us; 5.8 / 7.9 / 8.2 us with the
+// descriptors written by the tokens' own workgroups after their rows; 9.9 / 11.4 / 13.0 us with counters and scans over
+// the keys in every workgroup.
 constexpr int kFusedPreload = 4;   // 16-byte chunks per thread held in registers across the planning
 
-template <int R>
-__global__ __launch_bounds__(kPlanThreads) void plan_dispatch_kernel(PlanArgs a, DispatchArgs m)
+__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a, DispatchArgs m)
 {
-    __shared__ PlaceLds<R> s;
-    const int tid = threadIdx.x;
-    const int t = blockIdx.x;   // the grid has max(N, 1) workgroups
-    const int Ct = m.C + m.Ca;
-    u32x4 v[kFusedPreload];
-    if (t < a.N) {
-#pragma unroll
-        for (int i = 0; i < kFusedPreload; ++i) {
-            const int c = tid + i * kPlanThreads;
-            if (c < m.C) v[i] = load16_stream(m.x + (size_t)t * m.C + c);
-            else if (c < Ct) v[i] = load16_stream(m.x_aux + (size_t)t * m.Ca + (c - m.C));
-        }
+    __shared__ SmallLds s;
+    const int b = blockIdx.x;
+    if (b == 0) {
+        small_counts(s, a);
+        return;
     }
-    place_tile<true, R>(s, a, 0, blockIdx.x == 0);
-    __syncthreads();
-    if (t >= a.N) return;
-    const int *slots = s.tile_slot + t * a.k;
+    if (b <= a.small_groups) {
+        const int p0 = (b - 1) * kSmallPairs;
+        small_place(s, a, p0, min(kSmallPairs, a.N * a.k - p0));
+        return;
+    }
+    const int tid = threadIdx.x;
+    const int t = b - 1 - a.small_groups;
+    const int Ct = m.C + m.Ca;
+    // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
+    const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
+    u32x4 v[kFusedPreload];
+#pragma unroll
+    for (int i = 0; i < kFusedPreload; ++i) {
+        const int c = tid + i * kSmallThreads;
+        if (c < Ct) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
+    }
+    const int slots = small_slots(s, a, t * a.k, a.k);
     for (int j = 0; j < a.k; ++j) {
-        const int slot = slots[j];
+        const int slot = __builtin_amdgcn_readlane(slots, j);
         if (slot < 0) continue;
+        u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
 #pragma unroll
         for (int i = 0; i < kFusedPreload; ++i) {
-            const int c = tid + i * kPlanThreads;
-            if (c < m.C) m.expert_buf[(size_t)slot * m.C + c] = v[i];
-            else if (c < Ct) m.expert_aux[(size_t)slot * m.Ca + (c - m.C)] = v[i];
+            const int c = tid + i * kSmallThreads;
+            if (c < Ct) (c < m.C ? dst : dst_aux)[c] = v[i];
         }
     }
     // rows longer than the preloaded part
-    for (int c = tid + kFusedPreload * kPlanThreads; c < Ct; c += kPlanThreads) {
-        const u32x4 u = c < m.C ? load16_stream(m.x + (size_t)t * m.C + c)
-                                : load16_stream(m.x_aux + (size_t)t * m.Ca + (c - m.C));
+    for (int c0 = kFusedPreload * kSmallThreads; c0 < Ct; c0 += kSmallThreads) {   // uniform, for readlane
+        const int c = c0 + tid;
+        u32x4 u;
+        if (c < Ct) u = load16_stream((c < m.C ? src : src_aux) + c);
         for (int j = 0; j < a.k; ++j) {
-            const int slot = slots[j];
+            const int slot = __builtin_amdgcn_readlane(slots, j);
             if (slot < 0) continue;
-            if (c < m.C) m.expert_buf[(size_t)slot * m.C + c] = u;
-            else m.expert_aux[(size_t)slot * m.Ca + (c - m.C)] = u;
+            u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
+            if (c < Ct) (c < m.C ? dst : dst_aux)[c] = u;
         }
     }
 }

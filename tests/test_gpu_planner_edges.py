@@ -1,0 +1,87 @@
+"""The planner's kernels at the sizes where their work is split - rounds and waves of the single-tile planner, its
+workgroups of eight pairs, tiles, invalid ids and repeated experts anywhere - against the descriptors worked out by
+sorting.  All whole numbers: no tolerance."""
+import numpy as np
+import pytest
+import torch
+
+from definitions import random_topk
+
+pytestmark = pytest.mark.gpu
+
+
+def plan_by_sorting(A, E, D):
+    """Every descriptor array; entries that no valid pair assigns are None or cut off."""
+    N, k = A.shape
+    e = A.reshape(-1).astype(np.int64)
+    ok = (e >= 0) & (e < E)
+    pair = np.arange(N * k)
+    token, dev = pair // k, np.where(ok, e // (E // D), -1)
+    order = pair[ok][np.argsort(e[ok], kind="stable")]
+    slot = np.full(N * k, -1)
+    slot[order] = np.arange(len(order))
+    # one row per (device, token), devices first; first: the pair that comes first among those of a (token, device)
+    rows, first_at = np.unique(dev[ok] * N + token[ok], return_index=True)
+    row = np.full(N * k, -1)
+    row[ok] = np.searchsorted(rows, dev[ok] * N + token[ok])
+    first = np.zeros(N * k, dtype=np.uint8)
+    first[pair[ok][first_at]] = 1
+    count = np.bincount(e[ok], minlength=E)
+    sends = np.bincount(rows // N, minlength=D) if len(rows) else np.zeros(D, dtype=np.int64)
+    return dict(exp_count=count, exp_off=np.concatenate([[0], np.cumsum(count)]), send_count=sends,
+                send_off=np.concatenate([[0], np.cumsum(sends)]), pair_slot=slot, pair_send_row=row, pair_first=first,
+                slot_pair=order, slot_token=order // k, slot_send_row=row[order], send_src=rows % N,
+                status=np.array([np.count_nonzero(~ok)])), ok
+
+
+def check(L, A, tag):
+    want, ok = plan_by_sorting(A, L.E, L.D)
+    got = L.to_host()
+    for name, w in want.items():
+        assert np.array_equal(getattr(got, name)[:len(w)], w), (tag, name)
+    cap = L.tile_tokens * L.k
+    for i in range(L.tile_count):
+        s = want["pair_slot"][i * cap:(i + 1) * cap]
+        s = np.sort(s[s >= 0])
+        tile = got.tile_slots[i * cap:(i + 1) * cap]
+        assert np.array_equal(tile[:len(s)], s) and np.all(tile[len(s):] == -1), (tag, "tile", i)
+
+
+def routing(seed, N, k, E, distinct, bad):
+    rng = np.random.default_rng(seed)
+    A = random_topk(rng, N, k, E, distinct)
+    if bad:
+        flat = A.reshape(-1)
+        at = rng.choice(len(flat), size=max(1, len(flat) // 9), replace=False)
+        flat[at] = rng.choice([-1, E, np.iinfo(np.int32).max, np.iinfo(np.int32).min], size=len(at))
+        A = flat.reshape(N, k)
+    return np.ascontiguousarray(A, dtype=np.int32)
+
+
+SINGLE_TILE = [(N, k, E, D) for k, E, D in [(1, 64, 8), (3, 24, 24), (7, 1024, 64), (8, 256, 8), (33, 96, 4), (64, 1024, 1024)]
+               for N in sorted({1, 2, 64 // k, 8 * (64 // k), 8 * (64 // k) + 1, 1024 // k, 2048 // k})]
+
+
+@pytest.mark.parametrize("bad", [False, True])
+@pytest.mark.parametrize("N,k,E,D", SINGLE_TILE)
+def test_single_tile_planner(N, k, E, D, bad):
+    import paper_2512_22036_amd as f
+    distinct = (N + k) % 2 == 0 and k <= E
+    A = routing(N * 64 + k, N, k, E, distinct, bad)
+    d_A = torch.from_numpy(A).cuda()
+    L = f.Layout(N, k, E, D)
+    assert L.tile_count == 1
+    L.mem.fill_(0x7B)
+    f.fusco_plan(L, d_A)
+    check(L, A, "plan")
+    # in one launch with the dispatch: the same descriptors, and the rows on their slots and nowhere else
+    F = f.Layout(N, k, E, D)
+    F.mem.fill_(0x7B)
+    x = torch.randint(0, 256, (N, 48), dtype=torch.uint8, device="cuda")
+    rows = torch.full((N * k, 48), 0xEE, dtype=torch.uint8, device="cuda")
+    f.fusco_plan_dispatch(F, d_A, x, rows)
+    assert torch.equal(F.mem, L.mem)
+    want, ok = plan_by_sorting(A, E, D)
+    n = len(want["slot_token"])
+    assert torch.equal(rows[:n], x[torch.from_numpy(want["slot_token"]).cuda()])
+    assert bool((rows[n:] == 0xEE).all())
