@@ -130,8 +130,15 @@ def _check(rc: int, what: str) -> None:
         raise FuscoError("%s failed: %s (%d)" % (what, load_library().fusco_status_string(rc).decode(), rc))
 
 
+# handle of a device's current stream without the torch.cuda.Stream object around it (2.5 us a call, as long as a
+# launch takes); absent from builds of torch without a GPU runtime, where no call gets this far
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

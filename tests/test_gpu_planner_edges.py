@@ -85,3 +85,12 @@ def test_single_tile_planner(N, k, E, D, bad):
     n = len(want["slot_token"])
     assert torch.equal(rows[:n], x[torch.from_numpy(want["slot_token"]).cuda()])
     assert bool((rows[n:] == 0xEE).all())
+
+
+def test_calls_without_a_stream_use_the_current_one():
+    from paper_2512_22036_amd import binding
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert binding._stream(None) == side.cuda_stream
+    assert binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert binding._stream(side) == side.cuda_stream
