@@ -18,7 +18,7 @@ constexpr int kWave = 64;
 constexpr int kPlanThreads = 1024;                      // 16 waves per planner workgroup
 constexpr int kPlanWaves = kPlanThreads / kWave;
 // A planner tile holds R * 1024 (token, expert) pairs, R rounds of 64 pairs per wave: one round for inputs of
-// up to 1024 pairs, two otherwise.  (Four would not fit 64 KiB of LDS.)
+// up to 1024 pairs, two otherwise.
 constexpr int kMaxRounds = 2;
 constexpr int kRoundPairs = kPlanThreads;               // pairs of one round of the whole workgroup
 constexpr int kMaxBins = FUSCO_MAX_E;

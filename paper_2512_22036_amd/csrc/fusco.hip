@@ -112,6 +112,8 @@ static PlanArgs plan_args(const fusco_layout *L, const int32_t *d_topk_idx, void
     a.tpt = tokens_per_tile(L->k, rounds);
     a.n_tiles = num_tiles(L->N, L->k, rounds);
     a.small_groups = a.n_tiles == 1 ? (L->P + kSmallPairs - 1) / kSmallPairs : 0;
+    const int round_tokens = kPlanWaves * (kWave / L->k);
+    a.rank_rounds = (a.tpt + round_tokens - 1) / round_tokens;
     a.stride = L->E + L->D + 1;
     a.tile_hist = (int32_t *)d_scratch;   // unused (may be NULL) when the input is a single tile
     a.chunk_tiles = chunk_tiles_for(a.n_tiles, rounds);
@@ -133,14 +135,14 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
     const PlanArgs a = plan_args(L, d_topk_idx, d_scratch, rounds);
     hipStream_t s = (hipStream_t)stream;
     const ArmedEvents ev;
-    const dim3 block(kPlanThreads), tiles((unsigned)a.n_tiles);
+    const dim3 tiles((unsigned)a.n_tiles), block(kPlanThreads);
     if (a.n_tiles == 1) {
         launch(plan_small_kernel, dim3(1u + (unsigned)a.small_groups), dim3(kSmallThreads), s, a, ev.start, ev.stop);
     } else {
         // inputs of several tiles are always planned in tiles of two rounds (plan_rounds)
-        launch(plan_count_kernel<kMaxRounds>, tiles, block, s, a, ev.start, nullptr);
+        launch(plan_rank_kernel, tiles, block, s, a, ev.start, nullptr);
         if (a.n_chunks > 0) launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks), block, s, a);
-        launch(plan_place_kernel<kMaxRounds>, tiles, block, s, a, nullptr, ev.stop);
+        launch(plan_place_kernel, tiles, block, s, a, nullptr, ev.stop);
     }
     return launch_status();
 }

@@ -14,6 +14,7 @@ struct PlanArgs {
     int32_t N, k, E, D, Eloc;
     uint32_t k_magic, eloc_magic;   // ceil(2^20 / k), ceil(2^20 / Eloc): see div20
     int32_t tpt;      // tokens per tile
+    int32_t rank_rounds;   // rounds of 16 waves x (64 / k) tokens in a tile
     int32_t n_tiles;
     int32_t small_groups;   // single-tile planner: workgroups that write descriptors
     int32_t stride;   // ints per tile in tile_hist: E expert counts, D device counts, 1 invalid count
@@ -34,16 +35,23 @@ __device__ __forceinline__ int bits_for(int nb)
     return n;
 }
 
-// Lanes of this wave that take part and hold the same key as the calling lane.
+// Lanes of this wave that take part and hold the same key as the calling lane.  STEP bits are compared between two
+// branches; bits above nbits are zero in every key that takes part and change nothing.
+template <int STEP = 2>
 __device__ __forceinline__ uint64_t same_key_lanes(int key, bool part, int nbits)
 {
-    uint64_t m = __builtin_amdgcn_ballot_w64(part);
-    for (int b = 0; b < nbits; ++b) {
-        const bool bit = (key >> b) & 1;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(bit);
-        m &= bit ? bal : ~bal;
+    const uint64_t all = __builtin_amdgcn_ballot_w64(part);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+    for (int b0 = 0; b0 < nbits; b0 += STEP) {
+#pragma unroll
+        for (int b = b0; b < b0 + STEP; ++b) {
+            const uint32_t bit = (uint32_t)((int)((uint32_t)key << (31 - b)) >> 31);   // all ones where the lane's bit is set
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(bit != 0);
+            lo &= ~((uint32_t)bal ^ bit);
+            hi &= ~((uint32_t)(bal >> 32) ^ bit);
+        }
     }
-    return m;
+    return (uint64_t)hi << 32 | lo;
 }
 
 // n / d for the small operands of the planner (n < 2048 with d <= 64, or n < 1024 with d <= 1024; the
@@ -73,77 +81,98 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
     return x;
 }
 
-// For the pair at tile-local index p, held by lane `lane` of a round of 64 consecutive pairs:
-// the tile-local index of the first entry of the same token whose expert lives on the same device
-// d (p itself if this pair is that first appearance), or -1 if d < 0.  Must be called by all lanes.
-// `same` receives the lanes of the round with the same device.  tile_dev holds the device of every
-// pair of the tile, row0 is the token's first pair.  Entries of the token inside this round are
-// compared with ballots; only a token that straddles the round's start needs LDS reads.
-__device__ __forceinline__ int first_pair_on_device(const int16_t *tile_dev, int p, int lane, int row0, int d, int dbits,
-                                                    uint64_t &same)
+// Pass 1 of the multi-tile planner: per tile, the counts of pairs per expert and of first (token, device) appearances
+// per device, and for every pair its rank among the tile's pairs of the same expert and its send row's rank among the
+// tile's rows of the same device.  The ranks are left, packed, in the pair's own places of pair_slot and
+// pair_send_row, where pass 2 reads them; the second kernel then only adds what lies before the tile.
+//
+// Ranks are stable and do not depend on atomics: lanes of a wave that hold the same key are found with ballots, and a
+// wave keeps its running count of every key in a byte of LDS; the 16 waves' bytes of a key lie next to each other, so
+// that one 16-byte read and four byte sums give the pairs in earlier waves.  A wave takes whole tokens (64 / k of them
+// per round), so that a device's first appearance in a token is settled among its lanes.
+constexpr int kRankRounds = 4;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens
+
+__device__ __forceinline__ int sum_bytes(u32x4 v)
 {
-    same = same_key_lanes(d, d >= 0, dbits);
-    if (d < 0) return -1;
-    const int base = p - lane;
-    for (int q = row0; q < base; ++q)
-        if (tile_dev[q] == d) return q;
-    const int l0 = max(row0 - base, 0);
-    const uint64_t before = same & (((uint64_t)1 << lane) - 1) & ~(((uint64_t)1 << l0) - 1);
-    return before ? base + __builtin_ctzll(before) : p;
+    return (int)__builtin_amdgcn_sad_u8(v[3], 0, __builtin_amdgcn_sad_u8(v[2], 0, __builtin_amdgcn_sad_u8(v[1], 0, __builtin_amdgcn_sad_u8(v[0], 0, 0))));
 }
 
-// Pass 1 of the multi-tile planner: per-tile counts of pairs per expert and of first
-// (token, device) appearances per device.  Lanes of a wave that hold the same key are found with
-// ballots and only one of them adds their number to the LDS counter, so a popular key does not
-// serialise the wave.  Counts do not depend on the order of the additions.
-template <int R>
-__global__ __launch_bounds__(kPlanThreads) void plan_count_kernel(PlanArgs a)
-{
-    __shared__ int16_t tile_dev[R * kRoundPairs];
-    __shared__ int hist[2 * kMaxBins + 1];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int tile = blockIdx.x;
-    const int tok0 = tile * a.tpt;
-    const int ntok = min(a.tpt, a.N - tok0);
-    const int npairs = ntok > 0 ? ntok * a.k : 0;
-    const int64_t pair0 = (int64_t)tok0 * a.k;
-    const int nb = a.E + a.D;
-    const int ebits = bits_for(a.E), dbits = bits_for(a.D);
-    const uint64_t lt = ((uint64_t)1 << lane) - 1;
+// packed ranks: experts in pair_slot, devices in pair_send_row; -1 for an invalid pair
+__device__ __forceinline__ int pack_rank(int rank, int key, bool first) { return rank | key << 11 | (int)first << 21; }
+__device__ __forceinline__ int packed_rank(int v) { return v & 2047; }
+__device__ __forceinline__ int packed_key(int v) { return v >> 11 & 1023; }
+__device__ __forceinline__ bool packed_first(int v) { return v >> 21 & 1; }
 
-    for (int b = tid; b <= nb; b += kPlanThreads) hist[b] = 0;
-    int ekey[R];
+__global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
+{
+    __shared__ u32x4 cnt[2 * kMaxBins];   // [key]: a byte per wave, experts then devices
+    __shared__ int invalid;
+    uint8_t *byte = (uint8_t *)cnt;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tok0 = blockIdx.x * a.tpt, ntok = min(a.tpt, a.N - tok0);
+    const int64_t pair0 = (int64_t)tok0 * a.k;
+    const int nb = a.E + a.D, ebits = bits_for(a.E), dbits = bits_for(a.D);
+    const int per_wave = div20(kWave, a.k_magic), tok = div20(lane, a.k_magic);
+    const uint64_t lt = ((uint64_t)1 << lane) - 1, not_before_token = ~(((uint64_t)1 << (tok * a.k)) - 1);
+
+    int raw[kRankRounds];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = r * kPlanThreads + tid;
-        int key = -1;
-        bool bad = false;
-        if (p < npairs) {
-            const int e = a.A[pair0 + p];
-            if ((unsigned)e < (unsigned)a.E) key = e;
-            else bad = true;
+    for (int r = 0; r < kRankRounds; ++r) {
+        const int t0 = (wave * a.rank_rounds + r) * per_wave;   // the wave's rounds follow one another in token order
+        raw[r] = r < a.rank_rounds && tok < per_wave && t0 + tok < ntok ? a.A[pair0 + t0 * a.k + lane] : -1;
+    }
+    for (int b = tid; b < nb; b += kPlanThreads) cnt[b] = u32x4{0, 0, 0, 0};
+    if (tid == 0) invalid = 0;
+    __syncthreads();
+
+    int erank[kRankRounds], drank[kRankRounds], bad = 0;
+    bool first[kRankRounds];
+#pragma unroll
+    for (int r = 0; r < kRankRounds; ++r) {
+        const int t0 = (wave * a.rank_rounds + r) * per_wave;
+        if (r >= a.rank_rounds || t0 >= ntok) break;   // uniform over the wave
+        const int e = raw[r];
+        const bool ok = (unsigned)e < (unsigned)a.E;
+        const int d = ok ? div20(e, a.eloc_magic) : -1;
+        bad += __builtin_popcountll(__builtin_amdgcn_ballot_w64(!ok && tok < per_wave && t0 + tok < ntok));
+        const int ebefore = ok ? byte[e * kPlanWaves + wave] : 0, dbefore = ok ? byte[(a.E + d) * kPlanWaves + wave] : 0;
+        const uint64_t em = same_key_lanes<4>(e, ok, ebits), same = same_key_lanes(d, ok, dbits);
+        const uint64_t of_token = same & not_before_token;   // from the token's first entry on the device
+        first[r] = ok && !(of_token & lt);
+        const uint64_t dm = same & __builtin_amdgcn_ballot_w64(first[r]);
+        erank[r] = ebefore + __builtin_popcountll(em & lt);
+        drank[r] = dbefore + __builtin_popcountll(dm & lt);
+        wave_lds_order();
+        if (ok && !(em & lt)) byte[e * kPlanWaves + wave] = (uint8_t)(ebefore + __builtin_popcountll(em));
+        if (first[r] && !(dm & lt)) byte[(a.E + d) * kPlanWaves + wave] = (uint8_t)(dbefore + __builtin_popcountll(dm));
+        wave_lds_order();
+        drank[r] = __shfl(drank[r], ok ? __builtin_ctzll(of_token) : lane, kWave);   // the token's row on the device
+    }
+    if (bad && lane == 0) atomicAdd(&invalid, bad);
+    __syncthreads();
+
+    int32_t *out = a.tile_hist + (int64_t)blockIdx.x * a.stride;
+    for (int b = tid; b < nb; b += kPlanThreads) out[b] = sum_bytes(cnt[b]);
+    if (tid == 0) out[nb] = invalid;
+    u32x4 earlier;   // the bytes of the waves before this one
+#pragma unroll
+    for (int q = 0; q < 4; ++q) earlier[q] = wave >= 4 * q + 4 ? ~0u : wave <= 4 * q ? 0u : (1u << 8 * (wave - 4 * q)) - 1;
+#pragma unroll
+    for (int r = 0; r < kRankRounds; ++r) {
+        const int t0 = (wave * a.rank_rounds + r) * per_wave;
+        if (r >= a.rank_rounds || t0 >= ntok) break;
+        if (tok >= per_wave || t0 + tok >= ntok) continue;
+        const int e = raw[r];
+        int ew = -1, dw = -1;
+        if ((unsigned)e < (unsigned)a.E) {
+            const int d = div20(e, a.eloc_magic);
+            ew = pack_rank(erank[r] + sum_bytes(cnt[e] & earlier), e, false);
+            dw = pack_rank(drank[r] + sum_bytes(cnt[a.E + d] & earlier), d, first[r]);
         }
-        ekey[r] = key;
-        tile_dev[p] = (int16_t)(key >= 0 ? div20(key, a.eloc_magic) : -1);
-        const uint64_t nbad = __builtin_amdgcn_ballot_w64(bad);
-        if (r == 0) __syncthreads();   // counters are zero from here on
-        if (nbad != 0 && lane == 0) atomicAdd(&hist[nb], __builtin_popcountll(nbad));
-        const uint64_t m = same_key_lanes(key, key >= 0, ebits);
-        if (key >= 0 && (m & lt) == 0) atomicAdd(&hist[key], __builtin_popcountll(m));
+        const int64_t p = pair0 + t0 * a.k + lane;
+        a.pair_slot[p] = ew;
+        a.pair_send_row[p] = dw;
     }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = r * kPlanThreads + tid;
-        const int d = tile_dev[p];
-        uint64_t same;
-        const bool first = first_pair_on_device(tile_dev, p, lane, div20(p, a.k_magic) * a.k, d, dbits, same) == p;
-        const uint64_t m = same & __builtin_amdgcn_ballot_w64(first);
-        if (first && (m & lt) == 0) atomicAdd(&hist[a.E + d], __builtin_popcountll(m));
-    }
-    __syncthreads();
-    int32_t *out = a.tile_hist + (int64_t)tile * a.stride;
-    for (int b = tid; b <= nb; b += kPlanThreads) out[b] = hist[b];
 }
 
 // Optional pass between counting and placing: sums the per-tile counts over chunks of consecutive
@@ -165,8 +194,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
         if (part < parts && b < ncol) {
             const int32_t *h = a.tile_hist + col0 + b;
             int sum = 0;
-#pragma unroll 8
-            for (int tl = t0 + part; tl < t1; tl += parts) sum += h[(int64_t)tl * a.stride];
+            for (int tl = t0 + part; tl < t1; tl += 8 * parts)   // eight loads in flight, also at the end of the list
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum += tl + i * parts < t1 ? h[(int64_t)(tl + i * parts) * a.stride] : 0;
             atomicAdd(&acc[b], sum);
         }
         __syncthreads();
@@ -175,338 +205,205 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
     }
 }
 
-// Shared LDS state of the placement kernel.
-template <int R>
-struct PlaceLds {
-    int16_t tile_dev[R * kRoundPairs];              // device of every pair, -1 for an invalid expert id
-    int tile_row[R * kRoundPairs];                  // send row of the pairs that are first appearances
-    int tile_slot[R * kRoundPairs];                 // expert-major slot of every pair
-    uint16_t wave_cnt[kPlanWaves][kMaxBins];   // per wave and key: running count, then prefix over waves
-    int base[kMaxBins];                        // per key: pairs in earlier tiles, then the tile's global start
-    int total[kMaxBins + 1];
-    int tile_pairs;                            // pairs of the tile with a valid expert id
+// Pass 2: every pair's slot and send row, from its rank in the tile (pass 1) and the counts of the other tiles; all
+// descriptor arrays.  One workgroup per tile.  The arrays indexed by slot, and tile_slots, are written in the tile's
+// transfer order (its slots ascending: expert by expert, tokens ascending): neighbouring threads then write
+// neighbouring slots of one expert, a few cache lines per wave instead of 64; the pairs meet their place in that
+// order through LDS.  Bound by latency: three barriers between the loads and the stores.  Kernel times of pass 1 + pass 2
+// (and the chunk pass between them), k = 8, us: 8192 tokens 5.6 + 7.2, 32768 tokens 6.0 + 4.6 + 8.0, 131072 tokens
+// 9.5 + 4.1 + 15.4, 4096 tokens with k = 2 4.7 + 4.7; before, with a pass 1 that only counted and a pass 2 that ranked
+// all pairs again (and prefixed 16 counters per key): 5.2 + 11.8, 5.3 + 4.3 + 14.2, 7.0 + 4.2 + 29.9, 3.8 + 8.6.
+constexpr int kTilePairs = kMaxRounds * kRoundPairs;
+constexpr int kCross = 12;           // rows of counts that a thread requests before anything else: 36 rows of 256 experts + 8 devices
+constexpr int kMaxChunks = 2 * (kMaxBins / kWave);   // groups of 64 experts, then groups of 64 devices
+
+// Sums of one column over the rows part, part + parts, ... of a list of n rows; rows below `limit` also count towards
+// `before`.  Loads are issued back to back: beyond the list they read its last row, and their values are left out.
+struct RowSums {
+    const char *rows;
+    int n, part, parts, limit;
+    uint32_t at, step, last;   // byte offsets: the thread's first row, from one of its rows to the next, the list's last row
+    int total, before;
+    __device__ __forceinline__ RowSums(const int32_t *r, int count, int part_, int parts_, int limit_, int stride, int column)
+        : rows((const char *)r), n(count), part(part_), parts(parts_), limit(limit_), at((uint32_t)(part_ * stride + column) * 4),
+          step((uint32_t)(parts_ * stride) * 4), last((uint32_t)(max(count - 1, 0) * stride + column) * 4), total(0), before(0) {}
+    template <int NV>
+    __device__ __forceinline__ void load(int (&v)[NV], int i0) const   // the thread's rows i0, i0 + 1, ...
+    {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if ((i0 + i) * parts >= n) break;   // uniform: nobody has a row left
+            v[i] = *(const int32_t *)(rows + min(at + (uint32_t)(i0 + i) * step, last));
+        }
+    }
+    template <int NV>
+    __device__ __forceinline__ void add(const int (&v)[NV], int i0)
+    {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int first = (i0 + i) * parts;
+            if (first >= n) break;
+            total += part < n - first ? v[i] : 0;
+            before += part < limit - first ? v[i] : 0;
+        }
+    }
+    __device__ __forceinline__ void walk(int i0)   // eight loads in flight
+    {
+        for (; i0 * parts < n; i0 += 8) {
+            int v[8];
+            load(v, i0);
+            add(v, i0);
+        }
+    }
 };
 
-// Counts of the other tiles, as the placement kernel needs them: thread (part, b) of the workgroup adds up,
-// for key b, the counts of tiles part, part + parts, ... (parts = groups of nb threads that fit the workgroup).
-// The first kCross of these loads depend on nothing the workgroup computes; place_tile issues
-// them right after its loads of the routing and uses the values only after the ranking inside the tile, so
-// that one memory latency is paid instead of three in a row (the counts were written by other XCDs in the
-// previous kernel and come from memory).  Not used with a chunk level.
-constexpr int kCross = 16;   // 48 tiles of 256 experts + 8 devices are covered without a loop
-
-template <int PF>
-__device__ __forceinline__ void cross_prefetch(const PlanArgs &a, int nb, int hist_off, int (&v)[PF])
+// (80 scalar registers: with more, a compute unit takes one workgroup of 16 waves at a time instead of two)
+__global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) void plan_place_kernel(PlanArgs a)
 {
+    // per group of threads and column: total over all tiles, and over the earlier ones (`before` again holds the place
+    // where the tile's run of the key starts, without its group's offset)
+    __shared__ int total[2 * kMaxBins], before[2 * kMaxBins];
+    __shared__ int tile_at[kMaxBins];                          // start of the expert's run in the tile, within its group
+    __shared__ int group_total[kMaxChunks], group_tile[kMaxChunks];   // sums over 64 experts or devices
+    __shared__ int slot_of[kTilePairs], row_of[kTilePairs];
+    __shared__ uint16_t sorted[kTilePairs];
     const int tid = threadIdx.x;
-    const int nb_pad = (nb + kWave - 1) / kWave * kWave;
-    const int parts = kPlanThreads / nb_pad;
-    const int part = tid / nb_pad, b = tid - part * nb_pad;
-    const bool active = a.chunk_tiles == 0 && part < parts && b < nb;
-    const int32_t *h = a.tile_hist + hist_off + b;
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-        const int tl = part + i * parts;
-        v[i] = active && tl < a.n_tiles ? h[(int64_t)tl * a.stride] : 0;
-    }
-}
-
-// Exclusive prefix sum of v[0 .. nb) in place, by the calling wave (all 64 lanes): each lane owns a run of
-// consecutive entries; *total receives the sum.
-__device__ __forceinline__ void wave_exclusive_scan(int *v, int nb, int *total)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int per = (nb + kWave - 1) / kWave;
-    const int lo = min(lane * per, nb), hi = min(lo + per, nb);
-    int sum = 0;
-    for (int b = lo; b < hi; ++b) sum += v[b];
-    const int incl = wave_inclusive_sum(sum);
-    int run = incl - sum;
-    for (int b = lo; b < hi; ++b) {
-        const int x = v[b];
-        v[b] = run;
-        run += x;
-    }
-    if (lane == kWave - 1) *total = incl;
-}
-
-// Clears the counters of rank_bins for nb bins.  The caller puts a barrier between this and rank_bins.
-template <int R>
-__device__ __forceinline__ void rank_clear(PlaceLds<R> &s, int nb)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    for (int b = lane; b < nb; b += kWave) s.wave_cnt[wave][b] = 0;
-    for (int b = tid; b < nb; b += kPlanThreads) {
-        s.total[b] = 0;
-        s.base[b] = 0;
-    }
-}
-
-// Stable ranking of the tile's pairs by key, in pair order, on top of the global order of tiles.
-// The bins are nE expert bins followed by nD device bins (either may be 0): expert keys are ranked into
-// slots of the expert-activation tensor, device keys (first appearances only) into send rows, in one
-// pass over a common set of counters.  key[i] is a bin, or -1 for an entry that does not take part; the
-// thread's NK entries are ranked in the order i = 0 .. NK-1, each index being one round of 64 consecutive
-// pairs of the wave.  On return pos[i] is the entry's global position inside its own family: (exclusive
-// offset of the key among the experts, or among the devices) + (entries with that key in earlier tiles) +
-// (earlier entries with that key in this tile).  tile_pos[i] is, for expert keys, the position among the
-// tile's own pairs in (expert, pair) order; s.tile_pairs receives their number.  Block 0 also writes the
-// per-key counts and their exclusive prefix sums.  hist_off: column of bin 0 in the per-tile counts.
-// pre_v: the first PF per-tile counts of this thread's key and part (cross_prefetch).
-template <int R, int NK, int PF>
-__device__ __forceinline__ void rank_bins(PlaceLds<R> &s, const PlanArgs &a, int tile, const int (&key)[NK],
-                                          int nE, int nD, int hist_off, const int (&pre_v)[PF], int (&pos)[NK],
-                                          int (&tile_pos)[NK])
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int nb = nE + nD;
-    // entries of one index i are all expert keys (i < expert_rounds) or all device keys, so lanes with the
-    // same key are found by comparing only as many bits as that family has
-    const int expert_rounds = nE == 0 ? 0 : (nD == 0 ? NK : NK / 2);
-    const int ebits = bits_for(nE), dbits = bits_for(nD);
-    const uint64_t lt = ((uint64_t)1 << lane) - 1;
-    int *tile_cnt = s.tile_row;   // the tile's own count per expert, then their prefix: tile_row is written later
-
-    // rank inside the wave's chunk; wave_cnt[wave][key] is the running count of the key (zero on entry:
-    // rank_clear, and a barrier, come before this call)
-    int rank[NK];
-#pragma unroll
-    for (int i = 0; i < NK; ++i) {
-        const bool part = key[i] >= 0;
-        const uint64_t m = i < expert_rounds ? same_key_lanes(key[i], part, ebits) : same_key_lanes(key[i] - nE, part, dbits);
-        const int before = part ? s.wave_cnt[wave][key[i]] : 0;
-        rank[i] = before + __builtin_popcountll(m & lt);
-        wave_lds_order();
-        if (part && (m & lt) == 0) s.wave_cnt[wave][key[i]] = (uint16_t)(before + __builtin_popcountll(m));
-        wave_lds_order();
-    }
-    __syncthreads();
-
-    // per key: total over all tiles and the part that lies in earlier tiles.  The workgroup splits
-    // the tiles into as many interleaved parts as it has groups of nb threads, so that every
-    // thread keeps only a few independent loads in flight; partial sums meet in LDS.
-    {
-        const int nb_pad = (nb + kWave - 1) / kWave * kWave;
-        const int parts = kPlanThreads / nb_pad;     // >= 1 because nb <= kMaxBins == kPlanThreads
-        const int part = tid / nb_pad, b = tid - part * nb_pad;
-        if (part < parts && b < nb) {
-            const int32_t *h = a.tile_hist + hist_off + b;
-            const int me = tile;
-            int tot = 0, pre = 0;
-            if (a.chunk_tiles == 0) {
-                // the first PF tiles of this part were requested at the start of the kernel
-#pragma unroll
-                for (int i = 0; i < PF; ++i) {
-                    tot += pre_v[i];
-                    pre += part + i * parts < me ? pre_v[i] : 0;
-                }
-#pragma unroll 8
-                for (int tl = part + PF * parts; tl < a.n_tiles; tl += parts) {
-                    const int v = h[(int64_t)tl * a.stride];
-                    tot += v;
-                    pre += tl < me ? v : 0;
-                }
-            } else {
-                // whole chunks from their sums, then the tiles of this workgroup's own chunk before it
-                const int32_t *ch = a.chunk_hist + hist_off + b;
-                const int my_chunk = me / a.chunk_tiles;
-#pragma unroll 8
-                for (int c = part; c < a.n_chunks; c += parts) {
-                    const int v = ch[(int64_t)c * a.stride];
-                    tot += v;
-                    pre += c < my_chunk ? v : 0;
-                }
-#pragma unroll 8
-                for (int tl = my_chunk * a.chunk_tiles + part; tl < me; tl += parts) pre += h[(int64_t)tl * a.stride];
-            }
-            atomicAdd(&s.total[b], tot);
-            atomicAdd(&s.base[b], pre);
-        }
-    }
-    __syncthreads();
-    if (tile == 0)
-        for (int b = tid; b < nb; b += kPlanThreads) {
-            if (b < nE) a.exp_count[b] = s.total[b];
-            else a.send_count[b - nE] = s.total[b];
-        }
-
-    // exclusive prefix sum over all bins, by wave 0; the devices' offsets start after the experts' total
-    if (wave == 0) wave_exclusive_scan(s.total, nb, &s.total[nb]);
-    __syncthreads();
-    const int experts_total = s.total[nE];   // 0 when there are no expert bins
-    if (tile == 0)
-        for (int b = tid; b <= nb; b += kPlanThreads) {
-            if (nE > 0 && b <= nE) a.exp_off[b] = s.total[b];
-            if (nD > 0 && b >= nE) a.send_off[b - nE] = s.total[b] - experts_total;
-        }
-
-    // per key: prefix of the per-wave counts, the global position where the tile's run starts, and the
-    // tile's own count per expert
-    for (int b = tid; b < nb; b += kPlanThreads) {
-        int run = 0;
-        for (int w = 0; w < kPlanWaves; ++w) {
-            const int c = s.wave_cnt[w][b];
-            s.wave_cnt[w][b] = (uint16_t)run;
-            run += c;
-        }
-        s.base[b] += s.total[b] - (b >= nE ? experts_total : 0);
-        if (b < nE) tile_cnt[b] = run;
-    }
-    __syncthreads();
-    // the tile's own exclusive prefix over the experts gives the order of its pairs by (expert, pair)
-    if (wave == 0 && nE > 0) wave_exclusive_scan(tile_cnt, nE, &s.tile_pairs);
-#pragma unroll
-    for (int i = 0; i < NK; ++i)
-        pos[i] = key[i] >= 0 ? s.base[key[i]] + s.wave_cnt[wave][key[i]] + rank[i] : -1;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NK; ++i)
-        tile_pos[i] = key[i] >= 0 && key[i] < nE ? tile_cnt[key[i]] + s.wave_cnt[wave][key[i]] + rank[i] : -1;
-    __syncthreads();
-}
-
-// Placement of one tile by one workgroup: pass 2 of the multi-tile planner.
-template <int R>
-__global__ __launch_bounds__(kPlanThreads) void plan_place_kernel(PlanArgs a)
-{
-    __shared__ PlaceLds<R> s;
-    const int tile = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int tok0 = tile * a.tpt;
-    const int ntok = min(a.tpt, a.N - tok0);
-    const int npairs = ntok > 0 ? ntok * a.k : 0;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tile = blockIdx.x, tok0 = tile * a.tpt, npairs = min(a.tpt, a.N - tok0) * a.k;
     const int64_t pair0 = (int64_t)tok0 * a.k;
-    // experts and devices share one ranking pass when their bins fit the counters together
-    const bool together = a.E + a.D <= kMaxBins;
+    const int nb = a.E + a.D;
+    const int egroups = (a.E + kWave - 1) / kWave, groups = egroups + (a.D + kWave - 1) / kWave;
 
-    int ekey[R], tl[R];   // expert id and tile-local token of the thread's pairs
-    int eraw[R];
+    int ew[kMaxRounds], dw[kMaxRounds];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        eraw[r] = p < npairs ? a.A[pair0 + p] : 0;
-    }
-    // counts of the other tiles: requested behind the routing, used after the ranking (see cross_prefetch)
-    int cross[kCross];
-    cross_prefetch<kCross>(a, together ? a.E + a.D : a.E, 0, cross);
-    rank_clear(s, together ? a.E + a.D : a.E);   // while the loads are on their way
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        int key = -1;
+    for (int r = 0; r < kMaxRounds; ++r) {
+        const int p = r * kPlanThreads + tid;
+        ew[r] = dw[r] = -1;
         if (p < npairs) {
-            const int e = eraw[r];
-            if ((unsigned)e < (unsigned)a.E) key = e;
+            ew[r] = a.pair_slot[pair0 + p];
+            dw[r] = a.pair_send_row[pair0 + p];
         }
-        tl[r] = div20(p, a.k_magic);
-        ekey[r] = key;
-        s.tile_dev[p] = (int16_t)(key >= 0 ? div20(key, a.eloc_magic) : -1);
+    }
+    // Rows to add up: all tiles; with a chunk level all chunks, and then the tiles of the tile's own chunk before it.
+    // Thread (part, c) takes rows part, part + parts, ... of column c (parts: groups of columns that fit the workgroup)
+    const bool chunked = a.chunk_tiles != 0;
+    const int chunk = chunked ? tile / a.chunk_tiles : 0;
+    const int32_t *rows1 = chunked ? a.chunk_hist : a.tile_hist, *rows2 = a.tile_hist + (int64_t)chunk * a.chunk_tiles * a.stride;
+    const int n1 = chunked ? a.n_chunks : a.n_tiles, limit1 = chunked ? chunk : tile, n2 = chunked ? tile - chunk * a.chunk_tiles : 0;
+    const int cols = min(nb, kPlanThreads), pad = (cols + kWave - 1) / kWave * kWave, parts = kPlanThreads / pad;
+    const int part = tid / pad, c = tid - part * pad;
+    // this tile's own count of the expert that the thread has in the first round of groups below
+    const int own0 = wave < egroups && tid < a.E ? a.tile_hist[(int64_t)tile * a.stride + tid] : 0;
+    if (part < parts && c < cols) {
+        RowSums s(rows1, n1, part, parts, limit1, a.stride, c), s2(rows2, n2, part, parts, 0, a.stride, c);
+        int v[kCross], v2[kCross];
+        s.load(v, 0);
+        s2.load(v2, 0);
+        s.add(v, 0);
+        s.walk(kCross);
+        s2.add(v2, 0);
+        s2.walk(kCross);
+        total[part * pad + c] = s.total;   // parts * pad <= 1024
+        before[part * pad + c] = s.before + s2.total;
+    }
+    // the columns beyond the workgroup's kPlanThreads (more than 1024 experts and devices, parts is 1): one thread each
+    for (int e = kPlanThreads + tid; e < nb; e += kPlanThreads) {
+        RowSums s(rows1, n1, 0, 1, limit1, a.stride, e), s2(rows2, n2, 0, 1, 0, a.stride, e);
+        s.walk(0);
+        s2.walk(0);
+        total[e] = s.total;
+        before[e] = s.before + s2.total;
     }
     __syncthreads();
-
-    // level 1: a token has one send row per device, taken at the device's first appearance among its entries
-    const int dbits = bits_for(a.D);
-    int dkey[R], jfirst[R];   // jfirst: the token's first pair on the same device
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        const int d = s.tile_dev[p];
-        uint64_t same;
-        jfirst[r] = first_pair_on_device(s.tile_dev, p, lane, tl[r] * a.k, d, dbits, same);
-        dkey[r] = jfirst[r] == p ? d : -1;
-    }
-
-    // level 2 receive side (expert-major slot of every pair) and level 1 (send row of every first appearance)
-    int slot[R], tile_pos[R], row[R];
-    if (together) {
-        int key2[2 * R], pos2[2 * R], tp2[2 * R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            key2[r] = ekey[r];
-            key2[R + r] = dkey[r] >= 0 ? a.E + dkey[r] : -1;
+    // Per group of 64 experts or devices, one wave: exclusive sums inside the group
+    for (int g = wave; g < groups; g += kPlanWaves) {
+        const bool expert = g < egroups;
+        const int e = expert ? g * kWave + lane : a.E + (g - egroups) * kWave + lane;   // column
+        const bool in = expert ? e < a.E : e < nb;
+        int tot = 0, pre = 0, own = 0;
+        if (in) {
+            if (expert) own = g == wave ? own0 : a.tile_hist[(int64_t)tile * a.stride + e];
+            for (int q = 0; q < parts; ++q) {
+                tot += total[q * pad + e];
+                pre += before[q * pad + e];
+            }
         }
-        rank_bins<R, 2 * R, kCross>(s, a, tile, key2, a.E, a.D, 0, cross, pos2, tp2);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            slot[r] = pos2[r];
-            tile_pos[r] = tp2[r];
-            row[r] = pos2[R + r];
+        const int incl = wave_inclusive_sum(tot), own_incl = wave_inclusive_sum(own);
+        if (tile == 0 && in) (expert ? a.exp_count + e : a.send_count + (e - a.E))[0] = tot;
+        wave_lds_order();
+        if (in) {
+            total[e] = incl - tot;   // offset inside the group (only this wave reads or writes column e from here to the barrier)
+            before[e] = incl - tot + pre;
+            if (expert) tile_at[e] = own_incl - own;
         }
-    } else {
-        int unused[R];
-        rank_bins<R, R, kCross>(s, a, tile, ekey, a.E, 0, 0, cross, slot, tile_pos);
-        int cross_d[kCross];   // (the second pass has no expert bins and leaves s.tile_pairs alone)
-        cross_prefetch<kCross>(a, a.D, a.E, cross_d);
-        rank_clear(s, a.D);
-        __syncthreads();
-        rank_bins<R, R, kCross>(s, a, tile, dkey, 0, a.D, a.E, cross_d, row, unused);
-    }
-    const int tile_pairs = s.tile_pairs;          // pairs of this tile with a valid expert id
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        s.tile_slot[p] = slot[r];
-        if (p < npairs) a.pair_slot[pair0 + p] = slot[r];
-    }
-
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        s.tile_row[p] = row[r];
-        if (p < npairs) {
-            a.pair_first[pair0 + p] = row[r] >= 0 ? 1 : 0;
-            if (row[r] >= 0) a.send_src[row[r]] = tok0 + tl[r];
+        if (lane == kWave - 1) {
+            group_total[g] = incl;
+            group_tile[g] = own_incl;
         }
     }
     __syncthreads();
-
-    // level 2 send side: every pair points at the send row of its token on its device
-    int srow[R];
+    // offsets of the groups, one per lane
+    const int of_group = lane < groups ? group_total[lane] : 0, of_tile = lane < groups ? group_tile[lane] : 0;
+    const int incl = wave_inclusive_sum(of_group), tile_incl = wave_inclusive_sum(of_tile);
+    const int group_off = incl - of_group, tile_group_off = tile_incl - of_tile;
+    const int experts_total = __builtin_amdgcn_readlane(incl, egroups - 1);
+    const int tile_pairs = __builtin_amdgcn_readlane(tile_incl, egroups - 1);   // pairs of this tile with a valid expert id
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        srow[r] = ekey[r] >= 0 ? s.tile_row[jfirst[r]] : -1;
-        if (p < npairs) a.pair_send_row[pair0 + p] = srow[r];
-    }
-    // The arrays indexed by slot are written in the tile's transfer order (its slots ascending: expert by expert,
-    // tokens ascending), which is also the order that is listed for dispatch: neighbouring threads then write
-    // neighbouring slots of one expert, a few cache lines per wave instead of 64.  The pairs meet their place in
-    // that order through LDS; sorted_pair reuses the per-wave counters, which the ranking no longer needs.
-    uint16_t *sorted_pair = &s.wave_cnt[0][0];
-    static_assert(sizeof(s.wave_cnt) >= R * kRoundPairs * sizeof(uint16_t), "sorted_pair fits the per-wave counters");
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = wave * (R * kWave) + r * kWave + lane;
-        if (tile_pos[r] >= 0) {
-            sorted_pair[tile_pos[r]] = (uint16_t)p;
-            // only pairs that are not a first appearance write here, and nobody reads their entry above
-            if (jfirst[r] != p) s.tile_row[p] = srow[r];
+    for (int r = 0; r < kMaxRounds; ++r) {
+        const int p = r * kPlanThreads + tid;
+        if (r * kPlanThreads >= npairs) break;   // uniform
+        const int e = packed_key(ew[r]), d = packed_key(dw[r]), rank = packed_rank(ew[r]);
+        const int eoff = __shfl(group_off, e / kWave, kWave), toff = __shfl(tile_group_off, e / kWave, kWave);
+        const int doff = __shfl(group_off, egroups + d / kWave, kWave) - experts_total;
+        if (p >= npairs) continue;
+        int slot = -1, row = -1;
+        bool first = false;
+        if (ew[r] >= 0) {
+            slot = before[e] + eoff + rank;
+            row = before[a.E + d] + doff + packed_rank(dw[r]);
+            first = packed_first(dw[r]);
+            sorted[tile_at[e] + toff + rank] = (uint16_t)p;
         }
+        slot_of[p] = slot;
+        row_of[p] = row;
+        a.pair_slot[pair0 + p] = slot;
+        a.pair_send_row[pair0 + p] = row;
+        a.pair_first[pair0 + p] = first ? 1 : 0;
+        if (first) a.send_src[row] = tok0 + div20(p, a.k_magic);
     }
     __syncthreads();
     const int cap = a.tpt * a.k;
     int32_t *order = a.tile_slots + (int64_t)tile * cap;
     for (int q = tid; q < cap; q += kPlanThreads) {
+        int sl = -1;
         if (q < tile_pairs) {
-            const int p = sorted_pair[q];
-            const int sl = s.tile_slot[p];
-            order[q] = sl;
+            const int p = sorted[q];
+            sl = slot_of[p];
             a.slot_pair[sl] = (int32_t)(pair0 + p);
             a.slot_token[sl] = tok0 + div20(p, a.k_magic);
-            a.slot_send_row[sl] = s.tile_row[p];
-        } else {
-            order[q] = -1;
+            a.slot_send_row[sl] = row_of[p];
         }
+        order[q] = sl;
     }
 
-    if (tile == 0 && wave == 0) {
-        // the last column of the counts holds the invalid ids of a tile (or of a chunk of tiles)
-        int bad = 0;
-        const int32_t *col = (a.chunk_tiles ? a.chunk_hist : a.tile_hist) + a.E + a.D;
-        const int rows = a.chunk_tiles ? a.n_chunks : a.n_tiles;
-        for (int r = lane; r < rows; r += kWave) bad += col[(int64_t)r * a.stride];
-        for (int d = kWave / 2; d > 0; d >>= 1) bad += __shfl_down(bad, d, kWave);
-        if (lane == 0) *a.status = bad;
+    if (tile == 0) {
+        for (int g = wave; g < groups; g += kPlanWaves) {
+            const int off = __builtin_amdgcn_readlane(group_off, g);
+            const int i = (g < egroups ? g : g - egroups) * kWave + lane;
+            if (g < egroups && i < a.E) a.exp_off[i] = total[i] + off;
+            if (g >= egroups && i < a.D) a.send_off[i] = total[a.E + i] + off - experts_total;
+        }
+        if (tid == 0) {
+            a.exp_off[a.E] = experts_total;
+            a.send_off[a.D] = __builtin_amdgcn_readlane(incl, kWave - 1) - experts_total;
+        }
+        if (wave == kPlanWaves - 1) {
+            // the last column of the counts holds the invalid ids of a tile (or of a chunk of tiles)
+            int bad = 0;
+            for (int r = lane; r < n1; r += kWave) bad += rows1[(int64_t)r * a.stride + nb];
+            bad = wave_inclusive_sum(bad);
+            if (lane == kWave - 1) *a.status = bad;
+        }
     }
 }
 

@@ -87,6 +87,27 @@ def test_single_tile_planner(N, k, E, D, bad):
     assert bool((rows[n:] == 0xEE).all())
 
 
+# tiles read one by one with the requested rows alone and with more (37 and more), with a chunk level (96 and more) whose
+# last chunk is ragged; rounds of whole tokens that fill a wave or not; more columns of counts than threads
+SEVERAL_TILES = [(257, 8, 256, 8), (683, 3, 24, 24), (293, 7, 1024, 64), (129, 33, 96, 4), (65, 64, 1024, 1024), (2049, 1, 64, 8),
+                 (9500, 8, 256, 8), (3000, 33, 1024, 1024), (24577, 8, 256, 64), (65900, 3, 24, 8), (7000, 33, 640, 640),
+                 (220000, 1, 16, 4)]
+
+
+@pytest.mark.parametrize("bad", [False, True])
+@pytest.mark.parametrize("N,k,E,D", SEVERAL_TILES)
+def test_several_tiles(N, k, E, D, bad):
+    import paper_2512_22036_amd as f
+    A = routing(N + k, N, k, E, not bad, bad)
+    if bad:
+        A[N // 3:N // 3 + 2048 // k + 1] = E - 1   # a tile of one expert: every pair of a wave has the same key
+    L = f.Layout(N, k, E, D)
+    assert L.tile_count > 1
+    L.mem.fill_(0x7B)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    check(L, A, "plan")
+
+
 def test_calls_without_a_stream_use_the_current_one():
     from paper_2512_22036_amd import binding
     side = torch.cuda.Stream()
