@@ -370,6 +370,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
         tiled_shape(L, Ct, threads, cpt, segs, per);
         a.segs = segs; a.seg_chunks = per;
+        a.through = whole_units(d_expert_buf, row_bytes); a.through_aux = whole_units(d_expert_aux, aux_row_bytes);
         // a source tensor that cannot stay in the memory-side cache is taken in chunks of whole rounds of tiles
         // whose rows fit half of it, every chunk after a sequential read of its source rows (touch_kernel)
         const size_t source_bytes = (size_t)L->N * (row_bytes + aux_row_bytes);
@@ -517,6 +518,7 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
     a.pair_send_row = L->pair_send_row; a.send_src = L->send_src; a.n_rows_dev = L->send_off + L->D;
     a.first = 0;
     a.n_rows = L->send_cap;
+    a.stores = kOutNonTemporal;
     int threads;
     combine_shape(a.C, threads, a.segs);
     const dim3 grid((unsigned)L->send_cap * (unsigned)a.segs);

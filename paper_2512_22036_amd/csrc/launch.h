@@ -153,6 +153,25 @@ int combine_first_row(int N, int k, size_t row_bytes)
     return recent >= (size_t)N ? 0 : N - (int)recent;
 }
 
+// Whether rows of row_bytes from p on consist of whole 64-byte units.  A write-through store that covers a part of such a
+// unit goes to memory as a partial write: rows of 14352 B 297 us in the tiled dispatch against 228 us with stores that
+// the L2 merges, rows of 8208 B 161 against 113 us; for whole units write-through is the faster one in a step
+// (14336 B: 380 against 401 us with combine, 14400 B: 388 against 413 us).
+bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_bytes) & 63u) == 0; }
+
+// Stores of combine's output rows.  Inputs that are bound by memory: non-temporal, past the memory-side cache - what
+// write-through and plain stores leave dirty there costs the reads of the kernels around them more than it saves
+// (a step with the experts' output in a tensor of its own, written through / non-temporal: 8192 tokens x 8 rows of
+// 14 KiB 377.7 / 366.8 us, 16384 x 8 x 8 KiB 434 / 428 us, 32768 x 8 x 14 KiB 1466 / 1447 us, fp32 8192 x 4 x 8 KiB with
+// its gradients 270 / 257 us; rows that are not whole units 8192 x 8 x 14352 B: combine 199 us written through, 209 us
+// plain, 178 us).  Small ones stay in that cache for their reader: written through where a wave's stores cover whole
+// units, plain otherwise (fp32 rows of 16 KiB from bf16 ones, 1024 tokens: 43.5 us written through, 41.0 us plain).
+OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes, bool every_other_16_bytes)
+{
+    if (y_bytes >= kCombineLatencyBoundBytes) return kOutNonTemporal;
+    return whole_units(out, row_bytes) && !every_other_16_bytes ? kOutThrough : kOutPlain;
+}
+
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked
 void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int y_dtype, const float *d_w,
                     void *d_out, int out_dtype, int32_t H, hipStream_t s, hipEvent_t e0 = nullptr,
@@ -167,6 +186,8 @@ void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int
     a.pair_send_row = nullptr; a.send_src = nullptr; a.n_rows_dev = nullptr;
     a.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
     a.first = combine_first_row(N, k, (size_t)a.C * 16);
+    a.stores = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4),
+                          y_dtype == FUSCO_BF16 && out_dtype == FUSCO_F32);
     if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_combine<true, true>(a, N, s, e0, e1);
     else if (y_dtype == FUSCO_BF16) launch_combine<true, false>(a, N, s, e0, e1);
     else if (out_dtype == FUSCO_BF16) launch_combine<false, true>(a, N, s, e0, e1);

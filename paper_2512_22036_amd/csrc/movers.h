@@ -60,6 +60,7 @@ struct DispatchArgs {
     int32_t k;
     int32_t C, Ca;   // 16-byte chunks per row in the main and in the aux plane
     int32_t write_expert, write_wire;
+    int32_t through, through_aux;   // tiled mode: expert rows (of the main and of the aux plane) start on 64-byte boundaries
 };
 
 constexpr int kXcds = 8;                                  // accelerator complexes of an MI355X
@@ -205,7 +206,9 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
             const int c = c0 + q * blockDim.x;
             u32x4 *dst = a.expert_buf + (size_t)slot * a.C + c;
             if (AUX && c >= a.C) dst = a.expert_aux + (size_t)slot * a.Ca + (c - a.C);
-            if (c < c_end) store16_through_stream(dst, v[q]);
+            if (c >= c_end) continue;
+            if (AUX && c >= a.C ? a.through_aux : a.through) store16_through_stream(dst, v[q]);
+            else __builtin_nontemporal_store(v[q], dst);
         }
     }
     if (pull) {
@@ -287,6 +290,22 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
     }
 }
 
+// Stores of combine's output rows (out_stores chooses).
+enum OutStores : int32_t { kOutThrough, kOutNonTemporal, kOutPlain };
+
+template <typename V>
+__device__ __forceinline__ void put_out(int32_t how, V *p, V v)
+{
+    if (how == kOutThrough) {
+        if constexpr (sizeof(V) == 16) store16_through(p, v);
+        else store8_through(p, v);
+    } else if (how == kOutNonTemporal) {
+        __builtin_nontemporal_store(v, p);
+    } else {
+        *p = v;
+    }
+}
+
 // Combine: every thread owns CPT 16-byte chunks of the output row, pulls the matching chunks of
 // the token's k rows (JU rows in flight at a time) and accumulates in fp32 with one fused
 // multiply-add per term in ascending j.
@@ -300,6 +319,7 @@ struct CombineArgs {
     int32_t first;   // row handled by workgroup 0; the walk goes upwards from there and wraps around
     int32_t n_rows;  // rows of the walk (tokens, or send rows in the per-send-row mode)
     int32_t segs;    // workgroups per row: the columns of a row longer than one workgroup covers
+    int32_t stores;  // of the output rows: OutStores
     // per-send-row mode (level 2 reversed): one workgroup per send row, only the token's entries on that row
     const int32_t *pair_send_row, *send_src, *n_rows_dev;
 };
@@ -395,17 +415,17 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
             for (int q = 0; q < EPC / 2; ++q) pk[q] = to_bf16(acc[i][2 * q]) | (to_bf16(acc[i][2 * q + 1]) << 16);
             if constexpr (Y_BF16) {
                 u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-                store16_through((u32x4 *)((uint16_t *)a.out + e0), o);
+                put_out(a.stores, (u32x4 *)((uint16_t *)a.out + e0), o);
             } else {
                 u32x2 o = {pk[0], pk[1]};
-                store8_through((u32x2 *)((uint16_t *)a.out + e0), o);
+                put_out(a.stores, (u32x2 *)((uint16_t *)a.out + e0), o);
             }
         } else {
 #pragma unroll
             for (int h = 0; h < EPC / 4; ++h) {
                 u32x4 o = {__float_as_uint(acc[i][4 * h]), __float_as_uint(acc[i][4 * h + 1]),
                            __float_as_uint(acc[i][4 * h + 2]), __float_as_uint(acc[i][4 * h + 3])};
-                store16_through((u32x4 *)((float *)a.out + e0) + h, o);
+                put_out(a.stores, (u32x4 *)((float *)a.out + e0) + h, o);
             }
         }
     }

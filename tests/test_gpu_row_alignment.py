@@ -1,0 +1,83 @@
+"""Rows that do not consist of whole 64-byte units - by their size or by where the tensor starts - take other stores
+than rows that do: tiled dispatch (both planes) and combine's output, at the sizes where the choice is made.  Moved
+bytes are compared with torch.equal; combine's sums bit for bit with the oracle's (fp32 fused multiply-adds in order,
+one rounding), so there is no tolerance."""
+import numpy as np
+import pytest
+import torch
+
+from definitions import random_topk
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_at(rows, row_bytes, offset):
+    """A [rows, row_bytes] byte tensor that starts `offset` bytes into its allocation, filled with 0xEE, and the whole."""
+    room = torch.full((rows * row_bytes + 256,), 0xEE, dtype=torch.uint8, device="cuda")
+    return room[offset:offset + rows * row_bytes].view(rows, row_bytes), room
+
+
+@pytest.mark.parametrize("row_bytes,aux_bytes,offset", [(4096, 0, 0), (4096, 0, 16), (4112, 0, 0), (4160, 64, 0), (4160, 224, 0),
+                                                        (4096, 128, 32), (5008, 48, 48), (48, 16, 0), (16384 + 16, 0, 16)])
+def test_tiled_dispatch(row_bytes, aux_bytes, offset):
+    import paper_2512_22036_amd as f
+    N, k, E, D = 4200, 8, 64, 8
+    rng = np.random.default_rng(row_bytes + aux_bytes + offset)
+    A = torch.from_numpy(random_topk(rng, N, k, E)).cuda()
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, A)
+    x = torch.randint(0, 256, (N, row_bytes), dtype=torch.uint8, device="cuda")
+    xa = torch.randint(0, 256, (N, aux_bytes), dtype=torch.uint8, device="cuda") if aux_bytes else None
+    eb, room = rows_at(L.P, row_bytes, offset)
+    ea, room_a = rows_at(L.P, aux_bytes, offset) if aux_bytes else (None, None)
+    assert f.fusco_probe_dispatch_kernel(2) == 0
+    try:
+        assert f.fusco_dispatch_in_transfer_order(L, row_bytes, aux_bytes)
+        f.fusco_dispatch(L, x, eb, x_aux=xa, expert_aux=ea)
+    finally:
+        f.fusco_probe_dispatch_kernel(0)
+    token = L.array("slot_token").long()
+    assert torch.equal(eb, x[token])
+    assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + eb.numel():] == 0xEE).all())
+    if aux_bytes:
+        assert torch.equal(ea, xa[token])
+        assert bool((room_a[:offset] == 0xEE).all()) and bool((room_a[offset + ea.numel():] == 0xEE).all())
+
+
+@pytest.mark.parametrize("N", [40, 2500])     # below and above 64 MiB of expert outputs
+@pytest.mark.parametrize("H", [4096, 4104])
+@pytest.mark.parametrize("offset", [0, 16])
+@pytest.mark.parametrize("y_f32,out_f32", [(False, False), (False, True), (True, False), (True, True)])
+def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
+    import paper_2512_22036_amd as f
+    k, E, D = 8, 64, 8
+    rng = np.random.default_rng(N + H)
+    A = random_topk(rng, N, k, E)
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    y = torch.randn((L.P, H), device="cuda").to(torch.float32 if y_f32 else torch.bfloat16)
+    w = torch.rand((N, k), device="cuda")
+    kind = torch.float32 if out_f32 else torch.bfloat16
+    out, room = rows_at(N, H * (4 if out_f32 else 2), offset)
+    out = out.view(kind)
+    f.fusco_combine(L, y, w, out)
+    slots = L.array("pair_slot").cpu().numpy()
+    few = np.unique(rng.integers(0, N, size=64))           # the oracle is slow: some tokens, first and last among them
+    few[0], few[-1] = 0, N - 1
+    pick = torch.from_numpy(slots.reshape(N, k)[few].reshape(-1)).cuda().long()
+    rows = y[pick].cpu()
+    rows = rows.numpy() if y_f32 else rows.view(torch.int16).numpy().view(np.uint16)
+    want32, want16 = oracle.combine_f32(rows, w[torch.from_numpy(few).cuda()].cpu().numpy(),
+                                        np.arange(len(few) * k, dtype=np.int32))
+    got = out[torch.from_numpy(few).cuda()].cpu()
+    if out_f32:
+        assert np.array_equal(got.numpy().view(np.uint32), want32.view(np.uint32))
+    else:
+        assert np.array_equal(got.view(torch.int16).numpy().view(np.uint16), want16)
+    # the others against the same sum in plain torch: k products and sums of one rounding each
+    exact = (w[:, :, None].double() * y[torch.from_numpy(slots).cuda().long()].view(N, k, H).double()).sum(1) if N < 100 else None
+    if exact is not None:
+        size = (w[:, :, None].double() * y[torch.from_numpy(slots).cuda().long()].view(N, k, H).double().abs()).sum(1)
+        bound = size * k * 2.0 ** -24 + (0 if out_f32 else exact.abs() * 2.0 ** -8)
+        assert bool(((out.double() - exact).abs() <= bound).all())
+    assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
