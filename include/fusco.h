@@ -155,7 +155,8 @@ int fusco_plan_static(fusco_layout *L, const int32_t *d_topk_idx, void *stream);
  * fusco_dispatch_in_transfer_order): every XCD of the GPU takes whole tiles of tokens and writes their rows
  * expert by expert with streaming stores, the tile's source rows being read from memory once and from the
  * XCD's L2 afterwards while they stay there.  A source tensor of more than 128 MiB is taken in chunks of tiles,
- * each chunk after a sequential read of its source rows (a few launches instead of one).  Otherwise every
+ * each chunk after a sequential read of its source rows (a few launches instead of one).  Where both tensors are
+ * written, the tile's send rows follow its pairs, device by device (for at most k devices).  Otherwise every
  * token's row is read once and stored to its k rows at once (token walk).
  * Rows are opaque bytes.  d_x: [N, row_bytes], row_bytes a positive multiple of 16.  An optional
  * second plane (e.g. per-block scales of an fp8 payload) of aux_row_bytes (multiple of 16, or 0

@@ -278,6 +278,12 @@ static bool tiled_shape(const fusco_layout *L, int Ct, int &threads, int &cpt, i
     return true;
 }
 
+// Whether fusco_dispatch that writes both tensors moves the rows of the receive tensors tile by tile after the pairs of
+// the tile (dispatch_tiled_kernel's WIRE): where the pairs alone would be moved in transfer order, and with at most as
+// many devices as entries per token, so that most of the (token, device) entries of a tile move a row.  (The receive
+// tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
+static bool wire_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes);
+
 // the conditions under which fusco_dispatch moves the rows tile by tile in transfer order
 static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, bool expert,
                                        bool wire, bool two_hop)
@@ -306,6 +312,12 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     if (row < kTiledShortRowBytes / 2 && source >= limit) return false;
     if (source > limit && !(L->k >= 8 || (L->k >= 5 && segs == 1))) return false;
     return true;
+}
+
+static bool wire_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes)
+{
+    return g_dispatch_kernel.load(std::memory_order_relaxed) == 0 && L->D <= L->k &&
+           dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, true, false, false);
 }
 
 int fusco_dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, uint32_t flags)
@@ -365,12 +377,16 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
 
     // Expert tensor alone, enough tiles to keep every XCD busy, and a tile's source rows small enough to stay
     // in one XCD's 4 MB L2: the rows are moved tile by tile in transfer order (dispatch_tiled_kernel).
-    if (dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
+    const bool tiled_wire = expert && wire && !two_hop && wire_in_transfer_order(L, row_bytes, aux_row_bytes);
+    if (tiled_wire || dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
         a.slot_token = L->slot_token; a.tile_slots = L->tile_slots;
         a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
         tiled_shape(L, Ct, threads, cpt, segs, per);
         a.segs = segs; a.seg_chunks = per;
-        a.through = whole_units(d_expert_buf, row_bytes); a.through_aux = whole_units(d_expert_aux, aux_row_bytes);
+        a.send_off = L->send_off; a.D = L->D;
+        a.through = whole_units(d_expert_buf, row_bytes) && (!wire || whole_units(d_send_buf, row_bytes));
+        a.through_aux = whole_units(d_expert_aux, aux_row_bytes) && (!wire || whole_units(d_send_aux, aux_row_bytes));
+        const uint64_t entries = (uint64_t)a.tile_cap + (tiled_wire ? (uint64_t)L->D * (uint64_t)L->tile_tokens : 0);
         // a source tensor that cannot stay in the memory-side cache is taken in chunks of whole rounds of tiles
         // whose rows fit half of it, every chunk after a sequential read of its source rows (touch_kernel)
         const size_t source_bytes = (size_t)L->N * (row_bytes + aux_row_bytes);
@@ -382,7 +398,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
             if (chunk_tiles < (size_t)kXcds) chunk_tiles = kXcds;
         }
         // the largest launch: a workgroup per row and segment of the chunk's tiles (checked before anything is launched)
-        if ((uint64_t)((chunk_tiles + kXcds - 1) / kXcds) * (uint64_t)a.tile_cap * (uint64_t)segs * kXcds > 0x7fffffffu)
+        if ((uint64_t)((chunk_tiles + kXcds - 1) / kXcds) * entries * (uint64_t)segs * kXcds > 0x7fffffffu)
             return FUSCO_ERR_INVALID_ARG;
         const dim3 tblock((unsigned)threads);
         // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
@@ -410,16 +426,21 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
                     launch_args(touch_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, (hipEvent_t) nullptr, (hipEvent_t) nullptr,
                            a.x_aux + t0 * (size_t)a.Ca, na);
             }
-            const unsigned tblocks = (unsigned)((tiles_here + kXcds - 1) / kXcds) * (unsigned)a.tile_cap * (unsigned)segs * kXcds;
+            const unsigned tblocks = (unsigned)((tiles_here + kXcds - 1) / kXcds) * (unsigned)entries * (unsigned)segs * kXcds;
             hipEvent_t e0 = first && !chunked ? ev.start : nullptr, e1 = last ? ev.stop : nullptr;
             const uint32_t tb = (uint32_t)tile0, th = (uint32_t)tiles_here;
             const dim3 tgrid(tblocks);
+#define FUSCO_TILED_AS(CPT, AUX, WIRE)                                                                \
+    do {                                                                                              \
+        if (pull) launch_args(dispatch_tiled_kernel<CPT, AUX, true, WIRE>, tgrid, tblock, lds, s, e0, e1, a, tb, th);  \
+        else launch_args(dispatch_tiled_kernel<CPT, AUX, false, WIRE>, tgrid, tblock, lds, s, e0, e1, a, tb, th);      \
+    } while (0)
 #define FUSCO_TILED(CPT)                                                                              \
     do {                                                                                              \
-        if (a.Ca && pull) launch_args(dispatch_tiled_kernel<CPT, true, true>, tgrid, tblock, lds, s, e0, e1, a, tb, th);        \
-        else if (a.Ca) launch_args(dispatch_tiled_kernel<CPT, true, false>, tgrid, tblock, lds, s, e0, e1, a, tb, th);          \
-        else if (pull) launch_args(dispatch_tiled_kernel<CPT, false, true>, tgrid, tblock, lds, s, e0, e1, a, tb, th);          \
-        else launch_args(dispatch_tiled_kernel<CPT, false, false>, tgrid, tblock, lds, s, e0, e1, a, tb, th);                   \
+        if (a.Ca && tiled_wire) FUSCO_TILED_AS(CPT, true, true);                                      \
+        else if (a.Ca) FUSCO_TILED_AS(CPT, true, false);                                              \
+        else if (tiled_wire) FUSCO_TILED_AS(CPT, false, true);                                        \
+        else FUSCO_TILED_AS(CPT, false, false);                                                       \
     } while (0)
             switch (cpt) {
             case 1: FUSCO_TILED(1); break;
@@ -427,6 +448,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
             default: FUSCO_TILED(4); break;
             }
 #undef FUSCO_TILED
+#undef FUSCO_TILED_AS
         }
         return launch_status();
     }
@@ -497,6 +519,9 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
         f.pair_slot = L->pair_slot; f.pair_send_row = L->pair_send_row; f.pair_first = L->pair_first;
         f.k = L->k;
         f.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
+        f.stores = out_stores((size_t)L->P * (size_t)f.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
+        // 4096 tokens x 8 rows of 14 KiB, 21700 partial rows: 228 us plain, 239 us written through, 280 us non-temporal
+        f.partial_stores = kOutPlain;
         int th = round_up(f.C, kWave);
         if (th > 1024) th = 1024;
         const dim3 fgrid((unsigned)L->N, (unsigned)((f.C + th - 1) / th));
@@ -518,7 +543,7 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
     a.pair_send_row = L->pair_send_row; a.send_src = L->send_src; a.n_rows_dev = L->send_off + L->D;
     a.first = 0;
     a.n_rows = L->send_cap;
-    a.stores = kOutNonTemporal;
+    a.stores = kOutPlain;
     int threads;
     combine_shape(a.C, threads, a.segs);
     const dim3 grid((unsigned)L->send_cap * (unsigned)a.segs);

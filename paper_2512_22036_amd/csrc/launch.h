@@ -165,11 +165,11 @@ bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_
 // 14 KiB 377.7 / 366.8 us, 16384 x 8 x 8 KiB 434 / 428 us, 32768 x 8 x 14 KiB 1466 / 1447 us, fp32 8192 x 4 x 8 KiB with
 // its gradients 270 / 257 us; rows that are not whole units 8192 x 8 x 14352 B: combine 199 us written through, 209 us
 // plain, 178 us).  Small ones stay in that cache for their reader: written through where a wave's stores cover whole
-// units, plain otherwise (fp32 rows of 16 KiB from bf16 ones, 1024 tokens: 43.5 us written through, 41.0 us plain).
-OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes, bool every_other_16_bytes)
+// units, plain otherwise.
+OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes)
 {
     if (y_bytes >= kCombineLatencyBoundBytes) return kOutNonTemporal;
-    return whole_units(out, row_bytes) && !every_other_16_bytes ? kOutThrough : kOutPlain;
+    return whole_units(out, row_bytes) ? kOutThrough : kOutPlain;
 }
 
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked
@@ -186,8 +186,7 @@ void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int
     a.pair_send_row = nullptr; a.send_src = nullptr; a.n_rows_dev = nullptr;
     a.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
     a.first = combine_first_row(N, k, (size_t)a.C * 16);
-    a.stores = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4),
-                          y_dtype == FUSCO_BF16 && out_dtype == FUSCO_F32);
+    a.stores = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
     if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_combine<true, true>(a, N, s, e0, e1);
     else if (y_dtype == FUSCO_BF16) launch_combine<true, false>(a, N, s, e0, e1);
     else if (out_dtype == FUSCO_BF16) launch_combine<false, true>(a, N, s, e0, e1);

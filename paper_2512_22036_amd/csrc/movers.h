@@ -60,6 +60,8 @@ struct DispatchArgs {
     int32_t k;
     int32_t C, Ca;   // 16-byte chunks per row in the main and in the aux plane
     int32_t write_expert, write_wire;
+    const int32_t *send_off;                  // tiled mode with the wire tensor: first send row of every device
+    int32_t D;
     int32_t through, through_aux;   // tiled mode: expert rows (of the main and of the aux plane) start on 64-byte boundaries
 };
 
@@ -153,20 +155,45 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
 // PULL: the first tile_tokens workgroups of a pass also read one source row of the tile each (see below).
 // AUX: the second plane exists.  A chunk's source and destination are picked by address selection, not by
 // branching, so that the loads of a thread are issued back to back (a branch per chunk costs 3 % here).
+// WIRE: the per-device receive tensors are written too.  After its pairs a tile has one entry
+// per device and token, device by device: the send rows of a tile's tokens on a device are neighbours, so an XCD writes
+// runs of up to tile_tokens rows, from source rows that are still in its L2; an entry whose token has no row on the
+// device does nothing.  4096 tokens x 8 rows of 14 KiB on 8 devices (21700 send rows), both tensors: 143 us, 157 us by
+// the token walk; in a step 392 against 417 us.
 // The launch covers the tiles [tile_base, tile_base + tiles_here).
-template <int CPT, bool AUX, bool PULL>
+template <int CPT, bool AUX, bool PULL, bool WIRE>
 __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uint32_t tile_base, uint32_t tiles_here)
 {
     // a tile is worked through a.segs times, once per column segment of the rows (one pass for rows that a
     // workgroup covers): the L2 then only has to hold that segment of the tile's source rows
     const uint32_t b = blockIdx.x, x = b & (kXcds - 1), i = b / kXcds;
-    const uint32_t per_tile = (uint32_t)a.tile_cap * (uint32_t)a.segs;
+    const uint32_t pairs = (uint32_t)a.tile_cap;
+    const uint32_t entries = WIRE ? pairs + (uint32_t)a.D * (uint32_t)a.tile_tokens : pairs;
+    const uint32_t per_tile = entries * (uint32_t)a.segs;
     const uint32_t round = i / per_tile, w = i - round * per_tile;
-    const uint32_t pass = w / (uint32_t)a.tile_cap, r = w - pass * (uint32_t)a.tile_cap;
+    const uint32_t pass = w / entries, r = w - pass * entries;
     const uint32_t local = x + kXcds * round;
     if (local >= tiles_here) return;
     const uint32_t tile = tile_base + local;
-    const int slot = a.tile_slots[(size_t)tile * a.tile_cap + r];
+    const bool wire = WIRE && r >= pairs;
+    // destination row, in the expert or in the wire tensor, and source token; -1: nothing to move
+    int row = -1, t = 0;
+    if (!wire) {
+        row = a.tile_slots[(size_t)tile * a.tile_cap + r];
+    } else {
+        const uint32_t q = r - pairs, d = q / (uint32_t)a.tile_tokens;
+        t = (int)(tile * (uint32_t)a.tile_tokens + (q - d * (uint32_t)a.tile_tokens));
+        if (t < a.N) {
+            // the token's entry for the device, by the device's range of send rows
+            const int lo = a.send_off[d], hi = a.send_off[d + 1];
+            const int32_t *rows = a.pair_send_row + (size_t)t * a.k;
+            for (int j = 0; j < a.k; ++j) {
+                const int s = rows[j];
+                row = s >= lo && s < hi ? s : row;
+            }
+        }
+    }
+    u32x4 *const out = wire ? a.send_buf : a.expert_buf, *const out_aux = wire ? a.send_aux : a.expert_aux;
     const int Ct = AUX ? a.C + a.Ca : a.C;
     // PULL: the first tile_tokens workgroups of a pass also read one source row of the tile each (the segment
     // of it that this pass moves) and drop it.  All of the tile's source rows are then on their way to the L2
@@ -186,8 +213,8 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
             if (c < p_end) p[q] = *src;
         }
     }
-    if (slot >= 0) {
-        const int t = a.slot_token[slot];
+    if (row >= 0) {
+        if (!wire) t = a.slot_token[row];
         // which segment a pass moves rotates with the token: the segments in use during a pass then lie at different
         // offsets in their rows, and rows whose size is a power of two do not all fall on the same sets of the L2
         const uint32_t seg = a.segs > 1 ? (pass + (uint32_t)t) % (uint32_t)a.segs : 0u;
@@ -204,8 +231,8 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
             const int c = c0 + q * blockDim.x;
-            u32x4 *dst = a.expert_buf + (size_t)slot * a.C + c;
-            if (AUX && c >= a.C) dst = a.expert_aux + (size_t)slot * a.Ca + (c - a.C);
+            u32x4 *dst = out + (size_t)row * a.C + c;
+            if (AUX && c >= a.C) dst = out_aux + (size_t)row * a.Ca + (c - a.C);
             if (c >= c_end) continue;
             if (AUX && c >= a.C ? a.through_aux : a.through) store16_through_stream(dst, v[q]);
             else __builtin_nontemporal_store(v[q], dst);
@@ -303,6 +330,28 @@ __device__ __forceinline__ void put_out(int32_t how, V *p, V v)
         __builtin_nontemporal_store(v, p);
     } else {
         *p = v;
+    }
+}
+
+// The eight floats of chunk c of a bf16 row, as chunks 2 c and 2 c + 1 of an fp32 row of n chunks.  Stored as they are, the
+// lanes of a wave would write every other 16 bytes twice; exchanged inside quads of lanes, each of the two stores covers
+// whole 64-byte units (combine to fp32 rows of 16 KiB, 8192 tokens x 8: 118 us, 132 us without the exchange, both
+// non-temporal).  Every lane of the wave takes part, also those whose chunk lies past the row.
+__device__ __forceinline__ void put_floats(int32_t how, u32x4 *row, int c, int n, const float (&f)[8])
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        u32x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int lo = (int)__float_as_uint(f[q]), hi = (int)__float_as_uint(f[4 + q]);
+            // lane j of a quad stores chunk j of the quad's first (second) four: the half j mod 2 of lane j / 2 (2 + j / 2)
+            const int from_lo = h == 0 ? __builtin_amdgcn_update_dpp(0, lo, 0x50, 0xf, 0xf, true) : __builtin_amdgcn_update_dpp(0, lo, 0xFA, 0xf, 0xf, true);
+            const int from_hi = h == 0 ? __builtin_amdgcn_update_dpp(0, hi, 0x50, 0xf, 0xf, true) : __builtin_amdgcn_update_dpp(0, hi, 0xFA, 0xf, 0xf, true);
+            o[q] = (uint32_t)((c & 1) ? from_hi : from_lo);
+        }
+        const int at = (c & ~3) * 2 + h * 4 + (c & 3);
+        if (at < n) put_out(how, row + at, o);
     }
 }
 
@@ -407,6 +456,10 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = c0 + i * blockDim.x;
+        if constexpr (Y_BF16 && !OUT_BF16) {
+            put_floats(a.stores, (u32x4 *)a.out + (size_t)r * a.C * 2, c, a.C * 2, acc[i]);
+            continue;
+        }
         if (c >= a.C) continue;
         const size_t e0 = ((size_t)r * a.C + c) * EPC;   // first output element of this chunk
         if constexpr (OUT_BF16) {
@@ -444,6 +497,7 @@ struct TwoHopArgs {
     const uint8_t *pair_first;
     int32_t k;
     int32_t C;   // 16-byte chunks per y row
+    int32_t stores, partial_stores;   // OutStores of the output rows and of the partial rows
 };
 
 template <bool Y_BF16, bool OUT_BF16>
@@ -453,7 +507,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
     constexpr int KMAX = 8;
     const int t = gridDim.x - 1 - blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
-    if (c >= a.C) return;
+    const bool in = c < a.C;   // lanes past the row take part in the exchange of put_floats
     const int32_t *slots = a.pair_slot + (size_t)t * a.k;
     const int32_t *rows = a.pair_send_row + (size_t)t * a.k;
     const uint8_t *first = a.pair_first + (size_t)t * a.k;
@@ -475,7 +529,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             lead[j] = first[j];
             if (slot >= 0) {
                 on[j] = true;
-                v[j] = load16_stream(a.y + (size_t)slot * a.C + c);
+                if (in) v[j] = load16_stream(a.y + (size_t)slot * a.C + c);
             }
         }
     }
@@ -502,16 +556,21 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
                 for (int q = 0; q < 4; ++q) acc[q] = __builtin_fmaf(wj[j], __uint_as_float(v[j][q]), acc[q]);
             }
         }
-        u32x4 *prow = (u32x4 *)(a.partial + ((size_t)row[f] * a.C + c) * EPC);
-#pragma unroll
-        for (int h = 0; h < EPC / 4; ++h) {
-            const u32x4 o = {__float_as_uint(acc[4 * h]), __float_as_uint(acc[4 * h + 1]),
-                             __float_as_uint(acc[4 * h + 2]), __float_as_uint(acc[4 * h + 3])};
-            prow[h] = o;
+        u32x4 *prow = (u32x4 *)a.partial + (size_t)row[f] * a.C * (EPC / 4);
+        if constexpr (Y_BF16) {
+            put_floats(a.partial_stores, prow, c, a.C * 2, acc);
+        } else if (in) {
+            const u32x4 o = {__float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]), __float_as_uint(acc[3])};
+            put_out(a.partial_stores, prow + c, o);
         }
 #pragma unroll
         for (int e = 0; e < EPC; ++e) total[e] = total[e] + acc[e];
     }
+    if constexpr (Y_BF16 && !OUT_BF16) {
+        put_floats(a.stores, (u32x4 *)a.out + (size_t)t * a.C * 2, c, a.C * 2, total);
+        return;
+    }
+    if (!in) return;
     const size_t e0 = ((size_t)t * a.C + c) * EPC;
     if constexpr (OUT_BF16) {
         uint32_t pk[EPC / 2];
@@ -519,17 +578,17 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
         for (int q = 0; q < EPC / 2; ++q) pk[q] = to_bf16(total[2 * q]) | (to_bf16(total[2 * q + 1]) << 16);
         if constexpr (Y_BF16) {
             const u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-            store16_through((u32x4 *)((uint16_t *)a.out + e0), o);
+            put_out(a.stores, (u32x4 *)((uint16_t *)a.out + e0), o);
         } else {
             const u32x2 o = {pk[0], pk[1]};
-            store8_through((u32x2 *)((uint16_t *)a.out + e0), o);
+            put_out(a.stores, (u32x2 *)((uint16_t *)a.out + e0), o);
         }
     } else {
 #pragma unroll
         for (int h = 0; h < EPC / 4; ++h) {
             const u32x4 o = {__float_as_uint(total[4 * h]), __float_as_uint(total[4 * h + 1]),
                              __float_as_uint(total[4 * h + 2]), __float_as_uint(total[4 * h + 3])};
-            store16_through((u32x4 *)((float *)a.out + e0) + h, o);
+            put_out(a.stores, (u32x4 *)((float *)a.out + e0) + h, o);
         }
     }
 }

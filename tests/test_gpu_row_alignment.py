@@ -81,3 +81,45 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
         bound = size * k * 2.0 ** -24 + (0 if out_f32 else exact.abs() * 2.0 ** -8)
         assert bool(((out.double() - exact).abs() <= bound).all())
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
+
+
+@pytest.mark.parametrize("N,k,E,D,row_bytes,aux_bytes,limit", [
+    (4200, 8, 256, 8, 8448, 0, 0),              # 17 tiles, the last one ragged; as many devices as entries
+    (4200, 8, 64, 4, 8192 + 16, 64, 0),         # rows that are not whole units, a second plane
+    (2300, 16, 64, 2, 8192, 0, 0),              # two devices: nearly every token has a row on both; 128 tokens per tile
+    (4200, 8, 64, 1, 8448, 48, 0),              # one device
+    (4200, 8, 64, 8, 16384 + 1040, 0, 0),       # two column segments
+    (4200, 8, 256, 8, 8448, 0, 16 << 20),       # source rows taken in chunks of 8 tiles
+])
+def test_both_tensors_tile_by_tile(N, k, E, D, row_bytes, aux_bytes, limit):
+    """Expert tensor of more than 256 MB and the receive tensors in one call: large enough for the tiles by itself.
+    Invalid ids and repeated experts among the entries; rows past the last send row stay untouched."""
+    import paper_2512_22036_amd as f
+    rng = np.random.default_rng(N + D)
+    A = random_topk(rng, N, k, E, distinct=False)
+    A[7, 2], A[N - 1, 0] = -1, E
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    x = torch.randint(0, 256, (N, row_bytes), dtype=torch.uint8, device="cuda")
+    xa = torch.randint(0, 256, (N, aux_bytes), dtype=torch.uint8, device="cuda") if aux_bytes else None
+
+    def filled(rows, width):
+        return torch.full((rows, width), 0xEE, dtype=torch.uint8, device="cuda") if width else None
+
+    got = dict(expert_buf=filled(L.P, row_bytes), expert_aux=filled(L.P, aux_bytes), send_buf=filled(L.send_cap, row_bytes),
+               send_aux=filled(L.send_cap, aux_bytes))
+    before = f.fusco_probe_source_chunk_bytes(limit) if limit else 0
+    try:
+        assert f.fusco_dispatch_in_transfer_order(L, row_bytes, aux_bytes)
+        f.fusco_dispatch(L, x, x_aux=xa, flags=f.DISPATCH_EXPERT | f.DISPATCH_WIRE, **got)
+    finally:
+        if limit:
+            f.fusco_probe_source_chunk_bytes(before)
+    valid = L.P - int(L.array("status").item())
+    U = int(L.array("send_off")[D].item())
+    token, source = L.array("slot_token")[:valid].long(), L.array("send_src")[:U].long()
+    assert torch.equal(got["expert_buf"][:valid], x[token]) and bool((got["expert_buf"][valid:] == 0xEE).all())
+    assert torch.equal(got["send_buf"][:U], x[source]) and bool((got["send_buf"][U:] == 0xEE).all())
+    if aux_bytes:
+        assert torch.equal(got["expert_aux"][:valid], xa[token]) and torch.equal(got["send_aux"][:U], xa[source])
+        assert bool((got["expert_aux"][valid:] == 0xEE).all()) and bool((got["send_aux"][U:] == 0xEE).all())
