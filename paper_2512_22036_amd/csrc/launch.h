@@ -159,17 +159,20 @@ int combine_first_row(int N, int k, size_t row_bytes)
 // (14336 B: 380 against 401 us with combine, 14400 B: 388 against 413 us).
 bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_bytes) & 63u) == 0; }
 
-// Stores of combine's output rows.  Inputs that are bound by memory: non-temporal, past the memory-side cache - what
-// write-through and plain stores leave dirty there costs the reads of the kernels around them more than it saves
-// (a step with the experts' output in a tensor of its own, written through / non-temporal: 8192 tokens x 8 rows of
-// 14 KiB 377.7 / 366.8 us, 16384 x 8 x 8 KiB 434 / 428 us, 32768 x 8 x 14 KiB 1466 / 1447 us, fp32 8192 x 4 x 8 KiB with
-// its gradients 270 / 257 us; rows that are not whole units 8192 x 8 x 14352 B: combine 199 us written through, 209 us
-// plain, 178 us).  Small ones stay in that cache for their reader: written through where a wave's stores cover whole
+// Stores of combine's output rows.  Inputs that are bound by memory: past the memory-side cache - what write-through
+// and plain stores leave dirty there costs the reads of the kernels around them more than it saves.  Steps with the
+// experts' output in a tensor of its own and other buffers in every step, written through / non-temporal / both at once,
+// us: 8192 tokens x 8 rows of 14 KiB 378.9 / 367.3 / 365.1, 16384 x 8 x 8 KiB 433.5 / 426.4 / 426.0, 32768 x 8 x 14 KiB
+// 1467 / 1437 / 1437.  (A loop over the same buffers whose x and output fit that cache together prefers to leave the
+// output there: 340.7 / 347.0 / 344.7 at 8192 x 8 x 14 KiB; 402 / 394 / 394 and 1461 / 1431 / 1429 at the other two.)
+// Rows that are not whole units, 8192 x 8 x 14352 B: combine 199 us written through, 209 us plain, 178 us
+// non-temporal.  Small outputs stay in that cache for their reader: written through where a wave's stores cover whole
 // units, plain otherwise.
 OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes)
 {
-    if (y_bytes >= kCombineLatencyBoundBytes) return kOutNonTemporal;
-    return whole_units(out, row_bytes) ? kOutThrough : kOutPlain;
+    const bool whole = whole_units(out, row_bytes);
+    if (y_bytes >= kCombineLatencyBoundBytes) return whole ? kOutThroughStream : kOutNonTemporal;
+    return whole ? kOutThrough : kOutPlain;
 }
 
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked

@@ -38,6 +38,10 @@ __device__ __forceinline__ void store16_through_stream(u32x4 *p, u32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
+__device__ __forceinline__ void store8_through_stream(u32x2 *p, u32x2 v)
+{
+    asm volatile("global_store_dwordx2 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
 // The same at system scope (sc0 sc1): for data that another agent may read once a flag says so.
 __device__ __forceinline__ void store16_system(u32x4 *p, u32x4 v)
 {
@@ -318,7 +322,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
 }
 
 // Stores of combine's output rows (out_stores chooses).
-enum OutStores : int32_t { kOutThrough, kOutNonTemporal, kOutPlain };
+enum OutStores : int32_t { kOutThrough, kOutThroughStream, kOutNonTemporal, kOutPlain };
 
 template <typename V>
 __device__ __forceinline__ void put_out(int32_t how, V *p, V v)
@@ -326,6 +330,9 @@ __device__ __forceinline__ void put_out(int32_t how, V *p, V v)
     if (how == kOutThrough) {
         if constexpr (sizeof(V) == 16) store16_through(p, v);
         else store8_through(p, v);
+    } else if (how == kOutThroughStream) {
+        if constexpr (sizeof(V) == 16) store16_through_stream(p, v);
+        else store8_through_stream(p, v);
     } else if (how == kOutNonTemporal) {
         __builtin_nontemporal_store(v, p);
     } else {
