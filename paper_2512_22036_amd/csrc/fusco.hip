@@ -113,7 +113,8 @@ static PlanArgs plan_args(const fusco_layout *L, const int32_t *d_topk_idx, void
     a.n_tiles = num_tiles(L->N, L->k, rounds);
     a.small_groups = a.n_tiles == 1 ? (L->P + kSmallPairs - 1) / kSmallPairs : 0;
     const int round_tokens = kPlanWaves * (kWave / L->k);
-    a.rank_rounds = (a.tpt + round_tokens - 1) / round_tokens;
+    const bool halved = chunk_tiles_for(a.n_tiles, rounds) == 0;
+    a.rank_rounds = ((halved ? first_half_tokens(a.tpt) : a.tpt) + round_tokens - 1) / round_tokens;
     a.stride = L->E + L->D + 1;
     a.tile_hist = (int32_t *)d_scratch;   // unused (may be NULL) when the input is a single tile
     a.chunk_tiles = chunk_tiles_for(a.n_tiles, rounds);
@@ -140,9 +141,14 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
         launch(plan_small_kernel, dim3(1u + (unsigned)a.small_groups), dim3(kSmallThreads), s, a, ev.start, ev.stop);
     } else {
         // inputs of several tiles are always planned in tiles of two rounds (plan_rounds)
-        launch(plan_rank_kernel, tiles, block, s, a, ev.start, nullptr);
-        if (a.n_chunks > 0) launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks), block, s, a);
-        launch(plan_place_kernel, tiles, block, s, a, nullptr, ev.stop);
+        if (a.n_chunks == 0) {
+            launch(plan_rank_kernel<true>, dim3(2u * (unsigned)a.n_tiles), block, s, a, ev.start, nullptr);
+            launch(plan_place_kernel<true>, tiles, block, s, a, nullptr, ev.stop);
+        } else {
+            launch(plan_rank_kernel<false>, tiles, block, s, a, ev.start, nullptr);
+            launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks), block, s, a);
+            launch(plan_place_kernel<false>, tiles, block, s, a, nullptr, ev.stop);
+        }
     }
     return launch_status();
 }

@@ -14,10 +14,10 @@ struct PlanArgs {
     int32_t N, k, E, D, Eloc;
     uint32_t k_magic, eloc_magic;   // ceil(2^20 / k), ceil(2^20 / Eloc): see div20
     int32_t tpt;      // tokens per tile
-    int32_t rank_rounds;   // rounds of 16 waves x (64 / k) tokens in a tile
+    int32_t rank_rounds;   // rounds of 16 waves x (64 / k) tokens of a workgroup of pass 1
     int32_t n_tiles;
     int32_t small_groups;   // single-tile planner: workgroups that write descriptors
-    int32_t stride;   // ints per tile in tile_hist: E expert counts, D device counts, 1 invalid count
+    int32_t stride;   // words per tile in tile_hist: E expert counts, D device counts, 1 invalid count; 16 bits for each half of the tile
     int32_t *tile_hist;
     int32_t chunk_tiles, n_chunks;   // 0, 0: no chunk level
     int32_t *chunk_hist;             // [n_chunks][stride]: tile_hist summed over the tiles of a chunk
@@ -90,7 +90,17 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
 // wave keeps its running count of every key in a byte of LDS; the 16 waves' bytes of a key lie next to each other, so
 // that one 16-byte read and four byte sums give the pairs in earlier waves.  A wave takes whole tokens (64 / k of them
 // per round), so that a device's first appearance in a token is settled among its lanes.
-constexpr int kRankRounds = 4;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens
+//
+// HALVED: a tile is shared by two workgroups, the first one taking half of its tokens (rounded
+// up): the ranking is bound by the instructions of its waves, and a compute unit ranks 1024 pairs in half the time of
+// 2048.  Their counts are the halves of the tile's 32-bit words (at most 1024 + 63 pairs each), and ranks are within the
+// half.  Chosen where there is no chunk level; with more tiles the chip is full and the halves only cost pass 2 (plan
+// alone, k = 8, one / two workgroups per tile: 1000 tokens 10.9 / 10.3 us, 16384 14.5 / 14.0, 24700 16.1 / 16.5,
+// 49152 17.0 / 18.3 us).
+constexpr int kRankRounds = 4;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens (half of it: 2)
+
+__host__ __device__ __forceinline__ int first_half_tokens(int tile_tokens) { return (tile_tokens + 1) / 2; }
+__device__ __forceinline__ int both_halves(int counts) { return (int)(((uint32_t)counts & 0xFFFFu) + ((uint32_t)counts >> 16)); }
 
 __device__ __forceinline__ int sum_bytes(u32x4 v)
 {
@@ -103,13 +113,17 @@ __device__ __forceinline__ int packed_rank(int v) { return v & 2047; }
 __device__ __forceinline__ int packed_key(int v) { return v >> 11 & 1023; }
 __device__ __forceinline__ bool packed_first(int v) { return v >> 21 & 1; }
 
+template <bool HALVED>
 __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
 {
     __shared__ u32x4 cnt[2 * kMaxBins];   // [key]: a byte per wave, experts then devices
     __shared__ int invalid;
     uint8_t *byte = (uint8_t *)cnt;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int tok0 = blockIdx.x * a.tpt, ntok = min(a.tpt, a.N - tok0);
+    // tokens from tile * tpt + half * split on; there may be none for the second half
+    const int tile = HALVED ? blockIdx.x >> 1 : blockIdx.x, half = HALVED ? blockIdx.x & 1 : 0;
+    const int split = HALVED ? first_half_tokens(a.tpt) : a.tpt;
+    const int tok0 = tile * a.tpt + half * split, ntok = min(half ? a.tpt - split : split, a.N - tok0);
     const int64_t pair0 = (int64_t)tok0 * a.k;
     const int nb = a.E + a.D, ebits = bits_for(a.E), dbits = bits_for(a.D);
     const int per_wave = div20(kWave, a.k_magic), tok = div20(lane, a.k_magic);
@@ -151,9 +165,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
     if (bad && lane == 0) atomicAdd(&invalid, bad);
     __syncthreads();
 
-    int32_t *out = a.tile_hist + (int64_t)blockIdx.x * a.stride;
-    for (int b = tid; b < nb; b += kPlanThreads) out[b] = sum_bytes(cnt[b]);
-    if (tid == 0) out[nb] = invalid;
+    int32_t *out = a.tile_hist + (int64_t)tile * a.stride;
+    for (int b = tid; b <= nb; b += kPlanThreads) {
+        const int c = b < nb ? sum_bytes(cnt[b]) : invalid;
+        if constexpr (HALVED) ((uint16_t *)(out + b))[half] = (uint16_t)c;
+        else out[b] = c;
+    }
     u32x4 earlier;   // the bytes of the waves before this one
 #pragma unroll
     for (int q = 0; q < 4; ++q) earlier[q] = wave >= 4 * q + 4 ? ~0u : wave <= 4 * q ? 0u : (1u << 8 * (wave - 4 * q)) - 1;
@@ -219,6 +236,7 @@ constexpr int kMaxChunks = 2 * (kMaxBins / kWave);   // groups of 64 experts, th
 
 // Sums of one column over the rows part, part + parts, ... of a list of n rows; rows below `limit` also count towards
 // `before`.  Loads are issued back to back: beyond the list they read its last row, and their values are left out.
+template <bool HALVED>
 struct RowSums {
     const char *rows;
     int n, part, parts, limit;
@@ -243,8 +261,9 @@ struct RowSums {
         for (int i = 0; i < NV; ++i) {
             const int first = (i0 + i) * parts;
             if (first >= n) break;
-            total += part < n - first ? v[i] : 0;
-            before += part < limit - first ? v[i] : 0;
+            const int c = HALVED ? both_halves(v[i]) : v[i];
+            total += part < n - first ? c : 0;
+            before += part < limit - first ? c : 0;
         }
     }
     __device__ __forceinline__ void walk(int i0)   // eight loads in flight
@@ -257,13 +276,16 @@ struct RowSums {
     }
 };
 
+// HALVED as in pass 1 (there is no chunk level then).
 // (80 scalar registers: with more, a compute unit takes one workgroup of 16 waves at a time instead of two)
+template <bool HALVED>
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) void plan_place_kernel(PlanArgs a)
 {
     // per group of threads and column: total over all tiles, and over the earlier ones (`before` again holds the place
     // where the tile's run of the key starts, without its group's offset)
     __shared__ int total[2 * kMaxBins], before[2 * kMaxBins];
     __shared__ int tile_at[kMaxBins];                          // start of the expert's run in the tile, within its group
+    __shared__ uint16_t half_cnt[HALVED ? 2 * kMaxBins : 1];   // the key's pairs in the first half of the tile
     __shared__ int group_total[kMaxChunks], group_tile[kMaxChunks];   // sums over 64 experts or devices
     __shared__ int slot_of[kTilePairs], row_of[kTilePairs];
     __shared__ uint16_t sorted[kTilePairs];
@@ -286,16 +308,18 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     }
     // Rows to add up: all tiles; with a chunk level all chunks, and then the tiles of the tile's own chunk before it.
     // Thread (part, c) takes rows part, part + parts, ... of column c (parts: groups of columns that fit the workgroup)
-    const bool chunked = a.chunk_tiles != 0;
+    const bool chunked = !HALVED && a.chunk_tiles != 0;
     const int chunk = chunked ? tile / a.chunk_tiles : 0;
     const int32_t *rows1 = chunked ? a.chunk_hist : a.tile_hist, *rows2 = a.tile_hist + (int64_t)chunk * a.chunk_tiles * a.stride;
     const int n1 = chunked ? a.n_chunks : a.n_tiles, limit1 = chunked ? chunk : tile, n2 = chunked ? tile - chunk * a.chunk_tiles : 0;
     const int cols = min(nb, kPlanThreads), pad = (cols + kWave - 1) / kWave * kWave, parts = kPlanThreads / pad;
     const int part = tid / pad, c = tid - part * pad;
-    // this tile's own count of the expert that the thread has in the first round of groups below
-    const int own0 = wave < egroups && tid < a.E ? a.tile_hist[(int64_t)tile * a.stride + tid] : 0;
+    // this tile's own counts of the column that the thread has in the first round of groups below
+    const int32_t *own_row = a.tile_hist + (int64_t)tile * a.stride;
+    const int col0 = wave < egroups ? tid : a.E + (wave - egroups) * kWave + lane;
+    const int own0 = col0 < (wave < egroups ? a.E : HALVED ? nb : 0) ? own_row[col0] : 0;
     if (part < parts && c < cols) {
-        RowSums s(rows1, n1, part, parts, limit1, a.stride, c), s2(rows2, n2, part, parts, 0, a.stride, c);
+        RowSums<HALVED> s(rows1, n1, part, parts, limit1, a.stride, c), s2(rows2, n2, part, parts, 0, a.stride, c);
         int v[kCross], v2[kCross];
         s.load(v, 0);
         s2.load(v2, 0);
@@ -308,7 +332,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     }
     // the columns beyond the workgroup's kPlanThreads (more than 1024 experts and devices, parts is 1): one thread each
     for (int e = kPlanThreads + tid; e < nb; e += kPlanThreads) {
-        RowSums s(rows1, n1, 0, 1, limit1, a.stride, e), s2(rows2, n2, 0, 1, 0, a.stride, e);
+        RowSums<HALVED> s(rows1, n1, 0, 1, limit1, a.stride, e), s2(rows2, n2, 0, 1, 0, a.stride, e);
         s.walk(0);
         s2.walk(0);
         total[e] = s.total;
@@ -322,7 +346,11 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         const bool in = expert ? e < a.E : e < nb;
         int tot = 0, pre = 0, own = 0;
         if (in) {
-            if (expert) own = g == wave ? own0 : a.tile_hist[(int64_t)tile * a.stride + e];
+            if (HALVED || expert) own = g == wave ? own0 : own_row[e];
+            if constexpr (HALVED) {
+                half_cnt[e] = (uint16_t)own;
+                own = expert ? both_halves(own) : 0;
+            }
             for (int q = 0; q < parts; ++q) {
                 tot += total[q * pad + e];
                 pre += before[q * pad + e];
@@ -347,6 +375,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     const int incl = wave_inclusive_sum(of_group), tile_incl = wave_inclusive_sum(of_tile);
     const int group_off = incl - of_group, tile_group_off = tile_incl - of_tile;
     const int experts_total = __builtin_amdgcn_readlane(incl, egroups - 1);
+    const int half_pairs = first_half_tokens(a.tpt) * a.k;
     const int tile_pairs = __builtin_amdgcn_readlane(tile_incl, egroups - 1);   // pairs of this tile with a valid expert id
 #pragma unroll
     for (int r = 0; r < kMaxRounds; ++r) {
@@ -359,10 +388,12 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         int slot = -1, row = -1;
         bool first = false;
         if (ew[r] >= 0) {
-            slot = before[e] + eoff + rank;
-            row = before[a.E + d] + doff + packed_rank(dw[r]);
+            const bool second = HALVED && p >= half_pairs;
+            const int in_tile = rank + (second ? half_cnt[e] : 0);
+            slot = before[e] + eoff + in_tile;
+            row = before[a.E + d] + doff + packed_rank(dw[r]) + (second ? half_cnt[a.E + d] : 0);
             first = packed_first(dw[r]);
-            sorted[tile_at[e] + toff + rank] = (uint16_t)p;
+            sorted[tile_at[e] + toff + in_tile] = (uint16_t)p;
         }
         slot_of[p] = slot;
         row_of[p] = row;
@@ -400,7 +431,10 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         if (wave == kPlanWaves - 1) {
             // the last column of the counts holds the invalid ids of a tile (or of a chunk of tiles)
             int bad = 0;
-            for (int r = lane; r < n1; r += kWave) bad += rows1[(int64_t)r * a.stride + nb];
+            for (int r = lane; r < n1; r += kWave) {
+                const int c = rows1[(int64_t)r * a.stride + nb];
+                bad += HALVED ? both_halves(c) : c;
+            }
             bad = wave_inclusive_sum(bad);
             if (lane == kWave - 1) *a.status = bad;
         }
