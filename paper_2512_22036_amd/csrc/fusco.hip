@@ -322,8 +322,14 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
 
 static bool wire_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes)
 {
-    return g_dispatch_kernel.load(std::memory_order_relaxed) == 0 && L->D <= L->k &&
-           dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, true, false, false);
+    if (g_dispatch_kernel.load(std::memory_order_relaxed) != 0 || L->D > L->k ||
+        !dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, true, false, false))
+        return false;
+    // up to twice the pairs' workgroups: a launch of all tiles has to stay below 2^32 threads
+    int threads, cpt, segs, per;
+    if (!tiled_shape(L, (int)((row_bytes + aux_row_bytes) / 16), threads, cpt, segs, per)) return false;
+    const uint64_t tiles = ((uint64_t)L->tile_count + kXcds - 1) / kXcds * kXcds;
+    return tiles * (uint64_t)L->tile_tokens * (uint64_t)(L->k + L->D) * (uint64_t)segs * (uint64_t)threads <= 0xffffffffu;
 }
 
 int fusco_dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, uint32_t flags)
