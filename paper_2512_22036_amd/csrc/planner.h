@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
 // transfer order (its slots ascending: expert by expert, tokens ascending): neighbouring threads then write
 // neighbouring slots of one expert, a few cache lines per wave instead of 64; the pairs meet their place in that
 // order through LDS.  Bound by latency: three barriers between the loads and the stores.  Kernel times of pass 1 + pass 2
-// (and the chunk pass between them), k = 8, us: 8192 tokens 5.6 + 7.2, 32768 tokens 6.0 + 4.6 + 8.0, 131072 tokens
+// (and the chunk pass between them), k = 8, us: 8192 tokens 4.5 + 6.6 (5.6 + 7.2 with one workgroup per tile in pass 1), 32768 tokens 6.0 + 4.6 + 8.0, 131072 tokens
 // 9.5 + 4.1 + 15.4, 4096 tokens with k = 2 4.7 + 4.7; before, with a pass 1 that only counted and a pass 2 that ranked
 // all pairs again (and prefixed 16 counters per key): 5.2 + 11.8, 5.3 + 4.3 + 14.2, 7.0 + 4.2 + 29.9, 3.8 + 8.6.
 constexpr int kTilePairs = kMaxRounds * kRoundPairs;
