@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
         // 64 segments or fewer that hold the wave's first byte: cum[lo] <= piece < cum[hi]
         while (hi - lo > kWave) {
             const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lo + lane * step < hi && probe <= piece));
-            lo += (max(c, 1) - 1) * step;   // lane 0 probes cum[lo]: c >= 1 for cumulative entries that ascend
+            lo += (max(c, 1) - 1) * step;   // lane 0 probes cum[lo]: c >= 1 for cumulative entries that ascend from 0
             hi = min(lo + step, hi);
             step = (hi - lo + kWave - 1) / kWave;
             probe = a.cum[min(lo + lane * step, hi)];
@@ -223,6 +223,11 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
                 dst_at[lane] = dofs - b + piece;
             }
             wave_lds_order();
+            // Whatever the list holds, the search below ends at a q with end[q - 1] <= pos < end[q], so for q > 0 segment
+            // w + q holds the unit and its entries were written just now.  q == 0 rests on begin <= piece + pos, which
+            // ascending cumulative bytes from 0 give; sizes whose sum wraps around 2^64 do not (a negative int64), and
+            // nothing may be read or written through entries that then are another segment's or nobody's.
+            const int from = begin <= piece ? 0 : (int)min(begin - piece, (uint64_t)kSegPieceBytes);
             const int last = __shfl(e_rel, kWave - 1, kWave);
 #pragma unroll
             for (int r = 0; r < kSegUnits; ++r) {
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
 #pragma unroll
                 for (int h = kWave / 2; h > 0; h >>= 1)
                     if (end[q + h - 1] <= pos) q += h;
-                if (pos >= valid[q]) {
+                if (pos >= valid[q] || (q == 0 && pos < from)) {
                     ++skipped;
                     continue;
                 }

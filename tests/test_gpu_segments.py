@@ -244,3 +244,36 @@ def test_scan_and_copy_at_the_edges_of_their_windows(fusco, oracle, n):
     valid = np.where(size % 16 == 0, size, 0)
     assert int(status.item()) == len(bad)
     assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(valid)]))
+
+
+@pytest.mark.parametrize("first", [0, 16, 40000])
+@pytest.mark.parametrize("n", [3, 65, 700, 9000])
+def test_sizes_that_wrap_touch_nothing_outside(fusco, n, first):
+    """Sizes whose cumulative bytes do not ascend (a negative int64 among them), or cumulative bytes that do not start
+    at 0: which segment a stream position belongs to is then nobody's promise, but every 16-byte unit is either moved by
+    a descriptor inside both buffers or skipped and counted.  Both sides have the same descriptors, so a unit that was
+    moved holds what its source holds at the same offset."""
+    rng = np.random.default_rng(n + first)
+    for trial in range(6):
+        size = rng.integers(0, 40, size=n).astype(np.int64) * 16
+        for i in rng.choice(n, size=min(n - 1, 1 + trial), replace=False):
+            size[i] = -16 * int(rng.integers(1, 3000))
+        size[-1] = max(size[-1], 0) + 16 * 4000            # the stream as a whole is not empty
+        span = 1 << 20
+        off = rng.integers(0, span // 16 - 2500, size=n).astype(np.int64) * 16
+        desc = desc_dev(off, size)
+        cum, status = scan(fusco, desc)
+        assert int(status.item()) == 0
+        assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(size)]))   # sums modulo 2^64
+        cum += first
+        capacity = min(max(int(cum[-1].item()), 16), span)
+        room = torch.randint(0, 255, (3, span), dtype=torch.uint8, device="cuda")
+        out = torch.full((3, span), 255, dtype=torch.uint8, device="cuda")
+        fusco.fusco_segments_copy(room[1], desc, out[1], desc, cum, capacity, status)
+        assert bool((out[0] == 255).all()) and bool((out[2] == 255).all())
+        assert bool(((out[1] == 255) | (out[1] == room[1])).all())
+        # the same list against the contiguous stream on either side: nothing outside the stream's buffer
+        for src_desc, dst_desc in ((desc, None), (None, desc)):
+            out.fill_(255)
+            fusco.fusco_segments_copy(room[1], src_desc, out[1], dst_desc, cum, capacity, status)
+            assert bool((out[0] == 255).all()) and bool((out[2] == 255).all())
