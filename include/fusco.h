@@ -184,7 +184,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
 /*
  * Host-only: 1 if fusco_dispatch with these row sizes and flags moves the rows tile by tile in the layout's
  * transfer order (tile_slots), 0 if it walks the tokens, negative on invalid arguments.  The transfer order
- * is used when only the expert tensor is written, k >= 2, the layout has at least 16 tiles, and the source
+ * is used when the expert tensor is written, alone or (for at most k devices) together with the receive tensors, k >= 2, the layout has at least 16 tiles, and the source
  * rows of one tile (tile_tokens * (row_bytes + aux_row_bytes)) fit the 4 MB L2 of an XCD whole (at most
  * 3840 KiB) or cut into up to eight column segments of at least 4 KiB each, which are then moved in as many
  * passes over the tile; and when the sizes make it pay: the expert tensor is larger than the 256 MB memory-side cache

@@ -71,8 +71,9 @@ int fusco_probe_consume_slices(const void *d_stream, uint64_t total_bytes, uint6
 /*
  * Study and test aid: which kernel every later fusco_dispatch of the process uses where it has a choice.
  * 0: automatic.  1: the token walk (one workgroup per token), also where the rows would be moved tile by tile in
- * transfer order.  2: the transfer order wherever its workgroup shape allows, also at sizes where the token walk
- * is preferred.  fusco_dispatch_in_transfer_order reflects the setting.  which < 0 only reads it.  Returns the
+ * transfer order.  2: for calls that write the expert tensor alone, the transfer order wherever its workgroup shape
+ * allows, also at sizes where the token walk is preferred; calls that write the receive tensors as well walk the tokens
+ * under 1 and 2 and have the transfer order by the automatic choice only.  fusco_dispatch_in_transfer_order reflects the setting.  which < 0 only reads it.  Returns the
  * previous setting, FUSCO_ERR_INVALID_ARG for which > 2.  The result of fusco_dispatch does not depend on it.
  */
 int fusco_probe_dispatch_kernel(int which);

@@ -284,22 +284,27 @@ static bool tiled_shape(const fusco_layout *L, int Ct, int &threads, int &cpt, i
     return true;
 }
 
-// Whether fusco_dispatch that writes both tensors moves the rows of the receive tensors tile by tile after the pairs of
-// the tile (dispatch_tiled_kernel's WIRE): where the pairs alone would be moved in transfer order, and with at most as
-// many devices as entries per token, so that most of the (token, device) entries of a tile move a row.  (The receive
-// tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
-static bool wire_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes);
-
-// the conditions under which fusco_dispatch moves the rows tile by tile in transfer order
+// The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or
+// both tensors, the rows of the receive tensors following the pairs of their tile (dispatch_tiled_kernel's WIRE).  Both
+// need the sizes at which the pairs alone are moved that way; the receive tensors also at most as many devices as
+// entries per token, so that most of the (token, device) entries of a tile move a row, and the automatic choice.  (The
+// receive tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
 static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, bool expert,
                                        bool wire, bool two_hop)
 {
     const int which = g_dispatch_kernel.load(std::memory_order_relaxed);
     if (which == 1) return false;
     int threads, cpt, segs, per;
-    if (!(expert && !wire && !two_hop && L->k >= 2 && L->tile_count >= kTiledMinTiles &&
+    if (!(expert && !two_hop && L->k >= 2 && L->tile_count >= kTiledMinTiles &&
           tiled_shape(L, (int)((row_bytes + aux_row_bytes) / 16), threads, cpt, segs, per)))
         return false;
+    if (wire) {
+        if (which != 0 || L->D > L->k) return false;
+        // up to twice the pairs' workgroups: a launch of all tiles has to stay below 2^32 threads
+        const uint64_t tiles = ((uint64_t)L->tile_count + kXcds - 1) / kXcds * kXcds;
+        if (tiles * (uint64_t)L->tile_tokens * (uint64_t)(L->k + L->D) * (uint64_t)segs * (uint64_t)threads > 0xffffffffu)
+            return false;
+    }
     if (which == 2) return true;
     // Sizes at which the token walk is as good or better (measured, 8 rows per token):
     // - an expert tensor that fits the memory-side cache: the walk's plain stores leave it there for its reader;
@@ -318,18 +323,6 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     if (row < kTiledShortRowBytes / 2 && source >= limit) return false;
     if (source > limit && !(L->k >= 8 || (L->k >= 5 && segs == 1))) return false;
     return true;
-}
-
-static bool wire_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes)
-{
-    if (g_dispatch_kernel.load(std::memory_order_relaxed) != 0 || L->D > L->k ||
-        !dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, true, false, false))
-        return false;
-    // up to twice the pairs' workgroups: a launch of all tiles has to stay below 2^32 threads
-    int threads, cpt, segs, per;
-    if (!tiled_shape(L, (int)((row_bytes + aux_row_bytes) / 16), threads, cpt, segs, per)) return false;
-    const uint64_t tiles = ((uint64_t)L->tile_count + kXcds - 1) / kXcds * kXcds;
-    return tiles * (uint64_t)L->tile_tokens * (uint64_t)(L->k + L->D) * (uint64_t)segs * (uint64_t)threads <= 0xffffffffu;
 }
 
 int fusco_dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, uint32_t flags)
@@ -387,10 +380,10 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
     ArmedEvents ev;
     if (two_hop) ev.start = ev.stop = nullptr;   // several kernels: armed events are dropped
 
-    // Expert tensor alone, enough tiles to keep every XCD busy, and a tile's source rows small enough to stay
-    // in one XCD's 4 MB L2: the rows are moved tile by tile in transfer order (dispatch_tiled_kernel).
-    const bool tiled_wire = expert && wire && !two_hop && wire_in_transfer_order(L, row_bytes, aux_row_bytes);
-    if (tiled_wire || dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
+    // Enough tiles to keep every XCD busy, and a tile's source rows small enough to stay in one XCD's 4 MB L2: the rows
+    // of the expert tensor, or of both tensors, are moved tile by tile in transfer order (dispatch_tiled_kernel).
+    if (dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
+        const bool tiled_wire = wire;
         a.slot_token = L->slot_token; a.tile_slots = L->tile_slots;
         a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
         tiled_shape(L, Ct, threads, cpt, segs, per);

@@ -1,0 +1,46 @@
+"""Which kernel fusco_dispatch takes, as its host-only query tells it: no GPU is needed, nothing is launched."""
+import ctypes
+
+import pytest
+
+EXPERT, WIRE, TWO_HOP, STREAMING = 1, 2, 4, 8
+
+
+@pytest.fixture(scope="module")
+def tiled():
+    import os
+
+    from paper_2512_22036_amd import binding
+    if not os.path.exists(binding.library_path()):
+        from paper_2512_22036_amd.build import build_library
+        build_library()
+    lib = binding.load_library()
+
+    def ask(N, k, E, D, row, aux=0, flags=0):
+        L = binding._CLayout()
+        # the block is never touched: binding is pointer arithmetic and the query reads the sizes
+        assert lib.fusco_layout_bind(ctypes.byref(L), N, k, E, D, 0x10000000, lib.fusco_layout_bytes(N, k, E, D)) == 0
+        rc = lib.fusco_dispatch_in_transfer_order(ctypes.byref(L), row, aux, flags)
+        assert rc in (0, 1)
+        return bool(rc)
+
+    ask.lib = lib
+    return ask
+
+
+def test_query_answers_for_calls_that_write_both_tensors(tiled):
+    both = EXPERT | WIRE
+    for row, aux in ((14336, 0), (14336, 224), (8448, 0), (16384 + 1040, 0)):
+        assert tiled(8192, 8, 256, 8, row, aux) and tiled(8192, 8, 256, 8, row, aux, both)
+        assert tiled(8192, 8, 256, 8, row, aux, both | STREAMING)
+        assert not tiled(8192, 8, 256, 8, row, aux, WIRE)                 # the receive tensors alone
+        assert not tiled(8192, 8, 256, 8, row, aux, both | TWO_HOP) and not tiled(8192, 8, 256, 8, row, aux, TWO_HOP)
+    assert not tiled(8192, 8, 256, 16, 14336, 0, both) and tiled(8192, 8, 256, 16, 14336)     # more devices than entries
+    assert not tiled(1000, 8, 256, 8, 14336, 0, both)                     # where the expert tensor alone walks, both do
+    knob = tiled.lib.fusco_probe_dispatch_kernel
+    for which in (1, 2):                                                  # both tensors: the automatic choice only
+        assert knob(which) == 0
+        try:
+            assert not tiled(8192, 8, 256, 8, 14336, 0, both) and tiled(8192, 8, 256, 8, 14336) == (which == 2)
+        finally:
+            assert knob(0) == which

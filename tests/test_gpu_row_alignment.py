@@ -110,7 +110,7 @@ def test_both_tensors_tile_by_tile(N, k, E, D, row_bytes, aux_bytes, limit):
                send_aux=filled(L.send_cap, aux_bytes))
     before = f.fusco_probe_source_chunk_bytes(limit) if limit else 0
     try:
-        assert f.fusco_dispatch_in_transfer_order(L, row_bytes, aux_bytes)
+        assert f.fusco_dispatch_in_transfer_order(L, row_bytes, aux_bytes, f.DISPATCH_EXPERT | f.DISPATCH_WIRE)
         f.fusco_dispatch(L, x, x_aux=xa, flags=f.DISPATCH_EXPERT | f.DISPATCH_WIRE, **got)
     finally:
         if limit:
