@@ -284,6 +284,16 @@ static bool tiled_shape(const fusco_layout *L, int Ct, int &threads, int &cpt, i
     return true;
 }
 
+// Tiles that a launch of the tiled dispatch covers: all of them, or, where the source tensor cannot stay in the
+// memory-side cache, as many whole rounds of tiles as have their source rows in half of it.
+static size_t tiles_per_launch(const fusco_layout *L, size_t row)
+{
+    const size_t limit = g_source_chunk_bytes.load(std::memory_order_relaxed);
+    if ((size_t)L->N * row <= limit) return (size_t)L->tile_count;
+    const size_t tiles = std::max<size_t>(limit / ((size_t)L->tile_tokens * row) / kXcds, 1) * kXcds;
+    return std::min(tiles, (size_t)L->tile_count);
+}
+
 // The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or
 // both tensors, the rows of the receive tensors following the pairs of their tile (dispatch_tiled_kernel's WIRE).  Both
 // need the sizes at which the pairs alone are moved that way; the receive tensors also at most as many devices as
@@ -298,13 +308,11 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     if (!(expert && !two_hop && L->k >= 2 && L->tile_count >= kTiledMinTiles &&
           tiled_shape(L, (int)((row_bytes + aux_row_bytes) / 16), threads, cpt, segs, per)))
         return false;
-    if (wire) {
-        if (which != 0 || L->D > L->k) return false;
-        // up to twice the pairs' workgroups: a launch of all tiles has to stay below 2^32 threads
-        const uint64_t tiles = ((uint64_t)L->tile_count + kXcds - 1) / kXcds * kXcds;
-        if (tiles * (uint64_t)L->tile_tokens * (uint64_t)(L->k + L->D) * (uint64_t)segs * (uint64_t)threads > 0xffffffffu)
-            return false;
-    }
+    if (wire && (which != 0 || L->D > L->k)) return false;
+    // a workgroup per entry and segment: the largest launch has to stay below 2^32 threads
+    const uint64_t tiles = (tiles_per_launch(L, row_bytes + aux_row_bytes) + kXcds - 1) / kXcds * kXcds;
+    const uint64_t entries = (uint64_t)L->tile_tokens * (uint64_t)(L->k + (wire ? L->D : 0));
+    if (tiles * entries * (uint64_t)segs * (uint64_t)threads > 0xffffffffu) return false;
     if (which == 2) return true;
     // Sizes at which the token walk is as good or better (measured, 8 rows per token):
     // - an expert tensor that fits the memory-side cache: the walk's plain stores leave it there for its reader;
@@ -392,19 +400,11 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         a.through = whole_units(d_expert_buf, row_bytes) && (!wire || whole_units(d_send_buf, row_bytes));
         a.through_aux = whole_units(d_expert_aux, aux_row_bytes) && (!wire || whole_units(d_send_aux, aux_row_bytes));
         const uint64_t entries = (uint64_t)a.tile_cap + (tiled_wire ? (uint64_t)L->D * (uint64_t)L->tile_tokens : 0);
-        // a source tensor that cannot stay in the memory-side cache is taken in chunks of whole rounds of tiles
-        // whose rows fit half of it, every chunk after a sequential read of its source rows (touch_kernel)
+        // a source tensor that cannot stay in the memory-side cache is taken in chunks of tiles, every chunk after a
+        // sequential read of its source rows (touch_kernel)
         const size_t source_bytes = (size_t)L->N * (row_bytes + aux_row_bytes);
-        const size_t chunk_limit = g_source_chunk_bytes.load(std::memory_order_relaxed);
-        size_t chunk_tiles = (size_t)L->tile_count;
-        const bool chunked = source_bytes > chunk_limit;
-        if (chunked) {
-            chunk_tiles = chunk_limit / ((size_t)L->tile_tokens * (row_bytes + aux_row_bytes)) / kXcds * kXcds;
-            if (chunk_tiles < (size_t)kXcds) chunk_tiles = kXcds;
-        }
-        // the largest launch: a workgroup per row and segment of the chunk's tiles (checked before anything is launched)
-        if ((uint64_t)((chunk_tiles + kXcds - 1) / kXcds) * entries * (uint64_t)segs * kXcds > 0x7fffffffu)
-            return FUSCO_ERR_INVALID_ARG;
+        const size_t chunk_tiles = tiles_per_launch(L, row_bytes + aux_row_bytes);
+        const bool chunked = source_bytes > g_source_chunk_bytes.load(std::memory_order_relaxed);
         const dim3 tblock((unsigned)threads);
         // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
         // taken in chunks, touch_kernel has just read them and the pull only costs (12 KiB segments at 8192 tokens:

@@ -44,3 +44,11 @@ def test_query_answers_for_calls_that_write_both_tensors(tiled):
             assert not tiled(8192, 8, 256, 8, 14336, 0, both) and tiled(8192, 8, 256, 8, 14336) == (which == 2)
         finally:
             assert knob(0) == which
+
+
+def test_launches_that_would_pass_the_thread_limit_walk_the_tokens(tiled):
+    # one wave per row: 28128 x 2048 x 64 threads fit a launch, 62504 x 2048 x 64 (1.9 x 2^32) do not
+    assert tiled(900_000, 64, 64, 8, 64) and not tiled(2_000_000, 64, 64, 8, 64)
+    assert tiled(4_000_000, 16, 64, 8, 16) and not tiled(8_000_000, 16, 64, 8, 16)
+    # a source tensor that is taken in chunks has launches of one chunk, however many tokens there are
+    assert tiled(2_000_000, 8, 64, 8, 14336)
