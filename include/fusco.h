@@ -156,7 +156,7 @@ int fusco_plan_static(fusco_layout *L, const int32_t *d_topk_idx, void *stream);
  * expert by expert with streaming stores, the tile's source rows being read from memory once and from the
  * XCD's L2 afterwards while they stay there.  A source tensor of more than 128 MiB is taken in chunks of tiles,
  * each chunk after a sequential read of its source rows (a few launches instead of one).  Where both tensors are
- * written, the tile's send rows follow its pairs, device by device (for at most k devices).  Otherwise every
+ * written, the tile's send rows follow its pairs, device by device (for few devices).  Otherwise every
  * token's row is read once and stored to its k rows at once (token walk).
  * Rows are opaque bytes.  d_x: [N, row_bytes], row_bytes a positive multiple of 16.  An optional
  * second plane (e.g. per-block scales of an fp8 payload) of aux_row_bytes (multiple of 16, or 0
@@ -184,14 +184,15 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
 /*
  * Host-only: 1 if fusco_dispatch with these row sizes and flags moves the rows tile by tile in the layout's
  * transfer order (tile_slots), 0 if it walks the tokens, negative on invalid arguments.  The transfer order
- * is used when the expert tensor is written, alone or (for at most k devices) together with the receive tensors, k >= 2, the layout has at least 16 tiles, and the source
+ * is used when the expert tensor is written, k >= 2, the layout has at least 16 tiles, and the source
  * rows of one tile (tile_tokens * (row_bytes + aux_row_bytes)) fit the 4 MB L2 of an XCD whole (at most
  * 3840 KiB) or cut into up to eight column segments of at least 4 KiB each, which are then moved in as many
  * passes over the tile; and when the sizes make it pay: the expert tensor is larger than the 256 MB memory-side cache
  * (a smaller one is left there by the token walk's plain stores for its reader), rows shorter than 8 KiB
  * come with a source tensor of at most 128 MiB (less than 128 MiB for rows shorter than 4 KiB), and a source
- * tensor of more than 128 MiB comes with k >= 8, or with k >= 5 and rows that need no column segments.  Both
- * ways write the same bytes.
+ * tensor of more than 128 MiB comes with k >= 8, or with k >= 5 and rows that need no column segments.  Calls that
+ * write the receive tensors as well have it on top of that with k >= 8, at most 8 devices and rows of at least 8 KiB,
+ * or with at most 2 devices and rows that need no column segments.  Both ways write the same bytes.
  */
 int fusco_dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, uint32_t flags);
 

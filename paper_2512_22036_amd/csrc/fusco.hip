@@ -294,11 +294,29 @@ static size_t tiles_per_launch(const fusco_layout *L, size_t row)
     return std::min(tiles, (size_t)L->tile_count);
 }
 
+// Whether the rows of the receive tensors are moved behind the pairs of their tile (dispatch_tiled_kernel's WIRE), at
+// sizes at which the pairs alone are.  A tile has an entry for every (token, device); one without a row costs its
+// workgroup, and finding the row costs a look at the token's k entries, so it pays for few devices or long rows.  Both
+// tensors, us, tiles / token walk:
+// - 8 devices, 8 rows per token of 256 experts, 8192 tokens: rows of 8 KiB 149 / 174, 9 KiB 194 / 199, 14 KiB 288 / 305,
+//   32 KiB 676 / 772; every token on 4 of the devices: 8 KiB 143 / 158, 10 KiB 193 / 194, 14 KiB 273 / 270 (4096 tokens 138 / 139,
+//   32768 tokens 1139 / 1182); on 2 of them 131 / 122, on one 128 / 109 (4096 tokens of 14 KiB).  16 rows per token of
+//   8 KiB 257 / 301 (on 4 devices 240 / 265), 32 rows 228 / 266, 64 rows 212 / 243 (4096 and 2048 tokens).
+// - more devices: 16 of them with 16 rows per token of 14 KiB 616 / 602, on 4 of them 579 / 458; 32 with 32 of 8 KiB
+//   397 / 350; 64 with 64 560 / 355; 10 with 10 of 10 KiB on 4 of them 258 / 231.
+// - rows shorter than 8 KiB: 8 devices 5.6 KiB 139 / 126, 1 KiB (65536 tokens) 303 / 170; 4 devices 4 KiB 152 / 151, 2 KiB
+//   131 / 151; 2 devices 5.6 KiB 84 / 95, 2 KiB 108 / 128; one device 74 / 86, 97 / 116.
+// - fewer than 8 rows per token: 4 devices, 4 rows of 14 KiB 176 / 159, 6 rows 260 / 216; 5 devices, 5 rows of 10 KiB 194 / 139;
+//   2 devices, whole rows: 6 rows of 10 KiB 118 / 131, 4 rows of 7.5 KiB 131 / 143; in column segments 6 rows of 14 KiB 202 / 185.
+// (The receive tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
+static bool both_in_transfer_order(const fusco_layout *L, size_t row, int segs)
+{
+    return (L->k >= 8 && L->D <= 8 && row >= kTiledShortRowBytes) || (L->D <= 2 && segs == 1);
+}
+
 // The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or
 // both tensors, the rows of the receive tensors following the pairs of their tile (dispatch_tiled_kernel's WIRE).  Both
-// need the sizes at which the pairs alone are moved that way; the receive tensors also at most as many devices as
-// entries per token, so that most of the (token, device) entries of a tile move a row, and the automatic choice.  (The
-// receive tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
+// need the sizes at which the pairs alone are moved that way; both_in_transfer_order says when the receive tensors are.
 static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, bool expert,
                                        bool wire, bool two_hop)
 {
@@ -308,7 +326,7 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     if (!(expert && !two_hop && L->k >= 2 && L->tile_count >= kTiledMinTiles &&
           tiled_shape(L, (int)((row_bytes + aux_row_bytes) / 16), threads, cpt, segs, per)))
         return false;
-    if (wire && (which != 0 || L->D > L->k)) return false;
+    if (wire && (which != 0 || !both_in_transfer_order(L, row_bytes + aux_row_bytes, segs))) return false;
     // a workgroup per entry and segment: the largest launch has to stay below 2^32 threads
     const uint64_t tiles = (tiles_per_launch(L, row_bytes + aux_row_bytes) + kXcds - 1) / kXcds * kXcds;
     const uint64_t entries = (uint64_t)L->tile_tokens * (uint64_t)(L->k + (wire ? L->D : 0));

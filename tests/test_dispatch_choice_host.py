@@ -35,7 +35,6 @@ def test_query_answers_for_calls_that_write_both_tensors(tiled):
         assert tiled(8192, 8, 256, 8, row, aux, both | STREAMING)
         assert not tiled(8192, 8, 256, 8, row, aux, WIRE)                 # the receive tensors alone
         assert not tiled(8192, 8, 256, 8, row, aux, both | TWO_HOP) and not tiled(8192, 8, 256, 8, row, aux, TWO_HOP)
-    assert not tiled(8192, 8, 256, 16, 14336, 0, both) and tiled(8192, 8, 256, 16, 14336)     # more devices than entries
     assert not tiled(1000, 8, 256, 8, 14336, 0, both)                     # where the expert tensor alone walks, both do
     knob = tiled.lib.fusco_probe_dispatch_kernel
     for which in (1, 2):                                                  # both tensors: the automatic choice only
@@ -52,3 +51,22 @@ def test_launches_that_would_pass_the_thread_limit_walk_the_tokens(tiled):
     assert tiled(4_000_000, 16, 64, 8, 16) and not tiled(8_000_000, 16, 64, 8, 16)
     # a source tensor that is taken in chunks has launches of one chunk, however many tokens there are
     assert tiled(2_000_000, 8, 64, 8, 14336)
+
+
+def test_both_tensors_walk_where_the_tiles_lose(tiled):
+    both = EXPERT | WIRE
+
+    def pair(*sizes):
+        return tiled(*sizes), tiled(*sizes, 0, both)
+
+    yes, no = (True, True), (True, False)      # the expert tensor alone, both tensors
+    # many devices, short rows, few rows per token: measured up to 1.8 times slower than the walk
+    assert pair(8192, 16, 256, 16, 14336) == no and pair(4096, 32, 256, 32, 8192) == no and pair(2048, 64, 512, 64, 8192) == no
+    assert pair(8192, 8, 256, 16, 14336) == no
+    assert pair(8192, 8, 256, 8, 5760) == no and pair(65536, 8, 256, 8, 1024) == no
+    assert pair(8192, 4, 64, 4, 14336) == no and pair(8192, 6, 60, 4, 14336) == no and pair(8192, 6, 60, 2, 14336) == no
+    # at most 8 devices with long rows and k >= 8, or at most 2 devices with whole rows
+    assert pair(8192, 8, 256, 8, 8192) == yes and pair(8192, 8, 256, 8, 8176) == no and pair(8192, 16, 256, 8, 8192) == yes
+    assert pair(8192, 10, 160, 5, 10240) == yes and pair(2048, 64, 512, 8, 8192) == yes
+    assert pair(8192, 8, 256, 2, 5760) == yes and pair(8192, 8, 256, 4, 5760) == no
+    assert pair(8192, 6, 60, 2, 10240) == yes and pair(8192, 6, 60, 1, 10240) == yes
