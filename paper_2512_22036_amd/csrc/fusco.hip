@@ -214,8 +214,11 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     m.k = L->k;
     m.C = (int32_t)(row_bytes / 16); m.Ca = (int32_t)(aux_row_bytes / 16);
     m.write_expert = 1; m.write_wire = 0;
+    const int Ct = m.C + m.Ca, most = kFusedChunks * kSmallThreads;
+    m.segs = (Ct + most - 1) / most;
+    m.seg_chunks = m.segs > 1 ? round_up((Ct + m.segs - 1) / m.segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
     const ArmedEvents ev;
-    const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N), block(kSmallThreads);
+    const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)m.segs), block(kSmallThreads);
     launch_args(plan_dispatch_kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, m);
     return launch_status();
 }

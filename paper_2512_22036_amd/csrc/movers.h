@@ -270,31 +270,34 @@ __global__ __launch_bounds__(256) void touch_kernel(const u32x4 *src, size_t n)
 // 7392 B (two planes, D = 64) and 256 tokens of 4 KiB (D = 8): 5.0 / 6.6 / 7.3 us; 5.8 / 7.9 / 8.2 us with the
 // descriptors written by the tokens' own workgroups after their rows; 9.9 / 11.4 / 13.0 us with counters and scans over
 // the keys in every workgroup.
-constexpr int kFusedPreload = 4;   // 16-byte chunks per thread held in registers across the planning
+// A row longer than a workgroup holds is cut into column segments, each with a workgroup (blockIdx.y) that finds the
+// slots for itself.  k = 8, against one workgroup that loops over its row after the first 32 KiB: 4 tokens of 128 KiB
+// 20.6 -> 6.3 us, 1 MiB 198 -> 11; 128 tokens of 40 KiB 14.5 -> 10.8 us, 128 KiB 47 -> 31; 256 tokens of 64 KiB 35.6 -> 31.0 us.
+// (Finding the slots twice costs more than it gives for many tokens of little more than 32 KiB: 500 tokens with k = 4 of 33 KiB
+// 16.0 -> 20.4 us, 64 KiB 37.2 -> 34.1 us.)
+constexpr int kFusedChunks = 4;   // 16-byte chunks per thread held in registers across the planning: 32 KiB a workgroup
 
 __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a, DispatchArgs m)
 {
     __shared__ SmallLds s;
-    const int b = blockIdx.x;
-    if (b == 0) {
-        small_counts(s, a);
-        return;
-    }
+    const int b = blockIdx.x, seg = blockIdx.y;
     if (b <= a.small_groups) {
+        if (seg != 0) return;
         const int p0 = (b - 1) * kSmallPairs;
-        small_place(s, a, p0, min(kSmallPairs, a.N * a.k - p0));
+        if (b == 0) small_counts(s, a);
+        else small_place(s, a, p0, min(kSmallPairs, a.N * a.k - p0));
         return;
     }
     const int tid = threadIdx.x;
     const int t = b - 1 - a.small_groups;
-    const int Ct = m.C + m.Ca;
+    const int c0 = seg * m.seg_chunks + tid, c_end = min(m.C + m.Ca, (seg + 1) * m.seg_chunks);
     // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
     const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
-    u32x4 v[kFusedPreload];
+    u32x4 v[kFusedChunks];
 #pragma unroll
-    for (int i = 0; i < kFusedPreload; ++i) {
-        const int c = tid + i * kSmallThreads;
-        if (c < Ct) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
+    for (int i = 0; i < kFusedChunks; ++i) {
+        const int c = c0 + i * kSmallThreads;
+        if (c < c_end) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
     }
     const int slots = small_slots(s, a, t * a.k, a.k);
     for (int j = 0; j < a.k; ++j) {
@@ -302,21 +305,9 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
         if (slot < 0) continue;
         u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
 #pragma unroll
-        for (int i = 0; i < kFusedPreload; ++i) {
-            const int c = tid + i * kSmallThreads;
-            if (c < Ct) (c < m.C ? dst : dst_aux)[c] = v[i];
-        }
-    }
-    // rows longer than the preloaded part
-    for (int c0 = kFusedPreload * kSmallThreads; c0 < Ct; c0 += kSmallThreads) {   // uniform, for readlane
-        const int c = c0 + tid;
-        u32x4 u;
-        if (c < Ct) u = load16_stream((c < m.C ? src : src_aux) + c);
-        for (int j = 0; j < a.k; ++j) {
-            const int slot = __builtin_amdgcn_readlane(slots, j);
-            if (slot < 0) continue;
-            u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
-            if (c < Ct) (c < m.C ? dst : dst_aux)[c] = u;
+        for (int i = 0; i < kFusedChunks; ++i) {
+            const int c = c0 + i * kSmallThreads;
+            if (c < c_end) (c < m.C ? dst : dst_aux)[c] = v[i];
         }
     }
 }

@@ -108,6 +108,32 @@ def test_several_tiles(N, k, E, D, bad):
     check(L, A, "plan")
 
 
+@pytest.mark.parametrize("row_bytes,aux_bytes", [(32768 - 16, 0), (32768, 0), (32768 + 16, 0), (32768, 16), (32752, 48), (65536, 0),
+                                                 (65536 + 16, 32), (40960, 32768 + 16), (98304 + 1040, 224)])
+@pytest.mark.parametrize("N,k,E,D", [(1, 8, 256, 8), (5, 3, 24, 24), (31, 64, 512, 8), (300, 6, 160, 5)])
+def test_single_launch_with_long_rows(N, k, E, D, row_bytes, aux_bytes):
+    """Rows around the 32 KiB that a workgroup of the fused call holds, and rows in several column segments, the second
+    plane beginning anywhere in a segment."""
+    import paper_2512_22036_amd as f
+    A = routing(N + row_bytes, N, k, E, False, N > 4)
+    d_A = torch.from_numpy(A).cuda()
+    F = f.Layout(N, k, E, D)
+    F.mem.fill_(0x7B)
+    planes = {}
+    for name, width in (("x", row_bytes), ("x_aux", aux_bytes)):
+        if width:
+            planes[name] = torch.randint(0, 256, (N, width), dtype=torch.uint8, device="cuda")
+            planes["expert_buf" if name == "x" else "expert_aux"] = torch.full((N * k + 1, width), 0xEE, dtype=torch.uint8, device="cuda")
+    f.fusco_plan_dispatch(F, d_A, **planes)
+    check(F, A, "fused")
+    want, ok = plan_by_sorting(A, E, D)
+    token = torch.from_numpy(want["slot_token"]).cuda()
+    for src, dst in (("x", "expert_buf"), ("x_aux", "expert_aux")):
+        if src in planes:
+            assert torch.equal(planes[dst][:len(token)], planes[src][token])
+            assert bool((planes[dst][len(token):] == 0xEE).all())
+
+
 def test_calls_without_a_stream_use_the_current_one():
     from paper_2512_22036_amd import binding
     side = torch.cuda.Stream()
