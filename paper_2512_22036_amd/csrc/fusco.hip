@@ -545,17 +545,11 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
         f.pair_slot = L->pair_slot; f.pair_send_row = L->pair_send_row; f.pair_first = L->pair_first;
         f.k = L->k;
         f.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
-        f.stores = out_stores((size_t)L->P * (size_t)f.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
-        // 4096 tokens x 8 rows of 14 KiB, 21700 partial rows: 228 us plain, 239 us written through, 280 us non-temporal
-        f.partial_stores = kOutPlain;
-        int th = round_up(f.C, kWave);
-        if (th > 1024) th = 1024;
-        const dim3 fgrid((unsigned)L->N, (unsigned)((f.C + th - 1) / th));
-        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16)
-            hipLaunchKernelGGL((combine_two_hop_kernel<true, true>), fgrid, dim3(th), 0, s, f);
-        else if (y_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_two_hop_kernel<true, false>), fgrid, dim3(th), 0, s, f);
-        else if (out_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_two_hop_kernel<false, true>), fgrid, dim3(th), 0, s, f);
-        else hipLaunchKernelGGL((combine_two_hop_kernel<false, false>), fgrid, dim3(th), 0, s, f);
+        const OutStores how = out_stores((size_t)L->P * (size_t)f.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
+        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_two_hop<true, true>(f, L->N, L->D, how, s);
+        else if (y_dtype == FUSCO_BF16) launch_two_hop<true, false>(f, L->N, L->D, how, s);
+        else if (out_dtype == FUSCO_BF16) launch_two_hop<false, true>(f, L->N, L->D, how, s);
+        else launch_two_hop<false, false>(f, L->N, L->D, how, s);
         return launch_status();
     }
     // general k: level 2 reversed (fp32 partial row per send row), then level 1 reversed
@@ -569,12 +563,11 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
     a.pair_send_row = L->pair_send_row; a.send_src = L->send_src; a.n_rows_dev = L->send_off + L->D;
     a.first = 0;
     a.n_rows = L->send_cap;
-    a.stores = kOutPlain;
     int threads;
     combine_shape(a.C, threads, a.segs);
     const dim3 grid((unsigned)L->send_cap * (unsigned)a.segs);
-    if (y_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_kernel<true, false, 1, 8, true>), grid, dim3(threads), 0, s, a);
-    else hipLaunchKernelGGL((combine_kernel<false, false, 1, 8, true>), grid, dim3(threads), 0, s, a);
+    if (y_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_kernel<true, false, 1, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
+    else hipLaunchKernelGGL((combine_kernel<false, false, 1, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
     // level 1 reversed: sum of the token's partial rows
     SumPartialsArgs b;
     b.partial = (const u32x4 *)d_partial;

@@ -63,6 +63,8 @@ void launch_args(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hip
     else hipLaunchKernelGGL(kernel, grid, block, (unsigned)lds, s, args...);
 }
 
+constexpr size_t kLdsBytes = (size_t)160 << 10;   // of a compute unit
+
 // Workgroup shape of combine_kernel for rows of C chunks: as many column segments as 1024 threads need, the
 // threads spread evenly over them (1280 chunks: two workgroups of 640 threads, not 1024 + 256).
 inline void combine_shape(int C, int &threads, int &segs)
@@ -79,16 +81,19 @@ inline void combine_shape(int C, int &threads, int &segs)
 constexpr size_t kCombineLatencyBoundBytes = (size_t)64 << 20;
 
 template <bool Y_BF16, bool OUT_BF16>
-void launch_combine(CombineArgs a, int N, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
     int threads;
     combine_shape(a.C, threads, a.segs);
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
-    if ((size_t)N * (size_t)a.k * (size_t)a.C * 16 < kCombineLatencyBoundBytes)
-        launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8>, grid, block, s, a, e0, e1);
-    else
-        launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2>, grid, block, s, a, e0, e1);
+    if ((size_t)N * (size_t)a.k * (size_t)a.C * 16 < kCombineLatencyBoundBytes) {
+        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutThrough>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutPlain>, grid, block, s, a, e0, e1);
+    } else {
+        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutNonTemporal>, grid, block, s, a, e0, e1);
+    }
 }
 
 // dst[r] = src[index(r)] for n_rows destination rows of C chunks (see gather_rows_kernel)
@@ -175,6 +180,27 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes)
     return whole ? kOutThrough : kOutPlain;
 }
 
+// Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many
+// devices (about as many partial rows written as half the rows read) and several rounds of tokens the kernel is faster
+// without it: dynamic LDS that it does not use keeps the second one out.  One / two workgroups per compute unit, 14 KiB rows,
+// k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458, 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8),
+// 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2 devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192
+// tokens); fp32 rows of 16 KiB 185 / 181.
+template <bool Y_BF16, bool OUT_BF16>
+void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
+{
+    const int threads = std::min(1024, round_up(a.C, kWave));
+    const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
+    const size_t lds = Y_BF16 && threads > 768 && D > 5 && a.k >= 4 && N >= 1024 ? kLdsBytes : 0;
+    const hipEvent_t none = nullptr;
+    switch (stores) {
+    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough>, grid, block, lds, s, none, none, a); break;
+    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream>, grid, block, lds, s, none, none, a); break;
+    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal>, grid, block, lds, s, none, none, a); break;
+    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain>, grid, block, lds, s, none, none, a); break;
+    }
+}
+
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked
 void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int y_dtype, const float *d_w,
                     void *d_out, int out_dtype, int32_t H, hipStream_t s, hipEvent_t e0 = nullptr,
@@ -189,11 +215,11 @@ void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int
     a.pair_send_row = nullptr; a.send_src = nullptr; a.n_rows_dev = nullptr;
     a.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
     a.first = combine_first_row(N, k, (size_t)a.C * 16);
-    a.stores = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
-    if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_combine<true, true>(a, N, s, e0, e1);
-    else if (y_dtype == FUSCO_BF16) launch_combine<true, false>(a, N, s, e0, e1);
-    else if (out_dtype == FUSCO_BF16) launch_combine<false, true>(a, N, s, e0, e1);
-    else launch_combine<false, false>(a, N, s, e0, e1);
+    const OutStores how = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
+    if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_combine<true, true>(a, N, how, s, e0, e1);
+    else if (y_dtype == FUSCO_BF16) launch_combine<true, false>(a, N, how, s, e0, e1);
+    else if (out_dtype == FUSCO_BF16) launch_combine<false, true>(a, N, how, s, e0, e1);
+    else launch_combine<false, false>(a, N, how, s, e0, e1);
 }
 
 }   // namespace
