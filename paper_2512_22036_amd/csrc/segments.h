@@ -22,16 +22,16 @@ constexpr int kSegPieceBytes = 4096;    // stream bytes handled by one of its wa
 constexpr int kSegUnits = kSegPieceBytes / 16 / kWave;   // 16-byte units per thread
 constexpr int kSegRunBlocks = 8;        // consecutive blocks taken by one XCD
 
-// Sizes of the thread's kScanItems consecutive descriptors from index i0 on (0 beyond n, and for a descriptor whose
-// offset or size is not a multiple of 16, which is counted in bad); returns their sum.
-__device__ __forceinline__ uint64_t scan_load(const fusco_segment *desc, int64_t n, int64_t i0, uint64_t (&size)[kScanItems],
-                                              int &bad)
+// Sizes of the thread's `items` (<= kScanItems) consecutive descriptors from index i0 on (0 beyond n, and for a descriptor
+// whose offset or size is not a multiple of 16, which is counted in bad); returns their sum.
+__device__ __forceinline__ uint64_t scan_load(const fusco_segment *desc, int64_t n, int64_t i0, int items,
+                                              uint64_t (&size)[kScanItems], int &bad)
 {
     uint64_t sum = 0;
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         size[q] = 0;
-        if (i0 + q >= n) continue;
+        if (q >= items || i0 + q >= n) continue;
         const fusco_segment d = desc[i0 + q];
         if ((d.offset | d.size) & 15u) ++bad;
         else size[q] = d.size;
@@ -84,7 +84,9 @@ __global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void se
     __shared__ unsigned long long before;
     __shared__ int finished, bad_total;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk, i0 = c0 + (int64_t)tid * kScanItems;
+    // a single workgroup spreads the list over all its threads (3000 descriptors: 3.5 us, 5.2 us with eight per thread)
+    const int items = SINGLE ? (int)((n + kScanSingleThreads - 1) / kScanSingleThreads) : kScanItems;
+    const int64_t c0 = (int64_t)blockIdx.x * kScanChunk, i0 = c0 + (int64_t)tid * items;
     if (tid == 0) {
         before = 0;
         finished = -1;
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void se
     }
     uint64_t size[kScanItems];
     int bad = 0;
-    const uint64_t sum = scan_load(desc, n, i0, size, bad);
+    const uint64_t sum = scan_load(desc, n, i0, items, size, bad);
     uint64_t incl = sum;
     for (int d = 1; d < kWave; d <<= 1) {
         const uint64_t up = __shfl_up(incl, d, kWave);
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void se
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         run += size[q];
-        if (i0 + q < n) __hip_atomic_store(cum + i0 + q + 1, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (q < items && i0 + q < n) __hip_atomic_store(cum + i0 + q + 1, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (blockIdx.x == 0 && tid == 0) cum[0] = 0;
     if (tid == 0) {

@@ -277,3 +277,15 @@ def test_sizes_that_wrap_touch_nothing_outside(fusco, n, first):
             out.fill_(255)
             fusco.fusco_segments_copy(room[1], src_desc, out[1], dst_desc, cum, capacity, status)
             assert bool((out[0] == 255).all()) and bool((out[2] == 255).all())
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2047, 3000, 4096, 4097, 7168, 7169])
+def test_scan_of_one_workgroup_spreads_the_list_over_its_threads(fusco, n):
+    """Lists around the multiples of 1024 descriptors, where a thread takes one more; misaligned ones among them."""
+    rng = np.random.default_rng(n)
+    size = rng.integers(0, 1 << 20, size=n).astype(np.int64) * 16
+    size[rng.random(n) < 0.1] += 4
+    cum, status = scan(fusco, desc_dev(np.zeros(n, dtype=np.int64), size))
+    valid = np.where(size % 16 == 0, size, 0)
+    assert int(status.item()) == int(np.count_nonzero(size % 16))
+    assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(valid)]))
