@@ -203,6 +203,16 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
         const int bytes = (int)min((uint64_t)kSegPieceBytes, total - piece);
         uint64_t begin = __shfl(probe, 0, kWave);
         int first = 0;   // units below this position belong to an earlier window
+        // The lookup of a unit ends at a q with end[q - 1] <= pos < end[q], whatever the list holds, so for q > 0 segment w + q
+        // covers the unit and its entries were written for this window.  q == 0 rests on begin <= piece + pos, which
+        // ascending cumulative bytes from 0 give; with sizes whose sum wraps around 2^64 (a negative int64) the search may end
+        // elsewhere, and the units before `begin` are skipped.
+        if (begin > piece) {
+            first = (int)min(begin - piece, (uint64_t)kSegPieceBytes);
+#pragma unroll
+            for (int r = 0; r < kSegUnits; ++r)
+                if ((r * kWave + lane) * 16 < min(first, bytes)) ++skipped;
+        }
         for (int64_t w = lo;; w += kWave) {
             const int64_t i = w + lane;
             const uint64_t e = a.cum[min(i + 1, a.n)];
@@ -225,11 +235,6 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
                 dst_at[lane] = dofs - b + piece;
             }
             wave_lds_order();
-            // Whatever the list holds, the search below ends at a q with end[q - 1] <= pos < end[q], so for q > 0 segment
-            // w + q holds the unit and its entries were written just now.  q == 0 rests on begin <= piece + pos, which
-            // ascending cumulative bytes from 0 give; sizes whose sum wraps around 2^64 do not (a negative int64), and
-            // nothing may be read or written through entries that then are another segment's or nobody's.
-            const int from = begin <= piece ? 0 : (int)min(begin - piece, (uint64_t)kSegPieceBytes);
             const int last = __shfl(e_rel, kWave - 1, kWave);
 #pragma unroll
             for (int r = 0; r < kSegUnits; ++r) {
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
 #pragma unroll
                 for (int h = kWave / 2; h > 0; h >>= 1)
                     if (end[q + h - 1] <= pos) q += h;
-                if (pos >= valid[q] || (q == 0 && pos < from)) {
+                if (pos >= valid[q]) {
                     ++skipped;
                     continue;
                 }
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
                 to[r] = dst_at[q] + (uint64_t)pos;
                 v[r] = load16_stream((const u32x4 *)(a.src + src_at[q] + (uint64_t)pos));
             }
-            first = last;
+            first = max(first, last);
             begin = __shfl(e, kWave - 1, kWave);
             if (last >= bytes || w + kWave >= a.n) break;
         }
