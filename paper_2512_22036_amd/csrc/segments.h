@@ -236,14 +236,21 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
             }
             wave_lds_order();
             const int last = __shfl(e_rel, kWave - 1, kWave);
+            // the segment of the window's first unit; often it reaches past the wave's bytes, and no unit needs the lookup
+            // (one segment of 1 MiB: 3.5 us, 4.1 us with it)
+            const uint64_t open = ~__builtin_amdgcn_ballot_w64(e_rel <= first);
+            const int q_first = open ? __builtin_ctzll(open) : 0;
+            const bool single = open && __builtin_amdgcn_readlane(e_rel, q_first) >= bytes;
 #pragma unroll
             for (int r = 0; r < kSegUnits; ++r) {
                 const int pos = (r * kWave + lane) * 16;
                 if (pos < first || pos >= last || pos >= bytes) continue;   // another window's, or beyond the stream
-                int q = 0;   // entries of `end` that are <= pos: at most 63, because pos < last
+                int q = single ? q_first : 0;   // entries of `end` that are <= pos: at most 63, because pos < last
+                if (!single) {
 #pragma unroll
-                for (int h = kWave / 2; h > 0; h >>= 1)
-                    if (end[q + h - 1] <= pos) q += h;
+                    for (int h = kWave / 2; h > 0; h >>= 1)
+                        if (end[q + h - 1] <= pos) q += h;
+                }
                 if (pos >= valid[q]) {
                     ++skipped;
                     continue;

@@ -289,3 +289,24 @@ def test_scan_of_one_workgroup_spreads_the_list_over_its_threads(fusco, n):
     valid = np.where(size % 16 == 0, size, 0)
     assert int(status.item()) == int(np.count_nonzero(size % 16))
     assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(valid)]))
+
+
+@pytest.mark.parametrize("sizes", [[1 << 20], [16], [4096, 16, 0, 0, 8192 - 16], [4096] * 70, [8192, 0] * 40, [0] * 70 + [1 << 16, 0, 16], [12288 + 16] * 64 + [1 << 18]])
+def test_segments_that_reach_past_a_waves_bytes(fusco, oracle, sizes):
+    """Segments of several 4 KiB pieces, on and off their edges, with empty ones between them and more than 64 in a list."""
+    size = np.array(sizes, dtype=np.int64)
+    rng = np.random.default_rng(len(sizes))
+    order = rng.permutation(len(size))
+    off = np.zeros(len(size), dtype=np.int64)
+    off[order] = np.cumsum(size[order]) - size[order]
+    total = int(size.sum())
+    src = rng.integers(0, 256, size=total, dtype=np.uint8)
+    desc = desc_dev(off, size)
+    cum, status = scan(fusco, desc)
+    packed = torch.full((total + 4096,), 0xCD, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(dev(src), desc, packed, None, cum, total, status)
+    back = torch.zeros(total, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(packed, None, back, desc, cum, total, status)
+    assert int(status.item()) == 0
+    assert np.array_equal(packed[:total].cpu().numpy(), oracle.segments_copy(src, size, src_off=off))
+    assert bool((packed[total:] == 0xCD).all()) and np.array_equal(back.cpu().numpy(), src)
