@@ -714,8 +714,9 @@ int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segme
     a.src_bytes = src_bytes; a.dst_bytes = dst_bytes;
     a.slice_bytes = slice_bytes; a.slice_fill = d_slice_fill; a.status = d_status;
     const dim3 grid((unsigned)blocks);
-    if (d_slice_fill) hipLaunchKernelGGL(segments_copy_kernel<true>, grid, dim3(kSegThreads), 0, s, a);
-    else hipLaunchKernelGGL(segments_copy_kernel<false>, grid, dim3(kSegThreads), 0, s, a);
+    if (d_slice_fill) launch(segments_copy_kernel<true, false>, grid, dim3(kSegThreads), s, a);
+    else if (stream_capacity > kSegStreamBytes) launch(segments_copy_kernel<false, true>, grid, dim3(kSegThreads), s, a);
+    else launch(segments_copy_kernel<false, false>, grid, dim3(kSegThreads), s, a);
     return launch_status();
 }
 

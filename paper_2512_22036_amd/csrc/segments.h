@@ -21,6 +21,11 @@ constexpr int kSegThreads = 256;
 constexpr int kSegPieceBytes = 4096;    // stream bytes handled by one of its waves
 constexpr int kSegUnits = kSegPieceBytes / 16 / kWave;   // 16-byte units per thread
 constexpr int kSegRunBlocks = 8;        // consecutive blocks taken by one XCD
+// Streams of more than this are written with non-temporal stores, smaller ones with plain stores, which leave them in the
+// memory-side cache for whoever reads them.  Unpack and a pass that reads the result, other buffers in every turn, us, non-temporal
+// / plain: 4 MB 9.7 / 9.6, 14 MB 17.5 / 16.2, 57 MB 59.4 / 53.2, 115 MB 110.6 / 101.0, 172 MB 162.1 / 161.0, 230 MB 213 / 216,
+// 287 MB 263 / 268; pack alike.  (Without the reader 5.6 / 5.1, 8.2 / 9.0, 24.9 / 24.6, 46.9 / 50.8, 69.7 / 76.2, 92 / 100, 115 / 124.)
+constexpr uint64_t kSegStreamBytes = (uint64_t)128 << 20;
 
 // Sizes of the thread's `items` (<= kScanItems) consecutive descriptors from index i0 on (0 beyond n, and for a descriptor
 // whose offset or size is not a multiple of 16, which is counted in bad); returns their sum.
@@ -158,10 +163,10 @@ struct SegCopyArgs {
 // An XCD takes runs of kSegRunBlocks neighbouring blocks: what it writes on a contiguous side are runs of 128 KiB.
 // Bound by memory once the search is short.  Measured, 287 MB in 40000 segments of 16 B to 14 KiB: pack 176 -> 106 us
 // (5.4 TB/s read and written), pack with 1 MiB slices 193 -> 124 us, unpack 178 -> 115 us.  A unit's load is issued as
-// soon as its segment is known: all four together take 119 and 125 us.  The rows are written with non-temporal
-// stores, which the L2 still merges into whole lines at the segments' ragged edges: unpack 115 us, against 124 us
-// with plain stores and 139 us with write-through ones; 8 KiB a wave 117 and 124 us, 2 KiB 117 us each.
-template <bool SLICES>
+// soon as its segment is known: all four together take 119 and 125 us.  8 KiB a wave take 117 and 124 us, 2 KiB 117 us each.
+// STREAM: non-temporal stores, which the L2 still merges into whole lines at the segments' ragged edges (write-through ones
+// 139 us in the unpack); for streams that the memory-side cache would not keep for their reader (kSegStreamBytes).
+template <bool SLICES, bool STREAM>
 __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs a)
 {
     __shared__ uint64_t s_src[kSegThreads], s_dst[kSegThreads];
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
     for (int r = 0; r < kSegUnits; ++r) {
         if (!ok[r]) continue;
         if constexpr (SLICES) store16_system((u32x4 *)(a.dst + to[r]), v[r]);
-        else __builtin_nontemporal_store(v[r], (u32x4 *)(a.dst + to[r]));
+        else put16<STREAM>((u32x4 *)(a.dst + to[r]), v[r]);
     }
     if (skipped) atomicAdd(a.status, skipped);
     if constexpr (SLICES) {

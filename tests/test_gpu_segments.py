@@ -310,3 +310,22 @@ def test_segments_that_reach_past_a_waves_bytes(fusco, oracle, sizes):
     assert int(status.item()) == 0
     assert np.array_equal(packed[:total].cpu().numpy(), oracle.segments_copy(src, size, src_off=off))
     assert bool((packed[total:] == 0xCD).all()) and np.array_equal(back.cpu().numpy(), src)
+
+
+@pytest.mark.parametrize("extra", [-16, 0, 16, 1 << 20])
+def test_copy_around_the_size_that_is_written_past_the_cache(fusco, extra):
+    """Streams of just under, exactly and just over 128 MiB take plain and non-temporal stores."""
+    total = (128 << 20) + extra
+    size = np.full(3, total // 48 * 16, dtype=np.int64)
+    size[1] = total - 2 * size[0]
+    off = np.array([size[1] + size[2], 0, size[1]], dtype=np.int64)
+    desc = desc_dev(off, size)
+    cum, status = scan(fusco, desc)
+    src = torch.randint(0, 256, (total,), dtype=torch.uint8, device="cuda")
+    packed = torch.full((total + 64,), 0xCD, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(src, desc, packed, None, cum, total, status)
+    assert torch.equal(packed[:total], torch.cat([src[o:o + n] for o, n in zip(off.tolist(), size.tolist())]))
+    assert bool((packed[total:] == 0xCD).all())
+    back = torch.full((total,), 0xAB, dtype=torch.uint8, device="cuda")
+    fusco.fusco_segments_copy(packed, None, back, desc, cum, total, status)
+    assert int(status.item()) == 0 and torch.equal(back, src)
