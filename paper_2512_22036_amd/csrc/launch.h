@@ -91,7 +91,8 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
         if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutThrough>, grid, block, s, a, e0, e1);
         else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutPlain>, grid, block, s, a, e0, e1);
     } else {
-        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
+        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThrough>, grid, block, s, a, e0, e1);
+        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
         else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutNonTemporal>, grid, block, s, a, e0, e1);
     }
 }
@@ -164,20 +165,30 @@ int combine_first_row(int N, int k, size_t row_bytes)
 // (14336 B: 380 against 401 us with combine, 14400 B: 388 against 413 us).
 bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_bytes) & 63u) == 0; }
 
-// Stores of combine's output rows.  Inputs that are bound by memory: past the memory-side cache - what write-through
-// and plain stores leave dirty there costs the reads of the kernels around them more than it saves.  Steps with the
-// experts' output in a tensor of its own and other buffers in every step, written through / non-temporal / both at once,
-// us: 8192 tokens x 8 rows of 14 KiB 378.9 / 367.3 / 365.1, 16384 x 8 x 8 KiB 433.5 / 426.4 / 426.0, 32768 x 8 x 14 KiB
-// 1467 / 1437 / 1437.  (A loop over the same buffers whose x and output fit that cache together prefers to leave the
-// output there: 340.7 / 347.0 / 344.7 at 8192 x 8 x 14 KiB; 402 / 394 / 394 and 1461 / 1431 / 1429 at the other two.)
-// Rows that are not whole units, 8192 x 8 x 14352 B: combine 199 us written through, 209 us plain, 178 us
-// non-temporal.  Small outputs stay in that cache for their reader: written through where a wave's stores cover whole
-// units, plain otherwise.
-OutStores out_stores(size_t y_bytes, const void *out, size_t row_bytes)
+// Stores of combine's output rows.
+// Large outputs of inputs that are bound by memory go past the memory-side cache: what write-through and plain stores leave
+// dirty there costs the reads of the kernels around them more than it saves.  Steps with the experts' output in a tensor of
+// its own and other buffers in every step, written through / non-temporal / both at once, us: 8192 tokens x 8 rows of
+// 14 KiB 378.9 / 367.3 / 365.1, 16384 x 8 x 8 KiB 433.5 / 426.4 / 426.0, 32768 x 8 x 14 KiB 1467 / 1437 / 1437.  (A loop over
+// the same buffers whose x and output fit that cache together prefers to leave the output there: 340.7 / 347.0 / 344.7 at
+// 8192 x 8 x 14 KiB; 402 / 394 / 394 and 1461 / 1431 / 1429 at the other two.)
+// Outputs of up to kReadBackBytes stay there for the operation that reads them next.  A step and an addition that reads its
+// output, k = 8, past the cache / written through, us, other buffers in every step and (in brackets) the output at the same
+// place in every step: 12 MiB of output 64.0 / 62.5 (57.8 / 55.7), 20 MiB 94.3 / 92.1 (82.5 / 80.9), 32 MiB 147.8 / 139.2
+// (126.7 / 125.7); k = 4, 32 MiB 93.5 / 89.4 (83.9 / 82.2); k = 2 72.7 / 67.6 (62.3 / 61.0).  Nobody reading it, the step
+// takes 49.9 / 52.3, 80.5 / 81.6, 121.5 / 123.3 us.  Larger ones: 56 MiB 221.3 / 220.8 (206.0 / 201.8; nobody 180.9 / 192.1),
+// 80 MiB 313.9 / 316.8 (289.9 / 284.7; nobody 259.4 / 271.1), 112 MiB 423 / 436 (nobody 371 / 380): what a reader gains is less
+// than the step loses, and from 96 MiB on the reader loses as well.
+// Rows that are not whole units, 8192 x 8 x 14352 B: combine 199 us written through, 209 us plain, 178 us non-temporal.
+// Outputs of inputs below kCombineLatencyBoundBytes: written through where a wave's stores cover whole units, plain otherwise.
+constexpr size_t kReadBackBytes = (size_t)32 << 20;
+
+OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_bytes)
 {
     const bool whole = whole_units(out, row_bytes);
-    if (y_bytes >= kCombineLatencyBoundBytes) return whole ? kOutThroughStream : kOutNonTemporal;
-    return whole ? kOutThrough : kOutPlain;
+    if (y_bytes < kCombineLatencyBoundBytes) return whole ? kOutThrough : kOutPlain;
+    if (!whole) return kOutNonTemporal;
+    return rows * row_bytes <= kReadBackBytes ? kOutThrough : kOutThroughStream;
 }
 
 // Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many
@@ -215,7 +226,7 @@ void combine_launch(const int32_t *pair_slot, int N, int k, const void *d_y, int
     a.pair_send_row = nullptr; a.send_src = nullptr; a.n_rows_dev = nullptr;
     a.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
     a.first = combine_first_row(N, k, (size_t)a.C * 16);
-    const OutStores how = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
+    const OutStores how = out_stores((size_t)N * (size_t)k * (size_t)a.C * 16, d_out, (size_t)N, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
     if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_combine<true, true>(a, N, how, s, e0, e1);
     else if (y_dtype == FUSCO_BF16) launch_combine<true, false>(a, N, how, s, e0, e1);
     else if (out_dtype == FUSCO_BF16) launch_combine<false, true>(a, N, how, s, e0, e1);

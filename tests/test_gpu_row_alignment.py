@@ -83,6 +83,30 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
 
 
+@pytest.mark.parametrize("N", [4095, 4096, 4097])     # 32 MiB of output is the largest that stays in the memory-side cache
+@pytest.mark.parametrize("two_hop", [False, True])
+def test_combine_output_around_the_size_that_goes_past_the_cache(N, two_hop):
+    import paper_2512_22036_amd as f
+    k, E, D, H = 8, 64, 8, 4096
+    rng = np.random.default_rng(N)
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(random_topk(rng, N, k, E)).cuda())
+    y = torch.randn((L.P, H), device="cuda").to(torch.bfloat16)
+    w = torch.full((N, k), 0.125, device="cuda")      # an exact mean of eight: any order of exact sums rounds the same
+    y = (y * 16).round().clamp(-127, 127)             # whole numbers: every partial sum is exact
+    out, room = rows_at(N, H * 2, 0)
+    out = out.view(torch.bfloat16)
+    if two_hop:
+        f.fusco_combine_two_hop(L, y, w, torch.empty((L.send_cap, H), device="cuda"), out)
+    else:
+        f.fusco_combine(L, y, w, out)
+    want = torch.zeros((N, H), dtype=torch.float32, device="cuda")
+    for rows in L.array("pair_slot").view(N, k).long().t():
+        want += y[rows].float()
+    assert torch.equal(out, (want / 8).to(torch.bfloat16))
+    assert bool((room[out.numel() * 2:] == 0xEE).all())
+
+
 @pytest.mark.parametrize("N,k,E,D,row_bytes,aux_bytes,limit", [
     (4200, 8, 256, 8, 8448, 0, 0),              # 17 tiles, the last one ragged; as many devices as entries
     (4200, 8, 64, 4, 8192 + 16, 64, 0),         # rows that are not whole units, a second plane
