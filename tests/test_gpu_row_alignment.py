@@ -147,3 +147,50 @@ def test_both_tensors_tile_by_tile(N, k, E, D, row_bytes, aux_bytes, limit):
     if aux_bytes:
         assert torch.equal(got["expert_aux"][:valid], xa[token]) and torch.equal(got["send_aux"][:U], xa[source])
         assert bool((got["expert_aux"][valid:] == 0xEE).all()) and bool((got["send_aux"][U:] == 0xEE).all())
+
+
+def test_both_tensors_tile_by_tile_over_random_shapes():
+    """40 random shapes at which the library itself moves both tensors tile by tile: many or few devices, long and short
+    rows, one or several column segments, a second plane, a ragged last tile, invalid ids and repeated experts."""
+    import paper_2512_22036_amd as f
+    both = f.DISPATCH_EXPERT | f.DISPATCH_WIRE
+    rng = np.random.default_rng(31)
+    seen, moved = set(), 0
+    for case in range(40):
+        few = case % 2 == 1                       # at most 2 devices: any k, rows that a workgroup holds whole
+        k = int(rng.choice([2, 3, 5, 6, 8, 16] if few else [8, 9, 10, 16, 24, 33, 64]))
+        D = int(rng.integers(1, 3)) if few else int(rng.integers(1, 9))
+        E = D * int(rng.integers(max(1, 16 // D), 33))
+        tokens = 2048 // k                        # per tile
+        row = 16 * int(rng.integers(1, 3840 * 64 // tokens + 1) if few else rng.integers(512, 2600))
+        aux = 16 * int(rng.choice([0, 0, 1, 3, 14]))
+        if few:
+            row = max(16, min(row, 16384 - 256) - aux)
+        if case == 5:
+            row, aux = 64, 0                      # one wave per row
+        N = max(17 * tokens, (256 << 20) // (k * (row + aux))) + int(rng.integers(1, 2 * tokens))
+        tag = "case %d: N=%d k=%d E=%d D=%d row=%d aux=%d" % (case, N, k, E, D, row, aux)
+        L = f.Layout(N, k, E, D)
+        if not f.fusco_dispatch_in_transfer_order(L, row, aux, both):
+            continue                              # a large source tensor of short rows, few entries per token: the walk
+        A = torch.randint(0, E, (N, k), dtype=torch.int32, device="cuda")
+        A[0, 0], A[N // 2, k - 1], A[N - 1, 1] = -1, E, -7
+        f.fusco_plan(L, A)
+        x = torch.randint(0, 256, (N, row), dtype=torch.uint8, device="cuda")
+        xa = torch.randint(0, 256, (N, aux), dtype=torch.uint8, device="cuda") if aux else None
+
+        def filled(rows, width):
+            return torch.full((rows, width), 0xEE, dtype=torch.uint8, device="cuda") if width else None
+
+        eb, ea, sb, sa = filled(L.P, row), filled(L.P, aux), filled(L.send_cap, row), filled(L.send_cap, aux)
+        f.fusco_dispatch(L, x, eb, x_aux=xa, expert_aux=ea, send_buf=sb, send_aux=sa, flags=both)
+        valid, U = L.P - 3, int(L.array("send_off")[D].item())
+        assert int(L.array("status").item()) == 3, tag
+        token, source = L.array("slot_token")[:valid].long(), L.array("send_src")[:U].long()
+        for src, expert, send in ((x, eb, sb), (xa, ea, sa)):
+            if src is not None:
+                assert torch.equal(expert[:valid], src[token]) and bool((expert[valid:] == 0xEE).all()), tag
+                assert torch.equal(send[:U], src[source]) and bool((send[U:] == 0xEE).all()), tag
+        moved += 1
+        seen.add((few, -(-(row + aux) // 16) > 1024, aux > 0, (row + aux) // 16 < 512))
+    assert moved >= 35 and len(seen) >= 6 and any(s[0] for s in seen) and any(s[1] for s in seen)
