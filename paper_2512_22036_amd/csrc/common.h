@@ -39,8 +39,10 @@ bool sizes_ok(int32_t N, int32_t k, int32_t E, int32_t D)
 
 // From this many tiles on, per-tile counts are first summed over chunks of tiles (one more small launch),
 // so that a placement workgroup reads about 2 * sqrt(tiles) rows of counts instead of one per tile.
-// Measured: with one round per tile the extra launch pays from about 320 tiles, with two rounds from 96.
-inline int chunk_min_tiles(int rounds) { return rounds == 1 ? 320 : 96; }
+// Measured, k = 8, 256 experts and 8 devices, plan alone with / without the chunks, us: 48 tiles 13.9 / 12.3, 80 tiles 14.9 /
+// 14.3, 96 tiles 15.1 / 15.3, 128 tiles 16.1 / 17.2, 256 tiles 18.0 / 26.0, 512 tiles 27.1 / 53.4; 1024 experts and 1024 devices, 128
+// tiles 29.3 / 41.4.  (Fewer columns cross later: 64 experts and 8 devices, 128 tiles 14.0 / 12.9.)
+constexpr int kChunkMinTiles = 96;
 
 inline int tokens_per_tile(int k, int rounds) { return rounds * kRoundPairs / k; }
 inline int num_tiles(int N, int k, int rounds)
@@ -60,7 +62,7 @@ inline int single_tile_rounds(int N, int k)
 
 // Rounds per tile of the planner for these sizes.  A tile is also the unit in which dispatch moves rows
 // (expert by expert inside a tile): two rounds give every expert twice as many neighbouring rows per tile,
-// which is worth more to dispatch (5 us at 8192 tokens x 8) than the 2-3 us the planner loses against one round.
+// which is worth 5 us to dispatch at 8192 tokens x 8 rows of 14 KiB, half of what the whole plan takes there.
 inline int plan_rounds(int N, int k)
 {
     const int single = single_tile_rounds(N, k);
@@ -68,16 +70,16 @@ inline int plan_rounds(int N, int k)
 }
 
 // tiles per chunk (a power of two near sqrt(n_tiles)), or 0 when the tiles are few enough to be read one by one
-inline int chunk_tiles_for(int n_tiles, int rounds)
+inline int chunk_tiles_for(int n_tiles)
 {
-    if (n_tiles < chunk_min_tiles(rounds)) return 0;
+    if (n_tiles < kChunkMinTiles) return 0;
     int c = 8;
     while (c * c < n_tiles) c *= 2;
     return c;
 }
-inline int num_chunks(int n_tiles, int rounds)
+inline int num_chunks(int n_tiles)
 {
-    const int c = chunk_tiles_for(n_tiles, rounds);
+    const int c = chunk_tiles_for(n_tiles);
     return c ? (n_tiles + c - 1) / c : 0;
 }
 

@@ -79,7 +79,7 @@ size_t fusco_scratch_bytes(int32_t N, int32_t k, int32_t E, int32_t D)
     if (!sizes_ok(N, k, E, D)) return 0;
     const int rounds = plan_rounds(N, k);
     const int tiles = num_tiles(N, k, rounds);
-    return align_up(((size_t)tiles + (size_t)num_chunks(tiles, rounds)) * (size_t)(E + D + 1) * 4, 256);
+    return align_up(((size_t)tiles + (size_t)num_chunks(tiles)) * (size_t)(E + D + 1) * 4, 256);
 }
 
 int fusco_layout_bind(fusco_layout *L, int32_t N, int32_t k, int32_t E, int32_t D, void *d_mem, size_t bytes)
@@ -113,12 +113,12 @@ static PlanArgs plan_args(const fusco_layout *L, const int32_t *d_topk_idx, void
     a.n_tiles = num_tiles(L->N, L->k, rounds);
     a.small_groups = a.n_tiles == 1 ? (L->P + kSmallPairs - 1) / kSmallPairs : 0;
     const int round_tokens = kPlanWaves * (kWave / L->k);
-    const bool halved = chunk_tiles_for(a.n_tiles, rounds) == 0;
+    const bool halved = chunk_tiles_for(a.n_tiles) == 0;
     a.rank_rounds = ((halved ? first_half_tokens(a.tpt) : a.tpt) + round_tokens - 1) / round_tokens;
     a.stride = L->E + L->D + 1;
     a.tile_hist = (int32_t *)d_scratch;   // unused (may be NULL) when the input is a single tile
-    a.chunk_tiles = chunk_tiles_for(a.n_tiles, rounds);
-    a.n_chunks = num_chunks(a.n_tiles, rounds);
+    a.chunk_tiles = chunk_tiles_for(a.n_tiles);
+    a.n_chunks = num_chunks(a.n_tiles);
     a.chunk_hist = a.tile_hist + (size_t)a.n_tiles * (size_t)a.stride;
     a.exp_count = L->exp_count; a.exp_off = L->exp_off; a.send_count = L->send_count; a.send_off = L->send_off;
     a.pair_slot = L->pair_slot; a.slot_pair = L->slot_pair; a.slot_token = L->slot_token; a.send_src = L->send_src;

@@ -75,9 +75,10 @@ inline void combine_shape(int C, int &threads, int &segs)
 }
 
 // Rows that a thread of combine_kernel has in flight at a time (JU).  Inputs that are bound by memory run a few
-// percent faster with two than with all eight of a token's rows (8192 tokens x 8 rows of 14 KiB: 172 us against
-// 178 us; 4096 tokens: 88 against 92 us; 32768 x 8 x 2 KiB: 95 against 97 us; 8 KiB rows: the same); small inputs
-// are bound by latency and take the token's rows at once.
+// percent faster with two than with all eight of a token's rows, k = 8, us: 8192 tokens of 14 KiB 178 / 181, 4096 tokens
+// 89 / 92, 1024 tokens (112 MiB) 23.7 / 26.0, 1024 of 8 KiB (64 MiB) 13.2 / 13.5, 32768 x 2 KiB 102 / 103; 16384 x 8 KiB the same.
+// Small inputs are bound by latency and take the token's rows at once: 256 tokens of 14 KiB (28 MiB) 8.0 / 7.6 (in
+// between they cross: 56 MiB 11.7 / 12.1, 66 MiB 17.1 / 16.9).
 constexpr size_t kCombineLatencyBoundBytes = (size_t)64 << 20;
 
 template <bool Y_BF16, bool OUT_BF16>

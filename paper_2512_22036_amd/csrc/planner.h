@@ -54,9 +54,9 @@ __device__ __forceinline__ uint64_t same_key_lanes(int key, bool part, int nbits
     return (uint64_t)hi << 32 | lo;
 }
 
-// n / d for the small operands of the planner (n < 2048 with d <= 64, or n < 1024 with d <= 1024; the
-// callers stay below: pair index in a tile < 1024 over k <= 64, expert id < 1024 over E / D)
-// through magic = ceil(2^20 / d): the error n * (magic * d - 2^20) / (d * 2^20) stays below 1 / d.
+// n / d for the small operands of the planner through magic = ceil(2^20 / d): a pair's index in a tile (below 2048; up to
+// 63 more in lanes whose result is not used) over k <= 64, an expert id below 1024 over E / D <= 1024.  The result is
+// exact while n * (magic * d - 2^20), which is below n * d, stays below 2^20, and n * magic below 2^32.
 __device__ __forceinline__ int div20(int n, uint32_t magic) { return (int)(((uint32_t)n * magic) >> 20); }
 
 // Orders LDS traffic between the lanes of one wave (no instruction is emitted: LDS serves the
@@ -277,7 +277,9 @@ struct RowSums {
 };
 
 // HALVED as in pass 1 (there is no chunk level then).
-// (80 scalar registers: with more, a compute unit takes one workgroup of 16 waves at a time instead of two)
+// 80 scalar registers: with more than 96 a compute unit holds one workgroup of 16 waves at a time instead of two; with up to
+// 96 (fewer spills) plans of few tiles take the same time (8192 tokens 10.6 us, 10.7 with 80), those of several tiles per
+// compute unit longer (k = 8, 98304 tokens 26.9 us, 23.9 with 80; 131072 tokens 29.0 and 27.1).
 template <bool HALVED>
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) void plan_place_kernel(PlanArgs a)
 {
