@@ -310,11 +310,13 @@ static size_t tiles_per_launch(const fusco_layout *L, size_t row)
 // - rows shorter than 8 KiB: 8 devices 5.6 KiB 139 / 126, 1 KiB (65536 tokens) 303 / 170; 4 devices 4 KiB 152 / 151, 2 KiB
 //   131 / 151; 2 devices 5.6 KiB 84 / 95, 2 KiB 108 / 128; one device 74 / 86, 97 / 116.
 // - fewer than 8 rows per token: 4 devices, 4 rows of 14 KiB 176 / 159, 6 rows 260 / 216; 5 devices, 5 rows of 10 KiB 194 / 139;
-//   2 devices, whole rows: 6 rows of 10 KiB 118 / 131, 4 rows of 7.5 KiB 131 / 143; in column segments 6 rows of 14 KiB 202 / 185.
+//   2 devices, whole rows: 6 rows of 10 KiB 118 / 131, 4 rows of 7.5 KiB 131 / 143, of 4.5 KiB 93 / 108; in column segments 6 rows
+//   of 14 KiB 202 / 185; one device, 4 rows of 2.3 KiB 151 / 138.
 // (The receive tensors alone are left to the token walk: 62 us against 71 us at 4096 tokens of 14 KiB with 21700 send rows.)
 static bool both_in_transfer_order(const fusco_layout *L, size_t row, int segs)
 {
-    return (L->k >= 8 && L->D <= 8 && row >= kTiledShortRowBytes) || (L->D <= 2 && segs == 1);
+    if (L->k >= 8 && L->D <= 8 && row >= kTiledShortRowBytes) return true;
+    return L->D <= 2 && segs == 1 && (L->k >= 8 || row >= kTiledShortRowBytes / 2);
 }
 
 // The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or

@@ -70,3 +70,4 @@ def test_both_tensors_walk_where_the_tiles_lose(tiled):
     assert pair(8192, 10, 160, 5, 10240) == yes and pair(2048, 64, 512, 8, 8192) == yes
     assert pair(8192, 8, 256, 2, 5760) == yes and pair(8192, 8, 256, 4, 5760) == no
     assert pair(8192, 6, 60, 2, 10240) == yes and pair(8192, 6, 60, 1, 10240) == yes
+    assert pair(41616, 4, 16, 1, 2320) == no and pair(20000, 4, 16, 1, 4096) == yes and pair(41616, 8, 16, 1, 2320) == yes

@@ -165,9 +165,9 @@ def test_both_tensors_tile_by_tile_over_random_shapes():
         row = 16 * int(rng.integers(1, 3840 * 64 // tokens + 1) if few else rng.integers(512, 2600))
         aux = 16 * int(rng.choice([0, 0, 1, 3, 14]))
         if few:
-            row = max(16, min(row, 16384 - 256) - aux)
+            row = max(16 if k >= 8 else 4096, min(row, 16384 - 256) - aux)
         if case == 5:
-            row, aux = 64, 0                      # one wave per row
+            k, tokens, row, aux = 8, 256, 64, 0   # one wave per row
         N = max(17 * tokens, (256 << 20) // (k * (row + aux))) + int(rng.integers(1, 2 * tokens))
         tag = "case %d: N=%d k=%d E=%d D=%d row=%d aux=%d" % (case, N, k, E, D, row, aux)
         L = f.Layout(N, k, E, D)
