@@ -180,7 +180,10 @@ bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_
 // takes 49.9 / 52.3, 80.5 / 81.6, 121.5 / 123.3 us.  Larger ones: 56 MiB 221.3 / 220.8 (206.0 / 201.8; nobody 180.9 / 192.1),
 // 80 MiB 313.9 / 316.8 (289.9 / 284.7; nobody 259.4 / 271.1), 112 MiB 423 / 436 (nobody 371 / 380): what a reader gains is less
 // than the step loses, and from 96 MiB on the reader loses as well.
-// Rows that are not whole units, 8192 x 8 x 14352 B: combine 199 us written through, 209 us plain, 178 us non-temporal.
+// Rows that are not whole units: 8192 x 8 x 14352 B, combine 199 us written through, 209 us plain, 178 us non-temporal; outputs
+// of up to kReadBackBytes written through all the same for their reader (step and addition, k = 8, non-temporal / written
+// through: 16 MiB in rows of 2 KiB 94.8 / 94.2 (82.5 / 78.6), 32 MiB in rows of 1 KiB 190.5 / 188.5 (174.9 / 172.0), of 8 KiB
+// 160.8 / 159.5 (140.3 / 139.4); nobody reading it 80.2 / 82.8, 166.1 / 167.9, 134.2 / 138.2).
 // Outputs of inputs below kCombineLatencyBoundBytes: written through where a wave's stores cover whole units, plain otherwise.
 constexpr size_t kReadBackBytes = (size_t)32 << 20;
 
@@ -188,8 +191,8 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 {
     const bool whole = whole_units(out, row_bytes);
     if (y_bytes < kCombineLatencyBoundBytes) return whole ? kOutThrough : kOutPlain;
-    if (!whole) return kOutNonTemporal;
-    return rows * row_bytes <= kReadBackBytes ? kOutThrough : kOutThroughStream;
+    if (rows * row_bytes <= kReadBackBytes) return kOutThrough;
+    return whole ? kOutThroughStream : kOutNonTemporal;
 }
 
 // Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many

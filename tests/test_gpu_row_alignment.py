@@ -83,11 +83,12 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
 
 
-@pytest.mark.parametrize("N", [4095, 4096, 4097])     # 32 MiB of output is the largest that stays in the memory-side cache
+# 32 MiB of output is the largest that stays in the memory-side cache; rows of whole 64-byte units and not
+@pytest.mark.parametrize("N,H", [(4095, 4096), (4096, 4096), (4097, 4096), (4088, 4104), (4089, 4104)])
 @pytest.mark.parametrize("two_hop", [False, True])
-def test_combine_output_around_the_size_that_goes_past_the_cache(N, two_hop):
+def test_combine_output_around_the_size_that_goes_past_the_cache(N, H, two_hop):
     import paper_2512_22036_amd as f
-    k, E, D, H = 8, 64, 8, 4096
+    k, E, D = 8, 64, 8
     rng = np.random.default_rng(N)
     L = f.Layout(N, k, E, D)
     f.fusco_plan(L, torch.from_numpy(random_topk(rng, N, k, E)).cuda())
