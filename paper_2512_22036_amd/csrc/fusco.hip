@@ -347,6 +347,10 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     //   tokens of 7 KiB, 209 against 177 us at 16384 tokens of 12 KiB) and with 5 or 6 rows per token when the rows
     //   are moved in column segments (358 against 303 us at 16384 tokens of 14 KiB, 6 rows per token); whole rows
     //   of 8-10 KiB with 5 or 6 rows per token come out even or up to 2 % ahead in the step.
+    //   This line dates from a combine that wrote every output through.  Behind one whose large outputs go past the
+    //   memory-side cache the tiles are ahead in a loop over the same buffers (tiles / walk: 4 rows 208 / 229 us at 32768
+    //   tokens of 7 KiB, 180 / 193 at 16384 of 12 KiB, 6 rows 299 / 314 at 16384 of 14 KiB; 4 rows of 14 KiB at 32768 tokens
+    //   still 486 / 448); it has not been moved, because other states of the caches have not been measured.
     const size_t row = row_bytes + aux_row_bytes, source = (size_t)L->N * row;
     const size_t limit = g_source_chunk_bytes.load(std::memory_order_relaxed);
     if ((size_t)L->P * row <= kCacheBytes) return false;

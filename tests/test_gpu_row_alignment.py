@@ -84,7 +84,8 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
 
 
 # 32 MiB of output is the largest that stays in the memory-side cache; rows of whole 64-byte units and not
-@pytest.mark.parametrize("N,H", [(4095, 4096), (4096, 4096), (4097, 4096), (4088, 4104), (4089, 4104)])
+@pytest.mark.parametrize("N,H", [(4095, 4096), (4096, 4096), (4097, 4096), (4088, 4104), (4089, 4104),
+                                 (1023, 7168), (1024, 7168)])   # two-hop: two workgroups on a compute unit, and one
 @pytest.mark.parametrize("two_hop", [False, True])
 def test_combine_output_around_the_size_that_goes_past_the_cache(N, H, two_hop):
     import paper_2512_22036_amd as f
