@@ -63,7 +63,8 @@ void launch_args(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hip
     else hipLaunchKernelGGL(kernel, grid, block, (unsigned)lds, s, args...);
 }
 
-constexpr size_t kLdsBytes = (size_t)160 << 10;   // of a compute unit
+// just over half of a compute unit's 160 KiB of LDS, which is handed out in 128 blocks of 1280 bytes
+constexpr size_t kOverHalfLds = (size_t)65 * 1280;
 
 // Workgroup shape of combine_kernel for rows of C chunks: as many column segments as 1024 threads need, the
 // threads spread evenly over them (1280 chunks: two workgroups of 640 threads, not 1024 + 256).
@@ -197,7 +198,7 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 
 // Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many
 // devices (about as many partial rows written as half the rows read) and several rounds of tokens the kernel is faster
-// without it: dynamic LDS that it does not use keeps the second one out.  One / two workgroups per compute unit, 14 KiB rows,
+// without it: dynamic LDS that it does not use keeps the second one out (and leaves room for kernels of other streams).  One / two workgroups per compute unit, 14 KiB rows,
 // k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458, 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8),
 // 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2 devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192
 // tokens); fp32 rows of 16 KiB 185 / 181.
@@ -206,7 +207,7 @@ void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStre
 {
     const int threads = std::min(1024, round_up(a.C, kWave));
     const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
-    const size_t lds = Y_BF16 && threads > 768 && D > 5 && a.k >= 4 && N >= 1024 ? kLdsBytes : 0;
+    const size_t lds = Y_BF16 && threads > 768 && D > 5 && a.k >= 4 && N >= 1024 ? kOverHalfLds : 0;
     const hipEvent_t none = nullptr;
     switch (stores) {
     case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough>, grid, block, lds, s, none, none, a); break;
