@@ -174,25 +174,22 @@ bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_
 // 14 KiB 378.9 / 367.3 / 365.1, 16384 x 8 x 8 KiB 433.5 / 426.4 / 426.0, 32768 x 8 x 14 KiB 1467 / 1437 / 1437.  (A loop over
 // the same buffers whose x and output fit that cache together prefers to leave the output there: 340.7 / 347.0 / 344.7 at
 // 8192 x 8 x 14 KiB; 402 / 394 / 394 and 1461 / 1431 / 1429 at the other two.)
-// Outputs of up to kReadBackBytes stay there for the operation that reads them next.  A step and an addition that reads its
-// output, k = 8, past the cache / written through, us, other buffers in every step and (in brackets) the output at the same
-// place in every step: 12 MiB of output 64.0 / 62.5 (57.8 / 55.7), 20 MiB 94.3 / 92.1 (82.5 / 80.9), 32 MiB 147.8 / 139.2
-// (126.7 / 125.7); k = 4, 32 MiB 93.5 / 89.4 (83.9 / 82.2); k = 2 72.7 / 67.6 (62.3 / 61.0).  Nobody reading it, the step
-// takes 49.9 / 52.3, 80.5 / 81.6, 121.5 / 123.3 us.  Larger ones: 56 MiB 221.3 / 220.8 (206.0 / 201.8; nobody 180.9 / 192.1),
-// 80 MiB 313.9 / 316.8 (289.9 / 284.7; nobody 259.4 / 271.1), 112 MiB 423 / 436 (nobody 371 / 380): what a reader gains is less
-// than the step loses, and from 96 MiB on the reader loses as well.
-// Rows that are not whole units: 8192 x 8 x 14352 B, combine 199 us written through, 209 us plain, 178 us non-temporal; outputs
-// of up to kReadBackBytes written through all the same for their reader (step and addition, k = 8, non-temporal / written
-// through: 16 MiB in rows of 2 KiB 94.8 / 94.2 (82.5 / 78.6), 32 MiB in rows of 1 KiB 190.5 / 188.5 (174.9 / 172.0), of 8 KiB
-// 160.8 / 159.5 (140.3 / 139.4); nobody reading it 80.2 / 82.8, 166.1 / 167.9, 134.2 / 138.2).
+// Where input and output together are at most kReadBackBytes, half that cache, the output stays there for the operation
+// that reads it next.  60 steps and trainings of random shapes, each alone and with an addition behind it that reads the
+// output, other buffers in every turn, time past the cache / written through: up to 100 MiB of both 1.02-1.06 with the
+// reader (one 8 MiB output of 65 MiB: 51.5 / 49.1 us; 20 MiB of 80 MiB: 54.7 / 51.5), 0.96-1.02 without; 100-128 MiB 0.99-1.08
+// and 0.94-1.03; 128-160 MiB 0.99-1.06 and 0.92-1.00; 160-190 MiB 0.98-1.05 and 0.92-1.00.  Larger: 8192 tokens x 8 x 14 KiB
+// 423 / 436 us with the reader, 371 / 380 without.
+// Rows that are not whole units gain from the cache like the others; past it they are not written through (8192 x 8 x
+// 14352 B: combine 199 us written through, 209 us plain, 178 us non-temporal).
 // Outputs of inputs below kCombineLatencyBoundBytes: written through where a wave's stores cover whole units, plain otherwise.
-constexpr size_t kReadBackBytes = (size_t)32 << 20;
+constexpr size_t kReadBackBytes = (size_t)128 << 20;
 
 OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_bytes)
 {
     const bool whole = whole_units(out, row_bytes);
     if (y_bytes < kCombineLatencyBoundBytes) return whole ? kOutThrough : kOutPlain;
-    if (rows * row_bytes <= kReadBackBytes) return kOutThrough;
+    if (y_bytes + rows * row_bytes <= kReadBackBytes) return kOutThrough;
     return whole ? kOutThroughStream : kOutNonTemporal;
 }
 

@@ -83,8 +83,9 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
 
 
-# 32 MiB of output is the largest that stays in the memory-side cache; rows of whole 64-byte units and not
-@pytest.mark.parametrize("N,H", [(4095, 4096), (4096, 4096), (4097, 4096), (4088, 4104), (4089, 4104),
+# 128 MiB of input and output are the most that leave the output in the memory-side cache (1820 tokens with rows of 8 KiB,
+# 1816 with rows of 8208 B, which are not whole 64-byte units)
+@pytest.mark.parametrize("N,H", [(1820, 4096), (1821, 4096), (1816, 4104), (1817, 4104), (4097, 4096),
                                  (1023, 7168), (1024, 7168)])   # two-hop: two workgroups on a compute unit, and one
 @pytest.mark.parametrize("two_hop", [False, True])
 def test_combine_output_around_the_size_that_goes_past_the_cache(N, H, two_hop):
