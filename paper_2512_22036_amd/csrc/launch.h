@@ -195,10 +195,10 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 
 // Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many
 // devices (about as many partial rows written as half the rows read) and several rounds of tokens the kernel is faster
-// without it: dynamic LDS that it does not use keeps the second one out (and leaves room for kernels of other streams).  One / two workgroups per compute unit, 14 KiB rows,
-// k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458, 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8),
-// 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2 devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192
-// tokens); fp32 rows of 16 KiB 185 / 181.
+// without it: dynamic LDS that it does not use keeps the second one out (and leaves room for kernels of other streams).
+// One / two workgroups per compute unit, 14 KiB rows, k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458,
+// 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8), 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2
+// devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192 tokens); fp32 rows of 16 KiB 185 / 181.
 template <bool Y_BF16, bool OUT_BF16>
 void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
 {
