@@ -15,6 +15,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
+constexpr int kXcds = 8;                                  // accelerator complexes of an MI355X
 constexpr int kPlanThreads = 1024;                      // 16 waves per planner workgroup
 constexpr int kPlanWaves = kPlanThreads / kWave;
 // A planner tile holds R * 1024 (token, expert) pairs, R rounds of 64 pairs per wave: one round for inputs of

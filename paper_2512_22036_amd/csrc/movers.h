@@ -69,7 +69,6 @@ struct DispatchArgs {
     int32_t through, through_aux;   // tiled mode: expert rows (of the main and of the aux plane) start on 64-byte boundaries
 };
 
-constexpr int kXcds = 8;                                  // accelerator complexes of an MI355X
 constexpr int kTiledMinTiles = 2 * kXcds;                 // fewer tiles would leave XCDs idle
 constexpr size_t kTiledMaxTileBytes = (size_t)3840 << 10; // source rows of one tile must fit a 4 MB L2
 constexpr size_t kSourceChunkBytes = (size_t)128 << 20;   // source rows of one chunk: half the 256 MB memory-side cache

@@ -113,6 +113,17 @@ __device__ __forceinline__ int packed_rank(int v) { return v & 2047; }
 __device__ __forceinline__ int packed_key(int v) { return v >> 11 & 1023; }
 __device__ __forceinline__ bool packed_first(int v) { return v >> 21 & 1; }
 
+// Which of n units (tiles, or halves of tiles, in token order) workgroup b of n takes.  Workgroup b runs on XCD b mod 8, and an
+// XCD takes a run of neighbouring units: what neighbouring tiles write next to each other in the arrays indexed by slot (a
+// tile has a few pairs of an expert, a part of a 64-byte unit) then meets in one L2 and leaves it as whole lines, and pass 2 reads
+// ranks that its own XCD has written.  Plan alone, k = 8, units dealt out in turn / in runs, us: 8192 tokens 11.15 / 10.93, 24000 tokens
+// 15.3 / 14.5, 131072 tokens 27.4 / 25.3, 524288 tokens 89.8 / 75.3; pass 2 alone with runs, 131072 tokens 26.3.
+__device__ __forceinline__ int unit_of_workgroup(uint32_t b, uint32_t n)
+{
+    const uint32_t x = b % kXcds, each = n / kXcds, more = n % kXcds;   // the first `more` XCDs have one unit more than the others
+    return (int)(x * each + min(x, more) + b / kXcds);
+}
+
 template <bool HALVED>
 __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
 {
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
     uint8_t *byte = (uint8_t *)cnt;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // tokens from tile * tpt + half * split on; there may be none for the second half
-    const int tile = HALVED ? blockIdx.x >> 1 : blockIdx.x, half = HALVED ? blockIdx.x & 1 : 0;
+    const int unit = unit_of_workgroup(blockIdx.x, gridDim.x), tile = HALVED ? unit >> 1 : unit, half = HALVED ? unit & 1 : 0;
     const int split = HALVED ? first_half_tokens(a.tpt) : a.tpt;
     const int tok0 = tile * a.tpt + half * split, ntok = min(half ? a.tpt - split : split, a.N - tok0);
     const int64_t pair0 = (int64_t)tok0 * a.k;
@@ -293,7 +304,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     __shared__ uint16_t sorted[kTilePairs];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int tile = blockIdx.x, tok0 = tile * a.tpt, npairs = min(a.tpt, a.N - tok0) * a.k;
+    const int tile = unit_of_workgroup(blockIdx.x, gridDim.x), tok0 = tile * a.tpt, npairs = min(a.tpt, a.N - tok0) * a.k;
     const int64_t pair0 = (int64_t)tok0 * a.k;
     const int nb = a.E + a.D;
     const int egroups = (a.E + kWave - 1) / kWave, groups = egroups + (a.D + kWave - 1) / kWave;
