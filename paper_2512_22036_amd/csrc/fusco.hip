@@ -109,6 +109,11 @@ static PlanArgs plan_args(const fusco_layout *L, const int32_t *d_topk_idx, void
     a.N = L->N; a.k = L->k; a.E = L->E; a.D = L->D; a.Eloc = L->E / L->D;
     a.k_magic = ((1u << 20) + a.k - 1) / a.k;
     a.eloc_magic = ((1u << 20) + a.Eloc - 1) / a.Eloc;
+    a.eloc_shift = -1;
+    a.ebits = bits_for(a.E);
+    a.dbits = bits_for(a.D);
+    for (int b = 0; 1 << b <= a.Eloc; ++b)
+        if (1 << b == a.Eloc) a.eloc_shift = b;
     a.tpt = tokens_per_tile(L->k, rounds);
     a.n_tiles = num_tiles(L->N, L->k, rounds);
     a.small_groups = a.n_tiles == 1 ? (L->P + kSmallPairs - 1) / kSmallPairs : 0;

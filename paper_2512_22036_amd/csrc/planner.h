@@ -13,6 +13,8 @@ struct PlanArgs {
     const int32_t *A;
     int32_t N, k, E, D, Eloc;
     uint32_t k_magic, eloc_magic;   // ceil(2^20 / k), ceil(2^20 / Eloc): see div20
+    int32_t eloc_shift;             // log2 of Eloc, -1 where it is no power of two
+    int32_t ebits, dbits;           // bits of an expert's and of a device's number
     int32_t tpt;      // tokens per tile
     int32_t rank_rounds;   // rounds of 16 waves x (64 / k) tokens of a workgroup of pass 1
     int32_t n_tiles;
@@ -28,36 +30,50 @@ struct PlanArgs {
     int32_t *status;
 };
 
-__device__ __forceinline__ int bits_for(int nb)
+__host__ __device__ __forceinline__ int bits_for(int nb)
 {
     int n = 0;
     while ((1 << n) < nb) ++n;
     return n;
 }
 
-// Lanes of this wave that take part and hold the same key as the calling lane.  STEP bits are compared between two
-// branches; bits above nbits are zero in every key that takes part and change nothing.
+// Narrows a set of lanes (lo, hi) to those whose keys agree with the calling lane's in bits [from, to), STEP bits between
+// two branches; a bit that is the same in all keys changes nothing, so bits above a key's may be compared too.
+template <int STEP>
+__device__ __forceinline__ void match_bits(int key, int from, int to, uint32_t &lo, uint32_t &hi)
+{
+    for (int b0 = from; b0 < to; b0 += STEP) {
+#pragma unroll
+        for (int b = b0; b < b0 + STEP; ++b) {
+            const int bit = __builtin_amdgcn_sbfe(key, b, 1);   // all ones where the lane's bit is set
+            const uint64_t set = __builtin_amdgcn_ballot_w64(bit != 0);
+            lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)set, bit, 0x90);           // lo & ~(set ^ bit)
+            hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(set >> 32), bit, 0x90);
+        }
+    }
+}
+
+// Lanes of this wave that take part and hold the same key as the calling lane.
 template <int STEP = 2>
 __device__ __forceinline__ uint64_t same_key_lanes(int key, bool part, int nbits)
 {
     const uint64_t all = __builtin_amdgcn_ballot_w64(part);
     uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
-    for (int b0 = 0; b0 < nbits; b0 += STEP) {
-#pragma unroll
-        for (int b = b0; b < b0 + STEP; ++b) {
-            const uint32_t bit = (uint32_t)((int)((uint32_t)key << (31 - b)) >> 31);   // all ones where the lane's bit is set
-            const uint64_t bal = __builtin_amdgcn_ballot_w64(bit != 0);
-            lo &= ~((uint32_t)bal ^ bit);
-            hi &= ~((uint32_t)(bal >> 32) ^ bit);
-        }
-    }
+    match_bits<STEP>(key, 0, nbits, lo, hi);
     return (uint64_t)hi << 32 | lo;
 }
+
+// Lanes of a set that come before the calling lane
+__device__ __forceinline__ int lanes_before(uint32_t lo, uint32_t hi) { return (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0)); }
 
 // n / d for the small operands of the planner through magic = ceil(2^20 / d): a pair's index in a tile (below 2048; up to
 // 63 more in lanes whose result is not used) over k <= 64, an expert id below 1024 over E / D <= 1024.  The result is
 // exact while n * (magic * d - 2^20), which is below n * d, stays below 2^20, and n * magic below 2^32.
-__device__ __forceinline__ int div20(int n, uint32_t magic) { return (int)(((uint32_t)n * magic) >> 20); }
+// Both factors have fewer than 24 bits.
+__device__ __forceinline__ int div20(int n, uint32_t magic) { return (int)(__umul24((uint32_t)n, magic) >> 20); }
+
+// device of a valid expert id (any value for another)
+__device__ __forceinline__ int device(const PlanArgs &a, int e) { return a.eloc_shift >= 0 ? e >> a.eloc_shift : div20(e, a.eloc_magic); }
 
 // Orders LDS traffic between the lanes of one wave (no instruction is emitted: LDS serves the
 // accesses of a wave in program order, the fences only stop the compiler from moving them).
@@ -97,7 +113,7 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
 // half.  Chosen where there is no chunk level; with more tiles the chip is full and the halves only cost pass 2 (plan
 // alone, k = 8, one / two workgroups per tile: 1000 tokens 10.9 / 10.3 us, 16384 14.5 / 14.0, 24700 16.1 / 16.5,
 // 49152 17.0 / 18.3 us).
-constexpr int kRankRounds = 4;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens (half of it: 2)
+constexpr int kRankRounds = 4, kHalfRounds = 2;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens, half of it
 
 __host__ __device__ __forceinline__ int first_half_tokens(int tile_tokens) { return (tile_tokens + 1) / 2; }
 __device__ __forceinline__ int both_halves(int counts) { return (int)(((uint32_t)counts & 0xFFFFu) + ((uint32_t)counts >> 16)); }
@@ -124,56 +140,104 @@ __device__ __forceinline__ int unit_of_workgroup(uint32_t b, uint32_t n)
     return (int)(x * each + min(x, more) + b / kXcds);
 }
 
+// The ranking of one workgroup's tokens [tok0, tok0 + ntok).  A wave's rounds follow one another in token order; each thread
+// has one pair of every round in which held() is true.
+template <int ROUNDS>   // at most
+struct Ranking {
+    int lane, wave, per_wave, tok, rounds, ntok;
+    int raw[ROUNDS];     // expert id as given
+    int erank[ROUNDS];   // rank among the wave's pairs of the expert
+    int drank[ROUNDS];   // rank of the token's row among the wave's rows of the device
+    bool first[ROUNDS];
+    __device__ __forceinline__ Ranking(const PlanArgs &a, int rounds_, int ntok_)
+        : lane(threadIdx.x & (kWave - 1)), wave(__builtin_amdgcn_readfirstlane(threadIdx.x / kWave)),
+          per_wave(div20(kWave, a.k_magic)), tok(div20(lane, a.k_magic)), rounds(rounds_), ntok(ntok_) {}
+    __device__ __forceinline__ int first_token(int r) const { return (wave * rounds + r) * per_wave; }
+    __device__ __forceinline__ bool done(int r) const { return r >= rounds || first_token(r) >= ntok; }   // uniform over the wave
+    __device__ __forceinline__ bool held(int r) const { return tok < per_wave && first_token(r) + tok < ntok; }
+    __device__ __forceinline__ int pair(const PlanArgs &a, int r) const { return first_token(r) * a.k + lane; }   // from tok0 on
+    __device__ __forceinline__ void load(const PlanArgs &a, int64_t pair0)
+    {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) raw[r] = r < rounds && held(r) ? a.A[pair0 + pair(a, r)] : -1;
+    }
+    // byte[key * kPlanWaves + wave]: the wave's running counts, all zero at the start; returns the number of invalid ids
+    __device__ __forceinline__ int rank(const PlanArgs &a, uint8_t *byte)
+    {
+        const uint64_t not_before_token = ~(((uint64_t)1 << (tok * a.k)) - 1);
+        int bad = 0;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            if (done(r)) break;
+            const int e = raw[r];
+            const bool ok = (unsigned)e < (unsigned)a.E;
+            const uint64_t part = __builtin_amdgcn_ballot_w64(ok);
+            bad += __builtin_popcountll(__builtin_amdgcn_ballot_w64(held(r)) & ~part);
+            // lanes of the same device, and of the same expert: where a device has a power of two of experts its number is the
+            // upper bits of theirs
+            const int d = device(a, e);
+            uint32_t dlo = (uint32_t)part, dhi = (uint32_t)(part >> 32), elo, ehi;
+            if (a.eloc_shift >= 0) {
+                match_bits<2>(e, a.eloc_shift, a.ebits, dlo, dhi);
+                elo = dlo;
+                ehi = dhi;
+                match_bits<4>(e, 0, a.eloc_shift, elo, ehi);
+            } else {
+                elo = dlo;
+                ehi = dhi;
+                match_bits<4>(e, 0, a.ebits, elo, ehi);
+                match_bits<2>(d, 0, a.dbits, dlo, dhi);
+            }
+            uint8_t *const ebyte = byte + (ok ? e : 0) * kPlanWaves + wave, *const dbyte = byte + (a.E + (ok ? d : 0)) * kPlanWaves + wave;
+            const int ebefore = *ebyte, dbefore = *dbyte;
+            const uint32_t tlo = dlo & (uint32_t)not_before_token, thi = dhi & (uint32_t)(not_before_token >> 32);   // from the token's first entry on the device
+            first[r] = ok && lanes_before(tlo, thi) == 0;
+            const uint64_t firsts = __builtin_amdgcn_ballot_w64(first[r]);
+            dlo &= (uint32_t)firsts;
+            dhi &= (uint32_t)(firsts >> 32);
+            const int ein = lanes_before(elo, ehi), din = lanes_before(dlo, dhi);
+            erank[r] = ebefore + ein;
+            wave_lds_order();
+            if (ok && ein == 0) *ebyte = (uint8_t)(ebefore + __builtin_popcount(elo) + __builtin_popcount(ehi));
+            if (first[r] && din == 0) *dbyte = (uint8_t)(dbefore + __builtin_popcount(dlo) + __builtin_popcount(dhi));
+            wave_lds_order();
+            // the token's row on the device
+            drank[r] = __shfl(dbefore + din, ok ? (tlo ? __builtin_ctz(tlo) : 32 + __builtin_ctz(thi)) : lane, kWave);
+        }
+        return bad;
+    }
+    // mask of the bytes of the waves before this one
+    __device__ __forceinline__ u32x4 earlier_waves() const
+    {
+        u32x4 earlier;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) earlier[q] = wave >= 4 * q + 4 ? ~0u : wave <= 4 * q ? 0u : (1u << 8 * (wave - 4 * q)) - 1;
+        return earlier;
+    }
+};
+
 template <bool HALVED>
 __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
 {
     __shared__ u32x4 cnt[2 * kMaxBins];   // [key]: a byte per wave, experts then devices
     __shared__ int invalid;
     uint8_t *byte = (uint8_t *)cnt;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tid = threadIdx.x;
     // tokens from tile * tpt + half * split on; there may be none for the second half
     const int unit = unit_of_workgroup(blockIdx.x, gridDim.x), tile = HALVED ? unit >> 1 : unit, half = HALVED ? unit & 1 : 0;
     const int split = HALVED ? first_half_tokens(a.tpt) : a.tpt;
-    const int tok0 = tile * a.tpt + half * split, ntok = min(half ? a.tpt - split : split, a.N - tok0);
+    const int tok0 = tile * a.tpt + half * split;
     const int64_t pair0 = (int64_t)tok0 * a.k;
-    const int nb = a.E + a.D, ebits = bits_for(a.E), dbits = bits_for(a.D);
-    const int per_wave = div20(kWave, a.k_magic), tok = div20(lane, a.k_magic);
-    const uint64_t lt = ((uint64_t)1 << lane) - 1, not_before_token = ~(((uint64_t)1 << (tok * a.k)) - 1);
-
-    int raw[kRankRounds];
-#pragma unroll
-    for (int r = 0; r < kRankRounds; ++r) {
-        const int t0 = (wave * a.rank_rounds + r) * per_wave;   // the wave's rounds follow one another in token order
-        raw[r] = r < a.rank_rounds && tok < per_wave && t0 + tok < ntok ? a.A[pair0 + t0 * a.k + lane] : -1;
-    }
+    const int nb = a.E + a.D;
+    constexpr int kRounds = HALVED ? kHalfRounds : kRankRounds;
+    Ranking<kRounds> k(a, a.rank_rounds, min(half ? a.tpt - split : split, a.N - tok0));
+    k.load(a, pair0);
     for (int b = tid; b < nb; b += kPlanThreads) cnt[b] = u32x4{0, 0, 0, 0};
     if (tid == 0) invalid = 0;
     __syncthreads();
 
-    int erank[kRankRounds], drank[kRankRounds], bad = 0;
-    bool first[kRankRounds];
-#pragma unroll
-    for (int r = 0; r < kRankRounds; ++r) {
-        const int t0 = (wave * a.rank_rounds + r) * per_wave;
-        if (r >= a.rank_rounds || t0 >= ntok) break;   // uniform over the wave
-        const int e = raw[r];
-        const bool ok = (unsigned)e < (unsigned)a.E;
-        const int d = ok ? div20(e, a.eloc_magic) : -1;
-        bad += __builtin_popcountll(__builtin_amdgcn_ballot_w64(!ok && tok < per_wave && t0 + tok < ntok));
-        const int ebefore = ok ? byte[e * kPlanWaves + wave] : 0, dbefore = ok ? byte[(a.E + d) * kPlanWaves + wave] : 0;
-        const uint64_t em = same_key_lanes<4>(e, ok, ebits), same = same_key_lanes(d, ok, dbits);
-        const uint64_t of_token = same & not_before_token;   // from the token's first entry on the device
-        first[r] = ok && !(of_token & lt);
-        const uint64_t dm = same & __builtin_amdgcn_ballot_w64(first[r]);
-        erank[r] = ebefore + __builtin_popcountll(em & lt);
-        drank[r] = dbefore + __builtin_popcountll(dm & lt);
-        wave_lds_order();
-        if (ok && !(em & lt)) byte[e * kPlanWaves + wave] = (uint8_t)(ebefore + __builtin_popcountll(em));
-        if (first[r] && !(dm & lt)) byte[(a.E + d) * kPlanWaves + wave] = (uint8_t)(dbefore + __builtin_popcountll(dm));
-        wave_lds_order();
-        drank[r] = __shfl(drank[r], ok ? __builtin_ctzll(of_token) : lane, kWave);   // the token's row on the device
-    }
-    if (bad && lane == 0) atomicAdd(&invalid, bad);
+    const int bad = k.rank(a, byte);
+    if (bad && k.lane == 0) atomicAdd(&invalid, bad);
     __syncthreads();
 
     int32_t *out = a.tile_hist + (int64_t)tile * a.stride;
@@ -182,22 +246,19 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
         if constexpr (HALVED) ((uint16_t *)(out + b))[half] = (uint16_t)c;
         else out[b] = c;
     }
-    u32x4 earlier;   // the bytes of the waves before this one
+    const u32x4 earlier = k.earlier_waves();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) earlier[q] = wave >= 4 * q + 4 ? ~0u : wave <= 4 * q ? 0u : (1u << 8 * (wave - 4 * q)) - 1;
-#pragma unroll
-    for (int r = 0; r < kRankRounds; ++r) {
-        const int t0 = (wave * a.rank_rounds + r) * per_wave;
-        if (r >= a.rank_rounds || t0 >= ntok) break;
-        if (tok >= per_wave || t0 + tok >= ntok) continue;
-        const int e = raw[r];
+    for (int r = 0; r < kRounds; ++r) {
+        if (k.done(r)) break;
+        if (!k.held(r)) continue;
+        const int e = k.raw[r];
         int ew = -1, dw = -1;
         if ((unsigned)e < (unsigned)a.E) {
-            const int d = div20(e, a.eloc_magic);
-            ew = pack_rank(erank[r] + sum_bytes(cnt[e] & earlier), e, false);
-            dw = pack_rank(drank[r] + sum_bytes(cnt[a.E + d] & earlier), d, first[r]);
+            const int d = device(a, e);
+            ew = pack_rank(k.erank[r] + sum_bytes(cnt[e] & earlier), e, false);
+            dw = pack_rank(k.drank[r] + sum_bytes(cnt[a.E + d] & earlier), d, k.first[r]);
         }
-        const int64_t p = pair0 + t0 * a.k + lane;
+        const int64_t p = pair0 + k.pair(a, r);
         a.pair_slot[p] = ew;
         a.pair_send_row[p] = dw;
     }
