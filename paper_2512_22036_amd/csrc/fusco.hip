@@ -146,7 +146,14 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
         launch(plan_small_kernel, dim3(1u + (unsigned)a.small_groups), dim3(kSmallThreads), s, a, ev.start, ev.stop);
     } else {
         // inputs of several tiles are always planned in tiles of two rounds (plan_rounds)
-        if (a.n_chunks == 0) {
+        if (planned_directly(L->N, L->k, L->D)) {
+            const dim3 parts((unsigned)(kDirectParts * a.n_tiles));
+            const uintptr_t at = (uintptr_t)d_topk_idx | (uintptr_t)L->k * 4;   // a token's ids start on multiples of this
+            const bool short_rows = L->k <= 4;
+            if (at % 16 == 0) launch(short_rows ? plan_direct_kernel<4, 4> : plan_direct_kernel<4, 8>, parts, block, s, a, ev.start, ev.stop);
+            else if (at % 8 == 0) launch(short_rows ? plan_direct_kernel<2, 4> : plan_direct_kernel<2, 8>, parts, block, s, a, ev.start, ev.stop);
+            else launch(short_rows ? plan_direct_kernel<1, 4> : plan_direct_kernel<1, 8>, parts, block, s, a, ev.start, ev.stop);
+        } else if (a.n_chunks == 0) {
             launch(plan_rank_kernel<true>, dim3(2u * (unsigned)a.n_tiles), block, s, a, ev.start, nullptr);
             launch(plan_place_kernel<true>, tiles, block, s, a, nullptr, ev.stop);
         } else {

@@ -515,6 +515,209 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     }
 }
 
+// Planner for inputs of a few tiles, in one launch: every workgroup counts the whole routing for itself instead of
+// reading counts that an earlier launch has left.  A workgroup ranks an eighth of a tile's tokens in one round (as pass 1
+// does) and adds the other tokens to counters in LDS, a token per thread; a token's devices are bits in two registers, and an
+// entry whose bit is set already adds no row.  Four counters per expert (and eight per device), taken by lane, keep popular
+// keys from serialising a wave's additions.  Bound by latency (routing, counters, scan, places: four barriers) and, from
+// about 8192 pairs on, by the additions, 0.14 us per 1024 pairs.  Kernel of one launch / the two launches it replaces, us:
+// 300 tokens x 8 5.1 / 8.6, 4096 x 2 5.3 / 8.5, 1537 x 6 5.7 / 9.5, 2000 x 10 7.5 / 10.2, 4096 x 8 8.6 / 9.6.  An eighth and
+// not half a tile per workgroup because its own pairs are a chain of their own: 1537 x 6 7.1 with halves, 6.3 with quarters.
+// VEC: ids that are read at once (a token's ids start on multiples of it); IDS: ids of a token that a thread requests at a
+// time, of 16 / IDS tokens (k <= 4: 4; 8000 x 1 6.3, 7.5 us with 8).
+constexpr int kDirectParts = 8;      // workgroups per tile
+constexpr int kDirectMaxD = 64;      // bits of the mask
+constexpr int kDirectMaxK = 16;      // a thread takes all of a token's ids: 600 tokens x 33 10.5 us, 9.9 with two launches
+constexpr int kDirectMaxTokens = 8192;
+// Sizes that the one launch is faster for, one / two launches, us: 6144 x 4 8.1 / 8.6, 8192 x 4 9.0 / 8.6, 8192 x 2 7.2 / 8.5,
+// 8192 x 1 6.4 / 8.5; 5400 x 6 9.3 / 9.9, 4096 x 8 8.6 / 9.6, 6144 x 8 11.1 / 10.0, 3200 x 10 9.6 / 10.8.
+inline int direct_max_pairs(int k) { return k <= 4 ? 24576 : 32768; }
+inline bool planned_directly(int N, int k, int D)
+{
+    return k <= kDirectMaxK && D <= kDirectMaxD && N <= kDirectMaxTokens && N * k <= direct_max_pairs(k);
+}
+constexpr int kEcopies = 4, kDcopies = 8;
+// where a token counts for a workgroup's experts: in an earlier tile, in the tile before the workgroup's own, in the tile after them, in a later tile
+constexpr int kPlaces = 4;
+
+__host__ __device__ __forceinline__ int direct_part_tokens(int tile_tokens) { return (tile_tokens + kDirectParts - 1) / kDirectParts; }
+
+struct DirectLds {
+    u32x4 rank[kMaxBins + kDirectMaxD];            // as in pass 1: a byte per wave and key
+    u32x4 ecount[kPlaces * kMaxBins];              // the other tokens' pairs by place and expert
+    int dcount[2 * kDirectMaxD * kDcopies];        // the other tokens' rows by device: before and after the workgroup's tokens
+    int slot_at[kMaxBins], tile_at[kMaxBins], own_at[kMaxBins], row_at[kDirectMaxD];
+    int group[3][kMaxBins / kWave];                // sums over 64 experts: all pairs, the tile's, the workgroup's
+    u32x4 sorted[kTilePairs / kDirectParts + kWave];   // the workgroup's pairs in the order of their slots: slot, pair, row, place in the tile
+};
+
+__device__ __forceinline__ int sum4(u32x4 v) { return (int)(v[0] + v[1] + v[2] + v[3]); }
+
+template <int VEC, int IDS>
+__global__ __launch_bounds__(kPlanThreads) void plan_direct_kernel(PlanArgs a)
+{
+    constexpr int TOKENS = 16 / IDS;
+    __shared__ DirectLds s;
+    const int tid = threadIdx.x;
+    const int unit = unit_of_workgroup(blockIdx.x, gridDim.x), tile = unit / kDirectParts, part = unit % kDirectParts;
+    const int each = direct_part_tokens(a.tpt), tile0 = tile * a.tpt, tile1 = min(tile0 + a.tpt, a.N);
+    const int tok0 = min(tile0 + part * each, tile1), tok1 = min(tok0 + each, tile1), ntok = tok1 - tok0;
+    const int pair0 = tok0 * a.k;
+    Ranking<1> k(a, 1, ntok);
+    k.load(a, pair0);
+        for (int b = tid; b < a.E + a.D; b += kPlanThreads) s.rank[b] = u32x4{0, 0, 0, 0};
+    for (int b = tid; b < kPlaces * a.E; b += kPlanThreads) s.ecount[b] = u32x4{0, 0, 0, 0};
+    for (int b = tid; b < 2 * kDirectMaxD * kDcopies; b += kPlanThreads) s.dcount[b] = 0;
+    __syncthreads();
+
+    // the other tokens: numbered without the workgroup's own
+    const int others = a.N - ntok;
+    for (int w0 = k.wave * kWave; w0 < others; w0 += kPlanThreads * TOKENS) {   // uniform over the wave
+        uint32_t lo[TOKENS], hi[TOKENS];
+        int t[TOKENS], *ec[TOKENS], *dc[TOKENS];
+        bool in[TOKENS];
+#pragma unroll
+        for (int u = 0; u < TOKENS; ++u) {
+            const int i = w0 + k.lane + u * kPlanThreads;
+            in[u] = i < others;
+            t[u] = i < tok0 ? i : i + ntok;
+            lo[u] = hi[u] = 0;
+            const int place = t[u] < tile0 ? 0 : t[u] < tok0 ? 1 : t[u] < tile1 ? 2 : 3;
+            ec[u] = (int *)(s.ecount + place * a.E) + (k.lane & (kEcopies - 1));
+            dc[u] = s.dcount + (i < tok0 ? 0 : kDirectMaxD * kDcopies) + (k.lane & (kDcopies - 1));
+        }
+        for (int j0 = 0; j0 < a.k; j0 += IDS) {
+            uint32_t e[TOKENS][IDS];
+#pragma unroll
+            for (int u = 0; u < TOKENS; ++u) {
+                const int32_t *ids = a.A + (int64_t)t[u] * a.k + j0;
+#pragma unroll
+                for (int j = 0; j < IDS; j += VEC) {
+                    typedef uint32_t vec __attribute__((ext_vector_type(VEC)));
+                    vec v = ~(vec)0;
+                    if (in[u] && j0 + j < a.k) v = *(const vec *)(ids + j);
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) e[u][j + q] = v[q];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < TOKENS; ++u) {
+                if (w0 + u * kPlanThreads >= others) break;   // uniform
+#pragma unroll
+                for (int j = 0; j < IDS; ++j) {
+                    if (j0 + j >= a.k) break;   // uniform
+                    const uint32_t id = e[u][j];
+                    if (id >= (uint32_t)a.E) continue;
+                    atomicAdd(ec[u] + id * kEcopies, 1);
+                    const int d = div20((int)id, a.eloc_magic);
+                    const uint32_t bit = 1u << (d & 31);
+                    if (bit & ~(d < 32 ? lo[u] : hi[u])) atomicAdd(dc[u] + d * kDcopies, 1);
+                    lo[u] |= d < 32 ? bit : 0u;
+                    hi[u] |= d < 32 ? 0u : bit;
+                }
+            }
+        }
+    }
+    k.rank(a, (uint8_t *)s.rank);
+    __syncthreads();
+
+    // a wave per 64 experts, and one for the devices: sums before the key, over all pairs, the tile's and the workgroup's
+    const int egroups = (a.E + kWave - 1) / kWave;
+    for (int g = k.wave; g <= egroups; g += kPlanWaves) {
+        if (g < egroups) {
+            const int e = g * kWave + k.lane;
+            int own = 0, in_tile = 0, total = 0, earlier = 0, in_tile_earlier = 0;
+            if (e < a.E) {
+                own = sum_bytes(s.rank[e]);
+                earlier = sum4(s.ecount[e]);
+                in_tile_earlier = sum4(s.ecount[a.E + e]);
+                in_tile = in_tile_earlier + own + sum4(s.ecount[2 * a.E + e]);
+                total = earlier + in_tile + sum4(s.ecount[3 * a.E + e]);
+                if (unit == 0) a.exp_count[e] = total;
+            }
+            const int total_incl = wave_inclusive_sum(total), tile_incl = wave_inclusive_sum(in_tile), own_incl = wave_inclusive_sum(own);
+            if (e < a.E) {
+                s.slot_at[e] = total_incl - total + earlier + in_tile_earlier;
+                s.tile_at[e] = tile_incl - in_tile + in_tile_earlier;
+                s.own_at[e] = own_incl - own;
+            }
+            if (k.lane == kWave - 1) {
+                s.group[0][g] = total_incl;
+                s.group[1][g] = tile_incl;
+                s.group[2][g] = own_incl;
+            }
+        } else {
+            const int d = k.lane;
+            int earlier = 0, total = 0;
+            if (d < a.D) {
+                const u32x4 *c = (const u32x4 *)(s.dcount + d * kDcopies), *later = c + kDirectMaxD * kDcopies / 4;
+                earlier = sum4(c[0]) + sum4(c[1]);
+                total = earlier + sum_bytes(s.rank[a.E + d]) + sum4(later[0]) + sum4(later[1]);
+            }
+            const int incl = wave_inclusive_sum(total);
+            s.row_at[d] = incl - total + earlier;
+            if (unit == 0 && d < a.D) {
+                a.send_count[d] = total;
+                a.send_off[d] = incl - total;
+            }
+            if (unit == 0 && d == kWave - 1) a.send_off[a.D] = incl;
+        }
+    }
+    __syncthreads();
+
+    int off[3], sum[3];   // offsets of the groups, one per lane, and the sums over all of them
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int v = k.lane < egroups ? s.group[q][k.lane] : 0, incl = wave_inclusive_sum(v);
+        off[q] = incl - v;
+        sum[q] = __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    if (!k.done(0)) {
+        const int e = k.raw[0];
+        const bool ok = (unsigned)e < (unsigned)a.E;
+        const int g = ok ? e / kWave : 0;
+        const int slot_off = __shfl(off[0], g, kWave), tile_off = __shfl(off[1], g, kWave), own_off = __shfl(off[2], g, kWave);
+        if (k.held(0)) {
+            const int p = pair0 + k.pair(a, 0);
+            int slot = -1, row = -1;
+            if (ok) {
+                const u32x4 earlier = k.earlier_waves();
+                const int d = device(a, e), rank = k.erank[0] + sum_bytes(s.rank[e] & earlier);
+                slot = s.slot_at[e] + slot_off + rank;
+                row = s.row_at[d] + k.drank[0] + sum_bytes(s.rank[a.E + d] & earlier);
+                s.sorted[s.own_at[e] + own_off + rank] = u32x4{(uint32_t)slot, (uint32_t)p, (uint32_t)row, (uint32_t)(s.tile_at[e] + tile_off + rank)};
+                if (k.first[0]) a.send_src[row] = tok0 + k.first_token(0) + k.tok;
+            }
+            a.pair_slot[p] = slot;
+            a.pair_send_row[p] = row;
+            a.pair_first[p] = ok && k.first[0] ? 1 : 0;
+        }
+    }
+    __syncthreads();
+    const int cap = a.tpt * a.k;
+    int32_t *order = a.tile_slots + (int64_t)tile * cap;
+    for (int q = tid; q < sum[2]; q += kPlanThreads) {
+        const u32x4 v = s.sorted[q];
+        const int slot = (int)v[0], p = (int)v[1];
+        a.slot_pair[slot] = p;
+        a.slot_token[slot] = tok0 + div20(p - pair0, a.k_magic);
+        a.slot_send_row[slot] = (int)v[2];
+        order[v[3]] = slot;
+    }
+    if (part == kDirectParts - 1)
+        for (int q = sum[1] + tid; q < cap; q += kPlanThreads) order[q] = -1;
+    if (unit == 0) {
+        for (int g = k.wave; g < egroups; g += kPlanWaves) {
+            const int at = __builtin_amdgcn_readlane(off[0], g), e = g * kWave + k.lane;
+            if (e < a.E) a.exp_off[e] = s.slot_at[e] + at;   // the first workgroup has no pairs before its own
+        }
+        if (tid == 0) {
+            a.exp_off[a.E] = sum[0];
+            *a.status = a.N * a.k - sum[0];
+        }
+    }
+}
+
 // Planner for inputs of a single tile (at most 2048 pairs), in one launch and without counters or scans over keys: a
 // pair's slot is the number of pairs that come before it in (expert, pair) order, and the workgroup that owns the
 // pair counts them by comparing its key with everybody's - the keys of all pairs fit the registers of one

@@ -108,6 +108,29 @@ def test_several_tiles(N, k, E, D, bad):
     check(L, A, "plan")
 
 
+# a few tiles in one launch: every width of the reads (by k and by where the routing lies), both ends of the sizes and one past
+# them, ragged last tiles and eighths of tiles, devices in one and in both halves of the mask, one past the mask
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("N,k,E,D", [(2049, 1, 16, 1), (8192, 1, 64, 32), (8193, 1, 64, 64), (1025, 2, 16, 4), (8192, 2, 128, 64),
+                                     (8192, 3, 96, 8), (6144, 4, 60, 4), (6145, 4, 64, 8), (5000, 5, 160, 5), (1537, 6, 160, 5),
+                                     (293, 7, 1024, 64), (257, 8, 256, 8), (4096, 8, 256, 64), (4097, 8, 256, 8), (3000, 8, 1023, 33),
+                                     (2000, 10, 384, 8), (129, 16, 64, 2), (2048, 16, 1024, 64), (2000, 12, 130, 65), (150, 17, 96, 4)])
+def test_few_tiles(N, k, E, D, offset):
+    import paper_2512_22036_amd as f
+    for bad in (False, True):
+        A = routing(N + k + offset, N, k, E, not bad, bad)
+        if bad:
+            A[N // 2:N // 2 + 300] = 0   # one expert many times
+        flat = torch.zeros(N * k + 4, dtype=torch.int32, device="cuda")
+        d_A = flat[offset:offset + N * k].view(N, k)
+        d_A.copy_(torch.from_numpy(A))
+        L = f.Layout(N, k, E, D)
+        assert L.tile_count > 1
+        L.mem.fill_(0x7B)
+        f.fusco_plan(L, d_A)
+        check(L, A, "plan")
+
+
 @pytest.mark.parametrize("row_bytes,aux_bytes", [(32768 - 16, 0), (32768, 0), (32768 + 16, 0), (32768, 16), (32752, 48), (65536, 0),
                                                  (65536 + 16, 32), (40960, 32768 + 16), (98304 + 1040, 224)])
 @pytest.mark.parametrize("N,k,E,D", [(1, 8, 256, 8), (5, 3, 24, 24), (31, 64, 512, 8), (300, 6, 160, 5)])
