@@ -66,6 +66,13 @@ void launch_args(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hip
 // just over half of a compute unit's 160 KiB of LDS, which is handed out in 128 blocks of 1280 bytes
 constexpr size_t kOverHalfLds = (size_t)65 * 1280;
 
+// Rows that a thread of combine_kernel has in flight at a time (JU).  Inputs that are bound by memory run a few
+// percent faster with two than with all eight of a token's rows, k = 8, us: 8192 tokens of 14 KiB 178 / 181, 4096 tokens
+// 89 / 92, 1024 tokens (112 MiB) 23.7 / 26.0, 1024 of 8 KiB (64 MiB) 13.2 / 13.5, 32768 x 2 KiB 102 / 103; 16384 x 8 KiB the same.
+// Small inputs are bound by latency and take the token's rows at once: 256 tokens of 14 KiB (28 MiB) 8.0 / 7.6 (in
+// between they cross: 56 MiB 11.7 / 12.1, 66 MiB 17.1 / 16.9).
+constexpr size_t kCombineLatencyBoundBytes = (size_t)64 << 20;
+
 // Workgroup shape of combine_kernel for rows of C chunks: as many column segments as 1024 threads need, the
 // threads spread evenly over them (1280 chunks: two workgroups of 640 threads, not 1024 + 256).
 inline void combine_shape(int C, int &threads, int &segs)
@@ -75,21 +82,30 @@ inline void combine_shape(int C, int &threads, int &segs)
     threads = round_up((C + segs - 1) / segs, kWave);
 }
 
-// Rows that a thread of combine_kernel has in flight at a time (JU).  Inputs that are bound by memory run a few
-// percent faster with two than with all eight of a token's rows, k = 8, us: 8192 tokens of 14 KiB 178 / 181, 4096 tokens
-// 89 / 92, 1024 tokens (112 MiB) 23.7 / 26.0, 1024 of 8 KiB (64 MiB) 13.2 / 13.5, 32768 x 2 KiB 102 / 103; 16384 x 8 KiB the same.
-// Small inputs are bound by latency and take the token's rows at once: 256 tokens of 14 KiB (28 MiB) 8.0 / 7.6 (in
-// between they cross: 56 MiB 11.7 / 12.1, 66 MiB 17.1 / 16.9).
-constexpr size_t kCombineLatencyBoundBytes = (size_t)64 << 20;
+// The same for inputs bound by latency: rows of more than 512 chunks in segments of 128 threads, which spread few tokens over
+// the chip, get going sooner than workgroups of 16 waves and finish more evenly; of 64 threads where even those are few.
+// Segments of 64 / 128 / the whole row, rows of 14 KiB, us: 4 tokens x 8 3.0 / 3.1 / 3.9, 64 x 8 4.7 / 5.4 / 6.0, 128 x 8
+// 6.2 / 6.1 / 6.6, 512 x 8 12.2 / 12.0 / 11.9, 1000 x 4 13.5 / 13.3 / 14.8, 3500 x 1 18.3 / 18.9 / 21.7.  Shorter rows: 4096
+// columns, 1000 x 2 5.9 / 5.6 / 5.5, 300 x 4 3.7 / 4.3 / 4.5; 2880 columns, 1537 x 6 15.8 / 16.7 / 15.6.
+inline void combine_shape_latency(int N, int C, int &threads, int &segs)
+{
+    combine_shape(C, threads, segs);
+    if (C <= 512) return;
+    const bool few = (int64_t)N * ((C + 127) / 128) < 512;
+    threads = few ? 64 : 128;
+    segs = (C + threads - 1) / threads;
+}
 
 template <bool Y_BF16, bool OUT_BF16>
 void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
+    const bool latency = (size_t)N * (size_t)a.k * (size_t)a.C * 16 < kCombineLatencyBoundBytes;
     int threads;
-    combine_shape(a.C, threads, a.segs);
+    if (latency) combine_shape_latency(N, a.C, threads, a.segs);
+    else combine_shape(a.C, threads, a.segs);
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
-    if ((size_t)N * (size_t)a.k * (size_t)a.C * 16 < kCombineLatencyBoundBytes) {
+    if (latency) {
         if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutThrough>, grid, block, s, a, e0, e1);
         else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutPlain>, grid, block, s, a, e0, e1);
     } else {
@@ -199,10 +215,15 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 // One / two workgroups per compute unit, 14 KiB rows, k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458,
 // 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8), 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2
 // devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192 tokens); fp32 rows of 16 KiB 185 / 181.
+// Small inputs are bound by latency and take their rows in segments of 256 threads; segments / whole rows, 14 KiB rows x 8, us:
+// 4 tokens 5.5 / 6.6, 128 11.6 / 12.6, 300 (33 MiB) 16.1 / 17.6, 500 (55 MiB) 24.6 / 24.3.
+constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20;
+
 template <bool Y_BF16, bool OUT_BF16>
 void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
 {
-    const int threads = std::min(1024, round_up(a.C, kWave));
+    const bool small = (size_t)N * (size_t)a.k * (size_t)a.C * 16 < kTwoHopSmallBytes;
+    const int threads = std::min(small ? 256 : 1024, round_up(a.C, kWave));
     const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
     const size_t lds = Y_BF16 && threads > 768 && D > 5 && a.k >= 4 && N >= 1024 ? kOverHalfLds : 0;
     const hipEvent_t none = nullptr;

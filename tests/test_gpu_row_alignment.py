@@ -83,6 +83,36 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
 
 
+# rows of more than 512 chunks of small inputs are cut into segments of 64 or 128 threads, two-hop rows into segments of 256:
+# row lengths around their edges, token counts on either side of 512 workgroups, the last and the first size past the limits
+# (64 MiB of experts' outputs; 48 MiB two-hop)
+@pytest.mark.parametrize("two_hop", [False, True])
+@pytest.mark.parametrize("N,k,C", [(1, 8, 513), (1, 1, 512), (3, 6, 575), (7, 8, 577), (63, 8, 1024), (64, 8, 1024), (65, 3, 1025), (102, 2, 640),
+                                   (103, 2, 639), (5, 5, 2049), (511, 8, 1024), (512, 8, 1024), (383, 8, 1024), (384, 8, 1024), (1000, 2, 896)])
+@pytest.mark.parametrize("y_f32,out_f32", [(False, False), (False, True), (True, False)])
+def test_combine_of_small_inputs_in_column_segments(N, k, C, two_hop, y_f32, out_f32):
+    import paper_2512_22036_amd as f
+    E, D = 64, 8
+    H = C * (4 if y_f32 else 8)
+    rng = np.random.default_rng(N + C)
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(random_topk(rng, N, k, E)).cuda())
+    y = torch.randint(-127, 128, (L.P, H), device="cuda").to(torch.float32 if y_f32 else torch.bfloat16)
+    w = torch.full((N, k), 0.125, device="cuda")      # whole numbers and a power of two: every sum is exact
+    kind = torch.float32 if out_f32 else torch.bfloat16
+    out, room = rows_at(N, H * (4 if out_f32 else 2), 0)
+    out = out.view(kind)
+    if two_hop:
+        f.fusco_combine_two_hop(L, y, w, torch.empty((L.send_cap, H), device="cuda"), out)
+    else:
+        f.fusco_combine(L, y, w, out)
+    want = torch.zeros((N, H), dtype=torch.float32, device="cuda")
+    for rows in L.array("pair_slot").view(N, k).long().t():
+        want += y[rows].float()
+    assert torch.equal(out, (want / 8).to(kind))
+    assert bool((room[out.numel() * out.element_size():] == 0xEE).all())
+
+
 # 128 MiB of input and output are the most that leave the output in the memory-side cache (1820 tokens with rows of 8 KiB,
 # 1816 with rows of 8208 B, which are not whole 64-byte units)
 @pytest.mark.parametrize("N,H", [(1820, 4096), (1821, 4096), (1816, 4104), (1817, 4104), (4097, 4096),
