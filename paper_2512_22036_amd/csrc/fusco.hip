@@ -231,7 +231,10 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     m.seg_chunks = m.segs > 1 ? round_up((Ct + m.segs - 1) / m.segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
     const ArmedEvents ev;
     const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)m.segs), block(kSmallThreads);
-    launch_args(plan_dispatch_kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, m);
+    const int cpt = (m.seg_chunks + kSmallThreads - 1) / kSmallThreads;
+    const auto kernel = m.Ca ? (cpt <= 1 ? plan_dispatch_kernel<1, true> : cpt <= 2 ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<4, true>)
+                             : (cpt <= 1 ? plan_dispatch_kernel<1, false> : cpt <= 2 ? plan_dispatch_kernel<2, false> : plan_dispatch_kernel<4, false>);
+    launch_args(kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, m);
     return launch_status();
 }
 

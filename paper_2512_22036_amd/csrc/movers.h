@@ -274,8 +274,12 @@ __global__ __launch_bounds__(256) void touch_kernel(const u32x4 *src, size_t n)
 // 20.6 -> 6.3 us, 1 MiB 198 -> 11; 128 tokens of 40 KiB 14.5 -> 10.8 us, 128 KiB 47 -> 31; 256 tokens of 64 KiB 35.6 -> 31.0 us.
 // (Finding the slots twice costs more than it gives for many tokens of little more than 32 KiB: 500 tokens with k = 4 of 33 KiB
 // 16.0 -> 20.4 us, 64 KiB 37.2 -> 34.1 us.)
-constexpr int kFusedChunks = 4;   // 16-byte chunks per thread held in registers across the planning: 32 KiB a workgroup
+// CPT: 16-byte chunks of the row (or of its segment) per thread, as few as cover it; AUX: the second plane exists.  Chosen at
+// compile time because every store of a slot is a branch of its own otherwise: CPT 4 and both planes always / as here, k = 8, us: 4
+// tokens of 14 KiB 4.9 / 3.9, of 7392 B in two planes 4.5 / 4.2, 128 tokens 7.1 / 6.2 and 5.7 / 5.4; 1000 x 2 x 1 KiB 9.2 / 7.8.
+constexpr int kFusedChunks = 4;   // most chunks per thread held in registers across the planning: 32 KiB a workgroup
 
+template <int CPT, bool AUX>
 __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a, DispatchArgs m)
 {
     __shared__ SmallLds s;
@@ -292,11 +296,11 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
     const int c0 = seg * m.seg_chunks + tid, c_end = min(m.C + m.Ca, (seg + 1) * m.seg_chunks);
     // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
     const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
-    u32x4 v[kFusedChunks];
+    u32x4 v[CPT];
 #pragma unroll
-    for (int i = 0; i < kFusedChunks; ++i) {
+    for (int i = 0; i < CPT; ++i) {
         const int c = c0 + i * kSmallThreads;
-        if (c < c_end) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
+        if (c < c_end) v[i] = load16_stream((!AUX || c < m.C ? src : src_aux) + c);
     }
     const int slots = small_slots(s, a, t * a.k, a.k);
     for (int j = 0; j < a.k; ++j) {
@@ -304,9 +308,9 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
         if (slot < 0) continue;
         u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
 #pragma unroll
-        for (int i = 0; i < kFusedChunks; ++i) {
+        for (int i = 0; i < CPT; ++i) {
             const int c = c0 + i * kSmallThreads;
-            if (c < c_end) (c < m.C ? dst : dst_aux)[c] = v[i];
+            if (c < c_end) (!AUX || c < m.C ? dst : dst_aux)[c] = v[i];
         }
     }
 }
