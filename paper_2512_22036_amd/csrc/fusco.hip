@@ -515,13 +515,19 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const bool stream_stores = streaming || (!two_hop && written > kCacheBytes);   // the second hop reads the rows at once
         const bool cached_loads = stream_stores && (size_t)L->N * row <= g_source_chunk_bytes.load(std::memory_order_relaxed);
         const int knob = g_walk_mode.load(std::memory_order_relaxed);
+        const bool eager = (uint64_t)L->N * (uint64_t)segs <= kWalkEagerGroups || !a.write_expert;
         const int mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0);
-#define FUSCO_WALK(CPT)                                                                       \
-    switch (mode) {                                                                           \
-    case 0: launch(dispatch_kernel<CPT, 0>, grid, block, s, a, ev.start, ev.stop); break;     \
-    case 1: launch(dispatch_kernel<CPT, 1>, grid, block, s, a, ev.start, ev.stop); break;     \
-    case 2: launch(dispatch_kernel<CPT, 2>, grid, block, s, a, ev.start, ev.stop); break;     \
-    default: launch(dispatch_kernel<CPT, 3>, grid, block, s, a, ev.start, ev.stop); break;    \
+#define FUSCO_WALK_AS(CPT, MODE)                                                                       \
+    do {                                                                                              \
+        if (eager) launch(dispatch_eager_kernel<CPT, MODE>, grid, block, s, a, ev.start, ev.stop);    \
+        else launch(dispatch_kernel<CPT, MODE>, grid, block, s, a, ev.start, ev.stop);                \
+    } while (0)
+#define FUSCO_WALK(CPT)                                                                               \
+    switch (mode) {                                                                                   \
+    case 0: FUSCO_WALK_AS(CPT, 0); break;                                                             \
+    case 1: FUSCO_WALK_AS(CPT, 1); break;                                                             \
+    case 2: FUSCO_WALK_AS(CPT, 2); break;                                                             \
+    default: FUSCO_WALK_AS(CPT, 3); break;                                                            \
     }
         switch (cpt) {
         case 1: FUSCO_WALK(1); break;
@@ -529,6 +535,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         default: FUSCO_WALK(4); break;
         }
 #undef FUSCO_WALK
+#undef FUSCO_WALK_AS
     }
     if (two_hop) {
         // second hop: every row of the expert tensor is pulled from its token's row in the receive
@@ -587,8 +594,8 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
     int threads;
     combine_shape(a.C, threads, a.segs);
     const dim3 grid((unsigned)L->send_cap * (unsigned)a.segs);
-    if (y_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_kernel<true, false, 1, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
-    else hipLaunchKernelGGL((combine_kernel<false, false, 1, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
+    if (y_dtype == FUSCO_BF16) hipLaunchKernelGGL((combine_kernel<true, false, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
+    else hipLaunchKernelGGL((combine_kernel<false, false, 8, kOutPlain, true>), grid, dim3(threads), 0, s, a);
     // level 1 reversed: sum of the token's partial rows
     SumPartialsArgs b;
     b.partial = (const u32x4 *)d_partial;

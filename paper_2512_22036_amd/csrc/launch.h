@@ -106,12 +106,16 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
     if (latency) {
-        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutThrough>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 8, kOutPlain>, grid, block, s, a, e0, e1);
+        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 8, kOutThrough>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, 8, kOutPlain>, grid, block, s, a, e0, e1);
+    } else if (a.k == 2) {   // both rows of a token at once: there is no third to keep memory busy meanwhile
+        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutThrough>, grid, block, s, a, e0, e1);
+        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutNonTemporal>, grid, block, s, a, e0, e1);
     } else {
-        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThrough>, grid, block, s, a, e0, e1);
-        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, 2, kOutNonTemporal>, grid, block, s, a, e0, e1);
+        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutThrough>, grid, block, s, a, e0, e1);
+        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutThroughStream>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutNonTemporal>, grid, block, s, a, e0, e1);
     }
 }
 

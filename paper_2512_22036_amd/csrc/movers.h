@@ -91,7 +91,7 @@ __device__ __forceinline__ void put16(u32x4 *p, u32x4 v)
     else *p = v;
 }
 
-template <int CPT, int MODE = 0>   // MODE bit 0: cached loads, bit 1: non-temporal stores
+template <int CPT, int MODE>   // MODE bit 0: cached loads, bit 1: non-temporal stores
 __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
 {
     // workgroup = (token, column segment), segments of one row next to each other in launch order, so that a
@@ -136,6 +136,53 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
             }
         }
     }
+}
+
+// The token walk of few workgroups: the token's slots (and send rows) come into the lanes of a wave with one load, and its rows
+// are stored without a wait between them.  In dispatch_kernel a slot is looked up when its row is stored, and that load waits
+// for the stores before it (loads and stores share a counter): every workgroup has one row on its way at a time.  With few
+// workgroups the waits are what the call takes (with them / here, us: 300 tokens x 8 x 14 KiB 9.3 / 7.7, 500 11.7 / 10.1, 400 x 8
+// x 4.1 KiB in two planes 5.3 / 4.2, 700 x 8 x 2 KiB 5.1 / 3.8); where there are many, memory is faster with fewer rows being
+// written at a time (8192 x 8 x 2 KiB 29.2 / 30.4, 4000 x 4 x 4.1 KiB in two planes 14.3 / 15.7, 32768 x 4 x 7 KiB 229 / 232).
+// Send rows alone, which are fewer than the pairs, always go this way (21700 rows of 14 KiB 62.2 / 59.5).
+constexpr uint64_t kWalkEagerGroups = 1024;
+
+template <int CPT, int MODE>
+__global__ __launch_bounds__(256) void dispatch_eager_kernel(DispatchArgs a)
+{
+    const int t = blockIdx.x / (uint32_t)a.segs, seg = blockIdx.x - (uint32_t)t * a.segs;
+    const int c_end = min(a.C + a.Ca, (seg + 1) * a.seg_chunks);
+    const int c0 = seg * a.seg_chunks + threadIdx.x;
+    // entry j's slot and send row in lane j; -1: none
+    const int lane = threadIdx.x & (kWave - 1);
+    int my_slot = -1, my_row = -1;
+    if (lane < a.k) {
+        const size_t p = (size_t)t * a.k + lane;
+        if (a.write_expert) my_slot = a.pair_slot[p];
+        if (a.write_wire && a.pair_first[p]) my_row = a.pair_send_row[p];
+    }
+    u32x4 v[CPT];
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+        const int c = min(c0 + i * (int)blockDim.x, c_end - 1);   // no branch between the loads: threads past the segment read its last chunk
+        const u32x4 *src = a.x + (size_t)t * a.C + c;
+        if (c >= a.C) src = a.x_aux + (size_t)t * a.Ca + (c - a.C);
+        v[i] = (MODE & 1) ? *src : load16_stream(src);
+    }
+    const auto store_all = [&](int mine, u32x4 *rows, u32x4 *rows_aux) {
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(mine >= 0); left; left &= left - 1) {
+            const int row = __builtin_amdgcn_readlane(mine, __builtin_ctzll(left));
+#pragma unroll
+            for (int i = 0; i < CPT; ++i) {
+                const int c = c0 + i * blockDim.x;
+                u32x4 *dst = rows + (size_t)row * a.C + c;
+                if (c >= a.C) dst = rows_aux + (size_t)row * a.Ca + (c - a.C);
+                if (c < c_end) put16<(MODE & 2) != 0>(dst, v[i]);
+            }
+        }
+    };
+    store_all(my_slot, a.expert_buf, a.expert_aux);
+    store_all(my_row, a.send_buf, a.send_aux);
 }
 
 // Dispatch in transfer order (the tile_slots list of the planner): one workgroup per destination row.  The
@@ -359,9 +406,8 @@ __device__ __forceinline__ void put_floats(u32x4 *row, int c, int n, const float
     }
 }
 
-// Combine: every thread owns CPT 16-byte chunks of the output row, pulls the matching chunks of
-// the token's k rows (JU rows in flight at a time) and accumulates in fp32 with one fused
-// multiply-add per term in ascending j.
+// Combine: every thread owns a 16-byte chunk of y's rows, pulls that chunk of the token's k rows and accumulates in fp32
+// with one fused multiply-add per term in ascending j.
 struct CombineArgs {
     const u32x4 *y;
     const float *w;
@@ -387,7 +433,53 @@ __device__ __forceinline__ uint32_t to_bf16(float f)
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-template <bool Y_BF16, bool OUT_BF16, int CPT, int JU, OutStores STORES, bool PER_SEND_ROW = false>
+// acc += w * v, one fused multiply-add per element
+template <bool Y_BF16, int EPC>
+__device__ __forceinline__ void add_row(float (&acc)[EPC], u32x4 v, float w)
+{
+    if constexpr (Y_BF16) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc[2 * q] = __builtin_fmaf(w, bf16_lo(v[q]), acc[2 * q]);
+            acc[2 * q + 1] = __builtin_fmaf(w, bf16_hi(v[q]), acc[2 * q + 1]);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] = __builtin_fmaf(w, __uint_as_float(v[q]), acc[q]);
+    }
+}
+
+// The next JU entries of `left`: all their loads without a branch or a wait between them, then the sums.
+template <bool Y_BF16, int JU, int EPC>
+__device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &left, int my_slot, float my_w, int c, float (&acc)[EPC])
+{
+    u32x4 v[JU];
+    float wj[JU];
+    const u32x4 *row[JU];
+#pragma unroll
+    for (int jj = 0; jj < JU; ++jj) {
+        const int j = __builtin_ctzll(left);
+        left &= left - 1;
+        row[jj] = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, j) * a.C;
+        wj[jj] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), j));
+    }
+    if (c < a.C) {
+#pragma unroll
+        for (int jj = 0; jj < JU; ++jj) v[jj] = load16_stream(row[jj] + c);
+    }
+#pragma unroll
+    for (int jj = 0; jj < JU; ++jj) add_row<Y_BF16>(acc, v[jj], wj[jj]);
+}
+
+// JU: rows of a token that a thread has in flight.
+// 8 (inputs bound by latency): slots and weights come into the lanes of a wave with one load each, and up to eight rows are
+// requested back to back.  Behind a branch per entry the compiler waited for each row before it requested the next; 1537 tokens
+// x 6 x 5760 B to fp32 15.5 -> 13.9 us, 1000 x 4 x 14 KiB 14.8 -> 13.1, 128 x 8 x 14 KiB 6.6 -> 6.1.
+// 1 or 2 (inputs bound by memory, which is faster the fewer rows are being read at a time): slots and weights are scalar
+// loads, which do not queue behind the rows, one step ahead of their use.  Rows in flight 1 / 2 / 4 / 8, us: 8192 x 8 x 14 KiB
+// 173 / 180 / 184 / 181, 16384 x 8 x 8 KiB 203 / 210 / 211 / 212, 32768 x 8 x 14 KiB 700 / 750 / 754 / 744; two entries per
+// token 20000 x 14 KiB 144 / 139 (slots in lanes instead: 155 with 1).
+template <bool Y_BF16, bool OUT_BF16, int JU, OutStores STORES, bool PER_SEND_ROW = false>
 __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
 {
     constexpr int EPC = Y_BF16 ? 8 : 4;   // elements per 16-byte chunk of y
@@ -403,86 +495,98 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
         if (r >= *a.n_rows_dev) return;
         t = a.send_src[r];
     }
-    const int c0 = seg * (blockDim.x * CPT) + threadIdx.x;
-    const int32_t *slots = a.pair_slot + (size_t)t * a.k;
-    const float *wt = a.w + (size_t)t * a.k;
+    const int c = seg * blockDim.x + threadIdx.x;
+    float acc[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
 
-    float acc[CPT][EPC];
+    if constexpr (JU <= 2) {
+        static_assert(!PER_SEND_ROW, "the entries of a send row are picked out in lanes");
+        const int32_t *slots = a.pair_slot + (size_t)t * a.k;
+        const float *wt = a.w + (size_t)t * a.k;
+        int slot[JU], next_slot[JU];
+        float wj[JU], next_w[JU];
+        const auto look_up = [&](int j0, int (&sl)[JU], float (&w)[JU]) {
 #pragma unroll
-    for (int i = 0; i < CPT; ++i)
+            for (int jj = 0; jj < JU; ++jj) {
+                const int j = min(j0 + jj, a.k - 1);
+                sl[jj] = j0 + jj < a.k ? slots[j] : -1;
+                w[jj] = wt[j];
+            }
+        };
+        look_up(0, slot, wj);
+        for (int j0 = 0; j0 < a.k; j0 += JU) {
+            look_up(j0 + JU, next_slot, next_w);
+            bool all = true;
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[i][e] = 0.0f;
-
-    for (int j0 = 0; j0 < a.k; j0 += JU) {
-        u32x4 v[JU][CPT];
-        float wj[JU];
-        bool on[JU];
+            for (int jj = 0; jj < JU; ++jj) all = all && slot[jj] >= 0;
+            if (c < a.C) {
+                if (all) {
+                    u32x4 v[JU];
 #pragma unroll
-        for (int jj = 0; jj < JU; ++jj) {
-            const int j = j0 + jj;
-            on[jj] = false;
-            if (j < a.k) {
-                const int slot = slots[j];
-                wj[jj] = wt[j];
-                bool take = slot >= 0;
-                if constexpr (PER_SEND_ROW) take = take && a.pair_send_row[(size_t)t * a.k + j] == r;
-                if (take) {
-                    on[jj] = true;
+                    for (int jj = 0; jj < JU; ++jj) v[jj] = load16_stream(a.y + (size_t)slot[jj] * a.C + c);
 #pragma unroll
-                    for (int i = 0; i < CPT; ++i) {
-                        const int c = c0 + i * blockDim.x;
-                        if (c < a.C) v[jj][i] = load16_stream(a.y + (size_t)slot * a.C + c);
-                    }
+                    for (int jj = 0; jj < JU; ++jj) add_row<Y_BF16>(acc, v[jj], wj[jj]);
+                } else if (JU > 1) {
+#pragma unroll
+                    for (int jj = 0; jj < JU; ++jj)
+                        if (slot[jj] >= 0) add_row<Y_BF16>(acc, load16_stream(a.y + (size_t)slot[jj] * a.C + c), wj[jj]);
                 }
             }
-        }
 #pragma unroll
-        for (int jj = 0; jj < JU; ++jj) {
-            if (!on[jj]) continue;
-#pragma unroll
-            for (int i = 0; i < CPT; ++i) {
-                if constexpr (Y_BF16) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        acc[i][2 * q] = __builtin_fmaf(wj[jj], bf16_lo(v[jj][i][q]), acc[i][2 * q]);
-                        acc[i][2 * q + 1] = __builtin_fmaf(wj[jj], bf16_hi(v[jj][i][q]), acc[i][2 * q + 1]);
-                    }
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        acc[i][q] = __builtin_fmaf(wj[jj], __uint_as_float(v[jj][i][q]), acc[i][q]);
-                }
+            for (int jj = 0; jj < JU; ++jj) {
+                slot[jj] = next_slot[jj];
+                wj[jj] = next_w[jj];
             }
         }
+    } else {
+        // entry j's slot and weight in lane j; -1: nothing to add
+        const int lane = threadIdx.x & (kWave - 1);
+        int my_slot = -1;
+        float my_w = 0.0f;
+        if (lane < a.k) {
+            const size_t p = (size_t)t * a.k + lane;
+            my_slot = a.pair_slot[p];
+            my_w = a.w[p];
+            if constexpr (PER_SEND_ROW) my_slot = a.pair_send_row[p] == r ? my_slot : -1;
+        }
+        uint64_t left = __builtin_amdgcn_ballot_w64(my_slot >= 0);   // entries still to be added, in ascending order
+        int n = __builtin_popcountll(left);
+        for (; n >= JU; n -= JU) combine_rows<Y_BF16, JU>(a, left, my_slot, my_w, c, acc);
+        if (n >= 4) {
+            combine_rows<Y_BF16, 4>(a, left, my_slot, my_w, c, acc);
+            n -= 4;
+        }
+        if (n >= 2) {
+            combine_rows<Y_BF16, 2>(a, left, my_slot, my_w, c, acc);
+            n -= 2;
+        }
+        if (n >= 1) combine_rows<Y_BF16, 1>(a, left, my_slot, my_w, c, acc);
     }
 
+    if constexpr (Y_BF16 && !OUT_BF16) {
+        put_floats<STORES>((u32x4 *)a.out + (size_t)r * a.C * 2, c, a.C * 2, acc);
+        return;
+    }
+    if (c >= a.C) return;
+    const size_t e0 = ((size_t)r * a.C + c) * EPC;   // first output element of this chunk
+    if constexpr (OUT_BF16) {
+        uint32_t pk[EPC / 2];
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-        const int c = c0 + i * blockDim.x;
-        if constexpr (Y_BF16 && !OUT_BF16) {
-            put_floats<STORES>((u32x4 *)a.out + (size_t)r * a.C * 2, c, a.C * 2, acc[i]);
-            continue;
-        }
-        if (c >= a.C) continue;
-        const size_t e0 = ((size_t)r * a.C + c) * EPC;   // first output element of this chunk
-        if constexpr (OUT_BF16) {
-            uint32_t pk[EPC / 2];
-#pragma unroll
-            for (int q = 0; q < EPC / 2; ++q) pk[q] = to_bf16(acc[i][2 * q]) | (to_bf16(acc[i][2 * q + 1]) << 16);
-            if constexpr (Y_BF16) {
-                u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
-                put_out<STORES>((u32x4 *)((uint16_t *)a.out + e0), o);
-            } else {
-                u32x2 o = {pk[0], pk[1]};
-                put_out<STORES>((u32x2 *)((uint16_t *)a.out + e0), o);
-            }
+        for (int q = 0; q < EPC / 2; ++q) pk[q] = to_bf16(acc[2 * q]) | (to_bf16(acc[2 * q + 1]) << 16);
+        if constexpr (Y_BF16) {
+            const u32x4 o = {pk[0], pk[1], pk[2], pk[3]};
+            put_out<STORES>((u32x4 *)((uint16_t *)a.out + e0), o);
         } else {
+            const u32x2 o = {pk[0], pk[1]};
+            put_out<STORES>((u32x2 *)((uint16_t *)a.out + e0), o);
+        }
+    } else {
 #pragma unroll
-            for (int h = 0; h < EPC / 4; ++h) {
-                u32x4 o = {__float_as_uint(acc[i][4 * h]), __float_as_uint(acc[i][4 * h + 1]),
-                           __float_as_uint(acc[i][4 * h + 2]), __float_as_uint(acc[i][4 * h + 3])};
-                put_out<STORES>((u32x4 *)((float *)a.out + e0) + h, o);
-            }
+        for (int h = 0; h < EPC / 4; ++h) {
+            const u32x4 o = {__float_as_uint(acc[4 * h]), __float_as_uint(acc[4 * h + 1]),
+                             __float_as_uint(acc[4 * h + 2]), __float_as_uint(acc[4 * h + 3])};
+            put_out<STORES>((u32x4 *)((float *)a.out + e0) + h, o);
         }
     }
 }
@@ -510,53 +614,52 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
     const int t = gridDim.x - 1 - blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
     const bool in = c < a.C;   // lanes past the row take part in the exchange of put_floats
-    const int32_t *slots = a.pair_slot + (size_t)t * a.k;
-    const int32_t *rows = a.pair_send_row + (size_t)t * a.k;
-    const uint8_t *first = a.pair_first + (size_t)t * a.k;
-    const float *wt = a.w + (size_t)t * a.k;
+    // entry j's slot, send row and weight in lane j; the entries with a slot are taken in ascending order
+    const int lane = threadIdx.x & (kWave - 1);
+    int my_slot = -1, my_row = -1;
+    float my_w = 0.0f;
+    bool my_first = false;
+    if (lane < a.k) {
+        const size_t p = (size_t)t * a.k + lane;
+        my_slot = a.pair_slot[p];
+        my_row = a.pair_send_row[p];
+        my_w = a.w[p];
+        my_first = a.pair_first[p];
+    }
+    uint64_t left = __builtin_amdgcn_ballot_w64(my_slot >= 0);
+    const uint64_t firsts = __builtin_amdgcn_ballot_w64(my_first);
+    const int n = __builtin_popcountll(left);
 
     u32x4 v[KMAX];
     int row[KMAX];
     float wj[KMAX];
-    bool on[KMAX], lead[KMAX];
+    bool lead[KMAX];
 #pragma unroll
     for (int j = 0; j < KMAX; ++j) {
-        on[j] = false;
-        lead[j] = false;
-        row[j] = -1;
-        if (j < a.k) {
-            const int slot = slots[j];
-            row[j] = rows[j];
-            wj[j] = wt[j];
-            lead[j] = first[j];
-            if (slot >= 0) {
-                on[j] = true;
-                if (in) v[j] = load16_stream(a.y + (size_t)slot * a.C + c);
-            }
-        }
+        if (j >= n) break;   // uniform
+        const int at = __builtin_ctzll(left);
+        left &= left - 1;
+        row[j] = __builtin_amdgcn_readlane(my_row, at);
+        wj[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), at));
+        lead[j] = firsts >> at & 1;
+        const u32x4 *src = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, at) * a.C;
+        v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
     }
     float total[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) total[e] = 0.0f;
 #pragma unroll
     for (int f = 0; f < KMAX; ++f) {
+        if (f >= n) break;
         if (!lead[f]) continue;
         float acc[EPC];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-            if (!on[j] || row[j] != row[f]) continue;
-            if constexpr (Y_BF16) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    acc[2 * q] = __builtin_fmaf(wj[j], bf16_lo(v[j][q]), acc[2 * q]);
-                    acc[2 * q + 1] = __builtin_fmaf(wj[j], bf16_hi(v[j][q]), acc[2 * q + 1]);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = __builtin_fmaf(wj[j], __uint_as_float(v[j][q]), acc[q]);
-            }
+        for (int j = f; j < KMAX; ++j) {
+            if (j >= n) break;
+            if (row[j] != row[f]) continue;
+            add_row<Y_BF16>(acc, v[j], wj[j]);
         }
         // plain stores: 4096 tokens x 8 rows of 14 KiB, 21700 partial rows 228 us, written through 239, non-temporal 280 us
         u32x4 *prow = (u32x4 *)a.partial + (size_t)row[f] * a.C * (EPC / 4);
@@ -612,26 +715,32 @@ __global__ __launch_bounds__(1024) void sum_partials_kernel(SumPartialsArgs a)
 {
     const int t = gridDim.x - 1 - blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
-    if (c >= a.C) return;
-    const int32_t *rows = a.pair_send_row + (size_t)t * a.k;
-    const uint8_t *first = a.pair_first + (size_t)t * a.k;
+    const bool in = c < a.C;   // lanes past the row hold entries too
+    const int lane = threadIdx.x & (kWave - 1);
+    int my_row = -1;   // entry j's partial row in lane j, where it is the first of its device
+    if (lane < a.k) {
+        const size_t p = (size_t)t * a.k + lane;
+        my_row = a.pair_first[p] ? a.pair_send_row[p] : -1;
+    }
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int j0 = 0; j0 < a.k; j0 += 8) {
-        u32x4 v[8];
-        bool on[8];
+    uint64_t left = __builtin_amdgcn_ballot_w64(my_row >= 0);
+    while (left) {
+        u32x4 v[4];
+        const int n = __builtin_popcountll(left);
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            const int j = j0 + jj;
-            on[jj] = j < a.k && first[j];
-            if (on[jj]) v[jj] = load16_stream(a.partial + (size_t)rows[j] * a.C + c);
+        for (int jj = 0; jj < 4; ++jj) {
+            if (jj >= n) break;   // uniform
+            v[jj] = load16_stream(a.partial + (size_t)__builtin_amdgcn_readlane(my_row, __builtin_ctzll(left)) * a.C + (in ? c : 0));
+            left &= left - 1;
         }
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            if (!on[jj]) continue;
+        for (int jj = 0; jj < 4; ++jj) {
+            if (jj >= n) break;
 #pragma unroll
             for (int q = 0; q < 4; ++q) acc[q] = acc[q] + __uint_as_float(v[jj][q]);
         }
     }
+    if (!in) return;
     const size_t e0 = ((size_t)t * a.C + c) * 4;
     if constexpr (OUT_BF16) {
         u32x2 o = {to_bf16(acc[0]) | (to_bf16(acc[1]) << 16), to_bf16(acc[2]) | (to_bf16(acc[3]) << 16)};

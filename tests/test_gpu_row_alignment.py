@@ -227,3 +227,43 @@ def test_both_tensors_tile_by_tile_over_random_shapes():
         moved += 1
         seen.add((few, -(-(row + aux) // 16) > 1024, aux > 0, (row + aux) // 16 < 512))
     assert moved >= 35 and len(seen) >= 6 and any(s[0] for s in seen) and any(s[1] for s in seen)
+
+
+# the token walk of few workgroups (up to 1024 of a row's column segments) and the one of many, both ends of the rule; send rows alone always
+# take the former; every pairing of loads and stores
+@pytest.mark.parametrize("N,k,row_bytes,aux_bytes", [(1, 1, 16, 0), (7, 64, 48, 16), (300, 8, 4112, 0), (1024, 3, 1040, 224), (1025, 3, 1040, 224),
+                                                     (512, 4, 16384 + 16, 0), (513, 4, 16384 + 16, 0), (30, 6, 40000, 32), (90, 8, 16368, 48)])
+@pytest.mark.parametrize("flags", [1, 2, 3])
+def test_token_walk(N, k, row_bytes, aux_bytes, flags):
+    import paper_2512_22036_amd as f
+    E, D = 128, 8
+    rng = np.random.default_rng(N + row_bytes)
+    A = random_topk(rng, N, k, E).astype(np.int32)
+    if N > 1:
+        A[N // 2] = -1                     # a token without a row, and one without its first entry
+        A[N // 3, 0] = E
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    x = torch.randint(0, 256, (N, row_bytes), dtype=torch.uint8, device="cuda")
+    xa = torch.randint(0, 256, (N, aux_bytes), dtype=torch.uint8, device="cuda") if aux_bytes else None
+    rows, sends = int(L.array("exp_off")[E]), int(L.array("send_off")[D])
+    token, src = L.array("slot_token")[:rows].long(), L.array("send_src")[:sends].long()
+    assert not f.fusco_dispatch_in_transfer_order(L, row_bytes, aux_bytes, flags)
+    for mode in range(5):
+        eb, room = rows_at(L.P, row_bytes, 0)
+        sb, room_s = rows_at(L.send_cap, row_bytes, 16)
+        ea, _ = rows_at(L.P, max(aux_bytes, 16), 0)
+        sa, _ = rows_at(L.send_cap, max(aux_bytes, 16), 0)
+        planes = dict(x_aux=xa, expert_aux=ea, send_aux=sa) if aux_bytes else {}
+        assert f.fusco_probe_dispatch_walk(mode) == 0
+        try:
+            f.fusco_dispatch(L, x, eb, send_buf=sb, flags=flags, **planes)
+        finally:
+            f.fusco_probe_dispatch_walk(0)
+        want = rows if flags & 1 else 0
+        assert torch.equal(eb[:want], x[token[:want]]) and bool((room[want * row_bytes:] == 0xEE).all())
+        want = sends if flags & 2 else 0
+        assert torch.equal(sb[:want], x[src[:want]]) and bool((room_s[16 + want * row_bytes:] == 0xEE).all())
+        if aux_bytes:
+            assert torch.equal(ea[:rows if flags & 1 else 0], xa[token[:rows if flags & 1 else 0]])
+            assert torch.equal(sa[:sends if flags & 2 else 0], xa[src[:sends if flags & 2 else 0]])
