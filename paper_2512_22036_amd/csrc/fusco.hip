@@ -262,21 +262,22 @@ static size_t lds_for_occupancy(int wgs)
     return (size_t)(128 / wgs) * 1280;
 }
 
-// Workgroups of the tiled dispatch per compute unit for rows (or column segments) of seg_bytes, source tensor
-// resident in the memory-side cache (16: no cap).  The kernel runs at the rate of its writes, which is higher the
-// fewer rows are being written at a time, as long as enough loads stay in flight: about 70-90 KiB of rows per compute
-// unit.  Measured at 8192 tokens x 8, dispatch alone, us, no cap / the cap chosen / one less: 5 KiB rows 66.6 /
-// 58.6 (12) / 58.9; 6 KiB 75.5 / 71.5 (12) / 71.7; 8 KiB 96.2 / 87.2 (12) / 87.8; 10 KiB 118.6 / 111.5 (8) / 113.8;
-// 12 KiB 140.2 / 131.9 (7) / 140.1; 13 KiB 151 / 146 (6) / 149; 14 KiB 165 / 157 (5) / 171; 15 KiB 173 / 164 (5) / 177;
-// two segments of 8 KiB 192.1 / 189.3 (12); of 12 KiB (4096 tokens) 142.2 / 135.1 (7).  Rows shorter than 4 KiB
-// are moved by workgroups of one or two waves, of which a compute unit should hold more than a cap allows.
-static int tiled_workgroups_per_cu(size_t seg_bytes)
+// Workgroups of the tiled dispatch per compute unit for rows (or column segments) of seg_bytes, source tensor taken in one
+// piece (16: no cap).  The kernel runs at the rate of its writes, which is higher the fewer rows are being written at a time,
+// as long as enough loads stay in flight: about 60-90 KiB of rows per compute unit.  Steps of 8192 tokens x 8, other buffers in every
+// step, us, no cap / the cap chosen / its neighbours: 5 KiB rows 131 / 131 (12) / 133 (10); 6 KiB 154.8 / 155.0 (12) / 154.5 (10);
+// 8 KiB 203 / 197.5 (10) / 199.6 (12), 201 (8); 10 KiB 264 / 257.5 (8) / 257.2 (7), 263 (10); 12 KiB 319 / 308 (6) / 312 (7), 315
+// (5); 13 KiB 352 / 339 (5) / 344 (6); 14 KiB 380 / 365 (5) / 374 (6), 369 (4); 15 KiB 394 / 379 (5) / 386 (6).  Source tensors that
+// do not stay in the memory-side cache next to an output of their size (116-128 MiB): 16384 x 8 KiB 430 / 420 (10) / 421 (12), 427
+// (8); 12200 x 10 KiB 414 / 404 (8) / 411 (6 and 10); 10800 x 11.5 KiB 422 / 414 (8) / 419 (6); 9100 x 14 KiB 426 / 412 (5) / 416 (6).
+// Rows shorter than 4 KiB are moved by workgroups of one or two waves, of which a compute unit should hold more than a cap allows.
+static int tiled_workgroups_per_cu(size_t seg_bytes, bool resident)
 {
     if (seg_bytes < 4096) return 16;
-    if (seg_bytes <= 8192) return 12;
+    if (seg_bytes <= 6144) return 12;
+    if (seg_bytes <= 8192) return 10;
     if (seg_bytes <= 10240) return 8;
-    if (seg_bytes <= 12288) return 7;
-    if (seg_bytes <= 13312) return 6;
+    if (seg_bytes <= 12288) return resident ? 6 : 8;
     return 5;
 }
 
@@ -450,15 +451,13 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const dim3 tblock((unsigned)threads);
         // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
         // taken in chunks, touch_kernel has just read them and the pull only costs (12 KiB segments at 8192 tokens:
-        // 322 us without it, 332 us with it).  The workgroups per compute unit are capped by the row size only while
-        // the source tensor and an output of its size stay in the memory-side cache from step to step.  Measured
-        // with 14 KiB rows, dispatch alone, 8 / 5 workgroups: 8192 tokens (112 MiB) 164 / 155 us, 8704 tokens
-        // (119 MiB) 191 / 188 us, 9216 tokens (126 MiB) 205 / 250 us, 32768 tokens without chunks 793 / 923 us.
+        // 322 us without it, 332 us with it).  The workgroups per compute unit are capped by the row size where it is taken in one
+        // piece; in chunks the cap costs (32768 tokens of 14 KiB, step, no cap / 8 / 5: 1407 / 1417 / 1570 us).
         const int occ_knob = g_tiled_occupancy.load(std::memory_order_relaxed);
         const int pull_knob = g_tiled_pull.load(std::memory_order_relaxed);
         const bool pull = pull_knob == 0 ? !chunked : pull_knob == 2;
         const int wgs = occ_knob > 0 ? occ_knob
-                        : (source_bytes <= kResidentSourceBytes ? tiled_workgroups_per_cu((size_t)per * 16) : 16);
+                        : (chunked ? 16 : tiled_workgroups_per_cu((size_t)per * 16, source_bytes <= kResidentSourceBytes));
         const size_t lds = lds_for_occupancy(wgs);
         for (size_t tile0 = 0; tile0 < (size_t)L->tile_count; tile0 += chunk_tiles) {
             const size_t tiles_here = std::min(chunk_tiles, (size_t)L->tile_count - tile0);

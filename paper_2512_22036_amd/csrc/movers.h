@@ -251,33 +251,36 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
     // own workgroup: with few workgroups per compute unit that wait is what a cold source tensor costs.
     const int tp = (int)(tile * (uint32_t)a.tile_tokens + r);
     const bool pull = PULL && r < (uint32_t)a.tile_tokens && tp < a.N;
-    u32x4 p[CPT];
-    const uint32_t pseg = a.segs > 1 ? (pass + (uint32_t)tp) % (uint32_t)a.segs : 0u;
-    const int p_end = min(Ct, (int)(pseg + 1) * a.seg_chunks), p0 = pseg * a.seg_chunks + threadIdx.x;
-    if (pull) {
+    // which segment a pass moves rotates with the token: the segments in use during a pass then lie at different
+    // offsets in their rows, and rows whose size is a power of two do not all fall on the same sets of the L2
+    const auto segment = [&](int token) { return a.segs > 1 ? (pass + (uint32_t)token) % (uint32_t)a.segs : 0u; };
+    // A thread requests the chunks of its own row one after the other, each when the one before has arrived, and a plain dispatch
+    // requests the pulled row before them: a workgroup then spends longer on its loads and fewer of them are storing at any
+    // moment.  Steps with the chunks requested at once / one after the other, us: 8192 x 8 x 14 KiB 377 / 363, in two planes of 7.2 KiB
+    // 277 / 273, 32768 x 8 x 14 KiB 1452 / 1407.  With the receive tensors the pulled row comes last, and threads past the
+    // segment's end read its last chunk with the others instead of branching around it (4096 x 8 x 14 KiB 376; 380 as above).
+    const auto load = [&](u32x4 (&v)[CPT], int token, uint32_t seg, bool own) {
+        const int c_end = min(Ct, (int)(seg + 1) * a.seg_chunks), c0 = seg * a.seg_chunks + threadIdx.x;
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
-            const int c = p0 + q * blockDim.x;
-            const u32x4 *src = a.x + (size_t)tp * a.C + c;
-            if (AUX && c >= a.C) src = a.x_aux + (size_t)tp * a.Ca + (c - a.C);
-            if (c < p_end) p[q] = *src;
+            const int at = c0 + q * (int)blockDim.x, c = WIRE ? min(at, c_end - 1) : at;
+            const u32x4 *src = a.x + (size_t)token * a.C + c;
+            if (AUX && c >= a.C) src = a.x_aux + (size_t)token * a.Ca + (c - a.C);
+            if (!WIRE && c >= c_end) continue;
+            v[q] = *src;
+            if (own) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         }
-    }
+    };
+    u32x4 v[CPT], p[CPT];
+    uint32_t seg = 0;
+    if (!WIRE && pull) load(p, tp, segment(tp), false);
     if (row >= 0) {
         if (!wire) t = a.slot_token[row];
-        // which segment a pass moves rotates with the token: the segments in use during a pass then lie at different
-        // offsets in their rows, and rows whose size is a power of two do not all fall on the same sets of the L2
-        const uint32_t seg = a.segs > 1 ? (pass + (uint32_t)t) % (uint32_t)a.segs : 0u;
-        const int c_end = min(Ct, (int)(seg + 1) * a.seg_chunks);   // this segment: chunks [seg * seg_chunks, c_end)
-        const int c0 = seg * a.seg_chunks + threadIdx.x;
-        u32x4 v[CPT];
-#pragma unroll
-        for (int q = 0; q < CPT; ++q) {
-            const int c = c0 + q * blockDim.x;
-            const u32x4 *src = a.x + (size_t)t * a.C + c;
-            if (AUX && c >= a.C) src = a.x_aux + (size_t)t * a.Ca + (c - a.C);
-            if (c < c_end) v[q] = *src;
-        }
+        seg = segment(t);
+        load(v, t, seg, true);
+    }
+    const auto store = [&] {
+        const int c_end = min(Ct, (int)(seg + 1) * a.seg_chunks), c0 = seg * a.seg_chunks + threadIdx.x;
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
             const int c = c0 + q * blockDim.x;
@@ -287,12 +290,15 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
             if (AUX && c >= a.C ? a.through_aux : a.through) store16_through_stream(dst, v[q]);
             else __builtin_nontemporal_store(v[q], dst);
         }
+    };
+    if (!pull) {
+        if (row >= 0) store();
+        return;
     }
-    if (pull) {
+    if (WIRE) load(p, tp, segment(tp), false);
+    if (row >= 0) store();
 #pragma unroll
-        for (int q = 0; q < CPT; ++q)
-            if (p0 + q * (int)blockDim.x < p_end) asm volatile("" ::"v"(p[q]));   // the value is not used: only the read matters
-    }
+    for (int q = 0; q < CPT; ++q) asm volatile("" ::"v"(p[q]));   // the value is not used: only the read matters
 }
 
 // Reads n 16-byte units once, 4 KiB per workgroup in address order, and drops them: afterwards they sit in the
@@ -775,8 +781,8 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherArgs a)
     u32x4 v[CPT];
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
-        const int c = c0 + i * blockDim.x;
-        if (c < a.C) v[i] = STREAM_LOAD ? load16_stream(a.src + (size_t)q * a.C + c) : a.src[(size_t)q * a.C + c];
+        const int c = min(c0 + i * (int)blockDim.x, a.C - 1);   // no branch between the loads
+        v[i] = STREAM_LOAD ? load16_stream(a.src + (size_t)q * a.C + c) : a.src[(size_t)q * a.C + c];
     }
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
