@@ -254,14 +254,6 @@ static std::atomic<int> g_walk_mode{0};
 // fusco_probe_dispatch_pull: 0 automatic, 1 off, 2 on
 static std::atomic<int> g_tiled_pull{0};
 
-// Dynamic LDS that lets `wgs` workgroups share a compute unit's 160 KiB of LDS, which is handed out in 128 blocks
-// of 1280 bytes (3 <= wgs <= 15; 13 comes out as 14; the kernels have no LDS of their own); 0 for no cap.
-static size_t lds_for_occupancy(int wgs)
-{
-    if (wgs < 3 || wgs > 15) return 0;
-    return (size_t)(128 / wgs) * 1280;
-}
-
 // Workgroups of the tiled dispatch per compute unit for rows (or column segments) of seg_bytes, source tensor taken in one
 // piece (16: no cap).  The kernel runs at the rate of its writes, which is higher the fewer rows are being written at a time,
 // as long as enough loads stay in flight: about 60-90 KiB of rows per compute unit.  Steps of 8192 tokens x 8, other buffers in every
@@ -573,10 +565,10 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
         f.k = L->k;
         f.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
         const OutStores how = out_stores((size_t)L->P * (size_t)f.C * 16, d_out, (size_t)L->N, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
-        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_two_hop<true, true>(f, L->N, L->D, how, s);
-        else if (y_dtype == FUSCO_BF16) launch_two_hop<true, false>(f, L->N, L->D, how, s);
-        else if (out_dtype == FUSCO_BF16) launch_two_hop<false, true>(f, L->N, L->D, how, s);
-        else launch_two_hop<false, false>(f, L->N, L->D, how, s);
+        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_two_hop<true, true>(f, L->N, how, s);
+        else if (y_dtype == FUSCO_BF16) launch_two_hop<true, false>(f, L->N, how, s);
+        else if (out_dtype == FUSCO_BF16) launch_two_hop<false, true>(f, L->N, how, s);
+        else launch_two_hop<false, false>(f, L->N, how, s);
         return launch_status();
     }
     // general k: level 2 reversed (fp32 partial row per send row), then level 1 reversed

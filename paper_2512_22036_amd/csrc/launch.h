@@ -66,11 +66,15 @@ void launch_args(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hip
 // just over half of a compute unit's 160 KiB of LDS, which is handed out in 128 blocks of 1280 bytes
 constexpr size_t kOverHalfLds = (size_t)65 * 1280;
 
-// Rows that a thread of combine_kernel has in flight at a time (JU).  Inputs that are bound by memory run a few
-// percent faster with two than with all eight of a token's rows, k = 8, us: 8192 tokens of 14 KiB 178 / 181, 4096 tokens
-// 89 / 92, 1024 tokens (112 MiB) 23.7 / 26.0, 1024 of 8 KiB (64 MiB) 13.2 / 13.5, 32768 x 2 KiB 102 / 103; 16384 x 8 KiB the same.
-// Small inputs are bound by latency and take the token's rows at once: 256 tokens of 14 KiB (28 MiB) 8.0 / 7.6 (in
-// between they cross: 56 MiB 11.7 / 12.1, 66 MiB 17.1 / 16.9).
+// Dynamic LDS that lets `wgs` workgroups share a compute unit's LDS (2 <= wgs <= 15; 13 comes out as 14; for kernels without LDS
+// of their own); 0 for no cap.
+inline size_t lds_for_occupancy(int wgs)
+{
+    if (wgs < 2 || wgs > 15) return 0;
+    return (size_t)(128 / wgs) * 1280;
+}
+
+// Inputs of fewer bytes are bound by latency, larger ones by memory (combine_kernel's JU, workgroup shapes, stores).
 constexpr size_t kCombineLatencyBoundBytes = (size_t)64 << 20;
 
 // Workgroup shape of combine_kernel for rows of C chunks: as many column segments as 1024 threads need, the
@@ -96,27 +100,41 @@ inline void combine_shape_latency(int N, int C, int &threads, int &segs)
     segs = (C + threads - 1) / threads;
 }
 
+template <bool Y_BF16, bool OUT_BF16, int JU>
+void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    // what is bound by latency is written through or plain, what is bound by memory in every way but plain (out_stores)
+    if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough>, grid, block, s, a, e0, e1);
+    if constexpr (JU >= 2)
+        if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain>, grid, block, s, a, e0, e1);
+    if constexpr (JU <= 2) {
+        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal>, grid, block, s, a, e0, e1);
+    }
+}
+
+// Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4 KiB
+// 13.4 / 13.0); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
+// scalars (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
+// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.
 template <bool Y_BF16, bool OUT_BF16>
 void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    const bool latency = (size_t)N * (size_t)a.k * (size_t)a.C * 16 < kCombineLatencyBoundBytes;
+    const size_t bytes = (size_t)N * (size_t)a.k * (size_t)a.C * 16;
+    const bool latency = bytes < kCombineLatencyBoundBytes;
     int threads;
     if (latency) combine_shape_latency(N, a.C, threads, a.segs);
     else combine_shape(a.C, threads, a.segs);
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
-    if (latency) {
-        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 8, kOutThrough>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, 8, kOutPlain>, grid, block, s, a, e0, e1);
-    } else if (a.k == 2) {   // both rows of a token at once: there is no third to keep memory busy meanwhile
-        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutThrough>, grid, block, s, a, e0, e1);
-        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutThroughStream>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, 2, kOutNonTemporal>, grid, block, s, a, e0, e1);
-    } else {
-        if (stores == kOutThrough) launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutThrough>, grid, block, s, a, e0, e1);
-        else if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutThroughStream>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, 1, kOutNonTemporal>, grid, block, s, a, e0, e1);
-    }
+    if (latency ? a.k <= 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2) : a.k == 2)
+        launch_combine_as<Y_BF16, OUT_BF16, 2>(a, grid, block, stores, s, e0, e1);
+    else if (!latency)
+        launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
+    else if (bytes < kCombineLatencyBoundBytes / 4)
+        launch_combine_as<Y_BF16, OUT_BF16, 8>(a, grid, block, stores, s, e0, e1);
+    else
+        launch_combine_as<Y_BF16, OUT_BF16, 4>(a, grid, block, stores, s, e0, e1);
 }
 
 // dst[r] = src[index(r)] for n_rows destination rows of C chunks (see gather_rows_kernel)
@@ -213,30 +231,43 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
     return whole ? kOutThroughStream : kOutNonTemporal;
 }
 
-// Two-hop combine.  A workgroup of 13 to 16 waves leaves room for a second one on its compute unit; with bf16 rows, many
-// devices (about as many partial rows written as half the rows read) and several rounds of tokens the kernel is faster
-// without it: dynamic LDS that it does not use keeps the second one out (and leaves room for kernels of other streams).
-// One / two workgroups per compute unit, 14 KiB rows, k = 8, us: 8 devices 228 / 234 (4096 tokens; 8192 tokens 445 / 458,
-// 1024 tokens 61.3 / 63.4, but 640 tokens 39.0 / 34.8), 16 devices 256 / 267, 6 devices 211 / 213, 4 devices 192 / 190, 2
-// devices 159 / 145; k = 4 135 / 137, k = 2 163 / 153 (8192 tokens); fp32 rows of 16 KiB 185 / 181.
-// Small inputs are bound by latency and take their rows in segments of 256 threads; segments / whole rows, 14 KiB rows x 8, us:
-// 4 tokens 5.5 / 6.6, 128 11.6 / 12.6, 300 (33 MiB) 16.1 / 17.6, 500 (55 MiB) 24.6 / 24.3.
-constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20;
+// Two-hop combine, by the bytes of its input.
+// Up to 20 MiB latency counts: a token's rows are requested at once.  From there to 96 MiB the rows of many waves are in flight
+// anyway, and memory is faster when a wave has one.  us, at once / one by one, rows of 14 KiB x 8: 4 tokens 4.2 / 4.7, 128 8.7 / 10.6, 200
+// (22 MiB) 13.6 / 12.6, 300 21.0 / 15.9, 640 45 / 39.  Up to 48 MiB rows are cut into segments of 256 threads (4 tokens 5.5 / 6.6 with
+// whole rows, 300 16.1 / 17.6, 500 24.6 / 24.3).
+// Larger inputs are bound by memory.  With three and more rows per token a compute unit gets no more than 16 waves, 12 for six and more
+// bf16 rows, which then keep enough in flight by requesting their rows at once; dynamic LDS that the kernel does not use keeps
+// further workgroups out.  us, no cap and one by one / 16 waves / 12: 8192 x 8 x 8 KiB on 16 devices 306 / 290 / 281, 4096 x 8 x 8 KiB on 8 133 / 127.6 /
+// 126.6, 30000 x 8 x 2 KiB 247 / 239 / 235, 8192 x 4 x 4 KiB 83 / 76.4 / 76.5, 8192 x 6 x 10 KiB (one workgroup of 10 waves) 235 / 228, 4096 x 8 x
+// 14 KiB (of 14) 228 / 224, fp32 9000 x 8 x 8 KiB 199 / 194 / 204, 9000 x 3 x 8 KiB 136 / 131 / 142; 9000 x 1 x 8 KiB 57 / 64 / 92.
+constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20, kTwoHopAtOnceBytes = (size_t)20 << 20, kTwoHopCappedBytes = (size_t)96 << 20;
 
-template <bool Y_BF16, bool OUT_BF16>
-void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
+template <bool Y_BF16, bool OUT_BF16, bool ONE_BY_ONE>
+void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
 {
-    const bool small = (size_t)N * (size_t)a.k * (size_t)a.C * 16 < kTwoHopSmallBytes;
-    const int threads = std::min(small ? 256 : 1024, round_up(a.C, kWave));
-    const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
-    const size_t lds = Y_BF16 && threads > 768 && D > 5 && a.k >= 4 && N >= 1024 ? kOverHalfLds : 0;
     const hipEvent_t none = nullptr;
     switch (stores) {
-    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough>, grid, block, lds, s, none, none, a); break;
-    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream>, grid, block, lds, s, none, none, a); break;
-    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal>, grid, block, lds, s, none, none, a); break;
-    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain>, grid, block, lds, s, none, none, a); break;
+    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
+    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
+    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
+    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
     }
+}
+
+template <bool Y_BF16, bool OUT_BF16>
+void launch_two_hop(const TwoHopArgs &a, int N, OutStores stores, hipStream_t s)
+{
+    const size_t bytes = (size_t)N * (size_t)a.k * (size_t)a.C * 16;
+    const int threads = std::min(bytes < kTwoHopSmallBytes ? 256 : 1024, round_up(a.C, kWave));
+    const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
+    size_t lds = 0;
+    if (bytes >= kTwoHopCappedBytes && a.k >= 3) {
+        const int wgs = std::max(1, (Y_BF16 && a.k >= 6 ? 12 : 16) / (threads / kWave));
+        lds = wgs == 1 ? kOverHalfLds : lds_for_occupancy(wgs);
+    }
+    if (bytes >= kTwoHopAtOnceBytes && bytes < kTwoHopCappedBytes) launch_two_hop_as<Y_BF16, OUT_BF16, true>(a, grid, block, lds, stores, s);
+    else launch_two_hop_as<Y_BF16, OUT_BF16, false>(a, grid, block, lds, stores, s);
 }
 
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked

@@ -478,9 +478,9 @@ __device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &lef
 }
 
 // JU: rows of a token that a thread has in flight.
-// 8 (inputs bound by latency): slots and weights come into the lanes of a wave with one load each, and up to eight rows are
-// requested back to back.  Behind a branch per entry the compiler waited for each row before it requested the next; 1537 tokens
-// x 6 x 5760 B to fp32 15.5 -> 13.9 us, 1000 x 4 x 14 KiB 14.8 -> 13.1, 128 x 8 x 14 KiB 6.6 -> 6.1.
+// 4 or 8 (inputs bound by latency): slots and weights come into the lanes of a wave with one load each, and the rows are requested
+// back to back.  Behind a branch per entry the compiler waited for each row before it requested the next (with those waits / without, us:
+// 64 tokens x 8 x 14 KiB 6.0 / 3.1, 128 x 8 6.6 / 4.3, 1537 x 6 x 5760 B to fp32 15.5 / 13.9).
 // 1 or 2 (inputs bound by memory, which is faster the fewer rows are being read at a time): slots and weights are scalar
 // loads, which do not queue behind the rows, one step ahead of their use.  Rows in flight 1 / 2 / 4 / 8, us: 8192 x 8 x 14 KiB
 // 173 / 180 / 184 / 181, 16384 x 8 x 8 KiB 203 / 210 / 211 / 212, 32768 x 8 x 14 KiB 700 / 750 / 754 / 744; two entries per
@@ -612,7 +612,8 @@ struct TwoHopArgs {
     int32_t C;   // 16-byte chunks per y row
 };
 
-template <bool Y_BF16, bool OUT_BF16, OutStores STORES>
+// ONE_BY_ONE: a row is requested when the one before has arrived, otherwise all of them at once (launch_two_hop).
+template <bool Y_BF16, bool OUT_BF16, OutStores STORES, bool ONE_BY_ONE>
 __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
 {
     constexpr int EPC = Y_BF16 ? 8 : 4;
@@ -650,6 +651,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
         lead[j] = firsts >> at & 1;
         const u32x4 *src = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, at) * a.C;
         v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
+        if constexpr (ONE_BY_ONE) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     }
     float total[EPC];
 #pragma unroll
@@ -667,7 +669,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             if (row[j] != row[f]) continue;
             add_row<Y_BF16>(acc, v[j], wj[j]);
         }
-        // plain stores: 4096 tokens x 8 rows of 14 KiB, 21700 partial rows 228 us, written through 239, non-temporal 280 us
+        // plain stores: 4096 tokens x 8 rows of 14 KiB, 21700 partial rows 224 us, written through 247, non-temporal 296 us
         u32x4 *prow = (u32x4 *)a.partial + (size_t)row[f] * a.C * (EPC / 4);
         if constexpr (Y_BF16) {
             put_floats<kOutPlain>(prow, c, a.C * 2, acc);
