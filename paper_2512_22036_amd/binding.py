@@ -1,4 +1,5 @@
-"""ctypes binding of libfusco.so: same names as the C boundary, argument marshalling only.
+"""Python binding of libfusco.so (ctypes; the shuffle's calls through _fastcall): same names as the C boundary, argument
+marshalling only.
 
 Every step of the shuffle runs in the library's HIP kernels.  This module checks tensor shapes
 against the layout (the C side sees bare pointers), passes pointers and the current HIP stream,
@@ -44,6 +45,7 @@ class _CLayout(ctypes.Structure):
 
 
 _lib = None
+_fast = None   # csrc/fastcall.cpp, bound to _lib
 
 
 def library_path() -> str:
@@ -52,7 +54,7 @@ def library_path() -> str:
 
 def load_library() -> ctypes.CDLL:
     """Load libfusco.so (built by paper_2512_22036_amd.build / __graft_entry__.build)."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -122,7 +124,22 @@ def load_library() -> ctypes.CDLL:
     lib.fusco_disaggregated_combine.restype = ctypes.c_int
     lib.fusco_disaggregated_combine.argtypes = [lp, lp, vp, ctypes.c_int, vp, vp, vp, vp, ctypes.c_int, i32, vp]
     _lib = lib
+    _fast = _bind_fastcall(lib)
     return lib
+
+
+def _bind_fastcall(lib):
+    """The module that makes the common calls without ctypes in between (csrc/fastcall.cpp), bound to the library's
+    entry points; None where it was not built or this torch cannot load it, and every call goes through ctypes."""
+    if not os.path.exists(os.path.join(_HERE, "_fastcall.so")):
+        return None
+    try:
+        from . import _fastcall
+    except ImportError:
+        return None
+    _fastcall.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+                     for name in ("fusco_plan", "fusco_dispatch", "fusco_plan_dispatch", "fusco_combine", "fusco_combine_two_hop")))
+    return _fastcall
 
 
 def _check(rc: int, what: str) -> None:
@@ -204,6 +221,10 @@ class Layout:
 
 
 def fusco_plan(layout: Layout, topk_idx: torch.Tensor, stream=None) -> None:
+    if stream is None and _fast is not None:
+        rc = _fast.plan(layout, topk_idx)
+        if rc is not None:
+            return _check(rc, "fusco_plan")
     if (not topk_idx.is_cuda or topk_idx.dtype != torch.int32 or not topk_idx.is_contiguous()
             or tuple(topk_idx.shape) != (layout.N, layout.k)):
         raise FuscoError("topk_idx must be a contiguous int32 device tensor of shape [N, k]")
@@ -224,6 +245,10 @@ def fusco_dispatch(layout: Layout, x: torch.Tensor, expert_buf: Optional[torch.T
                    x_aux: Optional[torch.Tensor] = None, expert_aux: Optional[torch.Tensor] = None,
                    send_buf: Optional[torch.Tensor] = None, send_aux: Optional[torch.Tensor] = None,
                    flags: int = 0, stream=None) -> None:
+    if stream is None and _fast is not None:
+        rc = _fast.dispatch(layout, x, expert_buf, x_aux, expert_aux, send_buf, send_aux, flags)
+        if rc is not None:
+            return _check(rc, "fusco_dispatch")
     rb = _rows(x, "x", layout.N)
     ab = _rows(x_aux, "x_aux", layout.N) if x_aux is not None else 0
     eff = (flags & ~DISPATCH_STREAMING) or DISPATCH_EXPERT
@@ -262,6 +287,10 @@ def fusco_plan_dispatch(layout: Layout, topk_idx: torch.Tensor, x: torch.Tensor,
                         stream=None) -> None:
     """fusco_plan and fusco_dispatch (expert tensor only) in one launch; inputs of one planner tile only
     (N <= 2048 // k), FuscoError otherwise."""
+    if stream is None and _fast is not None:
+        rc = _fast.plan_dispatch(layout, topk_idx, x, expert_buf, x_aux, expert_aux)
+        if rc is not None:
+            return _check(rc, "fusco_plan_dispatch")
     if (not topk_idx.is_cuda or topk_idx.dtype != torch.int32 or not topk_idx.is_contiguous()
             or tuple(topk_idx.shape) != (layout.N, layout.k)):
         raise FuscoError("topk_idx must be a contiguous int32 device tensor of shape [N, k]")
@@ -286,6 +315,10 @@ def _dtype_code(t: torch.Tensor, name: str) -> int:
 
 
 def fusco_combine(layout: Layout, y: torch.Tensor, w: torch.Tensor, out: torch.Tensor, stream=None) -> None:
+    if stream is None and _fast is not None:
+        rc = _fast.combine(layout, y, w, out)
+        if rc is not None:
+            return _check(rc, "fusco_combine")
     _rows(y, "y", layout.P)
     H = y.shape[1]
     _rows(out, "out", layout.N)
@@ -301,6 +334,10 @@ def fusco_combine(layout: Layout, y: torch.Tensor, w: torch.Tensor, out: torch.T
 
 def fusco_combine_two_hop(layout: Layout, y: torch.Tensor, w: torch.Tensor, partial: torch.Tensor,
                           out: torch.Tensor, stream=None) -> None:
+    if stream is None and _fast is not None:
+        rc = _fast.combine_two_hop(layout, y, w, partial, out)
+        if rc is not None:
+            return _check(rc, "fusco_combine_two_hop")
     _rows(y, "y", layout.P)
     H = y.shape[1]
     _rows(out, "out", layout.N)

@@ -36,6 +36,32 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
+FASTCALL_SRC = os.path.join(HERE, "csrc", "fastcall.cpp")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    """Compile the Python module that makes the common calls without ctypes in between (host code only)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+    if not os.path.isdir(os.path.join(rocm, "include", "hip")):
+        rocm = "/opt/rocm"
+    tmp = FASTCALL + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-I", INCLUDE]
+    for path in include_paths() + [sysconfig.get_paths()["include"], os.path.join(rocm, "include")]:
+        cmd += ["-isystem", path]
+    cmd += ["-o", tmp, FASTCALL_SRC, "-L", lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath," + lib]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
+
+
 EXAMPLE_SRC = os.path.join(ROOT, "examples", "c_abi_usage.c")
 EXAMPLE_BIN = os.path.join(ROOT, "examples", "c_abi_usage")
 
@@ -56,4 +82,5 @@ def build_c_example(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_fastcall(verbose=True))
     print(build_c_example(verbose=True))
