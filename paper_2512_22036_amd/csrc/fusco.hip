@@ -697,8 +697,11 @@ int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum,
     if (n < 0 || n > ((int64_t)1 << 26) || !d_cum || !d_status || (n > 0 && !d_desc)) return FUSCO_ERR_INVALID_ARG;
     if (((uintptr_t)d_desc | (uintptr_t)d_cum) & 7u) return FUSCO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (n <= kScanSingleThreads * kScanItems) {
+    if (n <= kScanSingleMax) {
         hipLaunchKernelGGL(segments_scan_kernel<true>, dim3(1), dim3(kScanSingleThreads), 0, s, d_desc, n, d_cum, d_status);
+    } else if (n <= kScanDirectMax) {
+        const dim3 chunks((unsigned)((n + kScanDirectChunk - 1) / kScanDirectChunk));
+        hipLaunchKernelGGL(segments_scan_direct_kernel, chunks, dim3(kScanDirectThreads), 0, s, d_desc, (int)n, d_cum, d_status);
     } else {
         const dim3 chunks((unsigned)((n + kScanChunk - 1) / kScanChunk));
         hipLaunchKernelGGL(segments_total_kernel, chunks, dim3(kScanThreads), 0, s, d_desc, n, d_cum, d_status);

@@ -329,3 +329,27 @@ def test_copy_around_the_size_that_is_written_past_the_cache(fusco, extra):
     back = torch.full((total,), 0xAB, dtype=torch.uint8, device="cuda")
     fusco.fusco_segments_copy(packed, None, back, desc, cum, total, status)
     assert int(status.item()) == 0 and torch.equal(back, src)
+
+
+@pytest.mark.parametrize("n", [3071, 3072, 3073, 4096, 4097, 6145, 16384 + 1, 32767, 32768, 32769])
+@pytest.mark.parametrize("bad", [0, 1, 700])
+def test_scan_around_the_lengths_of_its_launches(fusco, n, bad):
+    """One workgroup, one launch of workgroups that add up what lies before them, two launches: the lengths on either side of
+    each, with invalid descriptors anywhere (the first and the last among them) and sizes beyond 32 bits.  Whole numbers."""
+    rng = np.random.default_rng(n + bad)
+    size = rng.integers(0, 1 << 36, size=n).astype(np.int64) * 16
+    off = rng.integers(0, 1 << 30, size=n).astype(np.int64) * 16
+    at = rng.choice(n, size=bad, replace=False) if bad != 1 else np.array([n - 1])
+    if bad > 1:
+        at[0] = 0
+    size[at[::2]] += 8
+    off[at[1::2]] += 4
+    d_desc = desc_dev(off, size)
+    cum = torch.full((n + 1,), -1, dtype=torch.int64, device="cuda")
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        fusco.fusco_segments_scan(d_desc, cum, status)
+        good = size.copy()
+        good[at] = 0
+        assert int(status.item()) == len(np.unique(at))
+        assert np.array_equal(cum.cpu().numpy(), np.concatenate([[0], np.cumsum(good)]))
