@@ -217,24 +217,18 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
             return FUSCO_ERR_INVALID_ARG;
     }
     const PlanArgs a = plan_args(L, d_topk_idx, nullptr, rounds);
-    DispatchArgs m;
-    m.x = (const u32x4 *)d_x; m.x_aux = (const u32x4 *)d_x_aux;
-    m.expert_buf = (u32x4 *)d_expert_buf; m.expert_aux = (u32x4 *)d_expert_aux;
-    m.send_buf = nullptr; m.send_aux = nullptr;
-    m.pair_slot = L->pair_slot; m.pair_send_row = L->pair_send_row; m.pair_first = L->pair_first;
-    m.slot_token = nullptr; m.tile_slots = nullptr; m.tile_cap = 0; m.tile_tokens = 0; m.N = L->N; m.segs = 1; m.seg_chunks = 0;
-    m.k = L->k;
-    m.C = (int32_t)(row_bytes / 16); m.Ca = (int32_t)(aux_row_bytes / 16);
-    m.write_expert = 1; m.write_wire = 0;
-    const int Ct = m.C + m.Ca, most = kFusedChunks * kSmallThreads;
-    m.segs = (Ct + most - 1) / most;
-    m.seg_chunks = m.segs > 1 ? round_up((Ct + m.segs - 1) / m.segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
+    const FusedRows m = {(u32x4 *)d_expert_buf, (u32x4 *)d_expert_aux};
+    const u32x4 *x = (const u32x4 *)d_x, *x_aux = (const u32x4 *)d_x_aux;
+    const int C = (int)(row_bytes / 16), Ca = (int)(aux_row_bytes / 16), Ct = C + Ca, most = kFusedChunks * kSmallThreads;
+    const int segs = (Ct + most - 1) / most;
+    const int seg_chunks = segs > 1 ? round_up((Ct + segs - 1) / segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
     const ArmedEvents ev;
-    const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)m.segs), block(kSmallThreads);
-    const int cpt = (m.seg_chunks + kSmallThreads - 1) / kSmallThreads;
-    const auto kernel = m.Ca ? (cpt <= 1 ? plan_dispatch_kernel<1, true> : cpt <= 2 ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<4, true>)
-                             : (cpt <= 1 ? plan_dispatch_kernel<1, false> : cpt <= 2 ? plan_dispatch_kernel<2, false> : plan_dispatch_kernel<4, false>);
-    launch_args(kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, m);
+    const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)segs), block(kSmallThreads);
+    const int cpt = (seg_chunks + kSmallThreads - 1) / kSmallThreads;
+    const auto kernel = Ca ? (cpt <= 1 ? plan_dispatch_kernel<1, true> : cpt <= 2 ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<4, true>)
+                           : (cpt <= 1 ? plan_dispatch_kernel<1, false> : cpt <= 2 ? plan_dispatch_kernel<2, false> : plan_dispatch_kernel<4, false>);
+    launch_args(kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a.A, x, x_aux, a.N, a.k, a.k_magic, a.small_groups, C, Ca, seg_chunks,
+                m, a);
     return launch_status();
 }
 

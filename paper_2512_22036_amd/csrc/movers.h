@@ -332,10 +332,23 @@ __global__ __launch_bounds__(256) void touch_kernel(const u32x4 *src, size_t n)
 // tokens of 14 KiB 4.9 / 3.9, of 7392 B in two planes 4.5 / 4.2, 128 tokens 7.1 / 6.2 and 5.7 / 5.4; 1000 x 2 x 1 KiB 9.2 / 7.8.
 constexpr int kFusedChunks = 4;   // most chunks per thread held in registers across the planning: 32 KiB a workgroup
 
+// What a token's workgroup needs first are arguments of their own: they are all read at the start of the kernel, where members of a
+// structure were read branch by branch, each after a wait (4 tokens of 14 KiB 3.85 -> 3.5 us, 128 tokens 6.1 -> 5.9).
+struct FusedRows {
+    u32x4 *expert_buf, *expert_aux;
+};
+
 template <int CPT, bool AUX>
-__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a, DispatchArgs m)
+__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k,
+                                                                     uint32_t k_magic, int32_t small_groups, int32_t C, int32_t Ca,
+                                                                     int32_t seg_chunks, FusedRows m, PlanArgs a)
 {
     __shared__ SmallLds s;
+    a.A = A;
+    a.N = N;
+    a.k = k;
+    a.k_magic = k_magic;
+    a.small_groups = small_groups;
     const int b = blockIdx.x, seg = blockIdx.y;
     if (b <= a.small_groups) {
         if (seg != 0) return;
@@ -346,24 +359,24 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(PlanArgs a
     }
     const int tid = threadIdx.x;
     const int t = b - 1 - a.small_groups;
-    const int c0 = seg * m.seg_chunks + tid, c_end = min(m.C + m.Ca, (seg + 1) * m.seg_chunks);
+    const int c0 = seg * seg_chunks + tid, c_end = min(C + Ca, (seg + 1) * seg_chunks);
     // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
-    const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
+    const u32x4 *src = x + (size_t)t * C, *src_aux = x_aux + (size_t)t * Ca - C;
     u32x4 v[CPT];
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
         const int c = c0 + i * kSmallThreads;
-        if (c < c_end) v[i] = load16_stream((!AUX || c < m.C ? src : src_aux) + c);
+        if (c < c_end) v[i] = load16_stream((!AUX || c < C ? src : src_aux) + c);
     }
     const int slots = small_slots(s, a, t * a.k, a.k);
     for (int j = 0; j < a.k; ++j) {
         const int slot = __builtin_amdgcn_readlane(slots, j);
         if (slot < 0) continue;
-        u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
+        u32x4 *dst = m.expert_buf + (size_t)slot * C, *dst_aux = m.expert_aux + (size_t)slot * Ca - C;
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
             const int c = c0 + i * kSmallThreads;
-            if (c < c_end) (!AUX || c < m.C ? dst : dst_aux)[c] = v[i];
+            if (c < c_end) (!AUX || c < C ? dst : dst_aux)[c] = v[i];
         }
     }
 }
