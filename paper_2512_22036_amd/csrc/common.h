@@ -40,9 +40,9 @@ bool sizes_ok(int32_t N, int32_t k, int32_t E, int32_t D)
 
 // From this many tiles on, per-tile counts are first summed over chunks of tiles (one more small launch),
 // so that a placement workgroup reads about 2 * sqrt(tiles) rows of counts instead of one per tile.
-// Measured, k = 8, 256 experts and 8 devices, plan alone with / without the chunks, us: 48 tiles 13.9 / 12.3, 80 tiles 14.9 /
-// 14.3, 96 tiles 15.1 / 15.3, 128 tiles 16.1 / 17.2, 256 tiles 18.0 / 26.0, 512 tiles 27.1 / 53.4; 1024 experts and 1024 devices, 128
-// tiles 29.3 / 41.4.  (Fewer columns cross later: 64 experts and 8 devices, 128 tiles 14.0 / 12.9.)
+// Measured, k = 8, 256 experts and 8 devices, plan alone with / without the chunks, us: 49 tiles 13.9 / 11.6, 80 tiles 14.3 / 13.1, 94 tiles
+// 14.5 / 13.8, 98 tiles 14.7 / 13.9, 128 tiles 14.7 / 15.1, 157 tiles 15.4 / 18.0, 256 tiles 17.8 / 24.0; 1024 experts and 1024 devices, 128 tiles 23.6 /
+// 38.3.  (Fewer columns cross later: 64 experts and 8 devices, 128 tiles 13.4 / 11.6.)
 constexpr int kChunkMinTiles = 96;
 
 inline int tokens_per_tile(int k, int rounds) { return rounds * kRoundPairs / k; }

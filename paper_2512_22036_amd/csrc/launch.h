@@ -103,11 +103,9 @@ inline void combine_shape_latency(int N, int C, int &threads, int &segs)
 template <bool Y_BF16, bool OUT_BF16, int JU>
 void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    // what is bound by latency is written through or plain, what is bound by memory in every way but plain (out_stores)
     if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough>, grid, block, s, a, e0, e1);
-    if constexpr (JU >= 2)
-        if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain>, grid, block, s, a, e0, e1);
-    if constexpr (JU <= 2) {
+    if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain>, grid, block, s, a, e0, e1);
+    if constexpr (JU <= 4) {   // inputs bound by latency are written through or plain (out_stores)
         if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream>, grid, block, s, a, e0, e1);
         else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal>, grid, block, s, a, e0, e1);
     }
@@ -116,7 +114,11 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 // Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4 KiB
 // 13.4 / 13.0); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
 // scalars (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
-// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.
+// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below 16384
+// waves, two of the chip's fills (1200 x 8 x 8 KiB, 9600 waves, 17.9 with one / 16.2 with two; 600 x 8 x 16 KiB 20.9 / 19.1), four below 4096
+// (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).
+constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 16384;
+
 template <bool Y_BF16, bool OUT_BF16>
 void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
@@ -127,11 +129,16 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     else combine_shape(a.C, threads, a.segs);
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
-    if (latency ? a.k <= 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2) : a.k == 2)
-        launch_combine_as<Y_BF16, OUT_BF16, 2>(a, grid, block, stores, s, e0, e1);
-    else if (!latency)
+    const int64_t waves = (int64_t)N * ((a.C + kWave - 1) / kWave);
+    const bool two = latency ? a.k == 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2)
+                             : a.k == 2 || (waves >= kCombineFewWaves && waves < kCombineManyWaves);
+    if (a.k == 1)
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
-    else if (bytes < kCombineLatencyBoundBytes / 4)
+    else if (two)
+        launch_combine_as<Y_BF16, OUT_BF16, 2>(a, grid, block, stores, s, e0, e1);
+    else if (!latency && waves >= kCombineManyWaves)
+        launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
+    else if (latency && bytes < kCombineLatencyBoundBytes / 4)
         launch_combine_as<Y_BF16, OUT_BF16, 8>(a, grid, block, stores, s, e0, e1);
     else
         launch_combine_as<Y_BF16, OUT_BF16, 4>(a, grid, block, stores, s, e0, e1);

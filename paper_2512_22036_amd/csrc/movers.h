@@ -291,12 +291,22 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
             else __builtin_nontemporal_store(v[q], dst);
         }
     };
-    if (!pull) {
-        if (row >= 0) store();
-        return;
+    // The same workgroups read the descriptors of the XCD's next tile, an entry a lane, and drop them: the first two loads of every
+    // workgroup (slot, then its token) depend on each other and come from the L2 then.  Calls whose descriptors have left the
+    // caches - other tensors moved by a plan made earlier - wait for them in every workgroup otherwise, the longer the fewer workgroups
+    // there are: dispatch alone over changing buffers 8192 x 8 x 14 KiB 216 -> 186 us, 16384 x 8 x 8 KiB 234 -> 208, 9100 x 8 x 14 KiB
+    // 250 -> 218; right after the plan, no difference.  Not for rows of up to 2 KiB (65536 x 8 x 1040 B 177 / 207) nor for a source tensor taken in
+    // chunks (32768 x 8 x 14 KiB 733 / 766), nor with the receive tensors (4096 x 8 x 14 KiB, step 378 / 383).
+    int next_token = 0;
+    if (PULL && CPT > 1 && !WIRE && pass == 0 && r < (uint32_t)a.tile_tokens && local + kXcds < tiles_here && (int)threadIdx.x < a.k) {
+        const uint32_t e = r * (uint32_t)a.k + threadIdx.x;
+        const int next_row = e < pairs ? a.tile_slots[(size_t)(tile + kXcds) * a.tile_cap + e] : -1;
+        if (next_row >= 0) next_token = a.slot_token[next_row];
     }
-    if (WIRE) load(p, tp, segment(tp), false);
+    if (WIRE && pull) load(p, tp, segment(tp), false);
     if (row >= 0) store();
+    asm volatile("" ::"v"(next_token));
+    if (!pull) return;
 #pragma unroll
     for (int q = 0; q < CPT; ++q) asm volatile("" ::"v"(p[q]));   // the value is not used: only the read matters
 }
@@ -377,6 +387,46 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(const int3
         for (int i = 0; i < CPT; ++i) {
             const int c = c0 + i * kSmallThreads;
             if (c < c_end) (!AUX || c < C ? dst : dst_aux)[c] = v[i];
+        }
+    }
+}
+
+// The same for many tokens of rows of more than 16 KiB, which are bound by their writes: with members of structures read as they
+// are used and a branch per plane the rows are stored more slowly, which memory likes better (341 tokens x 6 x 40 KiB 18.1 us, 19.5 by
+// plan_dispatch_kernel<4, false>; 2048 x 1 x 32 KiB 25.6 / 27.2; 4 tokens x 8 x 128 KiB 6.5 / 5.9).
+constexpr int kFusedLongTokens = 64;   // more than these
+
+__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_long_kernel(PlanArgs a, DispatchArgs m)
+{
+    __shared__ SmallLds s;
+    const int b = blockIdx.x, seg = blockIdx.y;
+    if (b <= a.small_groups) {
+        if (seg != 0) return;
+        const int p0 = (b - 1) * kSmallPairs;
+        if (b == 0) small_counts(s, a);
+        else small_place(s, a, p0, min(kSmallPairs, a.N * a.k - p0));
+        return;
+    }
+    const int tid = threadIdx.x;
+    const int t = b - 1 - a.small_groups;
+    const int c0 = seg * m.seg_chunks + tid, c_end = min(m.C + m.Ca, (seg + 1) * m.seg_chunks);
+    // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
+    const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
+    u32x4 v[kFusedChunks];
+#pragma unroll
+    for (int i = 0; i < kFusedChunks; ++i) {
+        const int c = c0 + i * kSmallThreads;
+        if (c < c_end) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
+    }
+    const int slots = small_slots(s, a, t * a.k, a.k);
+    for (int j = 0; j < a.k; ++j) {
+        const int slot = __builtin_amdgcn_readlane(slots, j);
+        if (slot < 0) continue;
+        u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
+#pragma unroll
+        for (int i = 0; i < kFusedChunks; ++i) {
+            const int c = c0 + i * kSmallThreads;
+            if (c < c_end) (c < m.C ? dst : dst_aux)[c] = v[i];
         }
     }
 }

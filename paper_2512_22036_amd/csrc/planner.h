@@ -111,8 +111,8 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
 // up): the ranking is bound by the instructions of its waves, and a compute unit ranks 1024 pairs in half the time of
 // 2048.  Their counts are the halves of the tile's 32-bit words (at most 1024 + 63 pairs each), and ranks are within the
 // half.  Chosen where there is no chunk level; with more tiles the chip is full and the halves only cost pass 2 (plan
-// alone, k = 8, one / two workgroups per tile: 1000 tokens 10.9 / 10.3 us, 16384 14.5 / 14.0, 24700 16.1 / 16.5,
-// 49152 17.0 / 18.3 us).
+// alone, k = 8, one / two workgroups per tile, us: 5000 tokens 11.2 / 9.9, 16384 12.0 / 10.9, 24000 14.8 / 13.8; 40000 17.6 / 18.0, and 15.4 with
+// one and the chunk level).
 constexpr int kRankRounds = 4, kHalfRounds = 2;   // rounds of 16 waves x (64 / k) tokens that cover a tile of 2048 / k tokens, half of it
 
 __host__ __device__ __forceinline__ int first_half_tokens(int tile_tokens) { return (tile_tokens + 1) / 2; }
@@ -299,9 +299,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
 // transfer order (its slots ascending: expert by expert, tokens ascending): neighbouring threads then write
 // neighbouring slots of one expert, a few cache lines per wave instead of 64; the pairs meet their place in that
 // order through LDS.  Bound by latency: three barriers between the loads and the stores.  Kernel times of pass 1 + pass 2
-// (and the chunk pass between them), k = 8, us: 8192 tokens 4.5 + 6.6 (5.6 + 7.2 with one workgroup per tile in pass 1), 32768 tokens 6.0 + 4.6 + 8.0, 131072 tokens
-// 9.5 + 4.1 + 15.4, 4096 tokens with k = 2 4.7 + 4.7; before, with a pass 1 that only counted and a pass 2 that ranked
-// all pairs again (and prefixed 16 counters per key): 5.2 + 11.8, 5.3 + 4.3 + 14.2, 7.0 + 4.2 + 29.9, 3.8 + 8.6.
+// (and the chunk pass between them), k = 8, us: 8192 tokens 4.8 + 6.3, 131072 tokens 8.3 + 4.1 + 14.0; with a pass 1
+// that only counted and a pass 2 that ranked all pairs: 5.2 + 11.8, 7.0 + 4.2 + 29.9.
 constexpr int kTilePairs = kMaxRounds * kRoundPairs;
 constexpr int kCross = 12;           // rows of counts that a thread requests before anything else: 36 rows of 256 experts + 8 devices
 constexpr int kMaxChunks = 2 * (kMaxBins / kWave);   // groups of 64 experts, then groups of 64 devices

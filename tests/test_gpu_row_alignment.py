@@ -267,3 +267,26 @@ def test_token_walk(N, k, row_bytes, aux_bytes, flags):
         if aux_bytes:
             assert torch.equal(ea[:rows if flags & 1 else 0], xa[token[:rows if flags & 1 else 0]])
             assert torch.equal(sa[:sends if flags & 2 else 0], xa[src[:sends if flags & 2 else 0]])
+
+
+# rows in flight by the number of waves (4096 and 16384) and by k, for inputs on either side of 64 MiB; k = 1 and 2 have kernels of their own
+@pytest.mark.parametrize("N,k,H", [(1000, 64, 1024), (2047, 32, 1024), (2048, 32, 1024), (1170, 8, 7168), (1171, 8, 7168), (8191, 8, 1024), (8192, 8, 1024),
+                                   (4500, 1, 8192), (4500, 2, 8192), (300, 1, 520), (300, 2, 520), (2100, 3, 4096), (2900, 3, 4096)])
+def test_combine_by_waves(N, k, H):
+    import paper_2512_22036_amd as f
+    E, D = 64, 8
+    rng = np.random.default_rng(N + k)
+    A = random_topk(rng, N, k, E).astype(np.int32)
+    A[1::7, 0] = -1                       # an entry without a row
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    y = torch.randint(-15, 16, (L.P, H), device="cuda").to(torch.bfloat16)
+    w = torch.full((N, k), 0.5, device="cuda")        # whole numbers and a power of two: every sum is exact
+    out, room = rows_at(N, H * 4, 0)
+    out = out.view(torch.float32)
+    f.fusco_combine(L, y, w, out)
+    want = torch.zeros((N, H), dtype=torch.float32, device="cuda")
+    for rows in L.array("pair_slot").view(N, k).long().t():
+        want += torch.where((rows >= 0)[:, None], y[rows.clamp_min(0)].float(), 0.0)
+    assert torch.equal(out, want / 2)
+    assert bool((room[out.numel() * 4:] == 0xEE).all())
