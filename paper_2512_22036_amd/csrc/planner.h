@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
 // entry whose bit is set already adds no row.  Four counters per expert (and eight per device), taken by lane, keep popular
 // keys from serialising a wave's additions.  Bound by latency (routing, counters, scan, places: four barriers) and, from
 // about 8192 pairs on, by the additions, 0.14 us per 1024 pairs.  Kernel of one launch / the two launches it replaces, us:
-// 300 tokens x 8 5.1 / 8.6, 4096 x 2 5.3 / 8.5, 1537 x 6 5.7 / 9.5, 2000 x 10 7.5 / 10.2, 4096 x 8 8.6 / 9.6.  An eighth and
+// 300 tokens x 8 5.1 / 8.6, 4096 x 2 5.3 / 8.5, 1537 x 6 5.7 / 9.5, 2000 x 10 7.5 / 10.2.  An eighth and
 // not half a tile per workgroup because its own pairs are a chain of their own: 1537 x 6 7.1 with halves, 6.3 with quarters.
 // VEC: ids that are read at once (a token's ids start on multiples of it); IDS: ids of a token that a thread requests at a
 // time, of 16 / IDS tokens (k <= 4: 4; 8000 x 1 6.3, 7.5 us with 8).
@@ -528,9 +528,15 @@ constexpr int kDirectParts = 8;      // workgroups per tile
 constexpr int kDirectMaxD = 64;      // bits of the mask
 constexpr int kDirectMaxK = 16;      // a thread takes all of a token's ids: 600 tokens x 33 10.5 us, 9.9 with two launches
 constexpr int kDirectMaxTokens = 8192;
-// Sizes that the one launch is faster for, one / two launches, us: 6144 x 4 8.1 / 8.6, 8192 x 4 9.0 / 8.6, 8192 x 2 7.2 / 8.5,
-// 8192 x 1 6.4 / 8.5; 5400 x 6 9.3 / 9.9, 4096 x 8 8.6 / 9.6, 6144 x 8 11.1 / 10.0, 3200 x 10 9.6 / 10.8.
-inline int direct_max_pairs(int k) { return k <= 4 ? 24576 : 32768; }
+// Sizes up to which the one launch is the faster one whatever the routing.  Popular experts cost it additions to one address, and
+// the two launches are faster with them, so the line lies lower than for scores without a trend.  One launch / two, us; scores
+// without a trend, popular experts (by rank^-1.2), expert 0 in every token, all entries the same expert:
+// 3072 x 8, 256 experts on 8 devices 7.5 / 9.2, 8.3 / 8.5, 7.9 / 9.1, 9.6 / 8.4; 1024 experts on 64 devices 8.2 / 11.1, 9.0 / 10.2, 8.6 / 11.0, 10.2 / 10.1;
+// 4096 x 8, 256 experts 8.5 / 9.2, 9.8 / 8.7, 9.0 / 9.3, 11.5 / 8.5.
+// 4096 x 6, 160 experts 7.8 / 9.3, 8.6 / 9.0, 8.3 / 9.3, 9.8 / 8.9; 5461 x 6 9.3 / 9.5, 10.5 / 9.1, 9.8 / 9.5, 12.4 / 9.0.
+// 5120 x 4, 60 experts on 4 devices 7.4 / 8.1, 8.1 / 8.0, 8.0 / 8.1, 9.0 / 7.9; 6144 x 4 8.0 / 8.1, 8.8 / 8.0, 8.7 / 8.1, 10.0 / 7.9.
+// 8192 x 2, 16 experts on 4 devices 7.0 / 7.8, 7.8 / 7.7, 7.9 / 7.7, 8.2 / 7.7.
+inline int direct_max_pairs(int k) { return k <= 4 ? 20480 : 24576; }
 inline bool planned_directly(int N, int k, int D)
 {
     return k <= kDirectMaxK && D <= kDirectMaxD && N <= kDirectMaxTokens && N * k <= direct_max_pairs(k);
@@ -564,7 +570,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_direct_kernel(PlanArgs a)
     const int pair0 = tok0 * a.k;
     Ranking<1> k(a, 1, ntok);
     k.load(a, pair0);
-        for (int b = tid; b < a.E + a.D; b += kPlanThreads) s.rank[b] = u32x4{0, 0, 0, 0};
+    for (int b = tid; b < a.E + a.D; b += kPlanThreads) s.rank[b] = u32x4{0, 0, 0, 0};
     for (int b = tid; b < kPlaces * a.E; b += kPlanThreads) s.ecount[b] = u32x4{0, 0, 0, 0};
     for (int b = tid; b < 2 * kDirectMaxD * kDcopies; b += kPlanThreads) s.dcount[b] = 0;
     __syncthreads();

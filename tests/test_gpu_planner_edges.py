@@ -114,7 +114,10 @@ def test_several_tiles(N, k, E, D, bad):
 @pytest.mark.parametrize("N,k,E,D", [(2049, 1, 16, 1), (8192, 1, 64, 32), (8193, 1, 64, 64), (1025, 2, 16, 4), (8192, 2, 128, 64),
                                      (8192, 3, 96, 8), (6144, 4, 60, 4), (6145, 4, 64, 8), (5000, 5, 160, 5), (1537, 6, 160, 5),
                                      (293, 7, 1024, 64), (257, 8, 256, 8), (4096, 8, 256, 64), (4097, 8, 256, 8), (3000, 8, 1023, 33),
-                                     (2000, 10, 384, 8), (129, 16, 64, 2), (2048, 16, 1024, 64), (2000, 12, 130, 65), (150, 17, 96, 4)])
+                                     (2000, 10, 384, 8), (129, 16, 64, 2), (2048, 16, 1024, 64), (2000, 12, 130, 65), (150, 17, 96, 4),
+                                     # the most pairs of one launch and the next size: 20480 (k <= 4), 24576
+                                     (6826, 3, 96, 8), (6827, 3, 96, 8), (5120, 4, 60, 4), (5121, 4, 64, 8), (4915, 5, 160, 5), (4916, 5, 160, 5),
+                                     (3072, 8, 256, 64), (3073, 8, 256, 8), (1536, 16, 1024, 64), (1537, 16, 1024, 64)])
 def test_few_tiles(N, k, E, D, offset):
     import paper_2512_22036_amd as f
     for bad in (False, True):
