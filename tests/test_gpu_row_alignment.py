@@ -290,3 +290,28 @@ def test_combine_by_waves(N, k, H):
         want += torch.where((rows >= 0)[:, None], y[rows.clamp_min(0)].float(), 0.0)
     assert torch.equal(out, want / 2)
     assert bool((room[out.numel() * 4:] == 0xEE).all())
+
+
+# entries taken eight or four at a time with every number of them left over, absent ones among them; below and above 16 MiB
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 14, 15, 16, 19, 24, 64])
+@pytest.mark.parametrize("y_f32", [False, True])
+@pytest.mark.parametrize("mib", [1, 12, 18, 40])
+def test_combine_with_entries_left_over(k, y_f32, mib):
+    import paper_2512_22036_amd as f
+    E, D, H = 64, 8, 520
+    N = max(3, (mib << 20) // (k * H * (4 if y_f32 else 2)))
+    rng = np.random.default_rng(k + mib)
+    A = random_topk(rng, N, k, E).astype(np.int32)
+    A[rng.random((N, k)) < 0.2] = -1      # any number of entries with a row, in any place
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    y = torch.randint(-15, 16, (L.P, H), device="cuda").to(torch.float32 if y_f32 else torch.bfloat16)
+    w = torch.full((N, k), 0.5, device="cuda")        # whole numbers and a power of two: every sum is exact
+    out, room = rows_at(N, H * 4, 0)
+    out = out.view(torch.float32)
+    f.fusco_combine(L, y, w, out)
+    want = torch.zeros((N, H), dtype=torch.float32, device="cuda")
+    for rows in L.array("pair_slot").view(N, k).long().t():
+        want += torch.where((rows >= 0)[:, None], y[rows.clamp_min(0)].float(), 0.0)
+    assert torch.equal(out, want / 2)
+    assert bool((room[out.numel() * 4:] == 0xEE).all())
