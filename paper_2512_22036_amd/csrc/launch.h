@@ -105,7 +105,7 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 {
     if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough>, grid, block, s, a, e0, e1);
     if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain>, grid, block, s, a, e0, e1);
-    if constexpr (JU <= 4) {   // inputs bound by latency are written through or plain (out_stores)
+    if constexpr (JU > 0 && JU <= 4) {   // inputs bound by latency are written through or plain (out_stores)
         if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream>, grid, block, s, a, e0, e1);
         else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal>, grid, block, s, a, e0, e1);
     }
@@ -118,6 +118,11 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 // waves, two of the chip's fills (1200 x 8 x 8 KiB, 9600 waves, 17.9 with one / 16.2 with two; 600 x 8 x 16 KiB 20.9 / 19.1), four below 4096
 // (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).
 constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 16384;
+// Three to sixteen fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753 tokens x 6 x
+// 1600 B (7 MiB) 2.9 / 2.7, 256 x 7 x 5824 B 3.4 / 3.1; smaller 37 x 7 x 11 KiB 2.5 / 2.6, 12 x 12 x 27 KiB 2.8 / 3.1.  More than eight of them take two
+// rounds, and waiting for the first costs: 121 x 24 x 13 KiB (36 MiB) 7.7 / 8.2, 541 x 16 x 2912 B (24 MiB) 5.9 / 6.1, but 581 x 12 x 6912 B
+// (46 MiB) 10.6 / 9.9.  Two rows as above (893 x 2 x 15 KiB 7.6 / 8.1; 1642 x 2 x 4192 B 5.8 / 5.2).
+constexpr size_t kCombineSpacedBytes = (size_t)4 << 20, kCombineSpacedManyBytes = (size_t)40 << 20;
 
 template <bool Y_BF16, bool OUT_BF16>
 void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
@@ -132,6 +137,10 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     const int64_t waves = (int64_t)N * ((a.C + kWave - 1) / kWave);
     const bool two = latency ? a.k == 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2)
                              : a.k == 2 || (waves >= kCombineFewWaves && waves < kCombineManyWaves);
+    if constexpr (!Y_BF16) {
+        if (latency && a.k >= 3 && a.k <= 16 && bytes >= (a.k <= 8 ? kCombineSpacedBytes : kCombineSpacedManyBytes))
+            return launch_combine_as<Y_BF16, OUT_BF16, kSpacedRows>(a, grid, block, stores, s, e0, e1);
+    }
     if (a.k == 1)
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
     else if (two)

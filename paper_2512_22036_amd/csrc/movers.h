@@ -548,6 +548,12 @@ __device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &lef
 // loads, which do not queue behind the rows, one step ahead of their use.  Rows in flight 1 / 2 / 4 / 8, us: 8192 x 8 x 14 KiB
 // 173 / 180 / 184 / 181, 16384 x 8 x 8 KiB 203 / 210 / 211 / 212, 32768 x 8 x 14 KiB 700 / 750 / 754 / 744; two entries per
 // token 20000 x 14 KiB 144 / 139 (slots in lanes instead: 155 with 1).
+// kSpacedRows: eight rows, each slot looked up when the row before it has been requested.  The requests lie a scalar load apart, which is what
+// inputs of fp32 rows between the two prefer (one after the other / in lanes, back to back / so, us: 5298 tokens x 5 x 1088 B 9.6 / 7.1 /
+// 6.8, 1904 x 8 x 2976 B 9.5 / 9.7 / 9.1, 5151 x 3 x 3488 B 14.1 / 13.6 / 13.0).  Not for bf16 rows, whose sums take twice the registers: the
+// compiler waits for a row before it reuses them for the next one's address.
+constexpr int kSpacedRows = -8;
+
 template <bool Y_BF16, bool OUT_BF16, int JU, OutStores STORES, bool PER_SEND_ROW = false>
 __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
 {
@@ -569,7 +575,30 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
 
-    if constexpr (JU <= 2) {
+    if constexpr (JU == kSpacedRows) {
+        const int32_t *slots = a.pair_slot + (size_t)t * a.k;
+        const float *wt = a.w + (size_t)t * a.k;
+        constexpr int ROWS = -kSpacedRows;
+        for (int j0 = 0; j0 < a.k; j0 += ROWS) {
+            u32x4 v[ROWS];
+            float wj[ROWS];
+            bool on[ROWS];
+#pragma unroll
+            for (int jj = 0; jj < ROWS; ++jj) {
+                const int j = j0 + jj;
+                on[jj] = false;
+                if (j >= a.k) continue;
+                const int slot = slots[j];
+                wj[jj] = wt[j];
+                if (slot < 0) continue;
+                on[jj] = true;
+                if (c < a.C) v[jj] = load16_stream(a.y + (size_t)slot * a.C + c);
+            }
+#pragma unroll
+            for (int jj = 0; jj < ROWS; ++jj)
+                if (on[jj]) add_row<Y_BF16>(acc, v[jj], wj[jj]);
+        }
+    } else if constexpr (JU <= 2) {
         static_assert(!PER_SEND_ROW, "the entries of a send row are picked out in lanes");
         const int32_t *slots = a.pair_slot + (size_t)t * a.k;
         const float *wt = a.w + (size_t)t * a.k;
