@@ -114,10 +114,13 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 // Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4 KiB
 // 13.4 / 13.0); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
 // scalars (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
-// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below 16384
-// waves, two of the chip's fills (1200 x 8 x 8 KiB, 9600 waves, 17.9 with one / 16.2 with two; 600 x 8 x 16 KiB 20.9 / 19.1), four below 4096
-// (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).
-constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 16384;
+// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below 32768
+// waves, four of the chip's fills (one / two: 1200 x 8 x 8 KiB, 9600 waves, 17.9 / 16.2; 600 x 8 x 16 KiB, 9600, 20.9 / 19.1; 11426 x 6 x 1152 B, 22852,
+// 20.2 / 17.5; 13512 x 8 x 1104 B, 27024, 34.0 / 29.7; 5691 x 7 x 4096 B, 22764, 31.5 / 32.0; 6193 x 8 x 5968 B to fp32, 37158, 69.3 / 70.2), four below 4096
+// (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).  Many entries keep a wave busy longer and want one already from 16384 waves on (1417 x 24 x 15 KiB of fp32,
+// 21972, 88.0 / 92.0; 5614 x 24 x 3984 B, 22456, 93.4 / 96.6).
+constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 32768, kCombineManyWavesLong = 16384;
+constexpr int kCombineLongK = 16;   // entries from which a wave is busy long
 // Three to sixteen fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753 tokens x 6 x
 // 1600 B (7 MiB) 2.9 / 2.7, 256 x 7 x 5824 B 3.4 / 3.1; smaller 37 x 7 x 11 KiB 2.5 / 2.6, 12 x 12 x 27 KiB 2.8 / 3.1.  More than eight of them take two
 // rounds, and waiting for the first costs: 121 x 24 x 13 KiB (36 MiB) 7.7 / 8.2, 541 x 16 x 2912 B (24 MiB) 5.9 / 6.1, but 581 x 12 x 6912 B
@@ -135,8 +138,9 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     a.n_rows = N;
     const dim3 grid((unsigned)N * (unsigned)a.segs), block((unsigned)threads);
     const int64_t waves = (int64_t)N * ((a.C + kWave - 1) / kWave);
+    const int64_t many = a.k >= kCombineLongK ? kCombineManyWavesLong : kCombineManyWaves;
     const bool two = latency ? a.k == 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2)
-                             : a.k == 2 || (waves >= kCombineFewWaves && waves < kCombineManyWaves);
+                             : a.k == 2 || (waves >= kCombineFewWaves && waves < many);
     if constexpr (!Y_BF16) {
         if (latency && a.k >= 3 && a.k <= 16 && bytes >= (a.k <= 8 ? kCombineSpacedBytes : kCombineSpacedManyBytes))
             return launch_combine_as<Y_BF16, OUT_BF16, kSpacedRows>(a, grid, block, stores, s, e0, e1);
@@ -145,7 +149,7 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
     else if (two)
         launch_combine_as<Y_BF16, OUT_BF16, 2>(a, grid, block, stores, s, e0, e1);
-    else if (!latency && waves >= kCombineManyWaves)
+    else if (!latency && waves >= many)
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
     else if (latency && bytes < kCombineLatencyBoundBytes / 4)
         launch_combine_as<Y_BF16, OUT_BF16, 8>(a, grid, block, stores, s, e0, e1);

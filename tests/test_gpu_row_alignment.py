@@ -269,9 +269,9 @@ def test_token_walk(N, k, row_bytes, aux_bytes, flags):
             assert torch.equal(sa[:sends if flags & 2 else 0], xa[src[:sends if flags & 2 else 0]])
 
 
-# rows in flight by the number of waves (4096 and 16384) and by k, for inputs on either side of 64 MiB; k = 1 and 2 have kernels of their own
+# rows in flight by the number of waves (4096 and 32768) and by k, for inputs on either side of 64 MiB; k = 1 and 2 have kernels of their own
 @pytest.mark.parametrize("N,k,H", [(1000, 64, 1024), (2047, 32, 1024), (2048, 32, 1024), (1170, 8, 7168), (1171, 8, 7168), (8191, 8, 1024), (8192, 8, 1024),
-                                   (4500, 1, 8192), (4500, 2, 8192), (300, 1, 520), (300, 2, 520), (2100, 3, 4096), (2900, 3, 4096)])
+                                   (4681, 8, 3584), (4682, 8, 3584), (4500, 1, 8192), (4500, 2, 8192), (300, 1, 520), (300, 2, 520), (2100, 3, 4096), (2900, 3, 4096)])
 def test_combine_by_waves(N, k, H):
     import paper_2512_22036_amd as f
     E, D = 64, 8
