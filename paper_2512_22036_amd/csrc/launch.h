@@ -112,7 +112,7 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 }
 
 // Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4 KiB
-// 13.4 / 13.0); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
+// 13.4 / 13.0), for 24 and more entries, several rounds of them, from 32 MiB on (506 x 24 x 1600 B of fp32 5.2 / 6.4, 633 x 24 x 1504 B 6.3 / 7.4); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
 // scalars (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
 // 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below 32768
 // waves, four of the chip's fills (one / two: 1200 x 8 x 8 KiB, 9600 waves, 17.9 / 16.2; 600 x 8 x 16 KiB, 9600, 20.9 / 19.1; 11426 x 6 x 1152 B, 22852,
@@ -120,12 +120,12 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 // (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).  Many entries keep a wave busy longer and want one already from 16384 waves on (1417 x 24 x 15 KiB of fp32,
 // 21972, 88.0 / 92.0; 5614 x 24 x 3984 B, 22456, 93.4 / 96.6).
 constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 32768, kCombineManyWavesLong = 16384;
-constexpr int kCombineLongK = 16;   // entries from which a wave is busy long
-// Three to sixteen fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753 tokens x 6 x
+constexpr int kCombineLongK = 16, kCombineVeryLongK = 24;   // entries from which a wave is busy long
+// Three and more fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753 tokens x 6 x
 // 1600 B (7 MiB) 2.9 / 2.7, 256 x 7 x 5824 B 3.4 / 3.1; smaller 37 x 7 x 11 KiB 2.5 / 2.6, 12 x 12 x 27 KiB 2.8 / 3.1.  More than eight of them take two
 // rounds, and waiting for the first costs: 121 x 24 x 13 KiB (36 MiB) 7.7 / 8.2, 541 x 16 x 2912 B (24 MiB) 5.9 / 6.1, but 581 x 12 x 6912 B
-// (46 MiB) 10.6 / 9.9.  Two rows as above (893 x 2 x 15 KiB 7.6 / 8.1; 1642 x 2 x 4192 B 5.8 / 5.2).
-constexpr size_t kCombineSpacedBytes = (size_t)4 << 20, kCombineSpacedManyBytes = (size_t)40 << 20;
+// (46 MiB) 10.6 / 9.9, 626 x 64 x 1344 B (51 MiB) 14.7 / 12.9.  Two rows as above (893 x 2 x 15 KiB 7.6 / 8.1; 1642 x 2 x 4192 B 5.8 / 5.2).
+constexpr size_t kCombineSpacedBytes = (size_t)4 << 20, kCombineSpacedManyBytes = (size_t)42 << 20;
 
 template <bool Y_BF16, bool OUT_BF16>
 void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
@@ -142,7 +142,7 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     const bool two = latency ? a.k == 2 || (a.k <= 4 && bytes >= kCombineLatencyBoundBytes / 2)
                              : a.k == 2 || (waves >= kCombineFewWaves && waves < many);
     if constexpr (!Y_BF16) {
-        if (latency && a.k >= 3 && a.k <= 16 && bytes >= (a.k <= 8 ? kCombineSpacedBytes : kCombineSpacedManyBytes))
+        if (latency && a.k >= 3 && bytes >= (a.k <= 8 ? kCombineSpacedBytes : kCombineSpacedManyBytes))
             return launch_combine_as<Y_BF16, OUT_BF16, kSpacedRows>(a, grid, block, stores, s, e0, e1);
     }
     if (a.k == 1)
@@ -151,7 +151,7 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
         launch_combine_as<Y_BF16, OUT_BF16, 2>(a, grid, block, stores, s, e0, e1);
     else if (!latency && waves >= many)
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
-    else if (latency && bytes < kCombineLatencyBoundBytes / 4)
+    else if (latency && bytes < (a.k >= kCombineVeryLongK ? kCombineLatencyBoundBytes / 2 : kCombineLatencyBoundBytes / 4))
         launch_combine_as<Y_BF16, OUT_BF16, 8>(a, grid, block, stores, s, e0, e1);
     else
         launch_combine_as<Y_BF16, OUT_BF16, 4>(a, grid, block, stores, s, e0, e1);

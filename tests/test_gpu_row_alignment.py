@@ -292,11 +292,11 @@ def test_combine_by_waves(N, k, H):
     assert bool((room[out.numel() * 4:] == 0xEE).all())
 
 
-# entries taken eight or four at a time with every number of them left over, absent ones among them; below and above 16 MiB, and below
-# and above the 4, 40 and 64 MiB between which fp32 rows are spaced
-@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 14, 15, 16, 19, 24, 64])
+# entries taken eight or four at a time with every number of them left over, absent ones among them; below and above 16 and 32 MiB, and below
+# and above the 4, 42 and 64 MiB between which fp32 rows are spaced
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 14, 15, 16, 19, 23, 24, 29, 64])
 @pytest.mark.parametrize("y_f32", [False, True])
-@pytest.mark.parametrize("mib", [1, 4.2, 12, 18, 40, 44, 66])
+@pytest.mark.parametrize("mib", [1, 4.2, 12, 18, 31, 40, 44, 66])
 def test_combine_with_entries_left_over(k, y_f32, mib):
     import paper_2512_22036_amd as f
     E, D, H = 64, 8, 520
