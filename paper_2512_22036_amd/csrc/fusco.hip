@@ -567,10 +567,10 @@ int fusco_combine_two_hop(const fusco_layout *L, const void *d_y, int y_dtype, c
         f.k = L->k;
         f.C = (int32_t)((size_t)H * (y_dtype == FUSCO_BF16 ? 2 : 4) / 16);
         const OutStores how = out_stores((size_t)L->P * (size_t)f.C * 16, d_out, (size_t)L->N, (size_t)H * (out_dtype == FUSCO_BF16 ? 2 : 4));
-        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_two_hop<true, true>(f, L->N, how, s);
-        else if (y_dtype == FUSCO_BF16) launch_two_hop<true, false>(f, L->N, how, s);
-        else if (out_dtype == FUSCO_BF16) launch_two_hop<false, true>(f, L->N, how, s);
-        else launch_two_hop<false, false>(f, L->N, how, s);
+        if (y_dtype == FUSCO_BF16 && out_dtype == FUSCO_BF16) launch_two_hop<true, true>(f, L->N, L->D, how, s);
+        else if (y_dtype == FUSCO_BF16) launch_two_hop<true, false>(f, L->N, L->D, how, s);
+        else if (out_dtype == FUSCO_BF16) launch_two_hop<false, true>(f, L->N, L->D, how, s);
+        else launch_two_hop<false, false>(f, L->N, L->D, how, s);
         return launch_status();
     }
     // general k: level 2 reversed (fp32 partial row per send row), then level 1 reversed

@@ -111,20 +111,22 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
     }
 }
 
-// Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4 KiB
-// 13.4 / 13.0), for 24 and more entries, several rounds of them, from 32 MiB on (506 x 24 x 1600 B of fp32 5.2 / 6.4, 633 x 24 x 1504 B 6.3 / 7.4); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as
-// scalars (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
-// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below 32768
-// waves, four of the chip's fills (one / two: 1200 x 8 x 8 KiB, 9600 waves, 17.9 / 16.2; 600 x 8 x 16 KiB, 9600, 20.9 / 19.1; 11426 x 6 x 1152 B, 22852,
-// 20.2 / 17.5; 13512 x 8 x 1104 B, 27024, 34.0 / 29.7; 5691 x 7 x 4096 B, 22764, 31.5 / 32.0; 6193 x 8 x 5968 B to fp32, 37158, 69.3 / 70.2), four below 4096
-// (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).  Many entries keep a wave busy longer and want one already from 16384 waves on (1417 x 24 x 15 KiB of fp32,
-// 21972, 88.0 / 92.0; 5614 x 24 x 3984 B, 22456, 93.4 / 96.6).
+// Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4
+// KiB 13.4 / 13.0), for 24 and more entries, several rounds of them, from 32 MiB on (506 x 24 x 1600 B of fp32 5.2 / 6.4, 633 x 24 x 1504 B
+// 6.3 / 7.4); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as scalars
+// (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
+// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below
+// 32768 waves, four of the chip's fills (one / two: 1200 x 8 x 8 KiB, 9600 waves, 17.9 / 16.2; 600 x 8 x 16 KiB, 9600, 20.9 / 19.1; 11426 x
+// 6 x 1152 B, 22852, 20.2 / 17.5; 13512 x 8 x 1104 B, 27024, 34.0 / 29.7; 5691 x 7 x 4096 B, 22764, 31.5 / 32.0; 6193 x 8 x 5968 B to fp32,
+// 37158, 69.3 / 70.2), four below 4096 (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).  Many entries keep a wave busy longer and want one
+// already from 16384 waves on (1417 x 24 x 15 KiB of fp32, 21972, 88.0 / 92.0; 5614 x 24 x 3984 B, 22456, 93.4 / 96.6).
 constexpr int64_t kCombineFewWaves = 4096, kCombineManyWaves = 32768, kCombineManyWavesLong = 16384;
 constexpr int kCombineLongK = 16, kCombineVeryLongK = 24;   // entries from which a wave is busy long
-// Three and more fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753 tokens x 6 x
-// 1600 B (7 MiB) 2.9 / 2.7, 256 x 7 x 5824 B 3.4 / 3.1; smaller 37 x 7 x 11 KiB 2.5 / 2.6, 12 x 12 x 27 KiB 2.8 / 3.1.  More than eight of them take two
-// rounds, and waiting for the first costs: 121 x 24 x 13 KiB (36 MiB) 7.7 / 8.2, 541 x 16 x 2912 B (24 MiB) 5.9 / 6.1, but 581 x 12 x 6912 B
-// (46 MiB) 10.6 / 9.9, 626 x 64 x 1344 B (51 MiB) 14.7 / 12.9.  Two rows as above (893 x 2 x 15 KiB 7.6 / 8.1; 1642 x 2 x 4192 B 5.8 / 5.2).
+// Three and more fp32 rows per token are spaced (kSpacedRows) from these sizes to kCombineLatencyBoundBytes, us, back to back / spaced: 753
+// tokens x 6 x 1600 B (7 MiB) 2.9 / 2.7, 256 x 7 x 5824 B 3.4 / 3.1; smaller 37 x 7 x 11 KiB 2.5 / 2.6, 12 x 12 x 27 KiB 2.8 / 3.1.  More
+// than eight of them take two rounds, and waiting for the first costs: 121 x 24 x 13 KiB (36 MiB) 7.7 / 8.2, 541 x 16 x 2912 B (24 MiB) 5.9
+// / 6.1, but 581 x 12 x 6912 B (46 MiB) 10.6 / 9.9, 626 x 64 x 1344 B (51 MiB) 14.7 / 12.9.  Two rows as above (893 x 2 x 15 KiB 7.6 / 8.1;
+// 1642 x 2 x 4192 B 5.8 / 5.2).
 constexpr size_t kCombineSpacedBytes = (size_t)4 << 20, kCombineSpacedManyBytes = (size_t)42 << 20;
 
 template <bool Y_BF16, bool OUT_BF16>
@@ -251,43 +253,78 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
     return whole ? kOutThroughStream : kOutNonTemporal;
 }
 
-// Two-hop combine, by the bytes of its input.
-// Up to 20 MiB latency counts: a token's rows are requested at once.  From there to 96 MiB the rows of many waves are in flight
-// anyway, and memory is faster when a wave has one.  us, at once / one by one, rows of 14 KiB x 8: 4 tokens 4.2 / 4.7, 128 8.7 / 10.6, 200
-// (22 MiB) 13.6 / 12.6, 300 21.0 / 15.9, 640 45 / 39.  Up to 48 MiB rows are cut into segments of 256 threads (4 tokens 5.5 / 6.6 with
-// whole rows, 300 16.1 / 17.6, 500 24.6 / 24.3).
-// Larger inputs are bound by memory.  With three and more rows per token a compute unit gets no more than 16 waves, 12 for six and more
-// bf16 rows, which then keep enough in flight by requesting their rows at once; dynamic LDS that the kernel does not use keeps
-// further workgroups out.  us, no cap and one by one / 16 waves / 12: 8192 x 8 x 8 KiB on 16 devices 306 / 290 / 281, 4096 x 8 x 8 KiB on 8 133 / 127.6 /
-// 126.6, 30000 x 8 x 2 KiB 247 / 239 / 235, 8192 x 4 x 4 KiB 83 / 76.4 / 76.5, 8192 x 6 x 10 KiB (one workgroup of 10 waves) 235 / 228, 4096 x 8 x
-// 14 KiB (of 14) 228 / 224, fp32 9000 x 8 x 8 KiB 199 / 194 / 204, 9000 x 3 x 8 KiB 136 / 131 / 142; 9000 x 1 x 8 KiB 57 / 64 / 92.
-constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20, kTwoHopAtOnceBytes = (size_t)20 << 20, kTwoHopCappedBytes = (size_t)96 << 20;
+// Two-hop combine, by the bytes of its input and the waves of its launch.
+// Up to 11 MiB latency counts: a token's rows are requested at once (at once / in turn, us, rows of 14 KiB x 8: 4 tokens 4.2 / 4.7, 128 8.7
+// / 10.6).  From there on so many rows of bf16 are in flight that memory is faster with fewer: an entry is looked up and its row requested
+// when the row before it is there.  That takes enough waves, 4500 or, one to a token, 3000 (11-20 MiB: 3720 x 6 x 864 B, 3720 waves, 11.4 /
+// 10.6; 2523 x 8 x 880 B, 2523, 9.8 / 11.1; 2430 x 3 x 1648 B, 4860 waves, 10.0 / 8.9; 3061 x 4 x 1296 B, 6122, 11.2 / 9.9; 4096 x 2 x 2
+// KiB to fp32, 8192, 16.9 / 15.7; 443 x 4 x 7696 B, 3544, 8.7 / 9.6) or 20 MiB (700 x 8 x 6704 B, 4900, 24.1 / 17.7; 300 x 8 x 14 KiB 21.0
+// / 15.9); with 16384 waves they are in each other's way whatever they do, and at once is faster again (8192 x 8 x 1264 B, 16384, 34.8 /
+// 39.7; 8531 x 5 x 1920 B, 17062, 28.7 / 32.3), as it is where a token leaves a single partial row (one device, 3403 x 5 x 736 B 6.6 / 7.9,
+// 3590 x 5 x 2256 B 13.6 / 14.9).  fp32 rows, half the elements, are faster at once than in turn (4443 x 3 x 5184 B, 66 MiB, 22.7 / 26.7),
+// but with fewer than 7000 waves of 20 to 64 MiB still faster one by one (at once / one by one / in turn: 383 x 7 x 11 KiB 13.7 / 11.4 /
+// 14.9, 572 x 8 x 7328 B 13.1 / 11.6 / 14.6, 227 x 8 x 27.7 KiB 18.4 / 16.5 / 18.2).
+// Up to 48 MiB rows are cut into segments of up to 256 threads (4 tokens 5.5 / 6.6 with whole rows, 300 16.1 / 17.6, 500 24.6 / 24.3), but
+// not rows of little more than one (277 chunks: 1040 x 7 x 4432 B 19.6 in segments of 256 and 21 chunks, 15.9 whole).
+// Inputs of 96 MiB and more are bound by memory.  Where a token's rows leave at least two partial rows, a compute unit gets about 16 waves,
+// 12 for six and more bf16 rows (two_hop_workgroups), which keep enough in flight by requesting their rows at once; dynamic LDS that the
+// kernel does not use keeps further workgroups out.  us, no cap / capped: 8910 x 4 x 7024 B on 8 devices (2 workgroups of 7 waves) 160 /
+// 147, 12000 x 4 x 9 KiB on 4 (2 of 9; 1: 232) 227 / 214, 12679 x 4 x 9.8 KiB on 2 (2 of 10; 1: 230) 217 / 210, 3242 x 8 x 6032 B on 8 (2 of 6) 90 / 83, 7116 x 4 x 10 KiB on 16 (1 of 11) 210 / 196, 4096 x 8 x 14 KiB on 8 (1 of
+// 14) 228 / 224, fp32 8152 x 5 x 5792 B on 16 112 / 106.  Not on one device (6309 x 8 x 7264 B 96 / 105, 4240 x 6 x 10.7 KiB 70 / 78) nor
+// for three rows on few devices or in fp32 (108219 x 3 x 1104 B on 2 211 / 238, 33482 x 3 x 3200 B of fp32 on 4 120 / 128; bf16 on 8, 26723
+// x 3 x 4000 B, 211 / 200).  One or two narrow rows are taken in turn here too (53067 x 1 x 4 KiB 247 / 236, 128196 x 2 x 1536 B 257 / 250;
+// wider ones at once, 40696 x 2 x 4208 B 172 / 175).
+constexpr int kTwoHopWholeChunks = 352;
+constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20, kTwoHopInTurnBytes = (size_t)11 << 20, kTwoHopBusyBytes = (size_t)20 << 20;
+constexpr size_t kTwoHopCappedBytes = (size_t)96 << 20;
+constexpr int64_t kTwoHopSomeWaves = 4500, kTwoHopManyWaves = 16384, kTwoHopFewWavesF32 = 7000;
+constexpr int kTwoHopSomeTokens = 3000;
+constexpr int kTwoHopNarrowChunks = 256;
 
-template <bool Y_BF16, bool OUT_BF16, bool ONE_BY_ONE>
+template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS>
 void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
 {
     const hipEvent_t none = nullptr;
     switch (stores) {
-    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
-    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
-    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
-    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ONE_BY_ONE>, grid, block, lds, s, none, none, a); break;
+    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ROWS>, grid, block, lds, s, none, none, a); break;
+    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ROWS>, grid, block, lds, s, none, none, a); break;
+    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ROWS>, grid, block, lds, s, none, none, a); break;
+    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ROWS>, grid, block, lds, s, none, none, a); break;
     }
 }
 
+// Workgroups of `waves` waves per compute unit where their number is capped: up to 16 waves, but at least two workgroups of up to 10 waves; up to
+// 12 for six and more bf16 rows, and a single workgroup from 7 waves on (one / two of 7: 8192 x 8 x 7 KiB on 8 devices 232 / 224 us, but 4096 x 8
+// x 7 KiB 115 / 118 and 7404 x 8 x 7152 B on 16 259 / 267; of 8: 8192 x 8 x 8 KiB on 16 281 / 290).
+inline int two_hop_workgroups(int waves, bool y_bf16, int k)
+{
+    if (y_bf16 && k >= 6) return std::max(12 / waves, 1);
+    return std::max(16 / waves, waves <= 10 ? 2 : 1);
+}
+
 template <bool Y_BF16, bool OUT_BF16>
-void launch_two_hop(const TwoHopArgs &a, int N, OutStores stores, hipStream_t s)
+void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
 {
     const size_t bytes = (size_t)N * (size_t)a.k * (size_t)a.C * 16;
-    const int threads = std::min(bytes < kTwoHopSmallBytes ? 256 : 1024, round_up(a.C, kWave));
-    const dim3 grid((unsigned)N, (unsigned)((a.C + threads - 1) / threads)), block((unsigned)threads);
-    size_t lds = 0;
-    if (bytes >= kTwoHopCappedBytes && a.k >= 3) {
-        const int wgs = std::max(1, (Y_BF16 && a.k >= 6 ? 12 : 16) / (threads / kWave));
-        lds = wgs == 1 ? kOverHalfLds : lds_for_occupancy(wgs);
+    const int64_t waves = (int64_t)N * ((a.C + kWave - 1) / kWave);
+    const int segs = bytes >= kTwoHopSmallBytes ? (a.C + 1023) / 1024 : a.C <= kTwoHopWholeChunks ? 1 : (a.C + 255) / 256;
+    const int threads = round_up((a.C + segs - 1) / segs, kWave);
+    const dim3 grid((unsigned)N, (unsigned)segs), block((unsigned)threads);
+    if constexpr (Y_BF16) {
+        const bool in_turn = bytes >= kTwoHopCappedBytes ? a.k <= 2 && a.C <= kTwoHopNarrowChunks
+                                                         : D >= 2 && bytes >= kTwoHopInTurnBytes && waves < kTwoHopManyWaves &&
+                                                               (waves >= kTwoHopSomeWaves || N >= kTwoHopSomeTokens || bytes >= kTwoHopBusyBytes);
+        if (in_turn) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsInTurn>(a, grid, block, 0, stores, s);
+    } else {
+        if (bytes >= kTwoHopBusyBytes && bytes < kCombineLatencyBoundBytes && waves < kTwoHopFewWavesF32)
+            return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, s);
     }
-    if (bytes >= kTwoHopAtOnceBytes && bytes < kTwoHopCappedBytes) launch_two_hop_as<Y_BF16, OUT_BF16, true>(a, grid, block, lds, stores, s);
-    else launch_two_hop_as<Y_BF16, OUT_BF16, false>(a, grid, block, lds, stores, s);
+    size_t lds = 0;
+    if (bytes >= kTwoHopCappedBytes && D >= 2 && (a.k >= 4 || (Y_BF16 && a.k == 3 && D >= 4))) {
+        const int wgs = two_hop_workgroups(threads / kWave, Y_BF16, a.k);
+        lds = wgs == 1 ? kOverHalfLds : (size_t)(128 / wgs) * 1280;
+    }
+    launch_two_hop_as<Y_BF16, OUT_BF16, kRowsAtOnce>(a, grid, block, lds, stores, s);
 }
 
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked

@@ -706,8 +706,11 @@ struct TwoHopArgs {
     int32_t C;   // 16-byte chunks per y row
 };
 
-// ONE_BY_ONE: a row is requested when the one before has arrived, otherwise all of them at once (launch_two_hop).
-template <bool Y_BF16, bool OUT_BF16, OutStores STORES, bool ONE_BY_ONE>
+// How a token's rows are requested (launch_two_hop): all at once; each when the one before has arrived; or in turn, an entry being looked up only when
+// the row before it has arrived.
+enum TwoHopRows : int32_t { kRowsAtOnce, kRowsOneByOne, kRowsInTurn };
+
+template <bool Y_BF16, bool OUT_BF16, OutStores STORES, TwoHopRows ROWS>
 __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
 {
     constexpr int EPC = Y_BF16 ? 8 : 4;
@@ -715,37 +718,58 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
     const int t = gridDim.x - 1 - blockIdx.x;
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
     const bool in = c < a.C;   // lanes past the row take part in the exchange of put_floats
-    // entry j's slot, send row and weight in lane j; the entries with a slot are taken in ascending order
-    const int lane = threadIdx.x & (kWave - 1);
-    int my_slot = -1, my_row = -1;
-    float my_w = 0.0f;
-    bool my_first = false;
-    if (lane < a.k) {
-        const size_t p = (size_t)t * a.k + lane;
-        my_slot = a.pair_slot[p];
-        my_row = a.pair_send_row[p];
-        my_w = a.w[p];
-        my_first = a.pair_first[p];
-    }
-    uint64_t left = __builtin_amdgcn_ballot_w64(my_slot >= 0);
-    const uint64_t firsts = __builtin_amdgcn_ballot_w64(my_first);
-    const int n = __builtin_popcountll(left);
-
     u32x4 v[KMAX];
     int row[KMAX];
     float wj[KMAX];
-    bool lead[KMAX];
+    bool on[KMAX], lead[KMAX];
+    int n;   // entries held in v; absent ones among them are not on
+    if constexpr (ROWS == kRowsInTurn) {
+        const int32_t *slots = a.pair_slot + (size_t)t * a.k, *rows = a.pair_send_row + (size_t)t * a.k;
+        const uint8_t *first = a.pair_first + (size_t)t * a.k;
+        const float *wt = a.w + (size_t)t * a.k;
+        n = KMAX;
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        if (j >= n) break;   // uniform
-        const int at = __builtin_ctzll(left);
-        left &= left - 1;
-        row[j] = __builtin_amdgcn_readlane(my_row, at);
-        wj[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), at));
-        lead[j] = firsts >> at & 1;
-        const u32x4 *src = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, at) * a.C;
-        v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
-        if constexpr (ONE_BY_ONE) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        for (int j = 0; j < KMAX; ++j) {
+            on[j] = lead[j] = false;
+            row[j] = -1;
+            if (j >= a.k) continue;   // uniform
+            const int slot = slots[j];
+            row[j] = rows[j];
+            wj[j] = wt[j];
+            lead[j] = first[j];   // a byte: a vector load, behind the request before it and waited for ahead of the next
+            if (slot < 0) continue;
+            on[j] = true;
+            if (in) v[j] = load16_stream(a.y + (size_t)slot * a.C + c);
+        }
+    } else {
+        // entry j's slot, send row and weight in lane j; the entries with a slot are taken in ascending order
+        const int lane = threadIdx.x & (kWave - 1);
+        int my_slot = -1, my_row = -1;
+        float my_w = 0.0f;
+        bool my_first = false;
+        if (lane < a.k) {
+            const size_t p = (size_t)t * a.k + lane;
+            my_slot = a.pair_slot[p];
+            my_row = a.pair_send_row[p];
+            my_w = a.w[p];
+            my_first = a.pair_first[p];
+        }
+        uint64_t left = __builtin_amdgcn_ballot_w64(my_slot >= 0);
+        const uint64_t firsts = __builtin_amdgcn_ballot_w64(my_first);
+        n = __builtin_popcountll(left);
+#pragma unroll
+        for (int j = 0; j < KMAX; ++j) {
+            if (j >= n) break;   // uniform
+            const int at = __builtin_ctzll(left);
+            left &= left - 1;
+            on[j] = true;
+            row[j] = __builtin_amdgcn_readlane(my_row, at);
+            wj[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), at));
+            lead[j] = firsts >> at & 1;
+            const u32x4 *src = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, at) * a.C;
+            v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
+            if constexpr (ROWS == kRowsOneByOne) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        }
     }
     float total[EPC];
 #pragma unroll
@@ -760,7 +784,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
 #pragma unroll
         for (int j = f; j < KMAX; ++j) {
             if (j >= n) break;
-            if (row[j] != row[f]) continue;
+            if (!on[j] || row[j] != row[f]) continue;
             add_row<Y_BF16>(acc, v[j], wj[j]);
         }
         // plain stores: 4096 tokens x 8 rows of 14 KiB, 21700 partial rows 224 us, written through 247, non-temporal 296 us

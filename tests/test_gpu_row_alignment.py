@@ -116,7 +116,7 @@ def test_combine_of_small_inputs_in_column_segments(N, k, C, two_hop, y_f32, out
 # 128 MiB of input and output are the most that leave the output in the memory-side cache (1820 tokens with rows of 8 KiB,
 # 1816 with rows of 8208 B, which are not whole 64-byte units)
 @pytest.mark.parametrize("N,H", [(1820, 4096), (1821, 4096), (1816, 4104), (1817, 4104), (4097, 4096),
-                                 (1023, 7168), (1024, 7168)])   # two-hop: two workgroups on a compute unit, and one
+                                 (1023, 7168), (1024, 7168)])
 @pytest.mark.parametrize("two_hop", [False, True])
 def test_combine_output_around_the_size_that_goes_past_the_cache(N, H, two_hop):
     import paper_2512_22036_amd as f
@@ -316,3 +316,40 @@ def test_combine_with_entries_left_over(k, y_f32, mib):
         want += torch.where((rows >= 0)[:, None], y[rows.clamp_min(0)].float(), 0.0)
     assert torch.equal(out, want / 2)
     assert bool((room[out.numel() * 4:] == 0xEE).all())
+
+
+# two-hop combine around its limits: 11, 20, 48, 64 and 96 MiB of input, 3000 tokens, 4500, 7000 and 16384 waves, rows of 352 chunks; capped workgroups of 1 to 16 waves,
+# one and two devices; fp32 rows beside them
+@pytest.mark.parametrize("N,k,C,D", [(2250, 4, 80, 4), (2249, 4, 84, 4), (2250, 4, 75, 4), (1000, 4, 327, 4), (1000, 4, 328, 4), (500, 7, 352, 8), (500, 7, 353, 8),
+                                     (400, 5, 640, 8), (900, 8, 436, 8), (900, 8, 437, 8), (8191, 6, 79, 4), (8192, 6, 79, 4), (8192, 3, 250, 8), (8195, 3, 256, 8),
+                                     (50000, 2, 64, 4), (13000, 2, 256, 4), (13000, 2, 257, 4), (50000, 1, 128, 8), (25000, 4, 64, 1), (25000, 4, 63, 2), (12600, 8, 65, 8),
+                                     (4000, 4, 400, 8), (2600, 6, 410, 8), (3200, 4, 520, 4), (2000, 8, 576, 8), (2700, 4, 600, 2), (2000, 5, 670, 2), (1800, 3, 1200, 8),
+                                     (9000, 3, 256, 3), (9000, 3, 256, 4), (800, 8, 1040, 8), (2999, 6, 50, 8), (3000, 6, 50, 8),
+                                     (1749, 6, 256, 8), (1750, 6, 256, 8), (500, 8, 1000, 8), (550, 8, 1000, 8)])
+@pytest.mark.parametrize("y_f32,out_f32", [(False, False), (False, True), (True, True)])
+def test_two_hop_around_its_limits(N, k, C, D, y_f32, out_f32):
+    import paper_2512_22036_amd as f
+    E, H = 24, C * (4 if y_f32 else 8)
+    rng = np.random.default_rng(N + C)
+    A = random_topk(rng, N, k, E).astype(np.int32)
+    A[1::5, 0] = -1                       # an entry without a row
+    L = f.Layout(N, k, E, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    y = torch.randint(-15, 16, (L.P, H), device="cuda").to(torch.float32 if y_f32 else torch.bfloat16)
+    w = torch.full((N, k), 0.5, device="cuda")        # whole numbers and a power of two: every sum is exact
+    kind = torch.float32 if out_f32 else torch.bfloat16
+    out, room = rows_at(N, H * (4 if out_f32 else 2), 0)
+    out = out.view(kind)
+    partial = torch.full((L.send_cap, H), -1.0, device="cuda")
+    f.fusco_combine_two_hop(L, y, w, partial, out)
+    slots, sends = L.array("pair_slot").view(N, k).long(), L.array("pair_send_row").view(N, k).long()
+    want, want_partial = torch.zeros((N, H), device="cuda"), torch.zeros((L.send_cap, H), device="cuda")
+    for rows, send in zip(slots.t(), sends.t()):
+        here = rows >= 0
+        term = y[rows[here]].float() / 2
+        want[here] += term
+        want_partial[send[here]] += term   # a token has one row per device: no index twice
+    assert torch.equal(out, want.to(kind))
+    U = int(L.array("send_off")[D].item())
+    assert torch.equal(partial[:U], want_partial[:U]) and bool((partial[U:] == -1).all())
+    assert bool((room[out.numel() * out.element_size():] == 0xEE).all())
