@@ -508,7 +508,8 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const bool stream_stores = streaming || (!two_hop && written > kCacheBytes);   // the second hop reads the rows at once
         const bool cached_loads = stream_stores && (size_t)L->N * row <= g_source_chunk_bytes.load(std::memory_order_relaxed);
         const int knob = g_walk_mode.load(std::memory_order_relaxed);
-        const bool eager = (uint64_t)L->N * (uint64_t)segs <= kWalkEagerGroups || !a.write_expert;
+        const uint64_t groups = (uint64_t)L->N * (uint64_t)segs;
+        const bool eager = groups <= kWalkEagerGroups || (!a.write_expert && eager_send_rows(groups, L->N, L->k, L->D, Ct));
         const int mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0);
 #define FUSCO_WALK_AS(CPT, MODE)                                                                       \
     do {                                                                                              \

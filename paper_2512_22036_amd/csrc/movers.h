@@ -138,14 +138,36 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
     }
 }
 
-// The token walk of few workgroups: the token's slots (and send rows) come into the lanes of a wave with one load, and its rows
-// are stored without a wait between them.  In dispatch_kernel a slot is looked up when its row is stored, and that load waits
-// for the stores before it (loads and stores share a counter): every workgroup has one row on its way at a time.  With few
-// workgroups the waits are what the call takes (with them / here, us: 300 tokens x 8 x 14 KiB 9.3 / 7.7, 500 11.7 / 10.1, 400 x 8
-// x 4.1 KiB in two planes 5.3 / 4.2, 700 x 8 x 2 KiB 5.1 / 3.8); where there are many, memory is faster with fewer rows being
-// written at a time (8192 x 8 x 2 KiB 29.2 / 30.4, 4000 x 4 x 4.1 KiB in two planes 14.3 / 15.7, 32768 x 4 x 7 KiB 229 / 232).
-// Send rows alone, which are fewer than the pairs, always go this way (21700 rows of 14 KiB 62.2 / 59.5).
+// The token walk of few workgroups: the token's slots (and send rows) come into the lanes of a wave with one load, and its rows are stored
+// without a wait between them.  In dispatch_kernel a slot is looked up when its row is stored, and that load waits for the stores before it
+// (loads and stores share a counter): every workgroup has one row on its way at a time.  With few workgroups the waits are what the call
+// takes (with them / here, us: 300 tokens x 8 x 14 KiB 9.3 / 7.7, 500 11.7 / 10.1, 400 x 8 x 4.1 KiB in two planes 5.3 / 4.2, 700 x 8 x 2
+// KiB 5.1 / 3.8); where there are many, memory is faster with fewer rows being written at a time (8192 x 8 x 2 KiB 29.2 / 30.4, 4000 x 4 x
+// 4.1 KiB in two planes 14.3 / 15.7, 32768 x 4 x 7 KiB 229 / 232).  Between 1024 and 4000 workgroups short rows are still faster this way
+// and long ones are not (2443 x 8 x 496 B 7.9 / 5.5, 2181 x 10 x 1504 B 7.5 / 6.8, 1058 x 4 x 1568 B 3.3 / 2.9, but 3244 x 8 x 3 KiB 13.7 /
+// 14.8, 1838 x 8 x 8.4 KiB 30.5 / 31.6, 1487 x 6 x 12.5 KiB 26.5 / 28.6): the line is where none is slower.
 constexpr uint64_t kWalkEagerGroups = 1024;
+
+// The same for send rows alone, by workgroups (a row may take several), tokens, entries, devices and 16-byte chunks of a row; with the
+// waits / without, us.  Without them are faster:
+// - up to 1200 workgroups (1120 tokens x 6 x 4176 B on 4 devices 5.8 / 5.3; 1417 x 8 x 10.5 KiB on 16 23.5 / 26.1);
+// - rows of up to 1.5 KiB, where the look-ups count (24723 x 8 x 432 B on 8 25.4 / 19.2, 22730 x 8 x 1296 B on 16 81.8 / 66.9, 6294 x 8 x 1424 B
+//   on 4 11.8 / 10.1; 15757 x 16 x 832 B on 8 22.1 / 23.2), of up to 2 KiB from 6000 tokens on (53347 x 8 x 1696 B on 16, two hops, 540 / 490,
+//   8983 x 10 x 2016 B on 4 19.3 / 15.1, 29171 x 10 x 1568 B on 8 71.4 / 73.2; 3729 x 8 x 1760 B on 16 10.0 / 11.4);
+// - few rows of many entries (27147 x 6 x 1488 B on two 30.0 / 21.3, 1108 x 8 x 3824 B on two 4.2 / 3.6), longer ones from 3000 workgroups on
+//   (2748 x 10 x 19 KiB on one, 5496 workgroups, 23.7 / 19.5, 3344 x 16 x 8 KiB on two 16.6 / 15.3; 2100 x 8 x 10 KiB on one 9.5 / 10.0);
+// - rows of 12 to 16 KiB of 4000 tokens and more (4400 x 8 x 13.7 KiB on 16 110 / 104, 10356 x 8 x 12.9 KiB on 8 198 / 189);
+// - of tokens with one entry those of 4800 B and more (9367 x 4896 B 17.7 / 16.4; 7476 x 2864 B 10.0 / 10.5, 6931 x 704 B 4.2 / 4.5).
+// The others are faster with them (13477 x 8 x 3 KiB on 8 58.7 / 61.9, 2191 x 8 x 6 KiB on 8 14.0 / 15.6, 1787 x 2 x 10.3 KiB on one 8.2 / 9.4,
+// 1350 x 8 x 8.5 KiB on two 8.5 / 9.0, 27369 x 2 x 19 KiB on 8 300 / 309).
+inline bool eager_send_rows(uint64_t groups, int N, int k, int D, int chunks)
+{
+    if (groups <= 1200) return true;
+    if (k == 1) return chunks >= 300;
+    if (chunks <= 96 || (chunks <= 128 && N >= 6000)) return true;
+    if (k >= 3 * D && (chunks <= 256 || groups >= 3000)) return true;
+    return chunks >= 768 && chunks <= 1024 && N >= 4000;
+}
 
 template <int CPT, int MODE>
 __global__ __launch_bounds__(256) void dispatch_eager_kernel(DispatchArgs a)
@@ -706,8 +728,8 @@ struct TwoHopArgs {
     int32_t C;   // 16-byte chunks per y row
 };
 
-// How a token's rows are requested (launch_two_hop): all at once; each when the one before has arrived; or in turn, an entry being looked up only when
-// the row before it has arrived.
+// How a token's rows are requested (launch_two_hop): all at once; each when the one before has arrived; or in turn, an entry being looked
+// up only when the row before it has arrived.
 enum TwoHopRows : int32_t { kRowsAtOnce, kRowsOneByOne, kRowsInTurn };
 
 template <bool Y_BF16, bool OUT_BF16, OutStores STORES, TwoHopRows ROWS>

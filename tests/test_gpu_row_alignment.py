@@ -229,10 +229,13 @@ def test_both_tensors_tile_by_tile_over_random_shapes():
     assert moved >= 35 and len(seen) >= 6 and any(s[0] for s in seen) and any(s[1] for s in seen)
 
 
-# the token walk of few workgroups (up to 1024 of a row's column segments) and the one of many, both ends of the rule; send rows alone always
-# take the former; every pairing of loads and stores
+# the token walk of few workgroups (up to 1024 of a row's column segments) and the one of many, both ends of the rule; send rows alone go by
+# their size and number (8 devices); every pairing of loads and stores
 @pytest.mark.parametrize("N,k,row_bytes,aux_bytes", [(1, 1, 16, 0), (7, 64, 48, 16), (300, 8, 4112, 0), (1024, 3, 1040, 224), (1025, 3, 1040, 224),
-                                                     (512, 4, 16384 + 16, 0), (513, 4, 16384 + 16, 0), (30, 6, 40000, 32), (90, 8, 16368, 48)])
+                                                     (512, 4, 16384 + 16, 0), (513, 4, 16384 + 16, 0), (30, 6, 40000, 32), (90, 8, 16368, 48),
+                                                     (1200, 2, 2064, 0), (1201, 2, 1520, 16), (1201, 2, 1520, 32), (1201, 1, 4784, 0), (1201, 1, 4784, 16),
+                                                     (1300, 23, 4096, 0), (1300, 24, 4096, 0), (1300, 24, 4112, 0),
+                                                     (5999, 2, 2032, 16), (6000, 2, 2032, 16), (3999, 2, 12288, 0), (4000, 2, 12288, 0), (4000, 2, 12256, 16)])
 @pytest.mark.parametrize("flags", [1, 2, 3])
 def test_token_walk(N, k, row_bytes, aux_bytes, flags):
     import paper_2512_22036_amd as f
@@ -353,3 +356,20 @@ def test_two_hop_around_its_limits(N, k, C, D, y_f32, out_f32):
     U = int(L.array("send_off")[D].item())
     assert torch.equal(partial[:U], want_partial[:U]) and bool((partial[U:] == -1).all())
     assert bool((room[out.numel() * out.element_size():] == 0xEE).all())
+
+
+# send rows alone on one and two devices: few rows of many entries
+@pytest.mark.parametrize("N,k,D,row_bytes", [(1500, 3, 1, 20000), (1499, 3, 1, 20000), (1500, 2, 1, 20000), (1300, 6, 2, 4096), (1300, 6, 2, 4112), (1300, 5, 2, 4096)])
+def test_token_walk_of_send_rows_on_few_devices(N, k, D, row_bytes):
+    import paper_2512_22036_amd as f
+    rng = np.random.default_rng(N + k)
+    A = random_topk(rng, N, k, 16).astype(np.int32)
+    A[N // 2] = -1
+    L = f.Layout(N, k, 16, D)
+    f.fusco_plan(L, torch.from_numpy(A).cuda())
+    x = torch.randint(0, 256, (N, row_bytes), dtype=torch.uint8, device="cuda")
+    sb, room = rows_at(L.send_cap, row_bytes, 16)
+    f.fusco_dispatch(L, x, send_buf=sb, flags=2)
+    U = int(L.array("send_off")[D])
+    assert torch.equal(sb[:U], x[L.array("send_src")[:U].long()])
+    assert bool((room[16 + U * row_bytes:] == 0xEE).all())
