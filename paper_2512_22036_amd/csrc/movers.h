@@ -313,21 +313,8 @@ __global__ __launch_bounds__(256) void dispatch_tiled_kernel(DispatchArgs a, uin
             else __builtin_nontemporal_store(v[q], dst);
         }
     };
-    // The same workgroups read the descriptors of the XCD's next tile, an entry a lane, and drop them: the first two loads of every
-    // workgroup (slot, then its token) depend on each other and come from the L2 then.  Calls whose descriptors have left the
-    // caches - other tensors moved by a plan made earlier - wait for them in every workgroup otherwise, the longer the fewer workgroups
-    // there are: dispatch alone over changing buffers 8192 x 8 x 14 KiB 216 -> 186 us, 16384 x 8 x 8 KiB 234 -> 208, 9100 x 8 x 14 KiB
-    // 250 -> 218; right after the plan, no difference.  Not for rows of up to 2 KiB (65536 x 8 x 1040 B 177 / 207) nor for a source tensor taken in
-    // chunks (32768 x 8 x 14 KiB 733 / 766), nor with the receive tensors (4096 x 8 x 14 KiB, step 378 / 383).
-    int next_token = 0;
-    if (PULL && CPT > 1 && !WIRE && pass == 0 && r < (uint32_t)a.tile_tokens && local + kXcds < tiles_here && (int)threadIdx.x < a.k) {
-        const uint32_t e = r * (uint32_t)a.k + threadIdx.x;
-        const int next_row = e < pairs ? a.tile_slots[(size_t)(tile + kXcds) * a.tile_cap + e] : -1;
-        if (next_row >= 0) next_token = a.slot_token[next_row];
-    }
     if (WIRE && pull) load(p, tp, segment(tp), false);
     if (row >= 0) store();
-    asm volatile("" ::"v"(next_token));
     if (!pull) return;
 #pragma unroll
     for (int q = 0; q < CPT; ++q) asm volatile("" ::"v"(p[q]));   // the value is not used: only the read matters
