@@ -225,16 +225,13 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     const ArmedEvents ev;
     const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)segs), block(kSmallThreads);
     const int cpt = (seg_chunks + kSmallThreads - 1) / kSmallThreads;
-    if (cpt > 2 && L->N > kFusedLongTokens) {
-        DispatchArgs d = {};
-        d.x = x; d.x_aux = x_aux;
-        d.expert_buf = m.expert_buf; d.expert_aux = m.expert_aux;
-        d.C = C; d.Ca = Ca; d.seg_chunks = seg_chunks;
-        launch_args(plan_dispatch_long_kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a, d);
-        return launch_status();
-    }
-    const auto kernel = Ca ? (cpt <= 1 ? plan_dispatch_kernel<1, true> : cpt <= 2 ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<4, true>)
-                           : (cpt <= 1 ? plan_dispatch_kernel<1, false> : cpt <= 2 ? plan_dispatch_kernel<2, false> : plan_dispatch_kernel<4, false>);
+    const unsigned groups = grid.x * grid.y;
+    const bool four = groups > kFusedThree && groups <= kFusedFour;
+    const auto kernel = cpt <= 1   ? (four ? (Ca ? plan_dispatch_four_kernel<1, true> : plan_dispatch_four_kernel<1, false>)
+                                           : (Ca ? plan_dispatch_kernel<1, true> : plan_dispatch_kernel<1, false>))
+                        : cpt <= 2 ? (four ? (Ca ? plan_dispatch_four_kernel<2, true> : plan_dispatch_four_kernel<2, false>)
+                                           : (Ca ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<2, false>))
+                                   : (Ca ? plan_dispatch_four_kernel<4, true> : plan_dispatch_four_kernel<4, false>);
     launch_args(kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a.A, x, x_aux, a.N, a.k, a.k_magic, a.small_groups, C, Ca, seg_chunks,
                 m, a);
     return launch_status();

@@ -265,15 +265,15 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 // but with fewer than 7000 waves of 20 to 64 MiB still faster one by one (at once / one by one / in turn: 383 x 7 x 11 KiB 13.7 / 11.4 /
 // 14.9, 572 x 8 x 7328 B 13.1 / 11.6 / 14.6, 227 x 8 x 27.7 KiB 18.4 / 16.5 / 18.2).
 // Up to 48 MiB rows are cut into segments of up to 256 threads (4 tokens 5.5 / 6.6 with whole rows, 300 16.1 / 17.6, 500 24.6 / 24.3), but
-// not rows of little more than one (277 chunks: 1040 x 7 x 4432 B 19.6 in segments of 256 and 21 chunks, 15.9 whole).
-// Inputs of 96 MiB and more are bound by memory.  Where a token's rows leave at least two partial rows, a compute unit gets about 16 waves,
-// 12 for six and more bf16 rows (two_hop_workgroups), which keep enough in flight by requesting their rows at once; dynamic LDS that the
-// kernel does not use keeps further workgroups out.  us, no cap / capped: 8910 x 4 x 7024 B on 8 devices (2 workgroups of 7 waves) 160 /
-// 147, 12000 x 4 x 9 KiB on 4 (2 of 9; 1: 232) 227 / 214, 12679 x 4 x 9.8 KiB on 2 (2 of 10; 1: 230) 217 / 210, 3242 x 8 x 6032 B on 8 (2 of 6) 90 / 83, 7116 x 4 x 10 KiB on 16 (1 of 11) 210 / 196, 4096 x 8 x 14 KiB on 8 (1 of
-// 14) 228 / 224, fp32 8152 x 5 x 5792 B on 16 112 / 106.  Not on one device (6309 x 8 x 7264 B 96 / 105, 4240 x 6 x 10.7 KiB 70 / 78) nor
-// for three rows on few devices or in fp32 (108219 x 3 x 1104 B on 2 211 / 238, 33482 x 3 x 3200 B of fp32 on 4 120 / 128; bf16 on 8, 26723
-// x 3 x 4000 B, 211 / 200).  One or two narrow rows are taken in turn here too (53067 x 1 x 4 KiB 247 / 236, 128196 x 2 x 1536 B 257 / 250;
-// wider ones at once, 40696 x 2 x 4208 B 172 / 175).
+// not rows of little more than one (277 chunks: 1040 x 7 x 4432 B 19.6 in segments of 256 and 21 chunks, 15.9 whole). Inputs of 96 MiB and
+// more are bound by memory.  Where a token's rows leave at least two partial rows, a compute unit gets about 16 waves, 12 for six and more
+// bf16 rows (two_hop_workgroups), which keep enough in flight by requesting their rows at once; dynamic LDS that the kernel does not use
+// keeps further workgroups out.  us, no cap / capped: 8910 x 4 x 7024 B on 8 devices (2 workgroups of 7 waves) 160 / 147, 12000 x 4 x 9 KiB
+// on 4 (2 of 9; 1: 232) 227 / 214, 12679 x 4 x 9.8 KiB on 2 (2 of 10; 1: 230) 217 / 210, 3242 x 8 x 6032 B on 8 (2 of 6) 90 / 83, 7116 x 4
+// x 10 KiB on 16 (1 of 11) 210 / 196, 4096 x 8 x 14 KiB on 8 (1 of 14) 228 / 224, fp32 8152 x 5 x 5792 B on 16 112 / 106.  Not on one
+// device (6309 x 8 x 7264 B 96 / 105, 4240 x 6 x 10.7 KiB 70 / 78) nor for three rows on few devices or in fp32 (108219 x 3 x 1104 B on 2
+// 211 / 238, 33482 x 3 x 3200 B of fp32 on 4 120 / 128; bf16 on 8, 26723 x 3 x 4000 B, 211 / 200).  One or two narrow rows are taken in
+// turn here too (53067 x 1 x 4 KiB 247 / 236, 128196 x 2 x 1536 B 257 / 250; wider ones at once, 40696 x 2 x 4208 B 172 / 175).
 constexpr int kTwoHopWholeChunks = 352;
 constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20, kTwoHopInTurnBytes = (size_t)11 << 20, kTwoHopBusyBytes = (size_t)20 << 20;
 constexpr size_t kTwoHopCappedBytes = (size_t)96 << 20;

@@ -357,12 +357,17 @@ struct FusedRows {
     u32x4 *expert_buf, *expert_aux;
 };
 
+// plan_dispatch_four_kernel: 80 scalar registers at most.  With more a SIMD holds seven of its eight waves, and a compute unit three
+// workgroups instead of four.  Calls of a little more than 3 x 256 workgroups then take a second round of them (us, three / four: 682
+// tokens x 3 x 16 KiB, 939 workgroups, 12.4 / 9.9; 800 x 2 x 12 KiB, 1001, 9.9 / 8.3; with CPT 4 682 x 3 x 20 KiB 14.5 / 11.3, 300 x 6 x 40
+// KiB 18.0 / 16.2, 2048 x 1 x 32 KiB 27.2 / 24.9).  The registers are missed by calls of few tokens with many entries (3 x 33 x 1 KiB 6.3 /
+// 6.6), and of more than 1024 workgroups memory is faster with fewer of them writing (1024 x 2 x 16 KiB, 1281 workgroups, 12.0 / 14.4).
+constexpr int kFusedThree = 3 * 256, kFusedFour = 4 * 256;   // workgroups that are resident at once
+
 template <int CPT, bool AUX>
-__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k,
-                                                                     uint32_t k_magic, int32_t small_groups, int32_t C, int32_t Ca,
-                                                                     int32_t seg_chunks, FusedRows m, PlanArgs a)
+__device__ __forceinline__ void plan_dispatch(SmallLds &s, const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k, uint32_t k_magic,
+                                              int32_t small_groups, int32_t C, int32_t Ca, int32_t seg_chunks, FusedRows m, PlanArgs a)
 {
-    __shared__ SmallLds s;
     a.A = A;
     a.N = N;
     a.k = k;
@@ -400,45 +405,18 @@ __global__ __launch_bounds__(kSmallThreads) void plan_dispatch_kernel(const int3
     }
 }
 
-// The same for many tokens of rows of more than 16 KiB, which are bound by their writes: with members of structures read as they
-// are used and a branch per plane the rows are stored more slowly, which memory likes better (341 tokens x 6 x 40 KiB 18.1 us, 19.5 by
-// plan_dispatch_kernel<4, false>; 2048 x 1 x 32 KiB 25.6 / 27.2; 4 tokens x 8 x 128 KiB 6.5 / 5.9).
-constexpr int kFusedLongTokens = 64;   // more than these
-
-__global__ __launch_bounds__(kSmallThreads) void plan_dispatch_long_kernel(PlanArgs a, DispatchArgs m)
-{
-    __shared__ SmallLds s;
-    const int b = blockIdx.x, seg = blockIdx.y;
-    if (b <= a.small_groups) {
-        if (seg != 0) return;
-        const int p0 = (b - 1) * kSmallPairs;
-        if (b == 0) small_counts(s, a);
-        else small_place(s, a, p0, min(kSmallPairs, a.N * a.k - p0));
-        return;
+#define FUSCO_PLAN_DISPATCH(NAME, ATTRIBUTE)                                                                                                          \
+    template <int CPT, bool AUX>                                                                                                                      \
+    __global__ __launch_bounds__(kSmallThreads) ATTRIBUTE void NAME(const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k,       \
+                                                                    uint32_t k_magic, int32_t small_groups, int32_t C, int32_t Ca, int32_t seg_chunks, \
+                                                                    FusedRows m, PlanArgs a)                                                          \
+    {                                                                                                                                                 \
+        __shared__ SmallLds s;                                                                                                                        \
+        plan_dispatch<CPT, AUX>(s, A, x, x_aux, N, k, k_magic, small_groups, C, Ca, seg_chunks, m, a);                                                \
     }
-    const int tid = threadIdx.x;
-    const int t = b - 1 - a.small_groups;
-    const int c0 = seg * m.seg_chunks + tid, c_end = min(m.C + m.Ca, (seg + 1) * m.seg_chunks);
-    // source and destination of a chunk by address selection: c counts on from the main row's chunks into the aux row's
-    const u32x4 *src = m.x + (size_t)t * m.C, *src_aux = m.x_aux + (size_t)t * m.Ca - m.C;
-    u32x4 v[kFusedChunks];
-#pragma unroll
-    for (int i = 0; i < kFusedChunks; ++i) {
-        const int c = c0 + i * kSmallThreads;
-        if (c < c_end) v[i] = load16_stream((c < m.C ? src : src_aux) + c);
-    }
-    const int slots = small_slots(s, a, t * a.k, a.k);
-    for (int j = 0; j < a.k; ++j) {
-        const int slot = __builtin_amdgcn_readlane(slots, j);
-        if (slot < 0) continue;
-        u32x4 *dst = m.expert_buf + (size_t)slot * m.C, *dst_aux = m.expert_aux + (size_t)slot * m.Ca - m.C;
-#pragma unroll
-        for (int i = 0; i < kFusedChunks; ++i) {
-            const int c = c0 + i * kSmallThreads;
-            if (c < c_end) (c < m.C ? dst : dst_aux)[c] = v[i];
-        }
-    }
-}
+FUSCO_PLAN_DISPATCH(plan_dispatch_kernel, )
+FUSCO_PLAN_DISPATCH(plan_dispatch_four_kernel, __attribute__((amdgpu_num_sgpr(80))))
+#undef FUSCO_PLAN_DISPATCH
 
 // Stores of combine's output rows (out_stores chooses).  A template argument of the kernels: with a choice between the four
 // at every store the two-hop combine of 4 tokens x 8 rows of 14 KiB took 7.4 us instead of 6.1, of 256 tokens of 5.6 KiB 12.2

@@ -160,6 +160,31 @@ def test_single_launch_with_long_rows(N, k, E, D, row_bytes, aux_bytes):
             assert bool((planes[dst][len(token):] == 0xEE).all())
 
 
+@pytest.mark.parametrize("row_bytes,aux_bytes", [(2048, 0), (8192, 0), (8192, 16), (16384, 0), (16384, 64)])
+@pytest.mark.parametrize("N", [613, 614, 818, 819])
+def test_single_launch_by_resident_workgroups(N, row_bytes, aux_bytes):
+    """768, 769, 1024 and 1025 workgroups of the fused call (the chip holds three or four on a compute unit), with one, two
+    and four chunks per thread, a second plane."""
+    import paper_2512_22036_amd as f
+    k, E, D = 2, 64, 8
+    assert 1 + -(-N * k // 8) + N in (768, 769, 1024, 1025)
+    A = routing(N + row_bytes, N, k, E, False, True)
+    L = f.Layout(N, k, E, D)
+    L.mem.fill_(0x7B)
+    planes = {}
+    for name, width in (("x", row_bytes), ("x_aux", aux_bytes)):
+        if width:
+            planes[name] = torch.randint(0, 256, (N, width), dtype=torch.uint8, device="cuda")
+            planes["expert_buf" if name == "x" else "expert_aux"] = torch.full((N * k, width), 0xEE, dtype=torch.uint8, device="cuda")
+    f.fusco_plan_dispatch(L, torch.from_numpy(A).cuda(), **planes)
+    check(L, A, "fused")
+    token = torch.from_numpy(plan_by_sorting(A, E, D)[0]["slot_token"]).cuda()
+    for src, dst in (("x", "expert_buf"), ("x_aux", "expert_aux")):
+        if src in planes:
+            assert torch.equal(planes[dst][:len(token)], planes[src][token])
+            assert bool((planes[dst][len(token):] == 0xEE).all())
+
+
 def test_calls_without_a_stream_use_the_current_one():
     from paper_2512_22036_amd import binding
     side = torch.cuda.Stream()
