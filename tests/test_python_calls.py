@@ -45,6 +45,32 @@ CALLS = {
 }
 
 
+# the calls that csrc/fastcall.cpp makes itself; it leaves the others to ctypes
+PLAIN = sorted(set(CALLS) - {"dispatch unasked"})
+
+
+class Recorder:
+    """Stands in for the module and notes what each of its calls returned: None where the call is left to ctypes."""
+
+    def __init__(self, module):
+        self.module, self.seen = module, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            rc = getattr(self.module, name)(*args)
+            self.seen.append((name, rc))
+            return rc
+        return call
+
+
+@pytest.fixture
+def route(f, monkeypatch):
+    from paper_2512_22036_amd import binding
+    recorder = Recorder(binding._fast)
+    monkeypatch.setattr(binding, "_fast", recorder)
+    return recorder.seen
+
+
 def run(f, name, t, **s):
     L = f.Layout(N, k, E, D)
     L.mem.zero_()
@@ -55,10 +81,14 @@ def run(f, name, t, **s):
 
 
 @pytest.mark.parametrize("name", sorted(CALLS))
-def test_same_as_ctypes(f, name):
+def test_same_as_ctypes(f, name, route):
     a, b = tensors(f), tensors(f)
     here = torch.cuda.current_stream()
-    assert torch.equal(run(f, name, a), run(f, name, b, stream=here))
+    got = run(f, name, a)
+    assert [rc for _, rc in route][-1] == (0 if name in PLAIN else None) and all(rc == 0 for _, rc in route[:-1]), route
+    route.clear()
+    assert torch.equal(got, run(f, name, b, stream=here))
+    assert not route, "a call with a stream goes through ctypes"
     for key in a:
         assert torch.equal(a[key], b[key]), key
     # other kinds of tensor are accepted as they were
@@ -68,23 +98,34 @@ def test_same_as_ctypes(f, name):
         assert torch.equal(c[key].data, b[key]), key
 
 
-def test_current_stream(f):
-    side = torch.cuda.Stream()
+def test_current_stream(f, route):
+    """The calls go to the stream that is current: captured into a graph there, they do nothing before the graph runs."""
     t, want = tensors(f), tensors(f)
     for name in ("plan dispatch", "combine"):
         run(f, name, want)
+    L = f.Layout(N, k, E, D)
+    L.mem.zero_()
+    calls = lambda: (f.fusco_plan_dispatch(L, t["A"], t["x"], t["eb"]), f.fusco_combine(L, t["y"], t["w"], t["out"]))
     torch.cuda.synchronize()
-    with torch.cuda.stream(side):
-        torch.cuda._sleep(20000000)                    # the side stream is busy; the default stream is not
-        L = f.Layout(N, k, E, D)
-        f.fusco_plan_dispatch(L, t["A"], t["x"], t["eb"])
-        f.fusco_combine(L, t["y"], t["w"], t["out"])
-        done = torch.cuda.Event()
-        done.record()
-    torch.cuda.default_stream().synchronize()
-    assert not done.query()                            # the calls wait behind the sleep
-    side.synchronize()
-    assert torch.equal(t["out"], want["out"]) and torch.equal(t["eb"], want["eb"])
+    route.clear()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    assert [rc for _, rc in route] == [0, 0]
+    torch.cuda.synchronize()
+    assert not bool(t["out"].any()) and not bool(t["eb"].any()) and not bool(L.mem.any())
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(t["out"], want["out"]) and torch.equal(t["eb"], want["eb"])
+        for key in ("out", "eb"):
+            t[key].zero_()
+        L.mem.zero_()
+        calls()                                        # the same calls between the replays, on the default stream
+        torch.cuda.synchronize()
+        assert torch.equal(t["out"], want["out"]) and torch.equal(t["eb"], want["eb"])
+        for key in ("out", "eb"):
+            t[key].zero_()
 
 
 BROKEN = [("A", lambda v: v.long()), ("A", lambda v: v[:-1]), ("A", lambda v: v.t().contiguous().t()), ("A", lambda v: v.cpu()),
@@ -97,7 +138,7 @@ BROKEN = [("A", lambda v: v.long()), ("A", lambda v: v[:-1]), ("A", lambda v: v.
 
 
 @pytest.mark.parametrize("name", sorted(CALLS))
-def test_same_refusals(f, name):
+def test_same_refusals(f, name, route):
     L = f.Layout(N, k, E, D)
     t = tensors(f)
     f.fusco_plan(L, t["A"])
@@ -106,6 +147,7 @@ def test_same_refusals(f, name):
         b = dict(t)
         b[key] = change(t[key])
         said = []
+        route.clear()
         for s in (dict(), dict(stream=torch.cuda.current_stream())):
             try:
                 CALLS[name](f, L, b, **s)
@@ -113,5 +155,8 @@ def test_same_refusals(f, name):
             except (f.FuscoError, TypeError, AttributeError) as e:
                 said.append((type(e), str(e)))
         assert said[0] == said[1], (key, said)
+        assert len(route) == 1, route
+        if said[0] is not None:
+            assert route[0][1] != 0, (key, route)
         refused += said[0] is not None
     assert refused >= 4
