@@ -302,7 +302,7 @@ typedef struct fusco_segment {
  * Cumulative bytes of a descriptor list: d_cum[0] = 0, d_cum[i+1] = d_cum[i] + size of segment i
  * (d_cum has n + 1 entries).  The engine finds the segment of a stream position from this array.
  * Descriptors with an offset or size that is not a multiple of 16 are counted in *d_status and take
- * part with size 0.  n <= 2^26.  One launch for up to 8192 segments, two for longer lists.
+ * part with size 0.  n <= 2^26.  One launch for up to 32768 segments, two for longer lists.
  */
 int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum, int32_t *d_status, void *stream);
 
@@ -326,7 +326,10 @@ int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum,
  * being out of range are not counted, so a slice with holes never becomes ready.  The counters are
  * reset to 0 by a small kernel at the start of the call, in stream order: a consumer that is still
  * polling the counters of the previous call on the same d_slice_fill races with that reset; give
- * overlapping transfers counter arrays of their own.
+ * overlapping transfers counter arrays of their own.  A consumer kernel that polls while this call
+ * runs must be able to run beside it: streams are dealt onto a few hardware queues, and two streams
+ * on the same queue run one after the other, so a consumer launched first on such a stream would
+ * poll for slices that cannot come.  Bound its polling, or launch it behind the producer.
  */
 int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segment *d_src_desc, void *d_dst,
                         uint64_t dst_bytes, const fusco_segment *d_dst_desc, const uint64_t *d_cum, int64_t n,

@@ -145,6 +145,30 @@ def test_offsets_that_wrap_are_counted_and_touch_nothing(fusco):
     assert bool((room[0] == 0x5A).all()) and bool((room[2] == 0x5A).all())
 
 
+def streams_that_overlap(fusco):
+    """Two streams whose kernels run side by side, or None.  Streams are dealt onto a few hardware queues, and two on the
+    same queue run one after the other, whatever else has created streams before.  A consumer that polls for one small
+    slice, for a bounded time, sees it only when the copy launched behind it runs beside it."""
+    produce = torch.cuda.Stream()
+    size = np.full(4, 4096, dtype=np.int64)
+    d_desc = desc_dev(np.arange(4, dtype=np.int64) * 4096, size)
+    cum, status = scan(fusco, d_desc)
+    src, packed = torch.ones(16384, dtype=torch.uint8, device="cuda"), torch.zeros(16384, dtype=torch.uint8, device="cuda")
+    for _ in range(6):
+        consume = torch.cuda.Stream()
+        fill = torch.zeros(1, dtype=torch.int32, device="cuda")
+        report = torch.full((1, 4), -1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(consume):
+            fusco.fusco_probe_consume_slices(packed, 16384, 16384, fill, 1 << 15, report)
+        with torch.cuda.stream(produce):
+            fusco.fusco_segments_copy(src, d_desc, packed, None, cum, 16384, status, slice_bytes=16384, slice_fill=fill)
+        torch.cuda.synchronize()
+        if int(report[0, 0].item()) == 1:
+            return produce, consume
+    return None
+
+
 def test_consumer_on_another_stream_sees_complete_slices_only(fusco, oracle):
     """The slice protocol under concurrency (section 3.2, pipelined workflow: the consumer takes a slice as soon
     as it is ready).  A consumer workgroup on a second stream polls the per-slice byte counters while
@@ -165,7 +189,8 @@ def test_consumer_on_another_stream_sees_complete_slices_only(fusco, oracle):
 
     d_src, d_desc = dev(src), desc_dev(off, size)
     cum, status = scan(fusco, d_desc)
-    produce, consume = torch.cuda.Stream(), torch.cuda.Stream()
+    overlap = streams_that_overlap(fusco)
+    produce, consume = overlap or (torch.cuda.Stream(), torch.cuda.Stream())
     waited_total = 0
     for attempt in range(3):
         packed = torch.zeros(total + 4096, dtype=torch.uint8, device="cuda")
@@ -187,12 +212,14 @@ def test_consumer_on_another_stream_sees_complete_slices_only(fusco, oracle):
         assert set(ready.tolist()) <= {0, 1}
         # the one thing the protocol promises: a slice seen complete had all its bytes visible
         assert np.array_equal(sums[ready == 1], sums_want[ready == 1]), attempt
-        # the consumer's poll budget is far beyond the producer's run time, so it sees every slice
-        assert int(ready.sum()) == slices, (attempt, int(ready.sum()), slices)
+        # the consumer's poll budget is far beyond the producer's run time: running beside it, it sees every slice
+        assert overlap is None or int(ready.sum()) == slices, (attempt, int(ready.sum()), slices)
         waited_total += int((polls > 0).sum())
         print("attempt %d: consumer had to wait for %d of %d slices" % (attempt, int((polls > 0).sum()), slices), flush=True)
     # over three runs the consumer was at least once ahead of the producer (it starts first): the two did overlap
-    assert waited_total > 0
+    assert overlap is None or waited_total > 0
+    if overlap is None:
+        pytest.skip("no two streams ran side by side: what a complete counter promises was checked, the overlap was not")
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 2049, 8191, 8192, 8193, 6 * 2048, 257 * 2048 + 1, 600 * 2048])
