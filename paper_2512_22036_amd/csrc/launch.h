@@ -86,16 +86,20 @@ inline void combine_shape(int C, int &threads, int &segs)
     threads = round_up((C + segs - 1) / segs, kWave);
 }
 
-// The same for inputs bound by latency: rows of more than 512 chunks in segments of 128 threads, which spread few tokens over
-// the chip, get going sooner than workgroups of 16 waves and finish more evenly; of 64 threads where even those are few.
-// Segments of 64 / 128 / the whole row, rows of 14 KiB, us: 4 tokens x 8 3.0 / 3.1 / 3.9, 64 x 8 4.7 / 5.4 / 6.0, 128 x 8
-// 6.2 / 6.1 / 6.6, 512 x 8 12.2 / 12.0 / 11.9, 1000 x 4 13.5 / 13.3 / 14.8, 3500 x 1 18.3 / 18.9 / 21.7.  Shorter rows: 4096
-// columns, 1000 x 2 5.9 / 5.6 / 5.5, 300 x 4 3.7 / 4.3 / 4.5; 2880 columns, 1537 x 6 15.8 / 16.7 / 15.6.
+// The same for inputs bound by latency.  Fewer than 512 segments of 128 threads leave compute units without work: rows of more than 256
+// chunks are then cut into segments of 64 threads.  With more, rows of more than 512 chunks are cut into segments of 128, which get going
+// sooner than workgroups of 16 waves and finish more evenly.  Segments of 64 / 128 / the whole row, bf16 to bf16, us:
+// - rows of 14 KiB 4 tokens x 8 2.4 / 2.4 / 3.6, 64 x 8 3.2 / 3.1 / 4.5, 128 x 8 4.2 / 4.3 / 5.1, 512 x 8 11.5 / 11.5 / 11.6, 1000 x 4 12.7
+//   / 12.5 /
+// 13.1, 3500 x 1 16.4 / 16.3 / 19.0; of 520 chunks 60 x 8 2.9 / 3.1 / 3.7, 400 x 8 6.4 / 6.3 / 6.9;
+// - of 512 chunks 32 x 8 2.7 / 2.7 / 3.1, 1000 x 2 5.4 / 5.2 / 5.2; of 448 100 x 8 3.0 / 3.1 / 3.5, 400 x 8 5.8 / 5.7 / 5.8; of 360 1537 x
+//   6 to fp32 11.5 /
+// 11.2 / 11.2; of 256 100 x 8 2.9 / 2.8 / 2.9.
 inline void combine_shape_latency(int N, int C, int &threads, int &segs)
 {
     combine_shape(C, threads, segs);
-    if (C <= 512) return;
     const bool few = (int64_t)N * ((C + 127) / 128) < 512;
+    if (C <= (few ? 256 : 512)) return;
     threads = few ? 64 : 128;
     segs = (C + threads - 1) / threads;
 }

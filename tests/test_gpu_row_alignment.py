@@ -83,12 +83,13 @@ def test_combine_output(oracle, N, H, offset, y_f32, out_f32):
     assert bool((room[:offset] == 0xEE).all()) and bool((room[offset + out.numel() * out.element_size():] == 0xEE).all())
 
 
-# rows of more than 512 chunks of small inputs are cut into segments of 64 or 128 threads, two-hop rows into segments of 256:
+# rows of more than 256 or 512 chunks of small inputs are cut into segments of 64 or 128 threads, two-hop rows into segments of 256:
 # row lengths around their edges, token counts on either side of 512 workgroups, the last and the first size past the limits
 # (64 MiB of experts' outputs; 48 MiB two-hop)
 @pytest.mark.parametrize("two_hop", [False, True])
 @pytest.mark.parametrize("N,k,C", [(1, 8, 513), (1, 1, 512), (3, 6, 575), (7, 8, 577), (63, 8, 1024), (64, 8, 1024), (65, 3, 1025), (102, 2, 640),
-                                   (103, 2, 639), (5, 5, 2049), (511, 8, 1024), (512, 8, 1024), (383, 8, 1024), (384, 8, 1024), (1000, 2, 896)])
+                                   (103, 2, 639), (5, 5, 2049), (511, 8, 1024), (512, 8, 1024), (383, 8, 1024), (384, 8, 1024), (1000, 2, 896), (64, 8, 256), (64, 8, 257), (127, 8, 512),
+                                   (128, 8, 512), (170, 4, 384), (171, 4, 384)])
 @pytest.mark.parametrize("y_f32,out_f32", [(False, False), (False, True), (True, False)])
 def test_combine_of_small_inputs_in_column_segments(N, k, C, two_hop, y_f32, out_f32):
     import paper_2512_22036_amd as f
