@@ -89,12 +89,10 @@ inline void combine_shape(int C, int &threads, int &segs)
 // The same for inputs bound by latency.  Fewer than 512 segments of 128 threads leave compute units without work: rows of more than 256
 // chunks are then cut into segments of 64 threads.  With more, rows of more than 512 chunks are cut into segments of 128, which get going
 // sooner than workgroups of 16 waves and finish more evenly.  Segments of 64 / 128 / the whole row, bf16 to bf16, us:
-// - rows of 14 KiB 4 tokens x 8 2.4 / 2.4 / 3.6, 64 x 8 3.2 / 3.1 / 4.5, 128 x 8 4.2 / 4.3 / 5.1, 512 x 8 11.5 / 11.5 / 11.6, 1000 x 4 12.7
-//   / 12.5 /
-// 13.1, 3500 x 1 16.4 / 16.3 / 19.0; of 520 chunks 60 x 8 2.9 / 3.1 / 3.7, 400 x 8 6.4 / 6.3 / 6.9;
-// - of 512 chunks 32 x 8 2.7 / 2.7 / 3.1, 1000 x 2 5.4 / 5.2 / 5.2; of 448 100 x 8 3.0 / 3.1 / 3.5, 400 x 8 5.8 / 5.7 / 5.8; of 360 1537 x
-//   6 to fp32 11.5 /
-// 11.2 / 11.2; of 256 100 x 8 2.9 / 2.8 / 2.9.
+// - rows of 14 KiB 4 tokens x 8 2.4 / 2.4 / 3.6, 64 x 8 3.2 / 3.1 / 4.5, 128 x 8 4.2 / 4.3 / 5.1, 512 x 8 11.5 / 11.5 / 11.6, 1000 x 4
+//   12.7 / 12.5 / 13.1, 3500 x 1 16.4 / 16.3 / 19.0; of 520 chunks 60 x 8 2.9 / 3.1 / 3.7, 400 x 8 6.4 / 6.3 / 6.9;
+// - of 512 chunks 32 x 8 2.7 / 2.7 / 3.1, 1000 x 2 5.4 / 5.2 / 5.2; of 448 100 x 8 3.0 / 3.1 / 3.5, 400 x 8 5.8 / 5.7 / 5.8; of 360
+//   1537 x 6 to fp32 11.5 / 11.2 / 11.2; of 256 100 x 8 2.9 / 2.8 / 2.9.
 inline void combine_shape_latency(int N, int C, int &threads, int &segs)
 {
     combine_shape(C, threads, segs);
@@ -117,9 +115,9 @@ void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores st
 
 // Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4
 // KiB 13.4 / 13.0), for 24 and more entries, several rounds of them, from 32 MiB on (506 x 24 x 1600 B of fp32 5.2 / 6.4, 633 x 24 x 1504 B
-// 6.3 / 7.4); up to two entries per token, and up to four of 32 MiB and more, are already better off with two and the slots as scalars
+// 6.3 / 7.4); one entry per token takes one, and two entries, as three and four of 32 MiB and more, two with the slots as scalars
 // (four in lanes / that: 4096 x 2 x 2 KiB 5.6 / 5.5, 1500 x 4 x 8 KiB 11.6 / 11.2, 1000 x 4 x 14 KiB 13.4 / 13.2, but 1537 x 6 x 5760 B
-// 13.8 / 14.3).  Bound by memory: one, for two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below
+// 13.8 / 14.3).  Bound by memory: one, of two entries per token both.  One row a wave takes many waves to keep memory busy: two rows below
 // 32768 waves, four of the chip's fills (one / two: 1200 x 8 x 8 KiB, 9600 waves, 17.9 / 16.2; 600 x 8 x 16 KiB, 9600, 20.9 / 19.1; 11426 x
 // 6 x 1152 B, 22852, 20.2 / 17.5; 13512 x 8 x 1104 B, 27024, 34.0 / 29.7; 5691 x 7 x 4096 B, 22764, 31.5 / 32.0; 6193 x 8 x 5968 B to fp32,
 // 37158, 69.3 / 70.2), four below 4096 (1000 x 64 x 2 KiB, 2000 waves, 42.6 / 21.7).  Many entries keep a wave busy longer and want one
@@ -297,9 +295,9 @@ void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, O
     }
 }
 
-// Workgroups of `waves` waves per compute unit where their number is capped: up to 16 waves, but at least two workgroups of up to 10 waves; up to
-// 12 for six and more bf16 rows, and a single workgroup from 7 waves on (one / two of 7: 8192 x 8 x 7 KiB on 8 devices 232 / 224 us, but 4096 x 8
-// x 7 KiB 115 / 118 and 7404 x 8 x 7152 B on 16 259 / 267; of 8: 8192 x 8 x 8 KiB on 16 281 / 290).
+// Workgroups of `waves` waves per compute unit where their number is capped: up to 16 waves, but at least two workgroups of up to 10 waves;
+// up to 12 for six and more bf16 rows, and a single workgroup from 7 waves on (one / two of 7: 8192 x 8 x 7 KiB on 8 devices 232 / 224 us,
+// but 4096 x 8 x 7 KiB 115 / 118 and 7404 x 8 x 7152 B on 16 259 / 267; of 8: 8192 x 8 x 8 KiB on 16 281 / 290).
 inline int two_hop_workgroups(int waves, bool y_bf16, int k)
 {
     if (y_bf16 && k >= 6) return std::max(12 / waves, 1);

@@ -528,11 +528,12 @@ constexpr int kDirectParts = 8;      // workgroups per tile
 constexpr int kDirectMaxD = 64;      // bits of the mask
 constexpr int kDirectMaxK = 16;      // a thread takes all of a token's ids: 600 tokens x 33 10.5 us, 9.9 with two launches
 constexpr int kDirectMaxTokens = 8192;
-// Sizes up to which the one launch is the faster one whatever the routing.  Popular experts cost it additions to one address, and
-// the two launches are faster with them, so the line lies lower than for scores without a trend.  One launch / two, us; scores
+// Sizes up to which the one launch is the faster one or even, whatever a router gives.  Popular experts cost it additions to one address, and
+// the two launches are faster with them, so the line lies lower than for scores without a trend (a routing that names one expert in
+// every entry, which no router gives, is left behind from about 20000 pairs on).  One launch / two, us; scores
 // without a trend, popular experts (by rank^-1.2), expert 0 in every token, all entries the same expert:
-// 3072 x 8, 256 experts on 8 devices 7.5 / 9.2, 8.3 / 8.5, 7.9 / 9.1, 9.6 / 8.4; 1024 experts on 64 devices 8.2 / 11.1, 9.0 / 10.2, 8.6 / 11.0, 10.2 / 10.1;
-// 4096 x 8, 256 experts 8.5 / 9.2, 9.8 / 8.7, 9.0 / 9.3, 11.5 / 8.5.
+// 3072 x 8, 256 experts on 8 devices 7.5 / 9.2, 8.3 / 8.5, 7.9 / 9.1, 9.6 / 8.4; 4096 x 8 8.5 / 9.2, 9.8 / 8.7, 9.0 / 9.3, 11.5 / 8.5.
+// 3072 x 8, 1024 experts on 64 devices 8.2 / 11.1, 9.0 / 10.2, 8.6 / 11.0, 10.2 / 10.1.
 // 4096 x 6, 160 experts 7.8 / 9.3, 8.6 / 9.0, 8.3 / 9.3, 9.8 / 8.9; 5461 x 6 9.3 / 9.5, 10.5 / 9.1, 9.8 / 9.5, 12.4 / 9.0.
 // 5120 x 4, 60 experts on 4 devices 7.4 / 8.1, 8.1 / 8.0, 8.0 / 8.1, 9.0 / 7.9; 6144 x 4 8.0 / 8.1, 8.8 / 8.0, 8.7 / 8.1, 10.0 / 7.9.
 // 8192 x 2, 16 experts on 4 devices 7.0 / 7.8, 7.8 / 7.7, 7.9 / 7.7, 8.2 / 7.7.
@@ -542,7 +543,8 @@ inline bool planned_directly(int N, int k, int D)
     return k <= kDirectMaxK && D <= kDirectMaxD && N <= kDirectMaxTokens && N * k <= direct_max_pairs(k);
 }
 constexpr int kEcopies = 4, kDcopies = 8;
-// where a token counts for a workgroup's experts: in an earlier tile, in the tile before the workgroup's own, in the tile after them, in a later tile
+// where a token counts for a workgroup's experts: in an earlier tile, in the tile before the workgroup's own, in the tile after them, in a
+// later tile
 constexpr int kPlaces = 4;
 
 __host__ __device__ __forceinline__ int direct_part_tokens(int tile_tokens) { return (tile_tokens + kDirectParts - 1) / kDirectParts; }
