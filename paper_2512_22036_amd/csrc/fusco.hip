@@ -255,20 +255,22 @@ static std::atomic<int> g_tiled_pull{0};
 
 // Workgroups of the tiled dispatch per compute unit for rows (or column segments) of seg_bytes, source tensor taken in one
 // piece (16: no cap).  The kernel runs at the rate of its writes, which is higher the fewer rows are being written at a time,
-// as long as enough loads stay in flight: about 60-90 KiB of rows per compute unit.  Steps of 8192 tokens x 8, other buffers in every
-// step, us, no cap / the cap chosen / its neighbours: 5 KiB rows 131 / 131 (12) / 133 (10); 6 KiB 154.8 / 155.0 (12) / 154.5 (10);
-// 8 KiB 203 / 197.5 (10) / 199.6 (12), 201 (8); 10 KiB 264 / 257.5 (8) / 257.2 (7), 263 (10); 12 KiB 319 / 308 (6) / 312 (7), 315
-// (5); 13 KiB 352 / 339 (5) / 344 (6); 14 KiB 380 / 365 (5) / 374 (6), 369 (4); 15 KiB 394 / 379 (5) / 386 (6).  Source tensors that
-// do not stay in the memory-side cache next to an output of their size (116-128 MiB): 16384 x 8 KiB 430 / 420 (10) / 421 (12), 427
-// (8); 12200 x 10 KiB 414 / 404 (8) / 411 (6 and 10); 10800 x 11.5 KiB 422 / 414 (8) / 419 (6); 9100 x 14 KiB 426 / 412 (5) / 416 (6).
+// as long as enough loads stay in flight: about 60-100 KiB of rows per compute unit.  Steps of 8192 tokens x 8, other buffers in
+// every step, us, no cap / the cap chosen / its neighbours: 5 KiB rows 125.1 / 124.9 (12) / 126.8 (10); 6 KiB 145.5 / 145.6 (12) /
+// 146.1 (10); 8 KiB 209.3 / 202.9 (10) / 203.7 (12), 207.4 (8); 10 KiB 269 / 259 (8) / 262 (7), 265 (10); 12 KiB 308 / 298 (8) / 298
+// (7), 301 (6); 13 KiB 340 / 330 (6) / 333 (7), 337 (5); 14 KiB 371 / 354 (5) / 355 (6), 365 (4); 15 KiB 393 / 376 (5) / 378 (6).
+// Source tensors that do not stay in the memory-side cache next to an output of their size (116-128 MiB): 16384 x 8 KiB 435 / 423 (10)
+// / 423 (12), 430 (8); 12200 x 10 KiB 405 / 393 (8) / 394 (7), 400 (10); 10800 x 11.5 KiB 414 / 403 (8) / 405 (7), 412 (6); 9100 x 14
+// KiB 427 / 416 (5) / 412 (6).  Other shapes, step, 6 / 8 up to 12 KiB: 4096 x 10 x 10.75 KiB 181 / 175; 5 / 6 up to 13 KiB: 3000 x 32 x
+// 12.5 KiB 416 / 403, 4096 x 8 x 13 KiB 162 / 158, 9000 x 4 x 12.75 KiB even.
 // Rows shorter than 4 KiB are moved by workgroups of one or two waves, of which a compute unit should hold more than a cap allows.
-static int tiled_workgroups_per_cu(size_t seg_bytes, bool resident)
+static int tiled_workgroups_per_cu(size_t seg_bytes)
 {
     if (seg_bytes < 4096) return 16;
     if (seg_bytes <= 6144) return 12;
     if (seg_bytes <= 8192) return 10;
-    if (seg_bytes <= 10240) return 8;
-    if (seg_bytes <= 12288) return resident ? 6 : 8;
+    if (seg_bytes <= 12288) return 8;
+    if (seg_bytes <= 13312) return 6;
     return 5;
 }
 
@@ -355,9 +357,9 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
     //   are moved in column segments (358 against 303 us at 16384 tokens of 14 KiB, 6 rows per token); whole rows
     //   of 8-10 KiB with 5 or 6 rows per token come out even or up to 2 % ahead in the step.
     //   This line dates from a combine that wrote every output through.  Behind one whose large outputs go past the
-    //   memory-side cache the tiles are ahead in a loop over the same buffers (tiles / walk: 4 rows 208 / 229 us at 32768
-    //   tokens of 7 KiB, 180 / 193 at 16384 of 12 KiB, 6 rows 299 / 314 at 16384 of 14 KiB; 4 rows of 14 KiB at 32768 tokens
-    //   still 486 / 448); it has not been moved, because other states of the caches have not been measured.
+    //   memory-side cache the tiles are ahead in a loop over the same buffers (tiles / walk: 4 rows 202 / 231 us at 32768
+    //   tokens of 7 KiB, 175 / 191 at 16384 of 12 KiB, 6 rows 291 / 317 at 16384 of 14 KiB; 4 rows of 14 KiB at 32768 tokens
+    //   still 482 / 448); it has not been moved, because other states of the caches have not been measured.
     const size_t row = row_bytes + aux_row_bytes, source = (size_t)L->N * row;
     const size_t limit = g_source_chunk_bytes.load(std::memory_order_relaxed);
     if ((size_t)L->P * row <= kCacheBytes) return false;
@@ -448,7 +450,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const int pull_knob = g_tiled_pull.load(std::memory_order_relaxed);
         const bool pull = pull_knob == 0 ? !chunked : pull_knob == 2;
         const int wgs = occ_knob > 0 ? occ_knob
-                        : (chunked ? 16 : tiled_workgroups_per_cu((size_t)per * 16, source_bytes <= kResidentSourceBytes));
+                        : (chunked ? 16 : tiled_workgroups_per_cu((size_t)per * 16));
         const size_t lds = lds_for_occupancy(wgs);
         for (size_t tile0 = 0; tile0 < (size_t)L->tile_count; tile0 += chunk_tiles) {
             const size_t tiles_here = std::min(chunk_tiles, (size_t)L->tile_count - tile0);

@@ -74,7 +74,6 @@ constexpr size_t kTiledMaxTileBytes = (size_t)3840 << 10; // source rows of one 
 constexpr size_t kSourceChunkBytes = (size_t)128 << 20;   // source rows of one chunk: half the 256 MB memory-side cache
 constexpr size_t kCacheBytes = (size_t)256 << 20;         // the memory-side cache
 constexpr size_t kTiledShortRowBytes = 8192;              // rows below this are tiled only with a small source tensor
-constexpr size_t kResidentSourceBytes = (size_t)116 << 20; // largest source tensor that stays in that cache next to an output of its size
 
 // Loads and stores of the token walk (MODE of dispatch_kernel: bit 0 cached loads, bit 1 non-temporal stores).
 // Non-temporal stores go past the memory-side cache (a read that follows such a write runs at the cold rate,

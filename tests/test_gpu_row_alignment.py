@@ -18,7 +18,8 @@ def rows_at(rows, row_bytes, offset):
 
 
 @pytest.mark.parametrize("row_bytes,aux_bytes,offset", [(4096, 0, 0), (4096, 0, 16), (4112, 0, 0), (4160, 64, 0), (4160, 224, 0),
-                                                        (4096, 128, 32), (5008, 48, 48), (48, 16, 0), (16384 + 16, 0, 16)])
+                                                        (4096, 128, 32), (5008, 48, 48), (48, 16, 0), (16384 + 16, 0, 16),
+                                                        (12288, 0, 0), (12288, 16, 0), (13312, 0, 0), (13312, 0, 16), (13328, 0, 0)])
 def test_tiled_dispatch(row_bytes, aux_bytes, offset):
     import paper_2512_22036_amd as f
     N, k, E, D = 4200, 8, 64, 8
