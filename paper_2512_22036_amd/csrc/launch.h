@@ -263,9 +263,14 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 // KiB to fp32, 8192, 16.9 / 15.7; 443 x 4 x 7696 B, 3544, 8.7 / 9.6) or 20 MiB (700 x 8 x 6704 B, 4900, 24.1 / 17.7; 300 x 8 x 14 KiB 21.0
 // / 15.9); with 16384 waves they are in each other's way whatever they do, and at once is faster again (8192 x 8 x 1264 B, 16384, 34.8 /
 // 39.7; 8531 x 5 x 1920 B, 17062, 28.7 / 32.3), as it is where a token leaves a single partial row (one device, 3403 x 5 x 736 B 6.6 / 7.9,
-// 3590 x 5 x 2256 B 13.6 / 14.9).  fp32 rows, half the elements, are faster at once than in turn (4443 x 3 x 5184 B, 66 MiB, 22.7 / 26.7),
-// but with fewer than 7000 waves of 20 to 64 MiB still faster one by one (at once / one by one / in turn: 383 x 7 x 11 KiB 13.7 / 11.4 /
-// 14.9, 572 x 8 x 7328 B 13.1 / 11.6 / 14.6, 227 x 8 x 27.7 KiB 18.4 / 16.5 / 18.2).
+// 3590 x 5 x 2256 B 13.6 / 14.9).
+// From 20 MiB on wide rows are faster one by one, their entry looked up as they are added: of 144 chunks and more up to 64 MiB, of 400 and more
+// beyond (in turn / one by one: 2000 x 4 x 4 KiB on 64 devices 17.3 / 16.5, 2668 x 5 x 3696 B on 8 29.7 / 27.5, 3084 x 5 x 2432 B on 64 23.9 /
+// 23.6, 1200 x 8 x 7 KiB on 64, 66 MiB, 48.7 / 45.4; but 5632 x 6 x 1680 B on 8 35.0 / 37.7, 3967 x 6 x 2224 B on 16 33.2 / 33.5, 2652 x 8 x
+// 4304 B on 8, 87 MiB, 62.1 / 66.4; below 20 MiB 1008 x 3 x 6128 B on 2 9.9 / 11.9).
+// fp32 rows, half the elements, are faster at once than in turn (4443 x 3 x 5184 B, 66 MiB, 22.7 / 26.7), but with fewer
+// than 7000 waves of 20 to 64 MiB still faster one by one (at once / one by one / in turn: 383 x 7 x 11 KiB 13.7 / 11.4 / 14.9, 572 x 8 x
+// 7328 B 13.1 / 11.6 / 14.6, 227 x 8 x 27.7 KiB 18.4 / 16.5 / 18.2).
 // Up to 48 MiB rows are cut into segments of up to 256 threads (4 tokens 5.5 / 6.6 with whole rows, 300 16.1 / 17.6, 500 24.6 / 24.3), but
 // not rows of little more than one (277 chunks: 1040 x 7 x 4432 B 19.6 in segments of 256 and 21 chunks, 15.9 whole). Inputs of 96 MiB and
 // more are bound by memory.  Where a token's rows leave at least two partial rows, a compute unit gets about 16 waves, 12 for six and more
@@ -281,7 +286,7 @@ constexpr size_t kTwoHopSmallBytes = (size_t)48 << 20, kTwoHopInTurnBytes = (siz
 constexpr size_t kTwoHopCappedBytes = (size_t)96 << 20;
 constexpr int64_t kTwoHopSomeWaves = 4500, kTwoHopManyWaves = 16384, kTwoHopFewWavesF32 = 7000;
 constexpr int kTwoHopSomeTokens = 3000;
-constexpr int kTwoHopNarrowChunks = 256;
+constexpr int kTwoHopNarrowChunks = 256, kTwoHopWideChunks = 144, kTwoHopWiderChunks = 400;
 
 template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS>
 void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
@@ -316,6 +321,8 @@ void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStre
         const bool in_turn = bytes >= kTwoHopCappedBytes ? a.k <= 2 && a.C <= kTwoHopNarrowChunks
                                                          : D >= 2 && bytes >= kTwoHopInTurnBytes && waves < kTwoHopManyWaves &&
                                                                (waves >= kTwoHopSomeWaves || N >= kTwoHopSomeTokens || bytes >= kTwoHopBusyBytes);
+        const bool wide = bytes >= kTwoHopBusyBytes && a.C >= (bytes < kCombineLatencyBoundBytes ? kTwoHopWideChunks : kTwoHopWiderChunks);
+        if (in_turn && wide) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, s);
         if (in_turn) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsInTurn>(a, grid, block, 0, stores, s);
     } else {
         if (bytes >= kTwoHopBusyBytes && bytes < kCombineLatencyBoundBytes && waves < kTwoHopFewWavesF32)

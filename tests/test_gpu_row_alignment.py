@@ -323,14 +323,15 @@ def test_combine_with_entries_left_over(k, y_f32, mib):
     assert bool((room[out.numel() * 4:] == 0xEE).all())
 
 
-# two-hop combine around its limits: 11, 20, 48, 64 and 96 MiB of input, 3000 tokens, 4500, 7000 and 16384 waves, rows of 352 chunks; capped workgroups of 1 to 16 waves,
+# two-hop combine around its limits: 11, 20, 48, 64 and 96 MiB of input, 3000 tokens, 4500, 7000 and 16384 waves, rows of 144, 352 and 400 chunks; capped workgroups of 1 to 16 waves,
 # one and two devices; fp32 rows beside them
 @pytest.mark.parametrize("N,k,C,D", [(2250, 4, 80, 4), (2249, 4, 84, 4), (2250, 4, 75, 4), (1000, 4, 327, 4), (1000, 4, 328, 4), (500, 7, 352, 8), (500, 7, 353, 8),
                                      (400, 5, 640, 8), (900, 8, 436, 8), (900, 8, 437, 8), (8191, 6, 79, 4), (8192, 6, 79, 4), (8192, 3, 250, 8), (8195, 3, 256, 8),
                                      (50000, 2, 64, 4), (13000, 2, 256, 4), (13000, 2, 257, 4), (50000, 1, 128, 8), (25000, 4, 64, 1), (25000, 4, 63, 2), (12600, 8, 65, 8),
                                      (4000, 4, 400, 8), (2600, 6, 410, 8), (3200, 4, 520, 4), (2000, 8, 576, 8), (2700, 4, 600, 2), (2000, 5, 670, 2), (1800, 3, 1200, 8),
                                      (9000, 3, 256, 3), (9000, 3, 256, 4), (800, 8, 1040, 8), (2999, 6, 50, 8), (3000, 6, 50, 8),
-                                     (1749, 6, 256, 8), (1750, 6, 256, 8), (500, 8, 1000, 8), (550, 8, 1000, 8)])
+                                     (1749, 6, 256, 8), (1750, 6, 256, 8), (500, 8, 1000, 8), (550, 8, 1000, 8),
+                                     (2500, 5, 143, 8), (2500, 5, 144, 8), (1400, 8, 399, 8), (1400, 8, 400, 8), (600, 4, 546, 2), (600, 4, 547, 2)])
 @pytest.mark.parametrize("y_f32,out_f32", [(False, False), (False, True), (True, True)])
 def test_two_hop_around_its_limits(N, k, C, D, y_f32, out_f32):
     import paper_2512_22036_amd as f
