@@ -6,6 +6,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include <stdlib.h>
+#include <type_traits>
 #include "fusco.h"
 #include "fusco_probe.h"
 

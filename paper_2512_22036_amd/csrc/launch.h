@@ -102,14 +102,14 @@ inline void combine_shape_latency(int N, int C, int &threads, int &segs)
     segs = (C + threads - 1) / threads;
 }
 
-template <bool Y_BF16, bool OUT_BF16, int JU>
+template <bool Y_BF16, bool OUT_BF16, int JU, bool WIDENED = Y_BF16 && !OUT_BF16 && JU == 1>
 void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough>, grid, block, s, a, e0, e1);
-    if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain>, grid, block, s, a, e0, e1);
+    if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough, false, WIDENED>, grid, block, s, a, e0, e1);
+    if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain, false, WIDENED>, grid, block, s, a, e0, e1);
     if constexpr (JU > 0 && JU <= 4) {   // inputs bound by latency are written through or plain (out_stores)
-        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal>, grid, block, s, a, e0, e1);
+        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream, false, WIDENED>, grid, block, s, a, e0, e1);
+        else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal, false, WIDENED>, grid, block, s, a, e0, e1);
     }
 }
 
@@ -148,6 +148,9 @@ void launch_combine(CombineArgs a, int N, OutStores stores, hipStream_t s, hipEv
     if constexpr (!Y_BF16) {
         if (latency && a.k >= 3 && bytes >= (a.k <= 8 ? kCombineSpacedBytes : kCombineSpacedManyBytes))
             return launch_combine_as<Y_BF16, OUT_BF16, kSpacedRows>(a, grid, block, stores, s, e0, e1);
+    }
+    if constexpr (Y_BF16 && !OUT_BF16) {
+        if (a.k == 2 && !latency) return launch_combine_as<Y_BF16, OUT_BF16, 2, true>(a, grid, block, stores, s, e0, e1);
     }
     if (a.k == 1)
         launch_combine_as<Y_BF16, OUT_BF16, 1>(a, grid, block, stores, s, e0, e1);
@@ -255,6 +258,24 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
     return whole ? kOutThroughStream : kOutNonTemporal;
 }
 
+// Stores of the two-hop combine's partial rows, summed from bf16 rows (not in turn; in turn and from fp32 rows they are plain: in turn 2099 tokens x 4
+// x 2704 B 12.2 us plain, 15.1 through, from fp32 3989 x 8 x 8544 B 120 and 138).  Written through they leave the L2 while the call still
+// reads; the memory-side cache keeps them for whoever reads them.  us, plain / through, and with a pass that reads them:
+// - rows of whole 64-byte units 175 x 8 x 4736 B 6.4 / 4.7, 20.2 / 18.8; 503 x 8 x 6720 B 13.8 / 12.4, 30.3 / 29.8; 4096 x 8 x 8 KiB 126 / 120, 213 / 209; 6000 x
+//   6 x 10 KiB 165 / 158, 281 / 274;
+// - others, whose ends go to memory as partial writes, up to kPartialCutBytes of input 78 x 8 x 7568 B 5.0 / 4.1, 481 x 8 x 4784 B 9.3 / 9.0, beyond it 911 x 4
+//   x 8096 B 15.7 / 16.8, 1543 x 6 x 12752 B 73 / 83.
+// From kPartialStreamBytes of input on, partial rows of several times that cache, they go past it: what they leave there costs the next call
+// more than it gives a reader of the rows (plan, both tensors and two hops of 4096 x 8 x 14 KiB, written through / past the cache 372 / 359; the two hops
+// and a reader 370 / 378, of 8192 x 8 x 8 KiB 417 / 419, 13924 x 8 x 5440 B 577 / 578).
+constexpr size_t kPartialCutBytes = (size_t)20 << 20, kPartialStreamBytes = (size_t)400 << 20;
+
+inline OutStores partial_stores(size_t y_bytes, const void *partial, size_t row_bytes)
+{
+    if (!whole_units(partial, row_bytes)) return y_bytes < kPartialCutBytes ? kOutThrough : kOutPlain;
+    return y_bytes < kPartialStreamBytes ? kOutThrough : kOutThroughStream;
+}
+
 // Two-hop combine, by the bytes of its input and the waves of its launch.
 // Up to 11 MiB latency counts: a token's rows are requested at once (at once / in turn, us, rows of 14 KiB x 8: 4 tokens 4.2 / 4.7, 128 8.7
 // / 10.6).  From there on so many rows of bf16 are in flight that memory is faster with fewer: an entry is looked up and its row requested
@@ -288,16 +309,26 @@ constexpr int64_t kTwoHopSomeWaves = 4500, kTwoHopManyWaves = 16384, kTwoHopFewW
 constexpr int kTwoHopSomeTokens = 3000;
 constexpr int kTwoHopNarrowChunks = 256, kTwoHopWideChunks = 144, kTwoHopWiderChunks = 400;
 
-template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS>
-void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
+template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS, OutStores PARTIAL>
+void launch_two_hop_with(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
 {
     const hipEvent_t none = nullptr;
     switch (stores) {
-    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ROWS>, grid, block, lds, s, none, none, a); break;
-    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ROWS>, grid, block, lds, s, none, none, a); break;
-    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ROWS>, grid, block, lds, s, none, none, a); break;
-    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ROWS>, grid, block, lds, s, none, none, a); break;
+    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
+    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
+    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
+    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
     }
+}
+
+template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS>
+void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, OutStores partial, hipStream_t s)
+{
+    if constexpr (Y_BF16 && ROWS != kRowsInTurn) {
+        if (partial == kOutThrough) return launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutThrough>(a, grid, block, lds, stores, s);
+        if (partial == kOutThroughStream) return launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutThroughStream>(a, grid, block, lds, stores, s);
+    }
+    launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutPlain>(a, grid, block, lds, stores, s);
 }
 
 // Workgroups of `waves` waves per compute unit where their number is capped: up to 16 waves, but at least two workgroups of up to 10 waves;
@@ -313,6 +344,7 @@ template <bool Y_BF16, bool OUT_BF16>
 void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStream_t s)
 {
     const size_t bytes = (size_t)N * (size_t)a.k * (size_t)a.C * 16;
+    const OutStores partial = Y_BF16 ? partial_stores(bytes, a.partial, (size_t)a.C * 32) : kOutPlain;
     const int64_t waves = (int64_t)N * ((a.C + kWave - 1) / kWave);
     const int segs = bytes >= kTwoHopSmallBytes ? (a.C + 1023) / 1024 : a.C <= kTwoHopWholeChunks ? 1 : (a.C + 255) / 256;
     const int threads = round_up((a.C + segs - 1) / segs, kWave);
@@ -322,18 +354,18 @@ void launch_two_hop(const TwoHopArgs &a, int N, int D, OutStores stores, hipStre
                                                          : D >= 2 && bytes >= kTwoHopInTurnBytes && waves < kTwoHopManyWaves &&
                                                                (waves >= kTwoHopSomeWaves || N >= kTwoHopSomeTokens || bytes >= kTwoHopBusyBytes);
         const bool wide = bytes >= kTwoHopBusyBytes && a.C >= (bytes < kCombineLatencyBoundBytes ? kTwoHopWideChunks : kTwoHopWiderChunks);
-        if (in_turn && wide) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, s);
-        if (in_turn) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsInTurn>(a, grid, block, 0, stores, s);
+        if (in_turn && wide) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, partial, s);
+        if (in_turn) return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsInTurn>(a, grid, block, 0, stores, partial, s);
     } else {
         if (bytes >= kTwoHopBusyBytes && bytes < kCombineLatencyBoundBytes && waves < kTwoHopFewWavesF32)
-            return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, s);
+            return launch_two_hop_as<Y_BF16, OUT_BF16, kRowsOneByOne>(a, grid, block, 0, stores, partial, s);
     }
     size_t lds = 0;
     if (bytes >= kTwoHopCappedBytes && D >= 2 && (a.k >= 4 || (Y_BF16 && a.k == 3 && D >= 4))) {
         const int wgs = two_hop_workgroups(threads / kWave, Y_BF16, a.k);
         lds = wgs == 1 ? kOverHalfLds : (size_t)(128 / wgs) * 1280;
     }
-    launch_two_hop_as<Y_BF16, OUT_BF16, kRowsAtOnce>(a, grid, block, lds, stores, s);
+    launch_two_hop_as<Y_BF16, OUT_BF16, kRowsAtOnce>(a, grid, block, lds, stores, partial, s);
 }
 
 // out[t] = sum_j w[t, j] * y[pair_slot[t * k + j]] for N tokens; arguments already checked

@@ -438,26 +438,108 @@ __device__ __forceinline__ void put_out(V *p, V v)
     }
 }
 
-// The eight floats of chunk c of a bf16 row, as chunks 2 c and 2 c + 1 of an fp32 row of n chunks.  Stored as they are, the
-// lanes of a wave would write every other 16 bytes twice; exchanged inside quads of lanes, each of the two stores covers
-// whole 64-byte units (combine to fp32 rows of 16 KiB, 8192 tokens x 8: 118 us, 132 us without the exchange, both
-// non-temporal).  Every lane of the wave takes part, also those whose chunk lies past the row.
+__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+
+// fp32 -> bfloat16 bits, round to nearest even, NaN kept quiet
+__device__ __forceinline__ uint32_t to_bf16(float f)
+{
+    const uint32_t u = __float_as_uint(f);
+    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+
+// The 16 bytes of a row of C chunks that a thread takes, c: the thread's number in the row.  WIDENED, for rows of bf16 that become rows of
+// fp32, twice as long: 8 bytes in each half of the wave's 1 KiB, so that the 16 bytes of floats stored for each lie next to the
+// neighbour lanes' and a store of the wave covers 1 KiB of whole lines.  Read in one piece, the floats have to be exchanged between lanes
+// (put_floats) before their stores cover whole lines; that is the better one where loads and not stores are what counts.  A thread past
+// the row reads the row's last bytes and stores nothing.
+// Stores that covered every other 64 bytes of their lines had to meet in the L2: the two-hop combine of 4096 tokens x 8 x 14 KiB wrote its
+// partial rows plain in 226 us, through in 247, past the cache in 296; now 222, 217 and 215 (through and past the cache).
+struct WidenedPart {
+    int at[2];    // units of 8 bytes of the row of bf16, which are chunks of the row of floats
+    bool in[2];
+    __device__ __forceinline__ WidenedPart(int c, int C)
+    {
+        const int u = (c & ~(kWave - 1)) * 2 + (c & (kWave - 1));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            in[h] = u + h * kWave < 2 * C;
+            at[h] = min(u + h * kWave, 2 * C - 1);
+        }
+    }
+    __device__ __forceinline__ u32x4 load(const u32x4 *row) const
+    {
+        const u32x2 lo = __builtin_nontemporal_load((const u32x2 *)row + at[0]), hi = __builtin_nontemporal_load((const u32x2 *)row + at[1]);
+        return u32x4{lo[0], lo[1], hi[0], hi[1]};
+    }
+    // the thread's sums in the output's row, as floats or rounded to bf16
+    template <OutStores HOW>
+    __device__ __forceinline__ void store_f32(u32x4 *row, const float (&f)[8]) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x4 o = {__float_as_uint(f[4 * h]), __float_as_uint(f[4 * h + 1]), __float_as_uint(f[4 * h + 2]), __float_as_uint(f[4 * h + 3])};
+            if (in[h]) put_out<HOW>(row + at[h], o);
+        }
+    }
+    template <OutStores HOW>
+    __device__ __forceinline__ void store_bf16(u32x2 *row, const float (&f)[8]) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x2 o = {to_bf16(f[4 * h]) | to_bf16(f[4 * h + 1]) << 16, to_bf16(f[4 * h + 2]) | to_bf16(f[4 * h + 3]) << 16};
+            if (in[h]) put_out<HOW>(row + at[h], o);
+        }
+    }
+};
+
+// The same for rows whose sums keep their place: chunk c.
+struct PlainPart {
+    int c;
+    bool in[1];
+    __device__ __forceinline__ PlainPart(int c_, int C) : c(c_), in{c_ < C} {}
+    __device__ __forceinline__ u32x4 load(const u32x4 *row) const { return load16_stream(row + c); }
+};
+template <bool WIDENED>
+using Part = std::conditional_t<WIDENED, WidenedPart, PlainPart>;
+
+// The eight floats of chunk c of a bf16 row, as chunks 2 c and 2 c + 1 of an fp32 row of n chunks.  Stored as they are, the lanes of a
+// wave would write every other 16 bytes twice.  Exchanged inside quads of lanes, each of the two stores covers whole 64-byte units; unless the
+// stores are plain and meet in the L2, the second store of even quads and the first one of odd quads change places, and each covers
+// lines of 128 bytes (combine to fp32 rows, in 64 / 128 bytes, us: 10911 tokens x 4 x 13.4 KiB 157 / 147, 2469 x 2 x 1536 B 5.1 / 4.3, 5030 x 8 x
+// 5760 B 52.0 / 50.9).  Every lane of the wave takes part, also those whose chunk lies past the row.
 template <OutStores HOW>
 __device__ __forceinline__ void put_floats(u32x4 *row, int c, int n, const float (&f)[8])
 {
+    u32x4 quad[2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int lo = (int)__float_as_uint(f[q]), hi = (int)__float_as_uint(f[4 + q]);
+        // lane j of a quad gets chunk j of the quad's first (second) four: the half j mod 2 of lane j / 2 (2 + j / 2)
+        const int lo0 = __builtin_amdgcn_update_dpp(0, lo, 0x50, 0xf, 0xf, true), hi0 = __builtin_amdgcn_update_dpp(0, hi, 0x50, 0xf, 0xf, true);
+        const int lo1 = __builtin_amdgcn_update_dpp(0, lo, 0xFA, 0xf, 0xf, true), hi1 = __builtin_amdgcn_update_dpp(0, hi, 0xFA, 0xf, 0xf, true);
+        quad[0][q] = (uint32_t)((c & 1) ? hi0 : lo0);
+        quad[1][q] = (uint32_t)((c & 1) ? hi1 : lo1);
+    }
+    if constexpr (HOW == kOutPlain) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = (c & ~3) * 2 + h * 4 + (c & 3);
+            if (at < n) put_out<HOW>(row + at, quad[h]);
+        }
+        return;
+    }
+    u32x4 o[2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        o[0][q] = (uint32_t)__builtin_amdgcn_update_dpp((int)quad[0][q], (int)quad[1][q], 0x114, 0xf, 0xa, false);   // odd quads: from four lanes below
+        o[1][q] = (uint32_t)__builtin_amdgcn_update_dpp((int)quad[1][q], (int)quad[0][q], 0x104, 0xf, 0x5, false);   // even quads: from four lanes above
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        u32x4 o;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int lo = (int)__float_as_uint(f[q]), hi = (int)__float_as_uint(f[4 + q]);
-            // lane j of a quad stores chunk j of the quad's first (second) four: the half j mod 2 of lane j / 2 (2 + j / 2)
-            const int from_lo = h == 0 ? __builtin_amdgcn_update_dpp(0, lo, 0x50, 0xf, 0xf, true) : __builtin_amdgcn_update_dpp(0, lo, 0xFA, 0xf, 0xf, true);
-            const int from_hi = h == 0 ? __builtin_amdgcn_update_dpp(0, hi, 0x50, 0xf, 0xf, true) : __builtin_amdgcn_update_dpp(0, hi, 0xFA, 0xf, 0xf, true);
-            o[q] = (uint32_t)((c & 1) ? from_hi : from_lo);
-        }
-        const int at = (c & ~3) * 2 + h * 4 + (c & 3);
-        if (at < n) put_out<HOW>(row + at, o);
+        const int at = (c & ~7) * 2 + h * 8 + (c & 7);
+        if (at < n) put_out<HOW>(row + at, o[h]);
     }
 }
 
@@ -477,17 +559,6 @@ struct CombineArgs {
     const int32_t *pair_send_row, *send_src, *n_rows_dev;
 };
 
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
-
-// fp32 -> bfloat16 bits, round to nearest even, NaN kept quiet
-__device__ __forceinline__ uint32_t to_bf16(float f)
-{
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
 // acc += w * v, one fused multiply-add per element
 template <bool Y_BF16, int EPC>
 __device__ __forceinline__ void add_row(float (&acc)[EPC], u32x4 v, float w)
@@ -505,8 +576,8 @@ __device__ __forceinline__ void add_row(float (&acc)[EPC], u32x4 v, float w)
 }
 
 // The next JU entries of `left`: all their loads without a branch or a wait between them, then the sums.
-template <bool Y_BF16, int JU, int EPC>
-__device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &left, int my_slot, float my_w, int c, float (&acc)[EPC])
+template <bool Y_BF16, int JU, int EPC, typename PART>
+__device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &left, int my_slot, float my_w, const PART &part, float (&acc)[EPC])
 {
     u32x4 v[JU];
     float wj[JU];
@@ -518,9 +589,9 @@ __device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &lef
         row[jj] = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, j) * a.C;
         wj[jj] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), j));
     }
-    if (c < a.C) {
+    if (part.in[0]) {
 #pragma unroll
-        for (int jj = 0; jj < JU; ++jj) v[jj] = load16_stream(row[jj] + c);
+        for (int jj = 0; jj < JU; ++jj) v[jj] = part.load(row[jj]);
     }
 #pragma unroll
     for (int jj = 0; jj < JU; ++jj) add_row<Y_BF16>(acc, v[jj], wj[jj]);
@@ -538,9 +609,12 @@ __device__ __forceinline__ void combine_rows(const CombineArgs &a, uint64_t &lef
 // inputs of fp32 rows between the two prefer (one after the other / in lanes, back to back / so, us: 5298 tokens x 5 x 1088 B 9.6 / 7.1 /
 // 6.8, 1904 x 8 x 2976 B 9.5 / 9.7 / 9.1, 5151 x 3 x 3488 B 14.1 / 13.6 / 13.0).  Not for bf16 rows, whose sums take twice the registers: the
 // compiler waits for a row before it reuses them for the next one's address.
+// WIDENED: rows of bf16 to rows of fp32, one at a time or, in inputs bound by memory, the only two: a thread takes 8 bytes in two places
+// (exchange / so, us: 23518 x 1 x 8736 B 121 / 103, 2804 x 1 x 2800 B 7.0 / 6.1, 5038 x 8 x 9040 B 84 / 79, 22618 x 2 x 5024 B 87 / 78).  With several in
+// flight twice as many loads cost more than the exchange (399 x 8 x 2176 B 3.10 / 3.45, 595 x 12 x 14.2 KiB 24.2 / 26.2, 2469 x 2 x 1536 B 4.3 / 4.5).
 constexpr int kSpacedRows = -8;
 
-template <bool Y_BF16, bool OUT_BF16, int JU, OutStores STORES, bool PER_SEND_ROW = false>
+template <bool Y_BF16, bool OUT_BF16, int JU, OutStores STORES, bool PER_SEND_ROW = false, bool WIDENED = Y_BF16 && !OUT_BF16 && JU == 1>
 __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
 {
     constexpr int EPC = Y_BF16 ? 8 : 4;   // elements per 16-byte chunk of y
@@ -557,6 +631,7 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
         t = a.send_src[r];
     }
     const int c = seg * blockDim.x + threadIdx.x;
+    const Part<WIDENED> part(c, a.C);
     float acc[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.0f;
@@ -578,7 +653,7 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
                 wj[jj] = wt[j];
                 if (slot < 0) continue;
                 on[jj] = true;
-                if (c < a.C) v[jj] = load16_stream(a.y + (size_t)slot * a.C + c);
+                if (part.in[0]) v[jj] = part.load(a.y + (size_t)slot * a.C);
             }
 #pragma unroll
             for (int jj = 0; jj < ROWS; ++jj)
@@ -604,17 +679,17 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
             bool all = true;
 #pragma unroll
             for (int jj = 0; jj < JU; ++jj) all = all && slot[jj] >= 0;
-            if (c < a.C) {
+            if (part.in[0]) {
                 if (all) {
                     u32x4 v[JU];
 #pragma unroll
-                    for (int jj = 0; jj < JU; ++jj) v[jj] = load16_stream(a.y + (size_t)slot[jj] * a.C + c);
+                    for (int jj = 0; jj < JU; ++jj) v[jj] = part.load(a.y + (size_t)slot[jj] * a.C);
 #pragma unroll
                     for (int jj = 0; jj < JU; ++jj) add_row<Y_BF16>(acc, v[jj], wj[jj]);
                 } else if (JU > 1) {
 #pragma unroll
                     for (int jj = 0; jj < JU; ++jj)
-                        if (slot[jj] >= 0) add_row<Y_BF16>(acc, load16_stream(a.y + (size_t)slot[jj] * a.C + c), wj[jj]);
+                        if (slot[jj] >= 0) add_row<Y_BF16>(acc, part.load(a.y + (size_t)slot[jj] * a.C), wj[jj]);
                 }
             }
 #pragma unroll
@@ -636,21 +711,24 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
         }
         uint64_t left = __builtin_amdgcn_ballot_w64(my_slot >= 0);   // entries still to be added, in ascending order
         int n = __builtin_popcountll(left);
-        for (; n >= JU; n -= JU) combine_rows<Y_BF16, JU>(a, left, my_slot, my_w, c, acc);
+        for (; n >= JU; n -= JU) combine_rows<Y_BF16, JU>(a, left, my_slot, my_w, part, acc);
         // the entries left over are requested at once too: 1153 tokens x 7 x 736 B 3.7 us by fours, twos and ones, 3.2 so; 675 x 3 x
         // 1888 B of fp32 2.7 / 2.5
         switch (n) {
-        case 1: combine_rows<Y_BF16, 1>(a, left, my_slot, my_w, c, acc); break;
-        case 2: combine_rows<Y_BF16, 2>(a, left, my_slot, my_w, c, acc); break;
-        case 3: combine_rows<Y_BF16, 3>(a, left, my_slot, my_w, c, acc); break;
-        case 4: combine_rows<Y_BF16, 4>(a, left, my_slot, my_w, c, acc); break;
-        case 5: combine_rows<Y_BF16, 5>(a, left, my_slot, my_w, c, acc); break;
-        case 6: combine_rows<Y_BF16, 6>(a, left, my_slot, my_w, c, acc); break;
-        case 7: combine_rows<Y_BF16, 7>(a, left, my_slot, my_w, c, acc); break;
+        case 1: combine_rows<Y_BF16, 1>(a, left, my_slot, my_w, part, acc); break;
+        case 2: combine_rows<Y_BF16, 2>(a, left, my_slot, my_w, part, acc); break;
+        case 3: combine_rows<Y_BF16, 3>(a, left, my_slot, my_w, part, acc); break;
+        case 4: combine_rows<Y_BF16, 4>(a, left, my_slot, my_w, part, acc); break;
+        case 5: combine_rows<Y_BF16, 5>(a, left, my_slot, my_w, part, acc); break;
+        case 6: combine_rows<Y_BF16, 6>(a, left, my_slot, my_w, part, acc); break;
+        case 7: combine_rows<Y_BF16, 7>(a, left, my_slot, my_w, part, acc); break;
         }
     }
 
-    if constexpr (Y_BF16 && !OUT_BF16) {
+    if constexpr (WIDENED) {
+        part.template store_f32<STORES>((u32x4 *)a.out + (size_t)r * a.C * 2, acc);
+        return;
+    } else if constexpr (Y_BF16 && !OUT_BF16) {
         put_floats<STORES>((u32x4 *)a.out + (size_t)r * a.C * 2, c, a.C * 2, acc);
         return;
     }
@@ -668,12 +746,8 @@ __global__ __launch_bounds__(1024) void combine_kernel(CombineArgs a)
             put_out<STORES>((u32x2 *)((uint16_t *)a.out + e0), o);
         }
     } else {
-#pragma unroll
-        for (int h = 0; h < EPC / 4; ++h) {
-            const u32x4 o = {__float_as_uint(acc[4 * h]), __float_as_uint(acc[4 * h + 1]),
-                             __float_as_uint(acc[4 * h + 2]), __float_as_uint(acc[4 * h + 3])};
-            put_out<STORES>((u32x4 *)((float *)a.out + e0) + h, o);
-        }
+        const u32x4 o = {__float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]), __float_as_uint(acc[3])};
+        put_out<STORES>((u32x4 *)((float *)a.out + e0), o);
     }
 }
 
@@ -696,14 +770,16 @@ struct TwoHopArgs {
 // up only when the row before it has arrived.
 enum TwoHopRows : int32_t { kRowsAtOnce, kRowsOneByOne, kRowsInTurn };
 
-template <bool Y_BF16, bool OUT_BF16, OutStores STORES, TwoHopRows ROWS>
+template <bool Y_BF16, bool OUT_BF16, OutStores STORES, TwoHopRows ROWS, OutStores PARTIAL>
 __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
 {
     constexpr int EPC = Y_BF16 ? 8 : 4;
     constexpr int KMAX = 8;
     const int t = gridDim.x - 1 - blockIdx.x;
+    constexpr bool WIDENED = Y_BF16 && ROWS != kRowsInTurn;   // in turn the loads are what counts (6851 x 8 x 1040 B 32.1, 33.9 us in two places)
     const int c = blockIdx.y * blockDim.x + threadIdx.x;
-    const bool in = c < a.C;   // lanes past the row take part in the exchange of put_floats
+    const bool in = c < a.C;
+    const Part<WIDENED> part(c, a.C);
     u32x4 v[KMAX];
     int row[KMAX];
     float wj[KMAX];
@@ -725,7 +801,7 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             lead[j] = first[j];   // a byte: a vector load, behind the request before it and waited for ahead of the next
             if (slot < 0) continue;
             on[j] = true;
-            if (in) v[j] = load16_stream(a.y + (size_t)slot * a.C + c);
+            if (in) v[j] = part.load(a.y + (size_t)slot * a.C);
         }
     } else {
         // entry j's slot, send row and weight in lane j; the entries with a slot are taken in ascending order
@@ -753,10 +829,14 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             wj[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), at));
             lead[j] = firsts >> at & 1;
             const u32x4 *src = a.y + (size_t)__builtin_amdgcn_readlane(my_slot, at) * a.C;
-            v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
+            if constexpr (WIDENED) v[j] = part.load(src);
+            else v[j] = load16_stream(src + (in ? c : 0));   // lanes past the row read its first chunk
             if constexpr (ROWS == kRowsOneByOne) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
         }
     }
+    // All rows are there before the first sum: waited for one by one behind the stores of the sums, they would wait for those too (128 tokens x 8 x 14
+    // KiB 8.5 us, 7.4 so; both with partial rows written through).
+    if constexpr (ROWS == kRowsAtOnce) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
     float total[EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) total[e] = 0.0f;
@@ -773,18 +853,23 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             if (!on[j] || row[j] != row[f]) continue;
             add_row<Y_BF16>(acc, v[j], wj[j]);
         }
-        // plain stores: 4096 tokens x 8 rows of 14 KiB, 21700 partial rows 224 us, written through 247, non-temporal 296 us
         u32x4 *prow = (u32x4 *)a.partial + (size_t)row[f] * a.C * (EPC / 4);
-        if constexpr (Y_BF16) {
-            put_floats<kOutPlain>(prow, c, a.C * 2, acc);
+        if constexpr (WIDENED) {
+            part.template store_f32<PARTIAL>(prow, acc);
+        } else if constexpr (Y_BF16) {
+            put_floats<PARTIAL>(prow, c, a.C * 2, acc);
         } else if (in) {
             const u32x4 o = {__float_as_uint(acc[0]), __float_as_uint(acc[1]), __float_as_uint(acc[2]), __float_as_uint(acc[3])};
-            prow[c] = o;
+            put_out<PARTIAL>(prow + c, o);
         }
 #pragma unroll
         for (int e = 0; e < EPC; ++e) total[e] = total[e] + acc[e];
     }
-    if constexpr (Y_BF16 && !OUT_BF16) {
+    if constexpr (WIDENED) {
+        if constexpr (OUT_BF16) part.template store_bf16<STORES>((u32x2 *)a.out + (size_t)t * a.C * 2, total);
+        else part.template store_f32<STORES>((u32x4 *)a.out + (size_t)t * a.C * 2, total);
+        return;
+    } else if constexpr (Y_BF16 && !OUT_BF16) {
         put_floats<STORES>((u32x4 *)a.out + (size_t)t * a.C * 2, c, a.C * 2, total);
         return;
     }
@@ -802,12 +887,8 @@ __global__ __launch_bounds__(1024) void combine_two_hop_kernel(TwoHopArgs a)
             put_out<STORES>((u32x2 *)((uint16_t *)a.out + e0), o);
         }
     } else {
-#pragma unroll
-        for (int h = 0; h < EPC / 4; ++h) {
-            const u32x4 o = {__float_as_uint(total[4 * h]), __float_as_uint(total[4 * h + 1]),
-                             __float_as_uint(total[4 * h + 2]), __float_as_uint(total[4 * h + 3])};
-            put_out<STORES>((u32x4 *)((float *)a.out + e0) + h, o);
-        }
+        const u32x4 o = {__float_as_uint(total[0]), __float_as_uint(total[1]), __float_as_uint(total[2]), __float_as_uint(total[3])};
+        put_out<STORES>((u32x4 *)((float *)a.out + e0), o);
     }
 }
 
