@@ -227,11 +227,23 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     const int cpt = (seg_chunks + kSmallThreads - 1) / kSmallThreads;
     const unsigned groups = grid.x * grid.y;
     const bool four = groups > kFusedThree && groups <= kFusedFour;
-    const auto kernel = cpt <= 1   ? (four ? (Ca ? plan_dispatch_four_kernel<1, true> : plan_dispatch_four_kernel<1, false>)
-                                           : (Ca ? plan_dispatch_kernel<1, true> : plan_dispatch_kernel<1, false>))
-                        : cpt <= 2 ? (four ? (Ca ? plan_dispatch_four_kernel<2, true> : plan_dispatch_four_kernel<2, false>)
-                                           : (Ca ? plan_dispatch_kernel<2, true> : plan_dispatch_kernel<2, false>))
-                                   : (Ca ? plan_dispatch_four_kernel<4, true> : plan_dispatch_four_kernel<4, false>);
+    const size_t written = (size_t)L->P * row_bytes;
+    const bool through = written >= kFusedThroughBytes && (size_t)L->k * (size_t)seg_chunks * 16 <= kFusedThroughGroup &&
+                         (written < kFusedThroughCutBytes || whole_units(d_expert_buf, row_bytes));
+    using Fused = decltype(&plan_dispatch_kernel<1, false, false>);
+    // by second plane and by stores, for one, two and four chunks a thread
+    static constexpr Fused kThree[2][2][2] = {{{plan_dispatch_kernel<1, false, false>, plan_dispatch_kernel<1, false, true>},
+                                               {plan_dispatch_kernel<1, true, false>, plan_dispatch_kernel<1, true, true>}},
+                                              {{plan_dispatch_kernel<2, false, false>, plan_dispatch_kernel<2, false, true>},
+                                               {plan_dispatch_kernel<2, true, false>, plan_dispatch_kernel<2, true, true>}}};
+    static constexpr Fused kFour[3][2][2] = {{{plan_dispatch_four_kernel<1, false, false>, plan_dispatch_four_kernel<1, false, true>},
+                                              {plan_dispatch_four_kernel<1, true, false>, plan_dispatch_four_kernel<1, true, true>}},
+                                             {{plan_dispatch_four_kernel<2, false, false>, plan_dispatch_four_kernel<2, false, true>},
+                                              {plan_dispatch_four_kernel<2, true, false>, plan_dispatch_four_kernel<2, true, true>}},
+                                             {{plan_dispatch_four_kernel<4, false, false>, plan_dispatch_four_kernel<4, false, true>},
+                                              {plan_dispatch_four_kernel<4, true, false>, plan_dispatch_four_kernel<4, true, true>}}};
+    const int shape = cpt <= 1 ? 0 : cpt <= 2 ? 1 : 2, second = Ca ? 1 : 0;
+    const Fused kernel = shape == 2 || four ? kFour[shape][second][through] : kThree[shape][second][through];
     launch_args(kernel, grid, block, 0, (hipStream_t)stream, ev.start, ev.stop, a.A, x, x_aux, a.N, a.k, a.k_magic, a.small_groups, C, Ca, seg_chunks,
                 m, a);
     return launch_status();
@@ -509,7 +521,8 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const int knob = g_walk_mode.load(std::memory_order_relaxed);
         const uint64_t groups = (uint64_t)L->N * (uint64_t)segs;
         const bool eager = groups <= kWalkEagerGroups || (!a.write_expert && eager_send_rows(groups, L->N, L->k, L->D, Ct));
-        const int mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0);
+        const bool through = !stream_stores && !eager && expert && !wire && a.Ca == 0 && walk_through(L->k, row, written);
+        const int mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0) + (through ? 4 : 0);
 #define FUSCO_WALK_AS(CPT, MODE)                                                                       \
     do {                                                                                              \
         if (eager) launch(dispatch_eager_kernel<CPT, MODE>, grid, block, s, a, ev.start, ev.stop);    \
@@ -520,6 +533,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
     case 0: FUSCO_WALK_AS(CPT, 0); break;                                                             \
     case 1: FUSCO_WALK_AS(CPT, 1); break;                                                             \
     case 2: FUSCO_WALK_AS(CPT, 2); break;                                                             \
+    case 4: launch(dispatch_kernel<CPT, 4>, grid, block, s, a, ev.start, ev.stop); break;             \
     default: FUSCO_WALK_AS(CPT, 3); break;                                                            \
     }
         switch (cpt) {

@@ -75,7 +75,7 @@ constexpr size_t kSourceChunkBytes = (size_t)128 << 20;   // source rows of one 
 constexpr size_t kCacheBytes = (size_t)256 << 20;         // the memory-side cache
 constexpr size_t kTiledShortRowBytes = 8192;              // rows below this are tiled only with a small source tensor
 
-// Loads and stores of the token walk (MODE of dispatch_kernel: bit 0 cached loads, bit 1 non-temporal stores).
+// Loads and stores of the token walk (MODE of dispatch_kernel: bit 0 cached loads, bit 1 non-temporal stores, bit 2 stores through the L2).
 // Non-temporal stores go past the memory-side cache (a read that follows such a write runs at the cold rate,
 // 5.7 TB/s for 256 MB, instead of 4.2 TB/s on rows that sit dirty in that cache); plain stores leave the rows
 // there, which is what a reader of a tensor of up to 256 MB wants.  With non-temporal stores a source tensor
@@ -90,7 +90,30 @@ __device__ __forceinline__ void put16(u32x4 *p, u32x4 v)
     else *p = v;
 }
 
-template <int CPT, int MODE>   // MODE bit 0: cached loads, bit 1: non-temporal stores
+// Bit 2: what plain stores leave dirty in the L2s is written back when the kernel ends, up to 32 MB that then go to memory with nothing else
+// on its way; rows written through go there at once.  The memory-side cache keeps both.  Plain / through, us, dispatch and a combine of
+// another tensor, and with the combine of the rows:
+// - one entry per token from kThroughBytesOne on: 9323 x 1600 B (14 MiB) 15.3 / 14.8, 15.5 / 14.9; 1993 x 24064 B 37.9 / 35.7, 35.3 / 33.2; 15616 x 7024 B
+//   87.9 / 85.1, 78.4 / 77.4; 13709 x 14 KiB 146 / 143, 120 / 117; 4127 x 1040 B (4 MiB) 7.9 / 8.1, 8.5 / 8.2;
+// - two and three from kThroughBytesFew on, rows of whole lines (128 bytes): 1191 x 2 x 4608 B 9.6 / 9.3, 8.8 / 9.2; 1605 x 2 x 5312 B 13.3 / 12.6, 13.0 / 13.1;
+//   4096 x 2 x 2 KiB 12.1 / 11.2; 6128 x 3 x 4 KiB 39.7 / 38.3, 36.1 / 34.6; 24291 x 2 x 4 KiB 107 / 106, 90 / 89; other rows 3146 x 2 x 3776 B 15.3 / 15.6, 20720
+//   x 2 x 5744 B 141 / 151; smaller 1832 x 2 x 2304 B 8.4 / 8.7;
+// - more entries come out even or lose: 9515 x 4 x 1 KiB 20.1 / 20.5, 4990 x 6 x 512 B 11.6 / 12.0, 2827 x 8 x 1344 B 15.5 / 15.7.
+constexpr size_t kThroughBytesOne = (size_t)8 << 20, kThroughBytesFew = (size_t)10 << 20;
+inline bool walk_through(int k, size_t row, size_t written)
+{
+    if (k == 1) return written >= kThroughBytesOne;
+    return k <= 3 && written >= kThroughBytesFew && row % 128 == 0;
+}
+
+template <int MODE>
+__device__ __forceinline__ void put_row(u32x4 *p, u32x4 v)
+{
+    if constexpr (MODE & 4) store16_through(p, v);
+    else put16<(MODE & 2) != 0>(p, v);
+}
+
+template <int CPT, int MODE>
 __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
 {
     // workgroup = (token, column segment), segments of one row next to each other in launch order, so that a
@@ -115,8 +138,8 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
             for (int i = 0; i < CPT; ++i) {
                 const int c = c0 + i * blockDim.x;
                 if (c >= c_end) continue;
-                if (c < a.C) put16<(MODE & 2) != 0>(a.expert_buf + (size_t)slot * a.C + c, v[i]);
-                else put16<(MODE & 2) != 0>(a.expert_aux + (size_t)slot * a.Ca + (c - a.C), v[i]);
+                if (c < a.C) put_row<MODE>(a.expert_buf + (size_t)slot * a.C + c, v[i]);
+                else put_row<MODE>(a.expert_aux + (size_t)slot * a.Ca + (c - a.C), v[i]);
             }
         }
     }
@@ -130,8 +153,8 @@ __global__ __launch_bounds__(256) void dispatch_kernel(DispatchArgs a)
             for (int i = 0; i < CPT; ++i) {
                 const int c = c0 + i * blockDim.x;
                 if (c >= c_end) continue;
-                if (c < a.C) put16<(MODE & 2) != 0>(a.send_buf + (size_t)row * a.C + c, v[i]);
-                else put16<(MODE & 2) != 0>(a.send_aux + (size_t)row * a.Ca + (c - a.C), v[i]);
+                if (c < a.C) put_row<MODE>(a.send_buf + (size_t)row * a.C + c, v[i]);
+                else put_row<MODE>(a.send_aux + (size_t)row * a.Ca + (c - a.C), v[i]);
             }
         }
     }
@@ -363,7 +386,7 @@ struct FusedRows {
 // 6.6), and of more than 1024 workgroups memory is faster with fewer of them writing (1024 x 2 x 16 KiB, 1281 workgroups, 12.0 / 14.4).
 constexpr int kFusedThree = 3 * 256, kFusedFour = 4 * 256;   // workgroups that are resident at once
 
-template <int CPT, bool AUX>
+template <int CPT, bool AUX, bool THROUGH>
 __device__ __forceinline__ void plan_dispatch(SmallLds &s, const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k, uint32_t k_magic,
                                               int32_t small_groups, int32_t C, int32_t Ca, int32_t seg_chunks, FusedRows m, PlanArgs a)
 {
@@ -399,19 +422,31 @@ __device__ __forceinline__ void plan_dispatch(SmallLds &s, const int32_t *A, con
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
             const int c = c0 + i * kSmallThreads;
-            if (c < c_end) (!AUX || c < C ? dst : dst_aux)[c] = v[i];
+            if (c >= c_end) continue;
+            if (AUX && c >= C) dst_aux[c] = v[i];   // rows of scales: short, and rarely whole units
+            else if (THROUGH) store16_through(dst + c, v[i]);
+            else dst[c] = v[i];
         }
     }
 }
 
+// THROUGH: the rows are written through instead of plain (as in the token walk, the write-back at the kernel's end is spread over
+// the kernel), from kFusedThroughBytes of rows on; below, the end of a small kernel is sooner reached than memory.  us, plain / through, alone, with a combine of another
+// tensor and with the combine of the rows: 128 x 8 x 7 KiB + 224 B 5.3 / 4.7, 9.8 / 9.1 (second); 219 x 8 x 11 KiB 7.4 / 6.3, 13.6 / 11.8, 13.1 / 12.5; 114 x 8 x 50 KiB 11.8 /
+// 9.6, 22.4 / 20.8, 21.9 / 21.5; 155 x 4 x 3584 B (2.1 MiB) 3.8 / 3.6, 6.5 / 6.2, 7.2 / 7.1; 124 x 8 x 1 KiB (1 MiB) 3.6 / 3.7.
+// Not where a workgroup writes more than kFusedThroughGroup, which it does at one store's latency after the other (24 x 16 x 32704 B 8.3 / 9.4, 15 x 33 x
+// 24640 B 13.3 / 15.0; 80 x 16 x 23200 B 10.8 / 9.3), nor rows that are no whole units from kFusedThroughCutBytes on (154 x 8 x 65232 B 16.7 / 16.2, 35.1 /
+// 36.1, 36.6 / 42.8; 912 x 1 x 14816 B 8.7 / 8.0, 16.7 / 16.1, 16.8 / 16.1).
+constexpr size_t kFusedThroughBytes = (size_t)2 << 20, kFusedThroughGroup = (size_t)384 << 10, kFusedThroughCutBytes = (size_t)16 << 20;
+
 #define FUSCO_PLAN_DISPATCH(NAME, ATTRIBUTE)                                                                                                          \
-    template <int CPT, bool AUX>                                                                                                                      \
+    template <int CPT, bool AUX, bool THROUGH>                                                                                                        \
     __global__ __launch_bounds__(kSmallThreads) ATTRIBUTE void NAME(const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k,       \
                                                                     uint32_t k_magic, int32_t small_groups, int32_t C, int32_t Ca, int32_t seg_chunks, \
                                                                     FusedRows m, PlanArgs a)                                                          \
     {                                                                                                                                                 \
         __shared__ SmallLds s;                                                                                                                        \
-        plan_dispatch<CPT, AUX>(s, A, x, x_aux, N, k, k_magic, small_groups, C, Ca, seg_chunks, m, a);                                                \
+        plan_dispatch<CPT, AUX, THROUGH>(s, A, x, x_aux, N, k, k_magic, small_groups, C, Ca, seg_chunks, m, a);                                                \
     }
 FUSCO_PLAN_DISPATCH(plan_dispatch_kernel, )
 FUSCO_PLAN_DISPATCH(plan_dispatch_four_kernel, __attribute__((amdgpu_num_sgpr(80))))
