@@ -750,11 +750,14 @@ int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segme
     a.src_desc = d_src_desc; a.dst_desc = d_dst_desc;
     a.cum = d_cum; a.n = n;
     a.src_bytes = src_bytes; a.dst_bytes = dst_bytes;
+    a.limit = blocks * kSegBlockBytes;
     a.slice_bytes = slice_bytes; a.slice_fill = d_slice_fill; a.status = d_status;
     const dim3 grid((unsigned)blocks);
-    if (d_slice_fill) launch(segments_copy_kernel<true, false>, grid, dim3(kSegThreads), s, a);
-    else if (stream_capacity > kSegStreamBytes) launch(segments_copy_kernel<false, true>, grid, dim3(kSegThreads), s, a);
-    else launch(segments_copy_kernel<false, false>, grid, dim3(kSegThreads), s, a);
+    const bool wide = d_slice_fill && slice_bytes >= kSegWideSlice && slice_bytes % kSegWideBlockBytes == 0 && stream_capacity >= kSegWideBytes;
+    if (wide) launch(segments_copy_kernel<true, false, kSegWideThreads>, dim3((unsigned)((blocks + 1) / 2)), dim3(kSegWideThreads), s, a);
+    else if (d_slice_fill) launch(segments_copy_kernel<true, false, kSegThreads>, grid, dim3(kSegThreads), s, a);
+    else if (stream_capacity > kSegStreamBytes) launch(segments_copy_kernel<false, true, kSegThreads>, grid, dim3(kSegThreads), s, a);
+    else launch(segments_copy_kernel<false, false, kSegThreads>, grid, dim3(kSegThreads), s, a);
     return launch_status();
 }
 

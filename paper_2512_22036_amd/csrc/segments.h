@@ -20,11 +20,19 @@ constexpr int kScanChunk = kScanThreads * kScanItems;    // descriptors per work
 constexpr int kScanSingleThreads = 1024, kScanSingleMax = 3 * kScanSingleThreads;
 constexpr int kScanDirectThreads = 1024, kScanDirectItems = 2, kScanDirectChunk = kScanDirectThreads * kScanDirectItems;
 constexpr int kScanDirectMax = 32768;
-constexpr int kSegBlockBytes = 16384;   // stream bytes handled by one workgroup of the copy kernel
-constexpr int kSegThreads = 256;
+constexpr int kSegThreads = 256;        // threads of a workgroup of the copy kernel
 constexpr int kSegPieceBytes = 4096;    // stream bytes handled by one of its waves
 constexpr int kSegUnits = kSegPieceBytes / 16 / kWave;   // 16-byte units per thread
-constexpr int kSegRunBlocks = 8;        // consecutive blocks taken by one XCD
+constexpr int kSegBlockBytes = kSegThreads / kWave * kSegPieceBytes;   // stream bytes handled by a workgroup
+constexpr int kSegRunBytes = 8 * kSegBlockBytes;                       // consecutive bytes taken by one XCD
+// With slices a workgroup adds what it has written to the slice's counter, and additions to one counter follow one another some 150 ns
+// apart: 64 workgroups of 256 threads per MiB kept a slice open longer than its bytes.  Slices of at least kSegWideSlice, in whole blocks of
+// workgroups of kSegWideThreads, are taken by those, streams below kSegWideBytes aside.  Pack, us, 256 / 512 / 1024 threads: slices of 1 MiB, 0.3 MB 6.4 / 6.6 /
+// 7.3, 21 MB 20.7 / 15.0 / 16.2, 36 MB 28.8 / 21.8 / 21.4, 286 MB 125 / 115 / 115, of 4 MiB 286 MB 158 / 121 / 116, of 256 KiB 411 MB 176 / 170 / 178, of 64 KiB
+// 4 MB 7.3 / 6.9 / 7.4, of 32 KiB 36 MB 18.4 / 19.0 / 18.8.  (A counter per wave: 286 MB 280; two blocks by one workgroup, whose second lookups wait behind
+// the first stores: 161.)
+constexpr int kSegWideThreads = 2 * kSegThreads, kSegWideBlockBytes = 2 * kSegBlockBytes;
+constexpr uint64_t kSegWideSlice = (uint64_t)64 << 10, kSegWideBytes = (uint64_t)2 << 20;
 // Streams of more than this are written with non-temporal stores, smaller ones with plain stores, which leave them in the
 // memory-side cache for whoever reads them.  Unpack and a pass that reads the result, other buffers in every turn, us, non-temporal
 // / plain: 4 MB 9.7 / 9.6, 14 MB 17.5 / 16.2, 57 MB 59.4 / 53.2, 115 MB 110.6 / 101.0, 172 MB 162.1 / 161.0, 230 MB 213 / 216,
@@ -106,6 +114,9 @@ __global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void se
         finished = -1;
         bad_total = 0;
     }
+    // the ends of the nearest earlier chunks are on their way together with the descriptors
+    uint64_t near = 0;
+    if (!SINGLE && tid < (int)blockIdx.x) near = __hip_atomic_load(cum + (blockIdx.x - tid) * (int64_t)kScanChunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint64_t size[kScanItems];
     int bad = 0;
     const uint64_t sum = scan_load(desc, n, i0, items, size, bad);
@@ -123,7 +134,7 @@ __global__ __launch_bounds__(SINGLE ? kScanSingleThreads : kScanThreads) void se
             const int64_t j = hi - 1 - tid;   // thread 0 has the nearest chunk
             uint64_t v = 0;
             if (j >= 0) {
-                v = __hip_atomic_load(cum + (j + 1) * kScanChunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                v = hi == blockIdx.x ? near : __hip_atomic_load(cum + (j + 1) * kScanChunk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (!(v & 1u)) atomicMax(&finished, kScanThreads - 1 - tid);
             }
             __syncthreads();
@@ -216,40 +227,47 @@ struct SegCopyArgs {
     const uint64_t *cum;
     int64_t n;
     uint64_t src_bytes, dst_bytes;
+    uint64_t limit;   // whole blocks of kSegBlockBytes that cover the stream's capacity: nothing behind them is copied
     uint64_t slice_bytes;
     uint32_t *slice_fill;
     int32_t *status;
 };
 
-// One workgroup per 16 KiB of the stream, one wave per 4 KiB of it: the wave finds the segment of its first byte by
+// One workgroup per 16 KiB of the stream (wide ones per 32 KiB), one wave per 4 KiB of it: the wave finds the segment of its first byte by
 // probing 64 cumulative entries at a time (three dependent loads for 40000 segments, where halving takes
 // sixteen), then reads the next 64 segments' ends and offsets in one go and looks its units up in them.
-// An XCD takes runs of kSegRunBlocks neighbouring blocks: what it writes on a contiguous side are runs of 128 KiB.
+// An XCD takes runs of neighbouring blocks: what it writes on a contiguous side are runs of 128 KiB.
 // Bound by memory once the search is short.  Measured, 287 MB in 40000 segments of 16 B to 14 KiB: pack 176 -> 106 us
 // (5.4 TB/s read and written), pack with 1 MiB slices 193 -> 124 us, unpack 178 -> 115 us.  A unit's load is issued as
 // soon as its segment is known: all four together take 119 and 125 us.  8 KiB a wave take 117 and 124 us, 2 KiB 117 us each.
 // STREAM: non-temporal stores, which the L2 still merges into whole lines at the segments' ragged edges (write-through ones
 // 139 us in the unpack); for streams that the memory-side cache would not keep for their reader (kSegStreamBytes).
-template <bool SLICES, bool STREAM>
-__global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs a)
+template <bool SLICES, bool STREAM, int THREADS>
+__global__ __launch_bounds__(THREADS) void segments_copy_kernel(SegCopyArgs a)
 {
-    __shared__ uint64_t s_src[kSegThreads], s_dst[kSegThreads];
-    __shared__ int s_end[kSegThreads], s_valid[kSegThreads];
+    constexpr uint32_t kBlockBytes = THREADS / kWave * kSegPieceBytes;
+    __shared__ uint64_t s_src[THREADS], s_dst[THREADS];
+    __shared__ int s_end[THREADS], s_valid[THREADS];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     // workgroup b runs on XCD b mod 8; the blocks after the last whole round of runs are taken in order
-    constexpr uint32_t round = kXcds * kSegRunBlocks;
+    constexpr uint32_t run = kSegRunBytes / kBlockBytes, round = kXcds * run;
     uint32_t block = blockIdx.x;
     if (block < gridDim.x / round * round) {
         const uint32_t in = block % round;
-        block += (in % kXcds) * kSegRunBlocks + in / kXcds - in;
+        block += (in % kXcds) * run + in / kXcds - in;
     }
-    const uint64_t base = (uint64_t)block * kSegBlockBytes;
+    const uint64_t base = (uint64_t)block * kBlockBytes;
     const uint64_t piece = base + (uint64_t)wave * kSegPieceBytes;
     // the first probes of the search below are on their way together with the stream's size
     int64_t lo = 0, hi = a.n, step = (a.n + kWave - 1) / kWave;
     uint64_t probe = a.cum[min(lane * step, hi)];
-    const uint64_t total = a.cum[a.n];
+    const uint64_t total = min(a.cum[a.n], a.limit);
     if (base >= total) return;
+    __shared__ int skipped_total, waves_done;
+    if constexpr (SLICES) {
+        if (threadIdx.x == 0) skipped_total = waves_done = 0;
+        __syncthreads();
+    }
     uint64_t *src_at = s_src + wave * kWave, *dst_at = s_dst + wave * kWave;
     int *end = s_end + wave * kWave, *valid = s_valid + wave * kWave;
     u32x4 v[kSegUnits];
@@ -342,19 +360,24 @@ __global__ __launch_bounds__(kSegThreads) void segments_copy_kernel(SegCopyArgs 
     if (skipped) atomicAdd(a.status, skipped);
     if constexpr (SLICES) {
         // A slice counts bytes only once they are in memory: the stores above are write-through at
-        // system scope (sc0 sc1), every thread waits for its own to complete, and only then one thread
-        // adds the bytes the workgroup has really written (skipped units are left out, so a slice with
+        // system scope (sc0 sc1), every wave waits for its own to complete, and the last one of the workgroup
+        // adds the bytes that the workgroup has really written (skipped units are left out, so a slice with
         // holes never reaches its size) with a system-scope atomic.  (A device-wide release fence
-        // would do too, but it writes back the whole L2 of the XCD each time.)
-        __shared__ int skipped_total;
-        if (threadIdx.x == 0) skipped_total = 0;
+        // would do too, but it writes back the whole L2 of the XCD each time.)  In wide workgroups nobody waits for the last wave (in
+        // narrow ones it makes no difference: 124.7 with two barriers, 123.6 without, small slices 18.4 and 18.7).
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
         if (skipped) atomicAdd(&skipped_total, skipped);
-        __syncthreads();
-        if (threadIdx.x == 0) {
+        bool last;
+        if constexpr (THREADS > kSegThreads) {
+            wave_lds_order();   // LDS serves a wave's additions in order: the last wave to arrive finds everybody's skipped units
+            last = lane == 0 && atomicAdd(&waves_done, 1) == THREADS / kWave - 1;
+        } else {
+            __syncthreads();
+            last = threadIdx.x == 0;
+        }
+        if (last) {
             const uint64_t left = total - base;
-            const uint32_t mine = (uint32_t)(left < kSegBlockBytes ? left : kSegBlockBytes);
+            const uint32_t mine = (uint32_t)(left < kBlockBytes ? left : kBlockBytes);
             __hip_atomic_fetch_add(a.slice_fill + base / a.slice_bytes, mine - 16u * (uint32_t)skipped_total,
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
