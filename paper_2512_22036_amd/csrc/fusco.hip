@@ -340,6 +340,19 @@ static bool both_in_transfer_order(const fusco_layout *L, size_t row, int segs)
     return L->D <= 2 && segs == 1 && (L->k >= 8 || row >= kTiledShortRowBytes / 2);
 }
 
+// Both tensors in two calls, the pairs tile by tile and the receive tensors by the token walk: source tensors of 72 MiB and more that are taken in one
+// piece, rows in whole 64-byte units.  They do not stay in the memory-side cache next to what is written for both, and the walk that reads them once
+// more, writing a third of the bytes, is the faster one.  In one launch / two, us, 4 to 8 devices: 9024 tokens x 8 x 8704 B 226 / 202, 8017 x 8 x 12 KiB 196 / 184,
+// 8192 x 8 x 14 KiB 305 / 293 (every token on 4 devices 294 / 267), 6849 x 8 x 17664 B 405 / 338, 11597 x 16 x 11 KiB 568 / 498, with a combine behind it
+// 8454 x 8 x 10432 B 395 / 381, 5579 x 10 x 20 KiB 544 / 514; even 6052 x 16 x 14016 B 332 / 338.  Less source 4096 x 8 x 14 KiB 135 / 137, 8192 x 8 x 8 KiB 148 / 157,
+// 6000 x 10 x 10 KiB 160 / 164; more 9796 x 10 x 13760 B 327 / 365, 20012 x 8 x 8704 B 466 / 450, 14701 x 10 x 13376 B 592 / 636; other rows 8092 x 8 x 14880 B 350 /
+// 393, 9780 x 10 x 10016 B 278 / 309; two devices 8659 x 8 x 12800 B 220 / 248.
+constexpr size_t kSeparateWireBytes = (size_t)72 << 20;
+static bool wire_separately(const fusco_layout *L, size_t source_bytes, bool whole)
+{
+    return whole && L->D > 2 && source_bytes >= kSeparateWireBytes && source_bytes <= g_source_chunk_bytes.load(std::memory_order_relaxed);
+}
+
 // The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or
 // both tensors, the rows of the receive tensors following the pairs of their tile (dispatch_tiled_kernel's WIRE).  Both
 // need the sizes at which the pairs alone are moved that way; both_in_transfer_order says when the receive tensors are.
@@ -440,6 +453,18 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
     // of the expert tensor, or of both tensors, are moved tile by tile in transfer order (dispatch_tiled_kernel).
     if (dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
         const bool tiled_wire = wire;
+        const bool whole = whole_units(d_expert_buf, row_bytes) && whole_units(d_expert_aux, aux_row_bytes) && whole_units(d_send_buf, row_bytes) &&
+                           whole_units(d_send_aux, aux_row_bytes);
+        if (wire && wire_separately(L, (size_t)L->N * (row_bytes + aux_row_bytes), whole)) {
+            const uint32_t stream_flag = streaming ? (uint32_t)FUSCO_DISPATCH_STREAMING : 0u;
+            g_time_start = ev.start;
+            const int rc = fusco_dispatch(L, d_x, row_bytes, d_x_aux, aux_row_bytes, d_expert_buf, d_expert_aux, nullptr, nullptr,
+                                          FUSCO_DISPATCH_EXPERT | stream_flag, stream);
+            if (rc != FUSCO_OK) return rc;
+            g_time_stop = ev.stop;
+            return fusco_dispatch(L, d_x, row_bytes, d_x_aux, aux_row_bytes, nullptr, nullptr, d_send_buf, d_send_aux,
+                                  FUSCO_DISPATCH_WIRE | stream_flag, stream);
+        }
         a.slot_token = L->slot_token; a.tile_slots = L->tile_slots;
         a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
         tiled_shape(L, Ct, threads, cpt, segs, per);
