@@ -154,12 +154,13 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
             else if (at % 8 == 0) launch(short_rows ? plan_direct_kernel<2, 4> : plan_direct_kernel<2, 8>, parts, block, s, a, ev.start, ev.stop);
             else launch(short_rows ? plan_direct_kernel<1, 4> : plan_direct_kernel<1, 8>, parts, block, s, a, ev.start, ev.stop);
         } else if (a.n_chunks == 0) {
-            launch(plan_rank_kernel<true>, dim3(2u * (unsigned)a.n_tiles), block, s, a, ev.start, nullptr);
-            launch(plan_place_kernel<true>, tiles, block, s, a, nullptr, ev.stop);
+            launch(plan_rank_kernel<true, false>, dim3(2u * (unsigned)a.n_tiles), block, s, a, ev.start, nullptr);
+            launch(plan_place_kernel<true, false>, tiles, block, s, a, nullptr, ev.stop);
         } else {
-            launch(plan_rank_kernel<false>, tiles, block, s, a, ev.start, nullptr);
-            launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks), block, s, a);
-            launch(plan_place_kernel<false>, tiles, block, s, a, nullptr, ev.stop);
+            const bool through = a.n_tiles >= kPlanThroughTiles;
+            launch(through ? plan_rank_kernel<false, true> : plan_rank_kernel<false, false>, tiles, block, s, a, ev.start, nullptr);
+            launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks, (unsigned)((a.stride + kChunkColumns - 1) / kChunkColumns)), block, s, a);
+            launch(through ? plan_place_kernel<false, true> : plan_place_kernel<false, false>, tiles, block, s, a, nullptr, ev.stop);
         }
     }
     return launch_status();

@@ -63,6 +63,21 @@ __device__ __forceinline__ uint64_t same_key_lanes(int key, bool part, int nbits
     return (uint64_t)hi << 32 | lo;
 }
 
+// Element i of an array, counted from a place that is the same for all lanes; i is small, so that a 32-bit offset does.
+template <typename T>
+__device__ __forceinline__ T &at(T *base, int i) { return *(T *)((char *)const_cast<std::remove_const_t<T> *>(base) + (uint32_t)i * (uint32_t)sizeof(T)); }
+
+// Stores v there, for runs of lanes next to each other.  THROUGH: through the L2 at once.  What plans of many tiles leave dirty there is only
+// written back when their kernels end (us, plain / through: 65536 tokens x 8 16.0 / 15.1, 131072 x 8 21.4 / 21.0, 200000 x 4 19.4 / 18.8, 100000 x 6 19.8 / 19.5; fewer
+// tiles 30000 x 10, 148 tiles, 15.4 / 16.1, 8192 x 8, 32, 9.7 / 10.2).  Not the arrays indexed by slot, whose runs are shorter than a line (131072 x 8 25.6).
+constexpr int kPlanThroughTiles = 200;
+template <bool THROUGH>
+__device__ __forceinline__ void put(int32_t *base, int i, int v)
+{
+    if constexpr (THROUGH) asm volatile("global_store_dword %0, %1, %2 sc1" ::"v"((uint32_t)i * 4), "v"(v), "s"(base) : "memory");
+    else at(base, i) = v;
+}
+
 // Lanes of a set that come before the calling lane
 __device__ __forceinline__ int lanes_before(uint32_t lo, uint32_t hi) { return (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0)); }
 
@@ -159,7 +174,7 @@ struct Ranking {
     __device__ __forceinline__ void load(const PlanArgs &a, int64_t pair0)
     {
 #pragma unroll
-        for (int r = 0; r < ROUNDS; ++r) raw[r] = r < rounds && held(r) ? a.A[pair0 + pair(a, r)] : -1;
+        for (int r = 0; r < ROUNDS; ++r) raw[r] = r < rounds && held(r) ? at(a.A + pair0, pair(a, r)) : -1;
     }
     // byte[key * kPlanWaves + wave]: the wave's running counts, all zero at the start; returns the number of invalid ids
     __device__ __forceinline__ int rank(const PlanArgs &a, uint8_t *byte)
@@ -216,7 +231,7 @@ struct Ranking {
     }
 };
 
-template <bool HALVED>
+template <bool HALVED, bool THROUGH>
 __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
 {
     __shared__ u32x4 cnt[2 * kMaxBins];   // [key]: a byte per wave, experts then devices
@@ -258,39 +273,52 @@ __global__ __launch_bounds__(kPlanThreads) void plan_rank_kernel(PlanArgs a)
             ew = pack_rank(k.erank[r] + sum_bytes(cnt[e] & earlier), e, false);
             dw = pack_rank(k.drank[r] + sum_bytes(cnt[a.E + d] & earlier), d, k.first[r]);
         }
-        const int64_t p = pair0 + k.pair(a, r);
-        a.pair_slot[p] = ew;
-        a.pair_send_row[p] = dw;
+        put<THROUGH>(a.pair_slot + pair0, k.pair(a, r), ew);
+        put<THROUGH>(a.pair_send_row + pair0, k.pair(a, r), dw);
     }
 }
 
-// Optional pass between counting and placing: sums the per-tile counts over chunks of consecutive
-// tiles.  One workgroup per chunk; the columns are covered 1024 at a time, and where fewer columns
-// than threads remain the tiles of the chunk are split over groups of threads.
+// Optional pass between counting and placing: sums the per-tile counts over chunks of consecutive tiles, and leaves in a tile's row
+// the sums of the chunk's earlier tiles, so that a workgroup of pass 2 reads one row of its chunk.  A workgroup takes kChunkColumns
+// columns of a chunk, its rows split over kChunkParts groups of threads.  Plan, k = 8, 256 experts on 8 devices, us, a workgroup per chunk that left
+// the sums alone (pass 2 added up the chunk's earlier tiles) / so: 65536 tokens 16.6 / 16.1, 131072 24.1 / 21.7; in columns of 64 / 128 100000 x 3 with 60
+// experts on 4 devices 13.9 / 13.2, 131072 x 8 21.1 / 21.0.
+constexpr int kChunkColumns = 2 * kWave, kChunkParts = kPlanThreads / kChunkColumns, kChunkRows = 4;   // kChunkRows: a thread's rows in registers
 __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
 {
-    __shared__ int acc[kPlanThreads];
-    const int tid = threadIdx.x;
-    const int chunk = blockIdx.x;
-    const int t0 = chunk * a.chunk_tiles, t1 = min(t0 + a.chunk_tiles, a.n_tiles);
-    for (int col0 = 0; col0 < a.stride; col0 += kPlanThreads) {
-        const int ncol = min(a.stride - col0, kPlanThreads);
-        const int pad = (ncol + kWave - 1) / kWave * kWave;
-        const int parts = kPlanThreads / pad;
-        const int part = tid / pad, b = tid - part * pad;
-        acc[tid] = 0;
-        __syncthreads();
-        if (part < parts && b < ncol) {
-            const int32_t *h = a.tile_hist + col0 + b;
-            int sum = 0;
-            for (int tl = t0 + part; tl < t1; tl += 8 * parts)   // eight loads in flight, also at the end of the list
+    __shared__ int sum[kChunkParts][kChunkColumns];
+    const int lane = threadIdx.x % kChunkColumns, part = threadIdx.x / kChunkColumns, chunk = blockIdx.x;
+    const int col = blockIdx.y * kChunkColumns + lane;
+    const int each = (a.chunk_tiles + kChunkParts - 1) / kChunkParts;
+    const int end = min((chunk + 1) * a.chunk_tiles, a.n_tiles), t0 = min(chunk * a.chunk_tiles + part * each, end), t1 = min(t0 + each, end);
+    const bool in = col < a.stride;
+    int32_t *const h = a.tile_hist + col;
+    int v[kChunkRows], mine = 0;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) sum += tl + i * parts < t1 ? h[(int64_t)(tl + i * parts) * a.stride] : 0;
-            atomicAdd(&acc[b], sum);
-        }
-        __syncthreads();
-        if (tid < ncol) a.chunk_hist[(int64_t)chunk * a.stride + col0 + tid] = acc[tid];
-        __syncthreads();
+    for (int i = 0; i < kChunkRows; ++i) v[i] = in && t0 + i < t1 ? h[(int64_t)(t0 + i) * a.stride] : 0;
+#pragma unroll
+    for (int i = 0; i < kChunkRows; ++i) mine += v[i];
+    for (int t = t0 + kChunkRows; t < t1; ++t) mine += in ? h[(int64_t)t * a.stride] : 0;
+    sum[part][lane] = mine;
+    __syncthreads();
+    int run = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < kChunkParts; ++q) {
+        const int n = sum[q][lane];
+        total += n;
+        run += q < part ? n : 0;
+    }
+    if (!in) return;
+    if (part == 0) a.chunk_hist[(int64_t)chunk * a.stride + col] = total;
+#pragma unroll
+    for (int i = 0; i < kChunkRows; ++i) {
+        if (t0 + i < t1) h[(int64_t)(t0 + i) * a.stride] = run;
+        run += v[i];
+    }
+    for (int t = t0 + kChunkRows; t < t1; ++t) {
+        const int n = h[(int64_t)t * a.stride];
+        h[(int64_t)t * a.stride] = run;
+        run += n;
     }
 }
 
@@ -299,8 +327,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_chunk_kernel(PlanArgs a)
 // transfer order (its slots ascending: expert by expert, tokens ascending): neighbouring threads then write
 // neighbouring slots of one expert, a few cache lines per wave instead of 64; the pairs meet their place in that
 // order through LDS.  Bound by latency: three barriers between the loads and the stores.  Kernel times of pass 1 + pass 2
-// (and the chunk pass between them), k = 8, us: 8192 tokens 4.8 + 6.3, 131072 tokens 8.3 + 4.1 + 14.0; with a pass 1
-// that only counted and a pass 2 that ranked all pairs: 5.2 + 11.8, 7.0 + 4.2 + 29.9.
+// (and the chunk pass between them), k = 8, us: 8192 tokens 3.8 + 6.4, 131072 tokens 7.7 + 3.1 + 12.6 (8.6 + 3.6 + 13.9 with plain stores and a chunk's
+// earlier tiles added up here); with a pass 1 that only counted and a pass 2 that ranked all pairs: 5.2 + 11.8, 7.0 + 4.2 + 29.9.  With many
+// tiles also bound by instructions: 330 vector instructions a wave, eight waves on a SIMD.
 constexpr int kTilePairs = kMaxRounds * kRoundPairs;
 constexpr int kCross = 12;           // rows of counts that a thread requests before anything else: 36 rows of 256 experts + 8 devices
 constexpr int kMaxChunks = 2 * (kMaxBins / kWave);   // groups of 64 experts, then groups of 64 devices
@@ -351,7 +380,7 @@ struct RowSums {
 // 80 scalar registers: with more than 96 a compute unit holds one workgroup of 16 waves at a time instead of two; with up to
 // 96 (fewer spills) plans of few tiles take the same time (8192 tokens 10.6 us, 10.7 with 80), those of several tiles per
 // compute unit longer (k = 8, 98304 tokens 26.9 us, 23.9 with 80; 131072 tokens 29.0 and 27.1).
-template <bool HALVED>
+template <bool HALVED, bool THROUGH>
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) void plan_place_kernel(PlanArgs a)
 {
     // per group of threads and column: total over all tiles, and over the earlier ones (`before` again holds the place
@@ -375,41 +404,40 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         const int p = r * kPlanThreads + tid;
         ew[r] = dw[r] = -1;
         if (p < npairs) {
-            ew[r] = a.pair_slot[pair0 + p];
-            dw[r] = a.pair_send_row[pair0 + p];
+            ew[r] = at(a.pair_slot + pair0, p);
+            dw[r] = at(a.pair_send_row + pair0, p);
         }
     }
-    // Rows to add up: all tiles; with a chunk level all chunks, and then the tiles of the tile's own chunk before it.
-    // Thread (part, c) takes rows part, part + parts, ... of column c (parts: groups of columns that fit the workgroup)
-    const bool chunked = !HALVED && a.chunk_tiles != 0;
-    const int chunk = chunked ? tile / a.chunk_tiles : 0;
-    const int32_t *rows1 = chunked ? a.chunk_hist : a.tile_hist, *rows2 = a.tile_hist + (int64_t)chunk * a.chunk_tiles * a.stride;
-    const int n1 = chunked ? a.n_chunks : a.n_tiles, limit1 = chunked ? chunk : tile, n2 = chunked ? tile - chunk * a.chunk_tiles : 0;
+    // Rows to add up: all tiles; with a chunk level (not HALVED) all chunks, and the tile's row, which then holds what its chunk's earlier
+    // tiles count.  Thread (part, c) takes rows part, part + parts, ... of column c (parts: groups of columns that fit the workgroup)
+    const int chunk = HALVED ? 0 : tile / a.chunk_tiles;
+    const int32_t *rows1 = HALVED ? a.tile_hist : a.chunk_hist;
+    const int n1 = HALVED ? a.n_tiles : a.n_chunks, limit1 = HALVED ? tile : chunk;
     const int cols = min(nb, kPlanThreads), pad = (cols + kWave - 1) / kWave * kWave, parts = kPlanThreads / pad;
     const int part = tid / pad, c = tid - part * pad;
-    // this tile's own counts of the column that the thread has in the first round of groups below
+    // this tile's own counts: its row, or what the next row of the chunk, or the chunk's, has more than its row
     const int32_t *own_row = a.tile_hist + (int64_t)tile * a.stride;
+    const int32_t *next_row = HALVED ? nullptr : (tile + 1 < min((chunk + 1) * a.chunk_tiles, a.n_tiles) ? own_row + a.stride : a.chunk_hist + (int64_t)chunk * a.stride);
+    const auto own_count = [&](int column) { return HALVED ? own_row[column] : next_row[column] - own_row[column]; };
+    // of the column that the thread has in the first round of groups below
     const int col0 = wave < egroups ? tid : a.E + (wave - egroups) * kWave + lane;
-    const int own0 = col0 < (wave < egroups ? a.E : HALVED ? nb : 0) ? own_row[col0] : 0;
+    const int own0 = col0 < (wave < egroups ? a.E : HALVED ? nb : 0) ? own_count(col0) : 0;
     if (part < parts && c < cols) {
-        RowSums<HALVED> s(rows1, n1, part, parts, limit1, a.stride, c), s2(rows2, n2, part, parts, 0, a.stride, c);
-        int v[kCross], v2[kCross];
+        RowSums<HALVED> s(rows1, n1, part, parts, limit1, a.stride, c);
+        int v[kCross];
         s.load(v, 0);
-        s2.load(v2, 0);
+        const int in_chunk = !HALVED && part == 0 ? own_row[c] : 0;
         s.add(v, 0);
         s.walk(kCross);
-        s2.add(v2, 0);
-        s2.walk(kCross);
         total[part * pad + c] = s.total;   // parts * pad <= 1024
-        before[part * pad + c] = s.before + s2.total;
+        before[part * pad + c] = s.before + in_chunk;
     }
     // the columns beyond the workgroup's kPlanThreads (more than 1024 experts and devices, parts is 1): one thread each
     for (int e = kPlanThreads + tid; e < nb; e += kPlanThreads) {
-        RowSums<HALVED> s(rows1, n1, 0, 1, limit1, a.stride, e), s2(rows2, n2, 0, 1, 0, a.stride, e);
+        RowSums<HALVED> s(rows1, n1, 0, 1, limit1, a.stride, e);
         s.walk(0);
-        s2.walk(0);
         total[e] = s.total;
-        before[e] = s.before + s2.total;
+        before[e] = s.before + (HALVED ? 0 : own_row[e]);
     }
     __syncthreads();
     // Per group of 64 experts or devices, one wave: exclusive sums inside the group
@@ -419,7 +447,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         const bool in = expert ? e < a.E : e < nb;
         int tot = 0, pre = 0, own = 0;
         if (in) {
-            if (HALVED || expert) own = g == wave ? own0 : own_row[e];
+            if (HALVED || expert) own = g == wave ? own0 : own_count(e);
             if constexpr (HALVED) {
                 half_cnt[e] = (uint16_t)own;
                 own = expert ? both_halves(own) : 0;
@@ -470,9 +498,9 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
         }
         slot_of[p] = slot;
         row_of[p] = row;
-        a.pair_slot[pair0 + p] = slot;
-        a.pair_send_row[pair0 + p] = row;
-        a.pair_first[pair0 + p] = first ? 1 : 0;
+        put<THROUGH>(a.pair_slot + pair0, p, slot);
+        put<THROUGH>(a.pair_send_row + pair0, p, row);
+        at(a.pair_first + pair0, p) = first ? 1 : 0;
         if (first) a.send_src[row] = tok0 + div20(p, a.k_magic);
     }
     __syncthreads();
@@ -487,7 +515,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_num_sgpr(80))) 
             a.slot_token[sl] = tok0 + div20(p, a.k_magic);
             a.slot_send_row[sl] = row_of[p];
         }
-        order[q] = sl;
+        put<THROUGH>(order, q, sl);
     }
 
     if (tile == 0) {
