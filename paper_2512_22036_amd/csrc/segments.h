@@ -376,6 +376,7 @@ __global__ __launch_bounds__(THREADS) void segments_copy_kernel(SegCopyArgs a)
             last = threadIdx.x == 0;
         }
         if (last) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // the skipped units are read behind the count of waves, also by the compiler
             const uint64_t left = total - base;
             const uint32_t mine = (uint32_t)(left < kBlockBytes ? left : kBlockBytes);
             __hip_atomic_fetch_add(a.slice_fill + base / a.slice_bytes, mine - 16u * (uint32_t)skipped_total,
