@@ -112,7 +112,8 @@ int fusco_probe_dispatch_occupancy(int wgs);
  * fit this many bytes (at least 8 tiles), each chunk with launches of its own: a sequential read of the chunk's
  * source rows, which leaves them in the 256 MB memory-side cache, then the chunk's tiles.  bytes = 0 only
  * reads the value; otherwise the value is replaced, for the whole process, and the previous one returned.
- * The default is 128 MiB.  The result of fusco_dispatch does not depend on it.
+ * The default is 128 MiB; as long as it is set, calls that write no receive tensors take up to 224 MiB in one
+ * piece (rows of at least 8 KiB).  The result of fusco_dispatch does not depend on it.
  */
 size_t fusco_probe_source_chunk_bytes(size_t bytes);
 

@@ -311,10 +311,24 @@ static bool tiled_shape(const fusco_layout *L, int Ct, int &threads, int &cpt, i
 
 // Tiles that a launch of the tiled dispatch covers: all of them, or, where the source tensor cannot stay in the
 // memory-side cache, as many whole rounds of tiles as have their source rows in half of it.
-static size_t tiles_per_launch(const fusco_layout *L, size_t row)
+//
+// Source tensors of more than kSourceChunkBytes stay in the memory-side cache long enough to be taken in one piece, with the pull and
+// the cap on workgroups, as far as kSourceWholeBytes when nothing but pairs is written past that cache: cutting them reads every source
+// row once more and leaves a last chunk of few tiles.  Steps over changing buffers, in chunks of 128 MiB / in one piece, us: 17000 tokens x 5 x 9 KiB (149
+// MiB) 374 / 333, 20000 x 8 x 8 KiB (156) 545 / 514, 20000 x 6 x 8 KiB 440 / 410, 14000 x 8 x 12 KiB (164) 551 / 529, 20000 x 10 x 10 KiB (195) 829 / 795, 26000 x 7 x 8 KiB
+// (203) 613 / 598, 26000 x 8 x 8208 B 747 / 723; 30000 x 8 x 8 KiB (234) 766 / 765, 24000 x 8 x 14 KiB (328) 1058 / 1090, 32768 x 8 x 14 KiB (448) 1425 / 1501.
+constexpr size_t kSourceWholeBytes = (size_t)224 << 20;
+static bool source_in_chunks(const fusco_layout *L, size_t row, bool wire)
 {
+    const size_t limit = g_source_chunk_bytes.load(std::memory_order_relaxed), source = (size_t)L->N * row;
+    if (limit == kSourceChunkBytes && !wire && row >= kTiledShortRowBytes && source <= kSourceWholeBytes) return false;
+    return source > limit;
+}
+
+static size_t tiles_per_launch(const fusco_layout *L, size_t row, bool wire)
+{
+    if (!source_in_chunks(L, row, wire)) return (size_t)L->tile_count;
     const size_t limit = g_source_chunk_bytes.load(std::memory_order_relaxed);
-    if ((size_t)L->N * row <= limit) return (size_t)L->tile_count;
     const size_t tiles = std::max<size_t>(limit / ((size_t)L->tile_tokens * row) / kXcds, 1) * kXcds;
     return std::min(tiles, (size_t)L->tile_count);
 }
@@ -368,7 +382,7 @@ static bool dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, 
         return false;
     if (wire && (which != 0 || !both_in_transfer_order(L, row_bytes + aux_row_bytes, segs))) return false;
     // a workgroup per entry and segment: the largest launch has to stay below 2^32 threads
-    const uint64_t tiles = (tiles_per_launch(L, row_bytes + aux_row_bytes) + kXcds - 1) / kXcds * kXcds;
+    const uint64_t tiles = (tiles_per_launch(L, row_bytes + aux_row_bytes, wire) + kXcds - 1) / kXcds * kXcds;
     const uint64_t entries = (uint64_t)L->tile_tokens * (uint64_t)(L->k + (wire ? L->D : 0));
     if (tiles * entries * (uint64_t)segs * (uint64_t)threads > 0xffffffffu) return false;
     if (which == 2) return true;
@@ -476,9 +490,8 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
         const uint64_t entries = (uint64_t)a.tile_cap + (tiled_wire ? (uint64_t)L->D * (uint64_t)L->tile_tokens : 0);
         // a source tensor that cannot stay in the memory-side cache is taken in chunks of tiles, every chunk after a
         // sequential read of its source rows (touch_kernel)
-        const size_t source_bytes = (size_t)L->N * (row_bytes + aux_row_bytes);
-        const size_t chunk_tiles = tiles_per_launch(L, row_bytes + aux_row_bytes);
-        const bool chunked = source_bytes > g_source_chunk_bytes.load(std::memory_order_relaxed);
+        const size_t chunk_tiles = tiles_per_launch(L, row_bytes + aux_row_bytes, wire);
+        const bool chunked = source_in_chunks(L, row_bytes + aux_row_bytes, wire);
         const dim3 tblock((unsigned)threads);
         // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
         // taken in chunks, touch_kernel has just read them and the pull only costs (12 KiB segments at 8192 tokens:
