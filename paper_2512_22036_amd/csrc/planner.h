@@ -70,11 +70,13 @@ __device__ __forceinline__ T &at(T *base, int i) { return *(T *)((char *)const_c
 // Stores v there, for runs of lanes next to each other.  THROUGH: through the L2 at once.  What plans of many tiles leave dirty there is only
 // written back when their kernels end (us, plain / through: 65536 tokens x 8 16.0 / 15.1, 131072 x 8 21.4 / 21.0, 200000 x 4 19.4 / 18.8, 100000 x 6 19.8 / 19.5; fewer
 // tiles 30000 x 10, 148 tiles, 15.4 / 16.1, 8192 x 8, 32, 9.7 / 10.2).  Not the arrays indexed by slot, whose runs are shorter than a line (131072 x 8 25.6).
+// A relaxed store at agent scope is that store (global_store_dword ... sc1) in a form that the compiler knows: what it must wait for between writing the
+// base's scalar registers and reading them here it sees for itself, which it would not for an asm statement.
 constexpr int kPlanThroughTiles = 200;
 template <bool THROUGH>
 __device__ __forceinline__ void put(int32_t *base, int i, int v)
 {
-    if constexpr (THROUGH) asm volatile("global_store_dword %0, %1, %2 sc1" ::"v"((uint32_t)i * 4), "v"(v), "s"(base) : "memory");
+    if constexpr (THROUGH) __hip_atomic_store(&at(base, i), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else at(base, i) = v;
 }
 
