@@ -118,6 +118,21 @@ int fusco_probe_dispatch_occupancy(int wgs);
 size_t fusco_probe_source_chunk_bytes(size_t bytes);
 
 /*
+ * Study and test aid, host-only: how fusco_dispatch moves the rows of a call with these row sizes, tensors and flags.  The pointers are
+ * looked at, not followed (where a tensor starts is part of the choice); those that the flags leave out may be NULL, and so may those of a
+ * plane of 0 bytes.  Returns one of the four ways, for the two that walk tokens together with how the walk stores, or a negative FUSCO_ERR_*.
+ */
+#define FUSCO_PROBE_ROUTE_TOKENS 0            /* the token walk */
+#define FUSCO_PROBE_ROUTE_TILES 1             /* the expert tensor tile by tile in transfer order */
+#define FUSCO_PROBE_ROUTE_BOTH_BY_TILES 2     /* both tensors tile by tile */
+#define FUSCO_PROBE_ROUTE_TILES_THEN_TOKENS 3 /* the expert tensor tile by tile, then a token walk for the receive tensors */
+#define FUSCO_PROBE_WALK_PLAIN 0
+#define FUSCO_PROBE_WALK_STREAMING 16         /* non-temporal stores */
+#define FUSCO_PROBE_WALK_THROUGH 32           /* stores through the L2 that stay in the memory-side cache */
+int fusco_probe_dispatch_route(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, const void *d_expert_buf, const void *d_expert_aux,
+                               const void *d_send_buf, const void *d_send_aux, uint32_t flags);
+
+/*
  * Measurement aid: kernel time without stream events between the kernels.  The next fusco_plan,
  * fusco_dispatch (fused modes), fusco_plan_dispatch or fusco_combine call made by the calling thread attaches the two HIP
  * events (hipEvent_t passed as void*, created with timing enabled) to its own kernels: start_event

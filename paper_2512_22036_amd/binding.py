@@ -22,7 +22,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfusco.so")
 
 EXPORTS = ("fusco_version", "fusco_status_string", "fusco_layout_bytes", "fusco_scratch_bytes",
-           "fusco_layout_bind", "fusco_plan", "fusco_plan_static", "fusco_dispatch", "fusco_dispatch_in_transfer_order", "fusco_combine", "fusco_plan_dispatch", "fusco_probe_copy", "fusco_probe_rows", "fusco_probe_pieces", "fusco_probe_consume_slices", "fusco_probe_time_next_call", "fusco_probe_source_chunk_bytes", "fusco_probe_dispatch_kernel", "fusco_probe_dispatch_occupancy", "fusco_probe_dispatch_pull", "fusco_probe_dispatch_walk",
+           "fusco_layout_bind", "fusco_plan", "fusco_plan_static", "fusco_dispatch", "fusco_dispatch_in_transfer_order", "fusco_combine", "fusco_plan_dispatch", "fusco_probe_copy", "fusco_probe_rows", "fusco_probe_pieces", "fusco_probe_consume_slices", "fusco_probe_time_next_call", "fusco_probe_source_chunk_bytes", "fusco_probe_dispatch_kernel", "fusco_probe_dispatch_occupancy", "fusco_probe_dispatch_pull", "fusco_probe_dispatch_walk", "fusco_probe_dispatch_route",
            "fusco_combine_two_hop", "fusco_balance_groups", "fusco_cross_node_load", "fusco_segments_scan", "fusco_segments_copy",
            "fusco_disaggregated_plan", "fusco_disaggregated_dispatch", "fusco_disaggregated_combine")
 
@@ -94,6 +94,8 @@ def load_library() -> ctypes.CDLL:
     lib.fusco_probe_dispatch_walk.argtypes = [ctypes.c_int]
     lib.fusco_probe_dispatch_pull.restype = ctypes.c_int
     lib.fusco_probe_dispatch_pull.argtypes = [ctypes.c_int]
+    lib.fusco_probe_dispatch_route.restype = ctypes.c_int
+    lib.fusco_probe_dispatch_route.argtypes = [ctypes.POINTER(_CLayout), sz, sz, vp, vp, vp, vp, u32]
     lib.fusco_probe_source_chunk_bytes.restype = ctypes.c_size_t
     lib.fusco_probe_source_chunk_bytes.argtypes = [sz]
     lib.fusco_probe_time_next_call.restype = ctypes.c_int
@@ -470,6 +472,21 @@ def fusco_probe_dispatch_pull(which: int = -1) -> int:
     rc = int(load_library().fusco_probe_dispatch_pull(int(which)))
     if rc < 0:
         _check(rc, "fusco_probe_dispatch_pull")
+    return rc
+
+
+ROUTE_TOKENS, ROUTE_TILES, ROUTE_BOTH_BY_TILES, ROUTE_TILES_THEN_TOKENS = 0, 1, 2, 3
+WALK_PLAIN, WALK_STREAMING, WALK_THROUGH = 0, 16, 32
+
+
+def fusco_probe_dispatch_route(layout: Layout, row_bytes: int, aux_row_bytes: int = 0, expert_buf=None, expert_aux=None, send_buf=None, send_aux=None,
+                               flags: int = DISPATCH_EXPERT) -> int:
+    """How fusco_dispatch moves the rows of a call with these sizes and tensors: one of ROUTE_*, for the two that walk tokens together with
+    one of WALK_* for the walk's stores (fusco_probe.h).  Host-only; the tensors are not read."""
+    rc = int(load_library().fusco_probe_dispatch_route(ctypes.byref(layout.c), row_bytes, aux_row_bytes, _ptr(expert_buf), _ptr(expert_aux),
+                                                       _ptr(send_buf), _ptr(send_aux), flags))
+    if rc < 0:
+        _check(rc, "fusco_probe_dispatch_route")
     return rc
 
 

@@ -419,107 +419,103 @@ int fusco_dispatch_in_transfer_order(const fusco_layout *L, size_t row_bytes, si
                                       flags & FUSCO_DISPATCH_TWO_HOP) ? 1 : 0;
 }
 
-int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, const void *d_x_aux,
-                   size_t aux_row_bytes, void *d_expert_buf, void *d_expert_aux, void *d_send_buf,
-                   void *d_send_aux, uint32_t flags, void *stream)
+// Which kernels fusco_dispatch takes for a call: the token walk; the pairs tile by tile; both tensors tile by tile; the pairs tile by tile
+// and the receive tensors by the token walk.
+enum DispatchRoute : int { kByTokens, kByTiles, kBothByTiles, kTilesThenTokens };
+
+// The tensors of a call that passed fusco_dispatch's checks, and what of them it writes.
+struct DispatchCall {
+    const void *x, *x_aux;
+    void *expert_buf, *expert_aux, *send_buf, *send_aux;
+    size_t row_bytes, aux_row_bytes;
+    bool expert, wire, two_hop, streaming;
+};
+
+static int dispatch_flags(uint32_t flags, DispatchCall &c)
 {
-    if (!layout_ok(L)) return FUSCO_ERR_INVALID_ARG;
-    const bool streaming = flags & FUSCO_DISPATCH_STREAMING;
+    c.streaming = flags & FUSCO_DISPATCH_STREAMING;
     flags &= ~FUSCO_DISPATCH_STREAMING;
     if (flags == 0) flags = FUSCO_DISPATCH_EXPERT;
     if (flags & ~(FUSCO_DISPATCH_EXPERT | FUSCO_DISPATCH_WIRE | FUSCO_DISPATCH_TWO_HOP)) return FUSCO_ERR_UNSUPPORTED;
-    const bool two_hop = flags & FUSCO_DISPATCH_TWO_HOP;
-    if (two_hop && streaming) return FUSCO_ERR_UNSUPPORTED;   // the second hop reads the first hop's rows at once
-    if (two_hop) flags |= FUSCO_DISPATCH_EXPERT | FUSCO_DISPATCH_WIRE;   // both tensors are produced
-    const bool expert = flags & FUSCO_DISPATCH_EXPERT, wire = flags & FUSCO_DISPATCH_WIRE;
-    if (row_bytes == 0 || row_bytes % 16 != 0 || aux_row_bytes % 16 != 0) return FUSCO_ERR_INVALID_ARG;
-    if ((row_bytes + aux_row_bytes) / 16 > kMaxRowChunks) return FUSCO_ERR_INVALID_ARG;
-    if (L->N == 0) return FUSCO_OK;   // nothing to move: the (empty) tensors may be NULL
-    if (!d_x || (aux_row_bytes && !d_x_aux)) return FUSCO_ERR_INVALID_ARG;
-    if (expert && (!d_expert_buf || (aux_row_bytes && !d_expert_aux))) return FUSCO_ERR_INVALID_ARG;
-    if (wire && (!d_send_buf || (aux_row_bytes && !d_send_aux))) return FUSCO_ERR_INVALID_ARG;
-    if (!aligned16(d_x) || !aligned16(d_x_aux) || !aligned16(d_expert_buf) || !aligned16(d_expert_aux) ||
-        !aligned16(d_send_buf) || !aligned16(d_send_aux))
-        return FUSCO_ERR_INVALID_ARG;
+    c.two_hop = flags & FUSCO_DISPATCH_TWO_HOP;
+    if (c.two_hop && c.streaming) return FUSCO_ERR_UNSUPPORTED;   // the second hop reads the first hop's rows at once
+    c.expert = c.two_hop || (flags & FUSCO_DISPATCH_EXPERT);      // two hops produce both tensors
+    c.wire = c.two_hop || (flags & FUSCO_DISPATCH_WIRE);
+    return FUSCO_OK;
+}
 
+static DispatchRoute dispatch_route(const fusco_layout *L, const DispatchCall &c)
+{
+    if (!dispatch_in_transfer_order(L, c.row_bytes, c.aux_row_bytes, c.expert, c.wire, c.two_hop)) return kByTokens;
+    if (!c.wire) return kByTiles;
+    const bool whole = whole_units(c.expert_buf, c.row_bytes) && whole_units(c.expert_aux, c.aux_row_bytes) && whole_units(c.send_buf, c.row_bytes) &&
+                       whole_units(c.send_aux, c.aux_row_bytes);
+    return wire_separately(L, (size_t)L->N * (c.row_bytes + c.aux_row_bytes), whole) ? kTilesThenTokens : kBothByTiles;
+}
+
+static DispatchArgs dispatch_args(const fusco_layout *L, const DispatchCall &c)
+{
     DispatchArgs a;
-    a.x = (const u32x4 *)d_x;
-    a.x_aux = (const u32x4 *)d_x_aux;
-    a.expert_buf = (u32x4 *)d_expert_buf; a.expert_aux = (u32x4 *)d_expert_aux;
-    a.send_buf = (u32x4 *)d_send_buf; a.send_aux = (u32x4 *)d_send_aux;
+    a.x = (const u32x4 *)c.x;
+    a.x_aux = (const u32x4 *)c.x_aux;
+    a.expert_buf = (u32x4 *)c.expert_buf; a.expert_aux = (u32x4 *)c.expert_aux;
+    a.send_buf = (u32x4 *)c.send_buf; a.send_aux = (u32x4 *)c.send_aux;
     a.pair_slot = L->pair_slot; a.pair_send_row = L->pair_send_row; a.pair_first = L->pair_first;
     a.slot_token = nullptr; a.tile_slots = nullptr; a.tile_cap = 0; a.tile_tokens = 0; a.N = L->N; a.segs = 1; a.seg_chunks = 0;
     a.k = L->k;
-    a.C = (int32_t)(row_bytes / 16);
-    a.Ca = (int32_t)(aux_row_bytes / 16);
-    a.write_expert = expert && !two_hop; a.write_wire = wire;
-    const int Ct = a.C + a.Ca;
+    a.C = (int32_t)(c.row_bytes / 16);
+    a.Ca = (int32_t)(c.aux_row_bytes / 16);
+    a.write_expert = c.expert && !c.two_hop; a.write_wire = c.wire;
+    return a;
+}
 
-    // token walk: as many column segments as workgroups of 256 threads x 4 chunks need, the chunks spread evenly
-    int segs = (Ct + 1023) / 1024;
-    int per = segs > 1 ? round_up((Ct + segs - 1) / segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
-    int cpt = per >= 512 ? 4 : (per >= 128 ? 2 : 1);
-    int threads = std::min(256, round_up((per + cpt - 1) / cpt, kWave));
-    hipStream_t s = (hipStream_t)stream;
-    ArmedEvents ev;
-    if (two_hop) ev.start = ev.stop = nullptr;   // several kernels: armed events are dropped
-
-    // Enough tiles to keep every XCD busy, and a tile's source rows small enough to stay in one XCD's 4 MB L2: the rows
-    // of the expert tensor, or of both tensors, are moved tile by tile in transfer order (dispatch_tiled_kernel).
-    if (dispatch_in_transfer_order(L, row_bytes, aux_row_bytes, expert, wire, two_hop)) {
-        const bool tiled_wire = wire;
-        const bool whole = whole_units(d_expert_buf, row_bytes) && whole_units(d_expert_aux, aux_row_bytes) && whole_units(d_send_buf, row_bytes) &&
-                           whole_units(d_send_aux, aux_row_bytes);
-        if (wire && wire_separately(L, (size_t)L->N * (row_bytes + aux_row_bytes), whole)) {
-            const uint32_t stream_flag = streaming ? (uint32_t)FUSCO_DISPATCH_STREAMING : 0u;
-            g_time_start = ev.start;
-            const int rc = fusco_dispatch(L, d_x, row_bytes, d_x_aux, aux_row_bytes, d_expert_buf, d_expert_aux, nullptr, nullptr,
-                                          FUSCO_DISPATCH_EXPERT | stream_flag, stream);
-            if (rc != FUSCO_OK) return rc;
-            g_time_stop = ev.stop;
-            return fusco_dispatch(L, d_x, row_bytes, d_x_aux, aux_row_bytes, nullptr, nullptr, d_send_buf, d_send_aux,
-                                  FUSCO_DISPATCH_WIRE | stream_flag, stream);
+// Enough tiles to keep every XCD busy, and a tile's source rows small enough to stay in one XCD's 4 MB L2: the rows
+// of the expert tensor, or of both tensors, are moved tile by tile in transfer order (dispatch_tiled_kernel).
+static int dispatch_tiles(const fusco_layout *L, const DispatchCall &c, hipStream_t s, hipEvent_t start, hipEvent_t stop)
+{
+    DispatchArgs a = dispatch_args(L, c);
+    int threads, cpt, segs, per;
+    tiled_shape(L, a.C + a.Ca, threads, cpt, segs, per);
+    const size_t row = c.row_bytes + c.aux_row_bytes;
+    a.slot_token = L->slot_token; a.tile_slots = L->tile_slots;
+    a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
+    a.segs = segs; a.seg_chunks = per;
+    a.send_off = L->send_off; a.D = L->D;
+    a.through = whole_units(c.expert_buf, c.row_bytes) && (!c.wire || whole_units(c.send_buf, c.row_bytes));
+    a.through_aux = whole_units(c.expert_aux, c.aux_row_bytes) && (!c.wire || whole_units(c.send_aux, c.aux_row_bytes));
+    const uint64_t entries = (uint64_t)a.tile_cap + (c.wire ? (uint64_t)L->D * (uint64_t)L->tile_tokens : 0);
+    // a source tensor that cannot stay in the memory-side cache is taken in chunks of tiles, every chunk after a
+    // sequential read of its source rows (touch_kernel)
+    const size_t chunk_tiles = tiles_per_launch(L, row, c.wire);
+    const bool chunked = source_in_chunks(L, row, c.wire);
+    const dim3 tblock((unsigned)threads);
+    // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
+    // taken in chunks, touch_kernel has just read them and the pull only costs (12 KiB segments at 8192 tokens:
+    // 322 us without it, 332 us with it).  The workgroups per compute unit are capped by the row size where it is taken in one
+    // piece; in chunks the cap costs (32768 tokens of 14 KiB, step, no cap / 8 / 5: 1407 / 1417 / 1570 us).
+    const int occ_knob = g_tiled_occupancy.load(std::memory_order_relaxed);
+    const int pull_knob = g_tiled_pull.load(std::memory_order_relaxed);
+    const bool pull = pull_knob == 0 ? !chunked : pull_knob == 2;
+    const int wgs = occ_knob > 0 ? occ_knob
+                    : (chunked ? 16 : tiled_workgroups_per_cu((size_t)per * 16));
+    const size_t lds = lds_for_occupancy(wgs);
+    for (size_t tile0 = 0; tile0 < (size_t)L->tile_count; tile0 += chunk_tiles) {
+        const size_t tiles_here = std::min(chunk_tiles, (size_t)L->tile_count - tile0);
+        const bool first = tile0 == 0, last = tile0 + tiles_here == (size_t)L->tile_count;
+        if (chunked) {
+            const size_t t0 = tile0 * (size_t)L->tile_tokens;
+            const size_t rows = std::min(tiles_here * (size_t)L->tile_tokens, (size_t)L->N - t0);
+            const size_t n = rows * (size_t)a.C, na = rows * (size_t)a.Ca;
+            launch_args(touch_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, first ? start : nullptr, (hipEvent_t) nullptr,
+                   a.x + t0 * (size_t)a.C, n);
+            if (na)
+                launch_args(touch_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, (hipEvent_t) nullptr, (hipEvent_t) nullptr,
+                       a.x_aux + t0 * (size_t)a.Ca, na);
         }
-        a.slot_token = L->slot_token; a.tile_slots = L->tile_slots;
-        a.tile_cap = L->tile_tokens * L->k; a.tile_tokens = L->tile_tokens;
-        tiled_shape(L, Ct, threads, cpt, segs, per);
-        a.segs = segs; a.seg_chunks = per;
-        a.send_off = L->send_off; a.D = L->D;
-        a.through = whole_units(d_expert_buf, row_bytes) && (!wire || whole_units(d_send_buf, row_bytes));
-        a.through_aux = whole_units(d_expert_aux, aux_row_bytes) && (!wire || whole_units(d_send_aux, aux_row_bytes));
-        const uint64_t entries = (uint64_t)a.tile_cap + (tiled_wire ? (uint64_t)L->D * (uint64_t)L->tile_tokens : 0);
-        // a source tensor that cannot stay in the memory-side cache is taken in chunks of tiles, every chunk after a
-        // sequential read of its source rows (touch_kernel)
-        const size_t chunk_tiles = tiles_per_launch(L, row_bytes + aux_row_bytes, wire);
-        const bool chunked = source_in_chunks(L, row_bytes + aux_row_bytes, wire);
-        const dim3 tblock((unsigned)threads);
-        // A source tensor that is taken in one piece has its rows pulled towards the L2 at the start of every tile;
-        // taken in chunks, touch_kernel has just read them and the pull only costs (12 KiB segments at 8192 tokens:
-        // 322 us without it, 332 us with it).  The workgroups per compute unit are capped by the row size where it is taken in one
-        // piece; in chunks the cap costs (32768 tokens of 14 KiB, step, no cap / 8 / 5: 1407 / 1417 / 1570 us).
-        const int occ_knob = g_tiled_occupancy.load(std::memory_order_relaxed);
-        const int pull_knob = g_tiled_pull.load(std::memory_order_relaxed);
-        const bool pull = pull_knob == 0 ? !chunked : pull_knob == 2;
-        const int wgs = occ_knob > 0 ? occ_knob
-                        : (chunked ? 16 : tiled_workgroups_per_cu((size_t)per * 16));
-        const size_t lds = lds_for_occupancy(wgs);
-        for (size_t tile0 = 0; tile0 < (size_t)L->tile_count; tile0 += chunk_tiles) {
-            const size_t tiles_here = std::min(chunk_tiles, (size_t)L->tile_count - tile0);
-            const bool first = tile0 == 0, last = tile0 + tiles_here == (size_t)L->tile_count;
-            if (chunked) {
-                const size_t t0 = tile0 * (size_t)L->tile_tokens;
-                const size_t rows = std::min(tiles_here * (size_t)L->tile_tokens, (size_t)L->N - t0);
-                const size_t n = rows * (size_t)a.C, na = rows * (size_t)a.Ca;
-                launch_args(touch_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, first ? ev.start : nullptr, (hipEvent_t) nullptr,
-                       a.x + t0 * (size_t)a.C, n);
-                if (na)
-                    launch_args(touch_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, s, (hipEvent_t) nullptr, (hipEvent_t) nullptr,
-                           a.x_aux + t0 * (size_t)a.Ca, na);
-            }
-            const unsigned tblocks = (unsigned)((tiles_here + kXcds - 1) / kXcds) * (unsigned)entries * (unsigned)segs * kXcds;
-            hipEvent_t e0 = first && !chunked ? ev.start : nullptr, e1 = last ? ev.stop : nullptr;
-            const uint32_t tb = (uint32_t)tile0, th = (uint32_t)tiles_here;
-            const dim3 tgrid(tblocks);
+        const unsigned tblocks = (unsigned)((tiles_here + kXcds - 1) / kXcds) * (unsigned)entries * (unsigned)segs * kXcds;
+        hipEvent_t e0 = first && !chunked ? start : nullptr, e1 = last ? stop : nullptr;
+        const uint32_t tb = (uint32_t)tile0, th = (uint32_t)tiles_here;
+        const dim3 tgrid(tblocks);
 #define FUSCO_TILED_AS(CPT, AUX, WIRE)                                                                \
     do {                                                                                              \
         if (pull) launch_args(dispatch_tiled_kernel<CPT, AUX, true, WIRE>, tgrid, tblock, lds, s, e0, e1, a, tb, th);  \
@@ -527,70 +523,151 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
     } while (0)
 #define FUSCO_TILED(CPT)                                                                              \
     do {                                                                                              \
-        if (a.Ca && tiled_wire) FUSCO_TILED_AS(CPT, true, true);                                      \
+        if (a.Ca && c.wire) FUSCO_TILED_AS(CPT, true, true);                                          \
         else if (a.Ca) FUSCO_TILED_AS(CPT, true, false);                                              \
-        else if (tiled_wire) FUSCO_TILED_AS(CPT, false, true);                                        \
+        else if (c.wire) FUSCO_TILED_AS(CPT, false, true);                                            \
         else FUSCO_TILED_AS(CPT, false, false);                                                       \
     } while (0)
-            switch (cpt) {
-            case 1: FUSCO_TILED(1); break;
-            case 2: FUSCO_TILED(2); break;
-            default: FUSCO_TILED(4); break;
-            }
+        switch (cpt) {
+        case 1: FUSCO_TILED(1); break;
+        case 2: FUSCO_TILED(2); break;
+        default: FUSCO_TILED(4); break;
+        }
 #undef FUSCO_TILED
 #undef FUSCO_TILED_AS
-        }
-        return launch_status();
     }
-    if ((uint64_t)L->N * (uint64_t)segs > 0x7fffffffu) return FUSCO_ERR_INVALID_ARG;
-    a.segs = segs; a.seg_chunks = per;
-    const dim3 grid((unsigned)L->N * (unsigned)segs), block((unsigned)threads);
-    {
-        // Loads and stores of the walk (dispatch_kernel's MODE).  Tensors of more than 256 MB in all cannot stay in
-        // the memory-side cache for their reader, and what plain stores leave of them there dirty only slows the
-        // next reader of memory down: they are written with non-temporal stores, as with FUSCO_DISPATCH_STREAMING.
-        // Measured in a dispatch + combine loop whose combine reads another tensor, plain / streaming, % of peak:
-        // 8192 tokens x 8 rows of 14 KiB 67.0 / 74.8, 16384 x 8 x 4 KiB 66.7 / 76.3, 32768 x 2 x 8 KiB 75.0 / 81.9,
-        // 32768 x 4 x 14 KiB 68.6 / 70.5, 65536 x 1 x 8 KiB 73.5 / 75.4; with the combine reading the rows just
-        // written 73.7 / 74.6, 71.1 / 76.2, 76.8 / 77.8, 70.0 / 70.3, 73.4 / 74.8.
-        const size_t row = row_bytes + aux_row_bytes;
-        const size_t written = ((expert && !two_hop ? (size_t)L->P : 0) + (wire ? (size_t)L->send_cap : 0)) * row;
-        const bool stream_stores = streaming || (!two_hop && written > kCacheBytes);   // the second hop reads the rows at once
-        const bool cached_loads = stream_stores && (size_t)L->N * row <= g_source_chunk_bytes.load(std::memory_order_relaxed);
-        const int knob = g_walk_mode.load(std::memory_order_relaxed);
-        const uint64_t groups = (uint64_t)L->N * (uint64_t)segs;
-        const bool eager = groups <= kWalkEagerGroups || (!a.write_expert && eager_send_rows(groups, L->N, L->k, L->D, Ct));
-        const bool through = !stream_stores && !eager && expert && !wire && a.Ca == 0 && walk_through(L->k, row, written);
-        const int mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0) + (through ? 4 : 0);
+    return launch_status();
+}
+
+// Shape, loads and stores of the token walk for a call.
+struct TokenWalk {
+    int threads, cpt, segs, per;
+    bool eager;   // a token's rows without waits between them (dispatch_eager_kernel)
+    int mode;     // dispatch_kernel's MODE
+};
+
+static TokenWalk token_walk(const fusco_layout *L, const DispatchCall &c)
+{
+    TokenWalk w;
+    const int Ct = (int)((c.row_bytes + c.aux_row_bytes) / 16);
+    // as many column segments as workgroups of 256 threads x 4 chunks need, the chunks spread evenly
+    w.segs = (Ct + 1023) / 1024;
+    w.per = w.segs > 1 ? round_up((Ct + w.segs - 1) / w.segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
+    w.cpt = w.per >= 512 ? 4 : (w.per >= 128 ? 2 : 1);
+    w.threads = std::min(256, round_up((w.per + w.cpt - 1) / w.cpt, kWave));
+    // Loads and stores of the walk (dispatch_kernel's MODE).  Tensors of more than 256 MB in all cannot stay in
+    // the memory-side cache for their reader, and what plain stores leave of them there dirty only slows the
+    // next reader of memory down: they are written with non-temporal stores, as with FUSCO_DISPATCH_STREAMING.
+    // Measured in a dispatch + combine loop whose combine reads another tensor, plain / streaming, % of peak:
+    // 8192 tokens x 8 rows of 14 KiB 67.0 / 74.8, 16384 x 8 x 4 KiB 66.7 / 76.3, 32768 x 2 x 8 KiB 75.0 / 81.9,
+    // 32768 x 4 x 14 KiB 68.6 / 70.5, 65536 x 1 x 8 KiB 73.5 / 75.4; with the combine reading the rows just
+    // written 73.7 / 74.6, 71.1 / 76.2, 76.8 / 77.8, 70.0 / 70.3, 73.4 / 74.8.
+    const bool write_expert = c.expert && !c.two_hop;
+    const size_t row = c.row_bytes + c.aux_row_bytes;
+    const size_t written = ((write_expert ? (size_t)L->P : 0) + (c.wire ? (size_t)L->send_cap : 0)) * row;
+    const bool stream_stores = c.streaming || (!c.two_hop && written > kCacheBytes);   // the second hop reads the rows at once
+    const bool cached_loads = stream_stores && (size_t)L->N * row <= g_source_chunk_bytes.load(std::memory_order_relaxed);
+    const int knob = g_walk_mode.load(std::memory_order_relaxed);
+    const uint64_t groups = (uint64_t)L->N * (uint64_t)w.segs;
+    w.eager = groups <= kWalkEagerGroups || (!write_expert && eager_send_rows(groups, L->N, L->k, L->D, Ct));
+    const bool through = !stream_stores && !w.eager && c.expert && !c.wire && c.aux_row_bytes == 0 && walk_through(L->k, row, written);
+    w.mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0) + (through ? 4 : 0);
+    return w;
+}
+
+static int dispatch_tokens(const fusco_layout *L, const DispatchCall &c, hipStream_t s, hipEvent_t start, hipEvent_t stop)
+{
+    const TokenWalk w = token_walk(L, c);
+    if ((uint64_t)L->N * (uint64_t)w.segs > 0x7fffffffu) return FUSCO_ERR_INVALID_ARG;
+    DispatchArgs a = dispatch_args(L, c);
+    a.segs = w.segs; a.seg_chunks = w.per;
+    const dim3 grid((unsigned)L->N * (unsigned)w.segs), block((unsigned)w.threads);
 #define FUSCO_WALK_AS(CPT, MODE)                                                                       \
     do {                                                                                              \
-        if (eager) launch(dispatch_eager_kernel<CPT, MODE>, grid, block, s, a, ev.start, ev.stop);    \
-        else launch(dispatch_kernel<CPT, MODE>, grid, block, s, a, ev.start, ev.stop);                \
+        if (w.eager) launch(dispatch_eager_kernel<CPT, MODE>, grid, block, s, a, start, stop);        \
+        else launch(dispatch_kernel<CPT, MODE>, grid, block, s, a, start, stop);                      \
     } while (0)
 #define FUSCO_WALK(CPT)                                                                               \
-    switch (mode) {                                                                                   \
+    switch (w.mode) {                                                                                 \
     case 0: FUSCO_WALK_AS(CPT, 0); break;                                                             \
     case 1: FUSCO_WALK_AS(CPT, 1); break;                                                             \
     case 2: FUSCO_WALK_AS(CPT, 2); break;                                                             \
-    case 4: launch(dispatch_kernel<CPT, 4>, grid, block, s, a, ev.start, ev.stop); break;             \
+    case 4: launch(dispatch_kernel<CPT, 4>, grid, block, s, a, start, stop); break;                   \
     default: FUSCO_WALK_AS(CPT, 3); break;                                                            \
     }
-        switch (cpt) {
-        case 1: FUSCO_WALK(1); break;
-        case 2: FUSCO_WALK(2); break;
-        default: FUSCO_WALK(4); break;
-        }
+    switch (w.cpt) {
+    case 1: FUSCO_WALK(1); break;
+    case 2: FUSCO_WALK(2); break;
+    default: FUSCO_WALK(4); break;
+    }
 #undef FUSCO_WALK
 #undef FUSCO_WALK_AS
-    }
-    if (two_hop) {
+    if (c.two_hop) {
         // second hop: every row of the expert tensor is pulled from its token's row in the receive
         // tensor of the expert's device (level-2 send descriptor), over the exp_off[E] assigned rows
-        launch_gather<false>(d_send_buf, d_expert_buf, L->slot_send_row, nullptr, L->exp_off + L->E, L->P, a.C, s);
+        launch_gather<false>(c.send_buf, c.expert_buf, L->slot_send_row, nullptr, L->exp_off + L->E, L->P, a.C, s);
         if (a.Ca)
-            launch_gather<false>(d_send_aux, d_expert_aux, L->slot_send_row, nullptr, L->exp_off + L->E, L->P, a.Ca, s);
+            launch_gather<false>(c.send_aux, c.expert_aux, L->slot_send_row, nullptr, L->exp_off + L->E, L->P, a.Ca, s);
     }
     return launch_status();
+}
+
+// The parts of a call whose pairs are moved tile by tile and whose receive tensors by a token walk of their own.
+static DispatchCall pairs_of(DispatchCall c)
+{
+    c.wire = false;
+    return c;
+}
+static DispatchCall send_rows_of(DispatchCall c)
+{
+    c.expert = false;
+    return c;
+}
+
+int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, const void *d_x_aux,
+                   size_t aux_row_bytes, void *d_expert_buf, void *d_expert_aux, void *d_send_buf,
+                   void *d_send_aux, uint32_t flags, void *stream)
+{
+    if (!layout_ok(L)) return FUSCO_ERR_INVALID_ARG;
+    DispatchCall c = {d_x, d_x_aux, d_expert_buf, d_expert_aux, d_send_buf, d_send_aux, row_bytes, aux_row_bytes, false, false, false, false};
+    const int rc = dispatch_flags(flags, c);
+    if (rc != FUSCO_OK) return rc;
+    if (row_bytes == 0 || row_bytes % 16 != 0 || aux_row_bytes % 16 != 0) return FUSCO_ERR_INVALID_ARG;
+    if ((row_bytes + aux_row_bytes) / 16 > kMaxRowChunks) return FUSCO_ERR_INVALID_ARG;
+    if (L->N == 0) return FUSCO_OK;   // nothing to move: the (empty) tensors may be NULL
+    if (!d_x || (aux_row_bytes && !d_x_aux)) return FUSCO_ERR_INVALID_ARG;
+    if (c.expert && (!d_expert_buf || (aux_row_bytes && !d_expert_aux))) return FUSCO_ERR_INVALID_ARG;
+    if (c.wire && (!d_send_buf || (aux_row_bytes && !d_send_aux))) return FUSCO_ERR_INVALID_ARG;
+    if (!aligned16(d_x) || !aligned16(d_x_aux) || !aligned16(d_expert_buf) || !aligned16(d_expert_aux) ||
+        !aligned16(d_send_buf) || !aligned16(d_send_aux))
+        return FUSCO_ERR_INVALID_ARG;
+
+    hipStream_t s = (hipStream_t)stream;
+    ArmedEvents ev;
+    if (c.two_hop) ev.start = ev.stop = nullptr;   // several kernels: armed events are dropped
+    switch (dispatch_route(L, c)) {
+    case kByTokens: return dispatch_tokens(L, c, s, ev.start, ev.stop);
+    case kTilesThenTokens: {
+        const int pairs = dispatch_tiles(L, pairs_of(c), s, ev.start, nullptr);
+        return pairs != FUSCO_OK ? pairs : dispatch_tokens(L, send_rows_of(c), s, nullptr, ev.stop);
+    }
+    default: return dispatch_tiles(L, c, s, ev.start, ev.stop);
+    }
+}
+
+int fusco_probe_dispatch_route(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, const void *d_expert_buf, const void *d_expert_aux,
+                               const void *d_send_buf, const void *d_send_aux, uint32_t flags)
+{
+    if (!layout_ok(L) || row_bytes == 0 || row_bytes % 16 != 0 || aux_row_bytes % 16 != 0 || (row_bytes + aux_row_bytes) / 16 > kMaxRowChunks)
+        return FUSCO_ERR_INVALID_ARG;
+    DispatchCall c = {nullptr, nullptr, (void *)d_expert_buf, (void *)d_expert_aux, (void *)d_send_buf, (void *)d_send_aux, row_bytes, aux_row_bytes,
+                      false, false, false, false};
+    const int rc = dispatch_flags(flags, c);
+    if (rc != FUSCO_OK) return rc;
+    const DispatchRoute route = dispatch_route(L, c);
+    if (route == kByTiles || route == kBothByTiles) return route;
+    const int mode = token_walk(L, route == kByTokens ? c : send_rows_of(c)).mode;
+    return route | (mode & 4 ? FUSCO_PROBE_WALK_THROUGH : mode & 2 ? FUSCO_PROBE_WALK_STREAMING : FUSCO_PROBE_WALK_PLAIN);
 }
 
 int fusco_combine(const fusco_layout *L, const void *d_y, int y_dtype, const float *d_w, void *d_out,

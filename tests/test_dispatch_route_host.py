@@ -1,0 +1,62 @@
+"""How fusco_dispatch moves the rows of a call, as the library's host-only query tells it from sizes, flags and the places of the tensors:
+no GPU is needed, nothing is launched, the pointers are never followed."""
+import ctypes
+
+import pytest
+
+EXPERT, WIRE, TWO_HOP, STREAMING = 1, 2, 4, 8
+TOKENS, TILES, BOTH, SEPARATE = 0, 1, 2, 3
+PLAIN, NONTEMPORAL, THROUGH = 0, 16, 32
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def route():
+    import os
+
+    from paper_2512_22036_amd import binding
+    if not os.path.exists(binding.library_path()):
+        from paper_2512_22036_amd.build import build_library
+        build_library()
+    lib = binding.load_library()
+    assert (binding.ROUTE_TOKENS, binding.ROUTE_TILES, binding.ROUTE_BOTH_BY_TILES, binding.ROUTE_TILES_THEN_TOKENS) == (TOKENS, TILES, BOTH, SEPARATE)
+    assert (binding.WALK_PLAIN, binding.WALK_STREAMING, binding.WALK_THROUGH) == (PLAIN, NONTEMPORAL, THROUGH)
+
+    def ask(N, k, E, D, row, aux=0, flags=0, at=0x10000000, wire_at=0x20000000, aux_at=0x30000000):
+        L = binding._CLayout()
+        assert lib.fusco_layout_bind(ctypes.byref(L), N, k, E, D, 0x10000000, lib.fusco_layout_bytes(N, k, E, D)) == 0
+        return lib.fusco_probe_dispatch_route(ctypes.byref(L), row, aux, at, aux_at if aux else None, wire_at, aux_at if aux else None, flags)
+
+    ask.lib = lib
+    return ask
+
+
+def test_route_agrees_with_the_transfer_order_query(route):
+    from paper_2512_22036_amd import binding
+    lib = route.lib
+    for N, k, E, D, row in ((8192, 8, 256, 8, 14336), (1000, 8, 256, 8, 14336), (8192, 4, 64, 8, 8192), (20000, 8, 128, 16, 8192), (32768, 8, 256, 8, 14336)):
+        L = binding._CLayout()
+        assert lib.fusco_layout_bind(ctypes.byref(L), N, k, E, D, 0x10000000, lib.fusco_layout_bytes(N, k, E, D)) == 0
+        for flags in (0, EXPERT, WIRE, EXPERT | WIRE, TWO_HOP, EXPERT | STREAMING, EXPERT | WIRE | STREAMING):
+            tiled = lib.fusco_dispatch_in_transfer_order(ctypes.byref(L), row, 0, flags)
+            assert (route(N, k, E, D, row, 0, flags) & 15 != TOKENS) == bool(tiled), (N, row, flags)
+
+
+def test_stores_of_the_token_walk(route):
+    assert route(4096, 8, 64, 8, 4096) == TOKENS | PLAIN                      # 128 MiB of rows: they stay for their reader
+    assert route(4096, 8, 64, 8, 4096, 0, STREAMING) == TOKENS | NONTEMPORAL
+    assert route(40000, 1, 64, 8, 8192) == TOKENS | NONTEMPORAL               # 312 MiB, one entry per token
+    assert route(40000, 1, 64, 8, 8192, 0, TWO_HOP) == TOKENS | PLAIN         # the second hop reads the first one's rows
+    knob = route.lib.fusco_probe_dispatch_walk
+    for setting, stores in ((1, PLAIN), (2, PLAIN), (3, NONTEMPORAL), (4, NONTEMPORAL)):
+        assert knob(setting) == 0
+        try:
+            assert route(40000, 1, 64, 8, 8192) == TOKENS | stores
+        finally:
+            assert knob(0) == setting
+
+
+def test_bad_arguments(route):
+    assert route(8192, 8, 256, 8, 0) < 0 and route(8192, 8, 256, 8, 24) < 0 and route(8192, 8, 256, 8, 16, 8) < 0
+    assert route(8192, 8, 256, 8, 1 << 21) < 0 and route(8192, 8, 256, 8, 16, 0, 16) < 0 and route(8192, 8, 256, 8, 16, 0, TWO_HOP | STREAMING) < 0
+    assert route.lib.fusco_probe_dispatch_route(None, 16, 0, None, None, None, None, 0) < 0
