@@ -32,3 +32,55 @@ def test_bench_reads_its_traffic_figures_from_the_summary():
     assert algorithmic <= got["dispatch"] <= 1.01 * algorithmic, got
     assert bench.measured_traffic("qwen3") == {}          # no summary for other workloads: reported as null
     assert "MEASURED_TRAFFIC_BYTES" not in open(os.path.join(ROOT, "bench.py")).read()
+
+
+def table_rows(heading):
+    """The rows of the first table behind a heading of the design notes, as lists of cells by the first cell's first word."""
+    text = open(os.path.join(ROOT, "DESIGN.md")).read()
+    lines = iter(text[text.index("\n" + heading) + 1:].split("\n")[1:])
+    line = next(lines)
+    while not line.startswith("|"):
+        line = next(lines)
+    width, rows = line.count("|"), {}
+    next(lines)
+    for line in lines:
+        if not line.startswith("|"):
+            break
+        assert line.count("|") == width, line
+        cells = [c.strip() for c in line.strip("|").split("|")]
+        rows[cells[0].split()[0]] = cells[1:]
+    return rows
+
+
+def test_input_table_describes_the_configurations():
+    import workloads
+    rows = table_rows("## 4. Synthetic inputs")
+    assert set(rows) == set(workloads.CONFIGS)
+    for name, (n, hidden, ekd, *_) in rows.items():
+        cfg = workloads.CONFIGS[name]
+        assert int(n) == cfg.N and int(hidden.split()[0]) == cfg.H, name
+        assert [int(v) for v in ekd.split("/")] == [cfg.E, cfg.k, cfg.D], name
+
+
+def test_configuration_table_holds_the_measured_summary():
+    import workloads
+    summary = open(os.path.join(ROOT, "profiles", "bench_all_configs.txt")).read()
+    rows = table_rows("### 6.6 All five configurations")
+    assert set(rows) == set(workloads.CONFIGS)
+
+    def span(cell):   # "1.5–2.5" or "1.5", in the notes or the summary; a span of equal ends is written either way
+        ends = [float(v) for v in re.split("[-–]", cell)]
+        return ends[0], ends[-1]
+
+    for name, (step, rate, plan, dispatch, combine, share) in rows.items():
+        m = re.search(rf"^{name}  +(\S+)  +(\S+)  +(\S+)  +(\S+)  +(\S+)$", summary, flags=re.M)
+        assert m, f"no row of {name} in the summary"
+        assert [span(c) for c in (step, dispatch, combine, plan)] == [span(m.group(i)) for i in (1, 2, 3, 5)], name
+        per_us = [workloads.CONFIGS[name].N / v for v in reversed(span(m.group(1)))]
+        figure = rate.split()[0].split("–")
+        for cell, want in zip((figure[0], figure[-1]), per_us):
+            # both are rounded to their last digit: N / step of the summary, whose steps are given to 0.1 us
+            digit = 10.0 ** -len(cell.partition(".")[2])
+            assert abs(float(cell) - want) <= 0.5 * digit + want * want / workloads.CONFIGS[name].N * 0.05 + 1e-9, (name, rate)
+        if not share.startswith("latency"):
+            assert span(share.split()[0]) == span(m.group(4)), name
