@@ -192,7 +192,7 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
  * come with a source tensor of at most 128 MiB (less than 128 MiB for rows shorter than 4 KiB), and a source
  * tensor of more than 128 MiB comes with k >= 8, or with k >= 5 and rows that need no column segments.  Calls that
  * write the receive tensors as well have it on top of that with k >= 8, at most 8 devices and rows of at least 8 KiB,
- * or with at most 2 devices and rows that need no column segments (of at least 4 KiB for k < 8); with more than 2 devices and
+ * or with at most 2 devices and rows that need no column segments (of at least 4 KiB for k < 8); with at least 4 devices and
  * 72 to 128 MiB of source rows in whole 64-byte units the receive tensors are then written by a token walk of their own.  All ways write
  * the same bytes.
  */

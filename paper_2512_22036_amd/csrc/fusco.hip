@@ -361,11 +361,13 @@ static bool both_in_transfer_order(const fusco_layout *L, size_t row, int segs)
 // 8192 x 8 x 14 KiB 305 / 293 (every token on 4 devices 294 / 267), 6849 x 8 x 17664 B 405 / 338, 11597 x 16 x 11 KiB 568 / 498, with a combine behind it
 // 8454 x 8 x 10432 B 395 / 381, 5579 x 10 x 20 KiB 544 / 514; even 6052 x 16 x 14016 B 332 / 338.  Less source 4096 x 8 x 14 KiB 135 / 137, 8192 x 8 x 8 KiB 148 / 157,
 // 6000 x 10 x 10 KiB 160 / 164; more 9796 x 10 x 13760 B 327 / 365, 20012 x 8 x 8704 B 466 / 450, 14701 x 10 x 13376 B 592 / 636; other rows 8092 x 8 x 14880 B 350 /
-// 393, 9780 x 10 x 10016 B 278 / 309; two devices 8659 x 8 x 12800 B 220 / 248.
+// 393, 9780 x 10 x 10016 B 278 / 309; two devices 8659 x 8 x 12800 B 220 / 248; three, whose send rows of up to 85 MiB of source would fit the memory-side
+// cache and be written plain, 9216 x 8 x 8 KiB with the plan 148 / 185 (161 past the cache), 9300 x 8 x 14 KiB 287 / 297.  With four (and 8 or more
+// entries) there is room for at least 288 MiB of send rows, which the walk writes past that cache as the tiles do.
 constexpr size_t kSeparateWireBytes = (size_t)72 << 20;
 static bool wire_separately(const fusco_layout *L, size_t source_bytes, bool whole)
 {
-    return whole && L->D > 2 && source_bytes >= kSeparateWireBytes && source_bytes <= g_source_chunk_bytes.load(std::memory_order_relaxed);
+    return whole && L->D >= 4 && source_bytes >= kSeparateWireBytes && source_bytes <= g_source_chunk_bytes.load(std::memory_order_relaxed);
 }
 
 // The conditions under which fusco_dispatch moves the rows tile by tile in transfer order: the expert tensor alone, or

@@ -56,6 +56,22 @@ def test_stores_of_the_token_walk(route):
             assert knob(0) == setting
 
 
+def test_both_tensors_in_two_launches_from_four_devices_on(route):
+    flags = EXPERT | WIRE
+    for N, row in ((9216, 8256), (9000, 9216), (9300, 14336)):   # 72 to 128 MiB of source
+        for D in (1, 2, 3):
+            assert route(N, 8, 96, D, row, 0, flags) & 15 != SEPARATE, (N, D)
+        assert route(N, 8, 96, 3, row, 0, flags) == BOTH
+        for D in (4, 6, 8):   # the send rows go past the memory-side cache, with the flag and without
+            assert route(N, 8, 96, D, row, 0, flags) == route(N, 8, 96, D, row, 0, flags | STREAMING) == SEPARATE | NONTEMPORAL
+        assert route(N, 8, 96, 8, row + 16, 0, flags) == BOTH                       # rows of partial units
+        assert route(N, 8, 96, 8, row, 0, flags, at=0x10000010) == BOTH
+        assert route(N, 8, 96, 8, row, 0, flags, wire_at=0x20000020) == BOTH
+    assert route(9139, 8, 96, 8, 8256, 0, flags) == BOTH                             # just below 72 MiB
+    assert route(16256, 8, 96, 8, 8256, 0, flags) == SEPARATE | NONTEMPORAL          # just below 128 MiB
+    assert route(16257, 8, 96, 8, 8256, 0, flags) == BOTH
+
+
 def test_bad_arguments(route):
     assert route(8192, 8, 256, 8, 0) < 0 and route(8192, 8, 256, 8, 24) < 0 and route(8192, 8, 256, 8, 16, 8) < 0
     assert route(8192, 8, 256, 8, 1 << 21) < 0 and route(8192, 8, 256, 8, 16, 0, 16) < 0 and route(8192, 8, 256, 8, 16, 0, TWO_HOP | STREAMING) < 0

@@ -10,10 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("N,D,row_bytes,aux_bytes", [(9215, 8, 8192, 0), (9216, 8, 8192, 0), (9216, 8, 8192 + 16, 0), (9216, 2, 8192, 0), (9145, 4, 8192, 64),
-                                                     (9145, 4, 8192, 80), (5000, 8, 16384, 0), (8192, 8, 16384, 0), (8193, 8, 16384, 0)])
+                                                     (9145, 4, 8192, 80), (5000, 8, 16384, 0), (8192, 8, 16384, 0), (8193, 8, 16384, 0),
+                                                     (9216, 3, 8192, 0), (9300, 3, 9216, 64)])
 def test_both_tensors(N, D, row_bytes, aux_bytes):
     import paper_2512_22036_amd as f
-    k, E = 8, 64
+    k, E = 8, 64 if D != 3 else 48
     A = random_topk(np.random.default_rng(N + row_bytes), N, k, E)
     A[N // 3, 2] = -1   # an entry without an expert
     L = f.Layout(N, k, E, D)
