@@ -58,7 +58,7 @@ def test_stores_of_the_token_walk(route):
 
 def test_both_tensors_in_two_launches_from_four_devices_on(route):
     flags = EXPERT | WIRE
-    for N, row in ((9216, 8256), (9000, 9216), (9300, 14336)):   # 72 to 128 MiB of source
+    for N, row in ((9216, 8256), (9000, 9280), (9300, 14336)):   # 72 to 128 MiB of source
         for D in (1, 2, 3):
             assert route(N, 8, 96, D, row, 0, flags) & 15 != SEPARATE, (N, D)
         assert route(N, 8, 96, 3, row, 0, flags) == BOTH
@@ -70,6 +70,20 @@ def test_both_tensors_in_two_launches_from_four_devices_on(route):
     assert route(9139, 8, 96, 8, 8256, 0, flags) == BOTH                             # just below 72 MiB
     assert route(16256, 8, 96, 8, 8256, 0, flags) == SEPARATE | NONTEMPORAL          # just below 128 MiB
     assert route(16257, 8, 96, 8, 8256, 0, flags) == BOTH
+
+
+def test_both_tensors_of_rows_that_fill_their_workgroups_in_two_launches_from_112_mib_on(route):
+    flags = EXPERT | WIRE
+    for row, devices in ((8192, (4, 5, 6, 8)), (10240, (4, 5)), (11264, (4, 5)), (12288, (4, 5, 6, 8))):
+        first = -(-(112 * MIB) // row)
+        for D in devices:
+            E = D * 16
+            assert route(first - 1, 8, E, D, row, 0, flags) == route(73 * MIB // row, 8, E, D, row, 0, flags) == BOTH
+            assert route(first, 8, E, D, row, 0, flags) == route(128 * MIB // row, 8, E, D, row, 0, flags) == SEPARATE | NONTEMPORAL
+            assert route(first - 1, 8, E, D, row - 64, 64, flags) == BOTH            # both planes together
+    for row, devices in ((8256, (4, 8)), (9216, (4, 8)), (10176, (4, 8)), (10240, (6, 8)), (12224, (6, 8)), (12352, (4, 8)), (14336, (4, 8)), (16384, (4, 8))):
+        for D in devices:
+            assert route(73 * MIB // row, 8, D * 16, D, row, 0, flags) == SEPARATE | NONTEMPORAL
 
 
 def test_bad_arguments(route):

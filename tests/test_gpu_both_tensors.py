@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,D,row_bytes,aux_bytes", [(9215, 8, 8192, 0), (9216, 8, 8192, 0), (9216, 8, 8192 + 16, 0), (9216, 2, 8192, 0), (9145, 4, 8192, 64),
                                                      (9145, 4, 8192, 80), (5000, 8, 16384, 0), (8192, 8, 16384, 0), (8193, 8, 16384, 0),
-                                                     (9216, 3, 8192, 0), (9300, 3, 9216, 64)])
+                                                     (9216, 3, 8192, 0), (9300, 3, 9216, 64), (14335, 8, 8192, 0), (14336, 8, 8192, 0),
+                                                     (9216, 4, 8256, 0), (7500, 4, 10240 - 64, 64)])
 def test_both_tensors(N, D, row_bytes, aux_bytes):
     import paper_2512_22036_amd as f
     k, E = 8, 64 if D != 3 else 48
@@ -42,7 +43,7 @@ def test_two_launches_of_one_call(streaming):
     """A call that writes the receive tensors by a launch of their own: armed events span both launches and are used up by the one call, and
     the streaming flag changes no byte."""
     import paper_2512_22036_amd as f
-    N, k, E, D, row = 11521, 8, 64, 8, 8192
+    N, k, E, D, row = 11521, 8, 64, 8, 8192 + 64   # rows of 8 KiB are not taken in two launches at this size
     flags = f.DISPATCH_EXPERT | f.DISPATCH_WIRE | (f.DISPATCH_STREAMING if streaming else 0)
     L = f.Layout(N, k, E, D)
     f.fusco_plan(L, torch.from_numpy(random_topk(np.random.default_rng(5), N, k, E)).cuda())
