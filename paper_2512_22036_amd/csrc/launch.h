@@ -232,6 +232,24 @@ int combine_first_row(int N, int k, size_t row_bytes)
 // (14336 B: 380 against 401 us with combine, 14400 B: 388 against 413 us).
 bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_bytes) & 63u) == 0; }
 
+// Stores of the token walk where nothing but one plane of the expert tensor is written, up to the size of the memory-side cache (bit 2 of dispatch_kernel's
+// MODE).  What plain stores leave dirty in the L2s is written back when the kernel ends, up to 32 MB that then go to memory with nothing else
+// on its way; rows written through go there at once.  The memory-side cache keeps both.  Plain / through, us, dispatch and a combine of
+// another tensor, and with the combine of the rows:
+// - one entry per token from kThroughBytesOne on: 9323 x 1600 B (14 MiB) 15.3 / 14.8, 15.5 / 14.9; 1993 x 24064 B 37.9 / 35.7, 35.3 / 33.2; 15616 x 7024 B
+//   87.9 / 85.1, 78.4 / 77.4; 13709 x 14 KiB 146 / 143, 120 / 117; 4127 x 1040 B (4 MiB) 7.9 / 8.1, 8.5 / 8.2;
+// - two and three from kThroughBytesFew on, rows of whole lines (128 bytes): 1191 x 2 x 4608 B 9.6 / 9.3, 8.8 / 9.2; 1605 x 2 x 5312 B 13.3 / 12.6, 13.0 / 13.1;
+//   4096 x 2 x 2 KiB 12.1 / 11.2; 6128 x 3 x 4 KiB 39.7 / 38.3, 36.1 / 34.6; 24291 x 2 x 4 KiB 107 / 106, 90 / 89; other rows 3146 x 2 x 3776 B 15.3 / 15.6, 20720
+//   x 2 x 5744 B 141 / 151; smaller 1832 x 2 x 2304 B 8.4 / 8.7; the tensor 16 bytes past a unit 20720 x 2 x 5760 B 129 / 140, 6128 x 3 x 4 KiB 43.5 / 49.7, 64
+//   bytes past a line 126 / 124, 41.0 / 40.8 (one entry per token, 16 bytes past, even: 15616 x 7 KiB 82.4 / 80.6, 84.7 / 85.3);
+// - more entries come out even or lose: 9515 x 4 x 1 KiB 20.1 / 20.5, 4990 x 6 x 512 B 11.6 / 12.0, 2827 x 8 x 1344 B 15.5 / 15.7.
+constexpr size_t kThroughBytesOne = (size_t)8 << 20, kThroughBytesFew = (size_t)10 << 20;
+inline bool walk_through(int k, const void *rows, size_t row, size_t written)
+{
+    if (k == 1) return written >= kThroughBytesOne;
+    return k <= 3 && written >= kThroughBytesFew && row % 128 == 0 && whole_units(rows, row);
+}
+
 // Stores of combine's output rows.
 // Large outputs of inputs that are bound by memory go past the memory-side cache: what write-through and plain stores leave
 // dirty there costs the reads of the kernels around them more than it saves.  Steps with the experts' output in a tensor of

@@ -56,6 +56,16 @@ def test_stores_of_the_token_walk(route):
             assert knob(0) == setting
 
 
+def test_rows_written_through_start_at_whole_units(route):
+    for k in (2, 3):
+        args = (12288, k, 64, 8, 4096)
+        assert route(*args) == route(*args, at=0x10000040) == route(*args, at=0x10000080) == TOKENS | THROUGH
+        for shift in (16, 32, 48, 80):   # stores of a wave would cover parts of units
+            assert route(*args, at=0x10000000 + shift) == TOKENS | PLAIN
+        assert route(12288, k, 64, 8, 4096 + 64) == TOKENS | PLAIN   # not rows of whole lines
+    assert route(24576, 1, 64, 8, 4096, at=0x10000010) == TOKENS | THROUGH   # one entry per token: either way
+
+
 def test_both_tensors_in_two_launches_from_four_devices_on(route):
     flags = EXPERT | WIRE
     for N, row in ((9216, 8256), (9000, 9280), (9300, 14336)):   # 72 to 128 MiB of source

@@ -55,3 +55,15 @@ def test_token_walk(N, k, row_bytes):
     assert not f.fusco_dispatch_in_transfer_order(L, row_bytes)
     f.fusco_dispatch(L, planes["x"], planes["expert_buf"])
     check(L, planes)
+
+
+# two and three entries: only from a whole 64-byte unit on; one entry from anywhere
+@pytest.mark.parametrize("N,k,row_bytes,shift,through", [(12288, 2, 4096, 16, False), (12288, 2, 4096, 64, True), (9000, 3, 4224, 48, False), (9000, 3, 4224, 0, True),
+                                                         (24577, 1, 2048, 16, True)])
+def test_token_walk_from_any_place(N, k, row_bytes, shift, through):
+    f, L, A, planes = setup(N, k, 64, 8, row_bytes, 0, shift)
+    f.fusco_plan(L, A)
+    route = f.fusco_probe_dispatch_route(L, row_bytes, expert_buf=planes["expert_buf"])
+    assert route == f.ROUTE_TOKENS | (f.WALK_THROUGH if through else f.WALK_PLAIN)
+    f.fusco_dispatch(L, planes["x"], planes["expert_buf"])
+    check(L, planes)
