@@ -585,7 +585,7 @@ static TokenWalk token_walk(const fusco_layout *L, const DispatchCall &c)
     const int knob = g_walk_mode.load(std::memory_order_relaxed);
     const uint64_t groups = (uint64_t)L->N * (uint64_t)w.segs;
     w.eager = groups <= kWalkEagerGroups || (!write_expert && eager_send_rows(groups, L->N, L->k, L->D, Ct));
-    const bool through = !stream_stores && !w.eager && c.expert && !c.wire && c.aux_row_bytes == 0 && walk_through(L->k, c.expert_buf, row, written);
+    const bool through = !stream_stores && !w.eager && c.expert && !c.wire && c.aux_row_bytes == 0 && walk_through(L->k, c.expert_buf, row, (size_t)L->N * row, written);
     w.mode = knob > 0 ? knob - 1 : (stream_stores ? 2 : 0) + (cached_loads ? 1 : 0) + (through ? 4 : 0);
     return w;
 }

@@ -234,20 +234,23 @@ bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_
 
 // Stores of the token walk where nothing but one plane of the expert tensor is written, up to the size of the memory-side cache (bit 2 of dispatch_kernel's
 // MODE).  What plain stores leave dirty in the L2s is written back when the kernel ends, up to 32 MB that then go to memory with nothing else
-// on its way; rows written through go there at once.  The memory-side cache keeps both.  Plain / through, us, dispatch and a combine of
-// another tensor, and with the combine of the rows:
-// - one entry per token from kThroughBytesOne on: 9323 x 1600 B (14 MiB) 15.3 / 14.8, 15.5 / 14.9; 1993 x 24064 B 37.9 / 35.7, 35.3 / 33.2; 15616 x 7024 B
-//   87.9 / 85.1, 78.4 / 77.4; 13709 x 14 KiB 146 / 143, 120 / 117; 4127 x 1040 B (4 MiB) 7.9 / 8.1, 8.5 / 8.2;
-// - two and three from kThroughBytesFew on, rows of whole lines (128 bytes): 1191 x 2 x 4608 B 9.6 / 9.3, 8.8 / 9.2; 1605 x 2 x 5312 B 13.3 / 12.6, 13.0 / 13.1;
-//   4096 x 2 x 2 KiB 12.1 / 11.2; 6128 x 3 x 4 KiB 39.7 / 38.3, 36.1 / 34.6; 24291 x 2 x 4 KiB 107 / 106, 90 / 89; other rows 3146 x 2 x 3776 B 15.3 / 15.6, 20720
-//   x 2 x 5744 B 141 / 151; smaller 1832 x 2 x 2304 B 8.4 / 8.7; the tensor 16 bytes past a unit 20720 x 2 x 5760 B 129 / 140, 6128 x 3 x 4 KiB 43.5 / 49.7, 64
-//   bytes past a line 126 / 124, 41.0 / 40.8 (one entry per token, 16 bytes past, even: 15616 x 7 KiB 82.4 / 80.6, 84.7 / 85.3);
+// on its way; rows written through go there at once, and the memory-side cache keeps them.  But rows that the L2s hold are also read from there: where source and
+// rows together are not much larger than the L2s, a loop over the same buffers whose reader follows at once loses by rows written through.  So they are from
+// kThroughBytes of both on.  Plain / through, us, dispatch and the combine of the rows over the same buffers, the same over changing buffers, and those with
+// a combine of another tensor:
+// - one entry per token: 2400 x 8 KiB (37 MiB of both) 14.1 / 15.3, 16.2 / 16.0, 18.9 / 18.5; 2900 x 8 KiB (45) 16.5 / 16.9, 18.3 / 17.8, 21.1 / 20.5; 7000 x 4 KiB (55)
+//   20.0 / 19.6, 21.3 / 21.3, 25.2 / 24.9; 5000 x 7 KiB (68) 26.1 / 23.2, 26.4 / 25.8, 30.2 / 29.7; 15616 x 7024 B 78.3 / 76.8, 80.3 / 78.5, 84.2 / 81.1;
+// - two and three, rows of whole lines (128 bytes): 4096 x 2 x 2 KiB (24) 9.6 / 11.5, 11.7 / 11.0, 12.9 / 12.7; 2048 x 2 x 6 KiB (36) 13.0 / 13.9, 14.6 / 14.3, 16.9 /
+//   16.8; 2048 x 2 x 8 KiB (48) 18.2 / 18.5, 18.7 / 18.0, 21.3 / 21.0; 3000 x 2 x 7 KiB (62) 24.2 / 22.9, 22.4 / 21.8, 27.5 / 27.3; 3200 x 3 x 4 KiB (50) 19.9 / 18.4,
+//   19.8 / 19.4, 22.4 / 22.4; 24291 x 2 x 4 KiB 102 / 100, 103 / 102, 105 / 103.  Behind a matrix product that reads the rows it is even up to 40 MiB and 1-4 % ahead
+//   from there on.  Rows in other units 20720 x 2 x 5744 B 141 / 151; the tensor 16 bytes past a unit 20720 x 2 x 5760 B 129 / 140, 6128 x 3 x 4 KiB 43.5 / 49.7,
+//   64 bytes past a line 126 / 124, 41.0 / 40.8 (one entry per token, 16 bytes past, even: 15616 x 7 KiB 82.4 / 80.6, 84.7 / 85.3);
 // - more entries come out even or lose: 9515 x 4 x 1 KiB 20.1 / 20.5, 4990 x 6 x 512 B 11.6 / 12.0, 2827 x 8 x 1344 B 15.5 / 15.7.
-constexpr size_t kThroughBytesOne = (size_t)8 << 20, kThroughBytesFew = (size_t)10 << 20;
-inline bool walk_through(int k, const void *rows, size_t row, size_t written)
+constexpr size_t kThroughBytes = (size_t)50 << 20;
+inline bool walk_through(int k, const void *rows, size_t row, size_t source, size_t written)
 {
-    if (k == 1) return written >= kThroughBytesOne;
-    return k <= 3 && written >= kThroughBytesFew && row % 128 == 0 && whole_units(rows, row);
+    if (k > 3 || source + written < kThroughBytes) return false;
+    return k == 1 || (row % 128 == 0 && whole_units(rows, row));
 }
 
 // Stores of combine's output rows.

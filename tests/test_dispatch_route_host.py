@@ -56,6 +56,17 @@ def test_stores_of_the_token_walk(route):
             assert knob(0) == setting
 
 
+def test_rows_written_through_where_the_l2s_cannot_hold_them(route):
+    for k, row in ((1, 2048), (1, 14336), (2, 2048), (2, 7168), (3, 4096)):
+        first = -(-(50 * MIB) // ((k + 1) * row))   # source and rows of 50 MiB
+        assert route(first, k, 64, 8, row) == TOKENS | THROUGH
+        assert route(first - 1, k, 64, 8, row) == TOKENS | PLAIN
+        last = 256 * MIB // (k * row)               # what is written fits the memory-side cache
+        assert route(last, k, 64, 8, row) == TOKENS | THROUGH and route(last + 1, k, 64, 8, row) != TOKENS | THROUGH
+    assert route(4096, 2, 16, 4, 2048) == TOKENS | PLAIN    # the smallest benchmark configuration
+    assert route(16384, 4, 64, 8, 2048) == TOKENS | PLAIN
+
+
 def test_rows_written_through_start_at_whole_units(route):
     for k in (2, 3):
         args = (12288, k, 64, 8, 4096)

@@ -46,7 +46,7 @@ def test_fused(N, k, row_bytes, aux_bytes, shift):
     check(L, planes)
 
 
-# one entry from 8 MiB on, two and three from 10 MiB on in rows of whole lines, four never; more than 1024 workgroups, rows cut into columns
+# one to four entries, rows of whole lines and others, a few of the calls large enough to be written through; more than 1024 workgroups, rows cut into columns
 @pytest.mark.parametrize("N,k,row_bytes", [(4095, 1, 2048), (4096, 1, 2048), (4097, 1, 2064), (8000, 1, 1040), (2100, 1, 20480 + 48), (5120, 2, 1024), (5119, 2, 1024),
                                            (5200, 2, 1040), (3500, 3, 1152), (1100, 2, 17408), (1100, 3, 16384 + 128), (3000, 4, 1024)])
 def test_token_walk(N, k, row_bytes):
@@ -59,7 +59,10 @@ def test_token_walk(N, k, row_bytes):
 
 # two and three entries: only from a whole 64-byte unit on; one entry from anywhere
 @pytest.mark.parametrize("N,k,row_bytes,shift,through", [(12288, 2, 4096, 16, False), (12288, 2, 4096, 64, True), (9000, 3, 4224, 48, False), (9000, 3, 4224, 0, True),
-                                                         (24577, 1, 2048, 16, True)])
+                                                         (24577, 1, 2048, 16, True),
+                                                         (12800, 1, 2048, 0, True), (12799, 1, 2048, 0, False), (8534, 2, 2048, 0, True), (8533, 2, 2048, 0, False),
+                                                         (3200, 3, 4096, 0, True), (3199, 3, 4096, 0, False), (1200, 2, 17408, 0, True), (1200, 3, 16384 + 128, 0, True),
+                                                         (2100, 1, 20480 + 48, 0, True), (26000, 1, 1040, 0, True)])
 def test_token_walk_from_any_place(N, k, row_bytes, shift, through):
     f, L, A, planes = setup(N, k, 64, 8, row_bytes, 0, shift)
     f.fusco_plan(L, A)
