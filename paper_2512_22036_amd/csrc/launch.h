@@ -105,12 +105,15 @@ inline void combine_shape_latency(int N, int C, int &threads, int &segs)
 template <bool Y_BF16, bool OUT_BF16, int JU, bool WIDENED = Y_BF16 && !OUT_BF16 && JU == 1>
 void launch_combine_as(const CombineArgs &a, dim3 grid, dim3 block, OutStores stores, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
 {
-    if (stores == kOutThrough) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough, false, WIDENED>, grid, block, s, a, e0, e1);
-    if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain, false, WIDENED>, grid, block, s, a, e0, e1);
-    if constexpr (JU > 0 && JU <= 4) {   // inputs bound by latency are written through or plain (out_stores)
-        if (stores == kOutThroughStream) launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream, false, WIDENED>, grid, block, s, a, e0, e1);
-        else launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal, false, WIDENED>, grid, block, s, a, e0, e1);
+    // Stores differ in speed alone.  Inputs bound by latency are written through or plain, inputs bound by memory (two rows WIDENED) never plain (out_stores).
+    if constexpr (JU > 0 && JU <= 4) {
+        if (stores == kOutThroughStream) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThroughStream, false, WIDENED>, grid, block, s, a, e0, e1);
+        if (stores == kOutNonTemporal) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutNonTemporal, false, WIDENED>, grid, block, s, a, e0, e1);
     }
+    if constexpr (!(WIDENED && JU == 2)) {
+        if (stores == kOutPlain) return launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutPlain, false, WIDENED>, grid, block, s, a, e0, e1);
+    }
+    launch(combine_kernel<Y_BF16, OUT_BF16, JU, kOutThrough, false, WIDENED>, grid, block, s, a, e0, e1);
 }
 
 // Rows in flight.  Bound by latency: eight, four from 16 MiB on (us, 64 tokens x 8 x 14 KiB 3.1 / 3.5, 512 x 8 12.0 / 11.7, 2000 x 8 x 4
@@ -287,8 +290,10 @@ OutStores out_stores(size_t y_bytes, const void *out, size_t rows, size_t row_by
 // - others, whose ends go to memory as partial writes, up to kPartialCutBytes of input 78 x 8 x 7568 B 5.0 / 4.1, 481 x 8 x 4784 B 9.3 / 9.0, beyond it 911 x 4
 //   x 8096 B 15.7 / 16.8, 1543 x 6 x 12752 B 73 / 83.
 // From kPartialStreamBytes of input on, partial rows of several times that cache, they go past it: what they leave there costs the next call
-// more than it gives a reader of the rows (plan, both tensors and two hops of 4096 x 8 x 14 KiB, written through / past the cache 372 / 359; the two hops
-// and a reader 370 / 378, of 8192 x 8 x 8 KiB 417 / 419, 13924 x 8 x 5440 B 577 / 578).
+// more than it gives a reader of the rows.  Written through / past the cache, us, the two hops and a pass that reads the partial rows; plan, both tensors and two hops; both:
+// 4096 x 8 x 14 KiB on 8 devices 382 / 379, 370 / 359, 536 / 533; 8192 x 8 x 8 KiB 432 / 422, 409 / 393, 605 / 594; 13924 x 8 x 5504 B 498 / 492, 518 / 486, 729 / 724;
+// 10000 x 6 x 8 KiB 436 / 431, 435 / 416, 624 / 611; 16384 x 4 x 7 KiB 457 / 452, 467 / 455, 666 / 662; 6849 x 8 x 9 KiB on 16 477 / 474, 469 / 452, 678 / 681; 5000 x 8
+// x 12 KiB on 4 295 / 290, 334 / 317, 450 / 445; 12000 x 8 x 14 KiB (1.3 GiB) 1105 / 1089, 1025 / 1043, 1511 / 1504.
 constexpr size_t kPartialCutBytes = (size_t)20 << 20, kPartialStreamBytes = (size_t)400 << 20;
 
 inline OutStores partial_stores(size_t y_bytes, const void *partial, size_t row_bytes)
@@ -334,11 +339,17 @@ template <bool Y_BF16, bool OUT_BF16, TwoHopRows ROWS, OutStores PARTIAL>
 void launch_two_hop_with(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, OutStores stores, hipStream_t s)
 {
     const hipEvent_t none = nullptr;
-    switch (stores) {
-    case kOutThrough: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
-    case kOutThroughStream: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
-    case kOutNonTemporal: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
-    default: launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ROWS, PARTIAL>, grid, block, lds, s, none, none, a); break;
+    // Stores differ in speed alone.  Outputs of the smaller inputs never go past the memory-side cache, those of the larger ones always (out_stores).
+    constexpr bool kLatencyBound = !Y_BF16 && ROWS == kRowsOneByOne, kPastCache = PARTIAL == kOutThroughStream;
+    if constexpr (!kLatencyBound) {
+        if (stores == kOutThroughStream)
+            return launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThroughStream, ROWS, PARTIAL>, grid, block, lds, s, none, none, a);
+        if (kPastCache || stores == kOutNonTemporal)
+            return launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutNonTemporal, ROWS, PARTIAL>, grid, block, lds, s, none, none, a);
+    }
+    if constexpr (!kPastCache) {
+        if (stores == kOutPlain) return launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutPlain, ROWS, PARTIAL>, grid, block, lds, s, none, none, a);
+        launch_args(combine_two_hop_kernel<Y_BF16, OUT_BF16, kOutThrough, ROWS, PARTIAL>, grid, block, lds, s, none, none, a);
     }
 }
 
@@ -347,7 +358,8 @@ void launch_two_hop_as(const TwoHopArgs &a, dim3 grid, dim3 block, size_t lds, O
 {
     if constexpr (Y_BF16 && ROWS != kRowsInTurn) {
         if (partial == kOutThrough) return launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutThrough>(a, grid, block, lds, stores, s);
-        if (partial == kOutThroughStream) return launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutThroughStream>(a, grid, block, lds, stores, s);
+        if constexpr (ROWS == kRowsAtOnce)   // rows of so large an input are not taken one by one
+            if (partial == kOutThroughStream) return launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutThroughStream>(a, grid, block, lds, stores, s);
     }
     launch_two_hop_with<Y_BF16, OUT_BF16, ROWS, kOutPlain>(a, grid, block, lds, stores, s);
 }
