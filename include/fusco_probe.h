@@ -133,6 +133,12 @@ int fusco_probe_dispatch_route(const fusco_layout *L, size_t row_bytes, size_t a
                                const void *d_send_buf, const void *d_send_aux, uint32_t flags);
 
 /*
+ * Study and test aid, host-only: 1 if fusco_plan writes this layout's arrays that are indexed by pair through the GPU's L2s, 0 if it leaves
+ * them there to be written back, negative on invalid arguments.  The result of fusco_plan does not depend on it.
+ */
+int fusco_probe_plan_through(const fusco_layout *L);
+
+/*
  * Measurement aid: kernel time without stream events between the kernels.  The next fusco_plan,
  * fusco_dispatch (fused modes), fusco_plan_dispatch or fusco_combine call made by the calling thread attaches the two HIP
  * events (hipEvent_t passed as void*, created with timing enabled) to its own kernels: start_event

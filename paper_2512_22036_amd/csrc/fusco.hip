@@ -157,13 +157,19 @@ int fusco_plan(fusco_layout *L, const int32_t *d_topk_idx, void *d_scratch, size
             launch(plan_rank_kernel<true, false>, dim3(2u * (unsigned)a.n_tiles), block, s, a, ev.start, nullptr);
             launch(plan_place_kernel<true, false>, tiles, block, s, a, nullptr, ev.stop);
         } else {
-            const bool through = a.n_tiles >= kPlanThroughTiles;
+            const bool through = plan_through(a.n_tiles, a.tpt * a.k);
             launch(through ? plan_rank_kernel<false, true> : plan_rank_kernel<false, false>, tiles, block, s, a, ev.start, nullptr);
             launch(plan_chunk_kernel, dim3((unsigned)a.n_chunks, (unsigned)((a.stride + kChunkColumns - 1) / kChunkColumns)), block, s, a);
             launch(through ? plan_place_kernel<false, true> : plan_place_kernel<false, false>, tiles, block, s, a, nullptr, ev.stop);
         }
     }
     return launch_status();
+}
+
+int fusco_probe_plan_through(const fusco_layout *L)
+{
+    if (!layout_ok(L)) return FUSCO_ERR_INVALID_ARG;
+    return chunk_tiles_for(L->tile_count) != 0 && plan_through(L->tile_count, L->tile_tokens * L->k) ? 1 : 0;
 }
 
 // Planner scratch that belongs to the library, for fusco_plan_static.  In host code the array's name is

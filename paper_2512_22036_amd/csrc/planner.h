@@ -68,11 +68,18 @@ template <typename T>
 __device__ __forceinline__ T &at(T *base, int i) { return *(T *)((char *)const_cast<std::remove_const_t<T> *>(base) + (uint32_t)i * (uint32_t)sizeof(T)); }
 
 // Stores v there, for runs of lanes next to each other.  THROUGH: through the L2 at once.  What plans of many tiles leave dirty there is only
-// written back when their kernels end (us, plain / through: 65536 tokens x 8 16.0 / 15.1, 131072 x 8 21.4 / 21.0, 200000 x 4 19.4 / 18.8, 100000 x 6 19.8 / 19.5; fewer
-// tiles 30000 x 10, 148 tiles, 15.4 / 16.1, 8192 x 8, 32, 9.7 / 10.2).  Not the arrays indexed by slot, whose runs are shorter than a line (131072 x 8 25.6).
+// written back when their kernels end (us, plain / through, over the same buffers and over more than the memory-side cache holds: 65536 tokens x 8 16.2 / 16.2,
+// 17.3 / 17.1, 131072 x 8 21.4 / 21.2, 22.5 / 22.2, 200000 x 4 18.5 / 18.1, 19.6 / 19.3, 262144 x 8, 1024 tiles, 35.5 / 35.2, 37.8 / 37.9; fewer tiles 30000 x
+// 10, 148 tiles, 15.4 / 16.1, 8192 x 8, 32, 9.7 / 10.2).  Not
+// - more than kPlanThroughMost tiles: 350000 x 8, 1368 tiles, 47.8 / 47.9, 50.1 / 50.3 (three sets of buffers 48.3 / 49.1), 524288 x 8 60.8 / 62.1, 67.0 / 68.1,
+//   1048576 x 8 123.6 / 131.3, 130.0 / 137.5;
+// - tiles whose pairs are no whole 64-byte units, whose stores go to memory as partial writes: 100000 x 6 19.7 / 20.0, 21.0 / 23.2, 136694 x 10 25.8 / 26.1, 27.3 /
+//   33.0, 60000 x 7 15.6 / 16.0, 16.8 / 17.1;
+// - the arrays indexed by slot, whose runs are shorter than a line (131072 x 8 25.6).
 // A relaxed store at agent scope is that store (global_store_dword ... sc1) in a form that the compiler knows: what it must wait for between writing the
 // base's scalar registers and reading them here it sees for itself, which it would not for an asm statement.
-constexpr int kPlanThroughTiles = 200;
+constexpr int kPlanThroughTiles = 200, kPlanThroughMost = 1024;
+inline bool plan_through(int n_tiles, int tile_pairs) { return n_tiles >= kPlanThroughTiles && n_tiles <= kPlanThroughMost && tile_pairs % 16 == 0; }
 template <bool THROUGH>
 __device__ __forceinline__ void put(int32_t *base, int i, int v)
 {
