@@ -139,6 +139,12 @@ int fusco_probe_dispatch_route(const fusco_layout *L, size_t row_bytes, size_t a
 int fusco_probe_plan_through(const fusco_layout *L);
 
 /*
+ * Study and test aid, host-only: 1 if fusco_segments_copy packs a stream of this capacity into slices of this size with workgroups of twice
+ * the usual width, 0 if not, negative for a slice size that it does not take.  The result does not depend on it.
+ */
+int fusco_probe_segments_wide(uint64_t stream_capacity, uint64_t slice_bytes);
+
+/*
  * Measurement aid: kernel time without stream events between the kernels.  The next fusco_plan,
  * fusco_dispatch (fused modes), fusco_plan_dispatch or fusco_combine call made by the calling thread attaches the two HIP
  * events (hipEvent_t passed as void*, created with timing enabled) to its own kernels: start_event

@@ -863,6 +863,12 @@ int fusco_segments_scan(const fusco_segment *d_desc, int64_t n, uint64_t *d_cum,
     return launch_status();
 }
 
+int fusco_probe_segments_wide(uint64_t stream_capacity, uint64_t slice_bytes)
+{
+    if (slice_bytes == 0 || slice_bytes % kSegBlockBytes != 0 || slice_bytes > ((uint64_t)1 << 31)) return FUSCO_ERR_INVALID_ARG;
+    return segments_wide(stream_capacity, slice_bytes) ? 1 : 0;
+}
+
 int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segment *d_src_desc, void *d_dst,
                         uint64_t dst_bytes, const fusco_segment *d_dst_desc, const uint64_t *d_cum, int64_t n,
                         uint64_t stream_capacity, uint64_t slice_bytes, uint32_t *d_slice_fill, int32_t *d_status,
@@ -890,8 +896,8 @@ int fusco_segments_copy(const void *d_src, uint64_t src_bytes, const fusco_segme
     a.limit = blocks * kSegBlockBytes;
     a.slice_bytes = slice_bytes; a.slice_fill = d_slice_fill; a.status = d_status;
     const dim3 grid((unsigned)blocks);
-    const bool wide = d_slice_fill && slice_bytes >= kSegWideSlice && slice_bytes % kSegWideBlockBytes == 0 && stream_capacity >= kSegWideBytes;
-    if (wide) launch(segments_copy_kernel<true, false, kSegWideThreads>, dim3((unsigned)((blocks + 1) / 2)), dim3(kSegWideThreads), s, a);
+    if (d_slice_fill && segments_wide(stream_capacity, slice_bytes))
+        launch(segments_copy_kernel<true, false, kSegWideThreads>, dim3((unsigned)((blocks + 1) / 2)), dim3(kSegWideThreads), s, a);
     else if (d_slice_fill) launch(segments_copy_kernel<true, false, kSegThreads>, grid, dim3(kSegThreads), s, a);
     else if (stream_capacity > kSegStreamBytes) launch(segments_copy_kernel<false, true, kSegThreads>, grid, dim3(kSegThreads), s, a);
     else launch(segments_copy_kernel<false, false, kSegThreads>, grid, dim3(kSegThreads), s, a);

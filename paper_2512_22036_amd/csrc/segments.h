@@ -26,13 +26,20 @@ constexpr int kSegUnits = kSegPieceBytes / 16 / kWave;   // 16-byte units per th
 constexpr int kSegBlockBytes = kSegThreads / kWave * kSegPieceBytes;   // stream bytes handled by a workgroup
 constexpr int kSegRunBytes = 8 * kSegBlockBytes;                       // consecutive bytes taken by one XCD
 // With slices a workgroup adds what it has written to the slice's counter, and additions to one counter follow one another some 150 ns
-// apart: 64 workgroups of 256 threads per MiB kept a slice open longer than its bytes.  Slices of at least kSegWideSlice, in whole blocks of
-// workgroups of kSegWideThreads, are taken by those, streams below kSegWideBytes aside.  Pack, us, 256 / 512 / 1024 threads: slices of 1 MiB, 0.3 MB 6.4 / 6.6 /
-// 7.3, 21 MB 20.7 / 15.0 / 16.2, 36 MB 28.8 / 21.8 / 21.4, 286 MB 125 / 115 / 115, of 4 MiB 286 MB 158 / 121 / 116, of 256 KiB 411 MB 176 / 170 / 178, of 64 KiB
-// 4 MB 7.3 / 6.9 / 7.4, of 32 KiB 36 MB 18.4 / 19.0 / 18.8.  (A counter per wave: 286 MB 280; two blocks by one workgroup, whose second lookups wait behind
-// the first stores: 161.)
+// apart: 64 workgroups of 256 threads per MiB kept a slice open longer than its bytes.  Slices in whole blocks of workgroups of kSegWideThreads are taken by
+// those: of kSegWideSlice and more, streams below kSegWideBytes aside, and of kSegWideShort and more in streams of kSegWideLong and more.  Pack, us, 256 / 512 / 1024
+// threads: slices of 1 MiB, 0.3 MB 6.4 / 6.6 / 7.3, 21 MB 20.7 / 15.0 / 16.2, 36 MB 28.8 / 21.8 / 21.4, 286 MB 125 / 115 / 115, of 4 MiB 286 MB 158 / 121 / 116, of
+// 256 KiB 411 MB 176 / 170 / 178, of 32 KiB 36 MB 18.4 / 19.0 / 18.8.  256 / 512 threads over the same buffers, and over buffers that change: slices of 256 KiB 6 MB
+// 9.4 / 9.3, 9.5 / 9.4, 12 MB 10.8 / 9.5, 11.2 / 10.4, 40 MB 20.5 / 19.5, 24.1 / 23.8; of 128 KiB 18 MB 10.5 / 11.6, 12.7 / 13.6, 40 MB 19.3 / 19.6, 23.4 / 23.9, 100
+// MB 40.4 / 39.5, 45.3 / 44.5, 250 MB 96.4 / 94.5, 107.3 / 104.5; of 64 KiB 18 MB 10.3 / 11.4, 12.8 / 13.6, 40 MB 18.9 / 19.7, 23.1 / 23.6, 100 MB 39.6 / 39.5, 44.7 /
+// 44.5.  (A counter per wave: 286 MB 280; two blocks by one workgroup, whose second lookups wait behind the first stores: 161.)
 constexpr int kSegWideThreads = 2 * kSegThreads, kSegWideBlockBytes = 2 * kSegBlockBytes;
-constexpr uint64_t kSegWideSlice = (uint64_t)64 << 10, kSegWideBytes = (uint64_t)2 << 20;
+constexpr uint64_t kSegWideSlice = (uint64_t)256 << 10, kSegWideShort = (uint64_t)64 << 10, kSegWideBytes = (uint64_t)2 << 20, kSegWideLong = (uint64_t)64 << 20;
+inline bool segments_wide(uint64_t stream_capacity, uint64_t slice_bytes)
+{
+    if (slice_bytes < kSegWideShort || slice_bytes % kSegWideBlockBytes != 0) return false;
+    return stream_capacity >= (slice_bytes >= kSegWideSlice ? kSegWideBytes : kSegWideLong);
+}
 // Streams of more than this are written with non-temporal stores, smaller ones with plain stores, which leave them in the
 // memory-side cache for whoever reads them.  Unpack and a pass that reads the result, other buffers in every turn, us, non-temporal
 // / plain: 4 MB 9.7 / 9.6, 14 MB 17.5 / 16.2, 57 MB 59.4 / 53.2, 115 MB 110.6 / 101.0, 172 MB 162.1 / 161.0, 230 MB 213 / 216,

@@ -13,8 +13,10 @@ def pack(total, slice_bytes, capacity, seed, holes):
     import paper_2512_22036_amd as f
     rng = np.random.default_rng(seed)
     size = []
-    while sum(size) < total:
-        size.append(min(int(rng.choice([16, 48, 4096, 16 * rng.integers(1, 900), 70000 // 16 * 16])), total - sum(size)))
+    left = total
+    while left:
+        size.append(min(int(rng.choice([16, 48, 4096, 16 * rng.integers(1, 900), 70000 // 16 * 16])), left))
+        left -= size[-1]
     size = np.array(size, dtype=np.int64)
     n = len(size)
     order = rng.permutation(n)
@@ -56,3 +58,10 @@ def test_pack_into_slices(total, slice_bytes, holes):
 @pytest.mark.parametrize("slice_bytes", [48 * KIB, 64 * KIB, 1024 * KIB])
 def test_streams_and_capacities_that_differ(slice_bytes, capacity):
     pack(2200 * KIB + 16, slice_bytes, capacity, capacity + slice_bytes, True)
+
+
+# slices of 256 KiB from 2 MiB on, shorter ones from 64 MiB on
+@pytest.mark.parametrize("slice_bytes,total", [(224 * KIB, 3000 * KIB + 48), (256 * KIB, 2048 * KIB - 16), (256 * KIB, 2300 * KIB + 16), (64 * KIB, 65536 * KIB - 80 * KIB),
+                                               (64 * KIB, 65536 * KIB + 16), (128 * KIB, 65536 * KIB)])
+def test_slices_on_both_sides_of_the_wide_workgroups(slice_bytes, total):
+    pack(total, slice_bytes, -(-total // slice_bytes) * slice_bytes, total + slice_bytes, True)
