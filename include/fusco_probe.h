@@ -139,6 +139,13 @@ int fusco_probe_dispatch_route(const fusco_layout *L, size_t row_bytes, size_t a
 int fusco_probe_plan_through(const fusco_layout *L);
 
 /*
+ * Study and test aid, host-only: 1 if fusco_plan_dispatch writes the rows of a call with these sizes through the GPU's L2s, 0 if it leaves them
+ * there to be written back, FUSCO_ERR_UNSUPPORTED for layouts that it does not take, FUSCO_ERR_INVALID_ARG for row sizes that it does not take.
+ * The tensor is not read; where it starts is part of the choice.  The result of fusco_plan_dispatch does not depend on it.
+ */
+int fusco_probe_plan_dispatch_through(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, const void *d_expert_buf);
+
+/*
  * Study and test aid, host-only: 1 if fusco_segments_copy packs a stream of this capacity into slices of this size with workgroups of twice
  * the usual width, 0 if not, negative for a slice size that it does not take.  The result does not depend on it.
  */

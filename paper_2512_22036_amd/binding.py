@@ -22,7 +22,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfusco.so")
 
 EXPORTS = ("fusco_version", "fusco_status_string", "fusco_layout_bytes", "fusco_scratch_bytes",
-           "fusco_layout_bind", "fusco_plan", "fusco_plan_static", "fusco_dispatch", "fusco_dispatch_in_transfer_order", "fusco_combine", "fusco_plan_dispatch", "fusco_probe_copy", "fusco_probe_rows", "fusco_probe_pieces", "fusco_probe_consume_slices", "fusco_probe_time_next_call", "fusco_probe_source_chunk_bytes", "fusco_probe_dispatch_kernel", "fusco_probe_dispatch_occupancy", "fusco_probe_dispatch_pull", "fusco_probe_dispatch_walk", "fusco_probe_dispatch_route", "fusco_probe_plan_through", "fusco_probe_segments_wide",
+           "fusco_layout_bind", "fusco_plan", "fusco_plan_static", "fusco_dispatch", "fusco_dispatch_in_transfer_order", "fusco_combine", "fusco_plan_dispatch", "fusco_probe_copy", "fusco_probe_rows", "fusco_probe_pieces", "fusco_probe_consume_slices", "fusco_probe_time_next_call", "fusco_probe_source_chunk_bytes", "fusco_probe_dispatch_kernel", "fusco_probe_dispatch_occupancy", "fusco_probe_dispatch_pull", "fusco_probe_dispatch_walk", "fusco_probe_dispatch_route", "fusco_probe_plan_through", "fusco_probe_plan_dispatch_through", "fusco_probe_segments_wide",
            "fusco_combine_two_hop", "fusco_balance_groups", "fusco_cross_node_load", "fusco_segments_scan", "fusco_segments_copy",
            "fusco_disaggregated_plan", "fusco_disaggregated_dispatch", "fusco_disaggregated_combine")
 
@@ -96,6 +96,8 @@ def load_library() -> ctypes.CDLL:
     lib.fusco_probe_dispatch_pull.argtypes = [ctypes.c_int]
     lib.fusco_probe_segments_wide.restype = ctypes.c_int
     lib.fusco_probe_segments_wide.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
+    lib.fusco_probe_plan_dispatch_through.restype = ctypes.c_int
+    lib.fusco_probe_plan_dispatch_through.argtypes = [ctypes.POINTER(_CLayout), sz, sz, vp]
     lib.fusco_probe_plan_through.restype = ctypes.c_int
     lib.fusco_probe_plan_through.argtypes = [ctypes.POINTER(_CLayout)]
     lib.fusco_probe_dispatch_route.restype = ctypes.c_int
@@ -499,6 +501,14 @@ def fusco_probe_plan_through(layout: Layout) -> bool:
     rc = int(load_library().fusco_probe_plan_through(ctypes.byref(layout.c)))
     if rc < 0:
         _check(rc, "fusco_probe_plan_through")
+    return bool(rc)
+
+
+def fusco_probe_plan_dispatch_through(layout: Layout, row_bytes: int, aux_row_bytes: int = 0, expert_buf=None) -> bool:
+    """Whether fusco_plan_dispatch writes the rows of such a call through the L2s (fusco_probe.h).  Host-only; the tensor is not read."""
+    rc = int(load_library().fusco_probe_plan_dispatch_through(ctypes.byref(layout.c), row_bytes, aux_row_bytes, _ptr(expert_buf)))
+    if rc < 0:
+        _check(rc, "fusco_probe_plan_dispatch_through")
     return bool(rc)
 
 

@@ -209,6 +209,29 @@ int fusco_plan_static(fusco_layout *L, const int32_t *d_topk_idx, void *stream)
     return fusco_plan(L, d_topk_idx, scratch, FUSCO_STATIC_SCRATCH_BYTES, stream);
 }
 
+// Column segments of the fused kernel's rows of Ct chunks (both planes), and chunks of a segment, which starts on a 1 KiB boundary of the row.
+static void fused_shape(int Ct, int &segs, int &seg_chunks)
+{
+    const int most = kFusedChunks * kSmallThreads;
+    segs = (Ct + most - 1) / most;
+    seg_chunks = segs > 1 ? round_up((Ct + segs - 1) / segs, kWave) : Ct;
+}
+
+static bool fused_rows_through(const fusco_layout *L, size_t row_bytes, int seg_chunks, const void *d_expert_buf)
+{
+    return fused_through(L->N, (size_t)L->P * row_bytes, (size_t)L->k * (size_t)seg_chunks * 16, whole_units(d_expert_buf, row_bytes));
+}
+
+int fusco_probe_plan_dispatch_through(const fusco_layout *L, size_t row_bytes, size_t aux_row_bytes, const void *d_expert_buf)
+{
+    if (!layout_ok(L) || row_bytes == 0 || row_bytes % 16 != 0 || aux_row_bytes % 16 != 0 || (row_bytes + aux_row_bytes) / 16 > kMaxRowChunks)
+        return FUSCO_ERR_INVALID_ARG;
+    if (single_tile_rounds(L->N, L->k) == 0) return FUSCO_ERR_UNSUPPORTED;
+    int segs, seg_chunks;
+    fused_shape((int)((row_bytes + aux_row_bytes) / 16), segs, seg_chunks);
+    return fused_rows_through(L, row_bytes, seg_chunks, d_expert_buf) ? 1 : 0;
+}
+
 int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *d_x, size_t row_bytes,
                         const void *d_x_aux, size_t aux_row_bytes, void *d_expert_buf, void *d_expert_aux,
                         void *stream)
@@ -226,17 +249,15 @@ int fusco_plan_dispatch(fusco_layout *L, const int32_t *d_topk_idx, const void *
     const PlanArgs a = plan_args(L, d_topk_idx, nullptr, rounds);
     const FusedRows m = {(u32x4 *)d_expert_buf, (u32x4 *)d_expert_aux};
     const u32x4 *x = (const u32x4 *)d_x, *x_aux = (const u32x4 *)d_x_aux;
-    const int C = (int)(row_bytes / 16), Ca = (int)(aux_row_bytes / 16), Ct = C + Ca, most = kFusedChunks * kSmallThreads;
-    const int segs = (Ct + most - 1) / most;
-    const int seg_chunks = segs > 1 ? round_up((Ct + segs - 1) / segs, kWave) : Ct;   // segments start on 1 KiB boundaries of the row
+    const int C = (int)(row_bytes / 16), Ca = (int)(aux_row_bytes / 16);
+    int segs, seg_chunks;
+    fused_shape(C + Ca, segs, seg_chunks);
     const ArmedEvents ev;
     const dim3 grid(1u + (unsigned)a.small_groups + (unsigned)L->N, (unsigned)segs), block(kSmallThreads);
     const int cpt = (seg_chunks + kSmallThreads - 1) / kSmallThreads;
     const unsigned groups = grid.x * grid.y;
     const bool four = groups > kFusedThree && groups <= kFusedFour;
-    const size_t written = (size_t)L->P * row_bytes;
-    const bool through = written >= kFusedThroughBytes && (size_t)L->k * (size_t)seg_chunks * 16 <= kFusedThroughGroup &&
-                         (written < kFusedThroughCutBytes || whole_units(d_expert_buf, row_bytes));
+    const bool through = fused_rows_through(L, row_bytes, seg_chunks, d_expert_buf);
     using Fused = decltype(&plan_dispatch_kernel<1, false, false>);
     // by second plane and by stores, for one, two and four chunks a thread
     static constexpr Fused kThree[2][2][2] = {{{plan_dispatch_kernel<1, false, false>, plan_dispatch_kernel<1, false, true>},

@@ -256,6 +256,27 @@ inline bool walk_through(int k, const void *rows, size_t row, size_t source, siz
     return k == 1 || (row % 128 == 0 && whole_units(rows, row));
 }
 
+// Stores of the fused plan + dispatch, whose workgroups write a token's k rows (or a column segment of them, `group` bytes) one after the other: written
+// through from kFusedThroughBytes of rows on; below, the end of a small kernel is sooner reached than memory.  us, plain / through, alone, with a combine of another
+// tensor and with the combine of the rows: 128 x 8 x 7 KiB + 224 B 5.3 / 4.7, 9.8 / 9.1 (second); 219 x 8 x 11 KiB 7.4 / 6.3, 13.6 / 11.8, 13.1 / 12.5; 114 x 8 x 50 KiB 11.8 /
+// 9.6, 22.4 / 20.8, 21.9 / 21.5; 155 x 4 x 3584 B (2.1 MiB) 3.8 / 3.6, 6.5 / 6.2, 7.2 / 7.1; 124 x 8 x 1 KiB (1 MiB) 3.6 / 3.7.
+// A workgroup that writes much does so at one store's latency after the other, and few of them do not hide it: groups of more than kFusedThroughShort
+// only from kFusedThroughTokens on, rows of partial units from kFusedThroughTokensCut on.  Kernel times with the combine of the rows and of another tensor, buffers
+// that change: 18 x 8 x 16 KiB 8.2 / 8.9, 8.0 / 8.3; 32 x 8 x 16 KiB 8.2 / 8.7, 8.2 / 8.4; 64 x 8 x 16 KiB 9.0 / 8.7, 9.1 / 8.8; 14 x 16 x 10.5 KiB 8.7 / 9.8, 8.4 / 9.2;
+// 52 x 16 x 10.5 KiB 10.4 / 10.1, 10.6 / 10.6; 24 x 8 x 32 KiB 10.4 / 10.9, 10.3 / 10.8; 10 x 24 x 8 KiB 9.8 / 10.8, 44 x 24 x 8 KiB 11.8 / 11.7; groups of 84 KiB
+// 24 x 8 x 10.5 KiB 8.2 / 8.1, 8.1 / 7.9; partial units 40 x 8 x 10400 B 8.4 / 8.9, 8.3 / 8.2, 18 x 8 x 15040 B 8.2 / 8.8, 8.0 / 8.2, 80 x 8 x 15040 B 9.7 / 9.4, 9.7 / 9.2.
+// Not groups of more than kFusedThroughMost (24 x 16 x 32704 B 8.3 / 9.4, 15 x 33 x 24640 B 13.3 / 15.0; 80 x 16 x 23200 B 10.8 / 9.3), nor rows that are no whole units
+// from kFusedThroughCutBytes on (154 x 8 x 65232 B 16.7 / 16.2, 35.1 / 36.1, 36.6 / 42.8; 912 x 1 x 14816 B 8.7 / 8.0, 16.7 / 16.1, 16.8 / 16.1).
+constexpr size_t kFusedThroughBytes = (size_t)2 << 20, kFusedThroughCutBytes = (size_t)16 << 20;
+constexpr size_t kFusedThroughShort = (size_t)96 << 10, kFusedThroughMost = (size_t)384 << 10;
+constexpr int kFusedThroughTokens = 48, kFusedThroughTokensCut = 64;
+inline bool fused_through(int N, size_t written, size_t group, bool whole)
+{
+    if (written < kFusedThroughBytes || group > kFusedThroughMost) return false;
+    if (!whole) return written < kFusedThroughCutBytes && N >= kFusedThroughTokensCut;
+    return group <= kFusedThroughShort || N >= kFusedThroughTokens;
+}
+
 // Stores of combine's output rows.
 // Large outputs of inputs that are bound by memory go past the memory-side cache: what write-through and plain stores leave
 // dirty there costs the reads of the kernels around them more than it saves.  Steps with the experts' output in a tensor of

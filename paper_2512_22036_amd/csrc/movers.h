@@ -415,15 +415,7 @@ __device__ __forceinline__ void plan_dispatch(SmallLds &s, const int32_t *A, con
     }
 }
 
-// THROUGH: the rows are written through instead of plain (as in the token walk, the write-back at the kernel's end is spread over
-// the kernel), from kFusedThroughBytes of rows on; below, the end of a small kernel is sooner reached than memory.  us, plain / through, alone, with a combine of another
-// tensor and with the combine of the rows: 128 x 8 x 7 KiB + 224 B 5.3 / 4.7, 9.8 / 9.1 (second); 219 x 8 x 11 KiB 7.4 / 6.3, 13.6 / 11.8, 13.1 / 12.5; 114 x 8 x 50 KiB 11.8 /
-// 9.6, 22.4 / 20.8, 21.9 / 21.5; 155 x 4 x 3584 B (2.1 MiB) 3.8 / 3.6, 6.5 / 6.2, 7.2 / 7.1; 124 x 8 x 1 KiB (1 MiB) 3.6 / 3.7.
-// Not where a workgroup writes more than kFusedThroughGroup, which it does at one store's latency after the other (24 x 16 x 32704 B 8.3 / 9.4, 15 x 33 x
-// 24640 B 13.3 / 15.0; 80 x 16 x 23200 B 10.8 / 9.3), nor rows that are no whole units from kFusedThroughCutBytes on (154 x 8 x 65232 B 16.7 / 16.2, 35.1 /
-// 36.1, 36.6 / 42.8; 912 x 1 x 14816 B 8.7 / 8.0, 16.7 / 16.1, 16.8 / 16.1).
-constexpr size_t kFusedThroughBytes = (size_t)2 << 20, kFusedThroughGroup = (size_t)384 << 10, kFusedThroughCutBytes = (size_t)16 << 20;
-
+// THROUGH: the rows are written through instead of plain: the write-back at the kernel's end is spread over the kernel, as in the token walk.
 #define FUSCO_PLAN_DISPATCH(NAME, ATTRIBUTE)                                                                                                          \
     template <int CPT, bool AUX, bool THROUGH>                                                                                                        \
     __global__ __launch_bounds__(kSmallThreads) ATTRIBUTE void NAME(const int32_t *A, const u32x4 *x, const u32x4 *x_aux, int32_t N, int32_t k,       \

@@ -34,7 +34,7 @@ def check(L, planes):
             assert bool((planes[dst][n:] == 0xEE).all())
 
 
-# 2 MiB of rows; 384 KiB written by a workgroup; 16 MiB of rows that are no whole 64-byte units; one, two, four chunks a thread and column segments;
+# 2 MiB of rows; up to 384 KiB written by a workgroup; 16 MiB of rows that are no whole 64-byte units; one, two, four chunks a thread and column segments;
 # 3 x 256 and 4 x 256 workgroups
 @pytest.mark.parametrize("N,k,row_bytes,aux_bytes", [(128, 8, 2032, 0), (128, 8, 2048, 0), (128, 8, 2048, 224), (127, 8, 2064, 48), (100, 4, 16384 + 16, 16),
                                                      (24, 16, 24576, 0), (24, 16, 24576 + 16, 0), (128, 8, 16384, 0), (128, 8, 16400, 0), (127, 8, 16400, 0),
@@ -69,4 +69,14 @@ def test_token_walk_from_any_place(N, k, row_bytes, shift, through):
     route = f.fusco_probe_dispatch_route(L, row_bytes, expert_buf=planes["expert_buf"])
     assert route == f.ROUTE_TOKENS | (f.WALK_THROUGH if through else f.WALK_PLAIN)
     f.fusco_dispatch(L, planes["x"], planes["expert_buf"])
+    check(L, planes)
+
+
+@pytest.mark.parametrize("N,k,row_bytes,shift,through", [(47, 8, 16384, 0, False), (48, 8, 16384, 0, True), (47, 16, 10752, 0, False), (49, 8, 32768, 0, True),
+                                                         (30, 8, 12288, 0, True), (63, 8, 10400, 0, False), (64, 8, 10400, 0, True), (64, 8, 8192, 16, True),
+                                                         (40, 8, 8192, 48, False), (40, 8, 8192, 64, True), (64, 32, 12288, 0, True)])
+def test_fused_on_both_sides_of_the_rule(N, k, row_bytes, shift, through):
+    f, L, A, planes = setup(N, k, 64, 8, row_bytes, 0, shift)
+    assert f.fusco_probe_plan_dispatch_through(L, row_bytes, expert_buf=planes["expert_buf"]) == through
+    f.fusco_plan_dispatch(L, A, **planes)
     check(L, planes)
