@@ -242,18 +242,20 @@ bool whole_units(const void *p, size_t row_bytes) { return (((uintptr_t)p | row_
 // kThroughBytes of both on.  Plain / through, us, dispatch and the combine of the rows over the same buffers, the same over changing buffers, and those with
 // a combine of another tensor:
 // - one entry per token: 2400 x 8 KiB (37 MiB of both) 14.1 / 15.3, 16.2 / 16.0, 18.9 / 18.5; 2900 x 8 KiB (45) 16.5 / 16.9, 18.3 / 17.8, 21.1 / 20.5; 7000 x 4 KiB (55)
-//   20.0 / 19.6, 21.3 / 21.3, 25.2 / 24.9; 5000 x 7 KiB (68) 26.1 / 23.2, 26.4 / 25.8, 30.2 / 29.7; 15616 x 7024 B 78.3 / 76.8, 80.3 / 78.5, 84.2 / 81.1;
+//   20.0 / 19.6, 21.3 / 21.3, 25.2 / 24.9; 5000 x 7 KiB (68) 26.1 / 23.2, 26.4 / 25.8, 30.2 / 29.7; 15616 x 7 KiB 65.9 / 64.3, 67.0 / 65.5, 81.4 / 78.8;
 // - two and three, rows of whole lines (128 bytes): 4096 x 2 x 2 KiB (24) 9.6 / 11.5, 11.7 / 11.0, 12.9 / 12.7; 2048 x 2 x 6 KiB (36) 13.0 / 13.9, 14.6 / 14.3, 16.9 /
 //   16.8; 2048 x 2 x 8 KiB (48) 18.2 / 18.5, 18.7 / 18.0, 21.3 / 21.0; 3000 x 2 x 7 KiB (62) 24.2 / 22.9, 22.4 / 21.8, 27.5 / 27.3; 3200 x 3 x 4 KiB (50) 19.9 / 18.4,
 //   19.8 / 19.4, 22.4 / 22.4; 24291 x 2 x 4 KiB 102 / 100, 103 / 102, 105 / 103.  Behind a matrix product that reads the rows it is even up to 40 MiB and 1-4 % ahead
 //   from there on.  Rows in other units 20720 x 2 x 5744 B 141 / 151; the tensor 16 bytes past a unit 20720 x 2 x 5760 B 129 / 140, 6128 x 3 x 4 KiB 43.5 / 49.7,
-//   64 bytes past a line 126 / 124, 41.0 / 40.8 (one entry per token, 16 bytes past, even: 15616 x 7 KiB 82.4 / 80.6, 84.7 / 85.3);
+//   64 bytes past a line 126 / 124, 41.0 / 40.8;
+// - rows that are no whole units gain where they are read next and lose where other memory is, one entry per token: 6000 x 8208 B 45.9 / 43.8, 47.1 / 47.7, 48.2 / 50.3;
+//   18000 x 8208 B 111 / 108, 112 / 109, 121 / 125; 14000 x 14352 B 150 / 145, 150 / 145, 153 / 160; 15616 x 7024 B 78.4 / 76.8, 80.0 / 78.3, 84.8 / 81.6: left plain;
 // - more entries come out even or lose: 9515 x 4 x 1 KiB 20.1 / 20.5, 4990 x 6 x 512 B 11.6 / 12.0, 2827 x 8 x 1344 B 15.5 / 15.7.
 constexpr size_t kThroughBytes = (size_t)50 << 20;
 inline bool walk_through(int k, const void *rows, size_t row, size_t source, size_t written)
 {
     if (k > 3 || source + written < kThroughBytes) return false;
-    return k == 1 || (row % 128 == 0 && whole_units(rows, row));
+    return whole_units(rows, row) && (k == 1 || row % 128 == 0);
 }
 
 // Stores of the fused plan + dispatch, whose workgroups write a token's k rows (or a column segment of them, `group` bytes) one after the other: written

@@ -74,7 +74,9 @@ def test_rows_written_through_start_at_whole_units(route):
         for shift in (16, 32, 48, 80):   # stores of a wave would cover parts of units
             assert route(*args, at=0x10000000 + shift) == TOKENS | PLAIN
         assert route(12288, k, 64, 8, 4096 + 64) == TOKENS | PLAIN   # not rows of whole lines
-    assert route(24576, 1, 64, 8, 4096, at=0x10000010) == TOKENS | THROUGH   # one entry per token: either way
+    one = (24576, 1, 64, 8, 4096 + 64)
+    assert route(*one) == route(*one, at=0x10000040) == TOKENS | THROUGH
+    assert route(*one, at=0x10000010) == route(24576, 1, 64, 8, 4096 + 16) == TOKENS | PLAIN
 
 
 def test_both_tensors_in_two_launches_from_four_devices_on(route):

@@ -57,12 +57,12 @@ def test_token_walk(N, k, row_bytes):
     check(L, planes)
 
 
-# two and three entries: only from a whole 64-byte unit on; one entry from anywhere
+# only rows of whole 64-byte units, for two and three entries of whole lines
 @pytest.mark.parametrize("N,k,row_bytes,shift,through", [(12288, 2, 4096, 16, False), (12288, 2, 4096, 64, True), (9000, 3, 4224, 48, False), (9000, 3, 4224, 0, True),
-                                                         (24577, 1, 2048, 16, True),
+                                                         (24577, 1, 2048, 16, False),
                                                          (12800, 1, 2048, 0, True), (12799, 1, 2048, 0, False), (8534, 2, 2048, 0, True), (8533, 2, 2048, 0, False),
                                                          (3200, 3, 4096, 0, True), (3199, 3, 4096, 0, False), (1200, 2, 17408, 0, True), (1200, 3, 16384 + 128, 0, True),
-                                                         (2100, 1, 20480 + 48, 0, True), (26000, 1, 1040, 0, True)])
+                                                         (2100, 1, 20480 + 48, 0, False), (26000, 1, 1088, 0, True)])
 def test_token_walk_from_any_place(N, k, row_bytes, shift, through):
     f, L, A, planes = setup(N, k, 64, 8, row_bytes, 0, shift)
     f.fusco_plan(L, A)
