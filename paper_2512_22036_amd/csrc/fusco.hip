@@ -342,8 +342,9 @@ static bool tiled_shape(const fusco_layout *L, int Ct, int &threads, int &cpt, i
 // Source tensors of more than kSourceChunkBytes stay in the memory-side cache long enough to be taken in one piece, with the pull and
 // the cap on workgroups, as far as kSourceWholeBytes when nothing but pairs is written past that cache: cutting them reads every source
 // row once more and leaves a last chunk of few tiles.  Steps over changing buffers, in chunks of 128 MiB / in one piece, us: 17000 tokens x 5 x 9 KiB (149
-// MiB) 374 / 333, 20000 x 8 x 8 KiB (156) 545 / 514, 20000 x 6 x 8 KiB 440 / 410, 14000 x 8 x 12 KiB (164) 551 / 529, 20000 x 10 x 10 KiB (195) 829 / 795, 26000 x 7 x 8 KiB
-// (203) 613 / 598, 26000 x 8 x 8208 B 747 / 723; 30000 x 8 x 8 KiB (234) 766 / 765, 24000 x 8 x 14 KiB (328) 1058 / 1090, 32768 x 8 x 14 KiB (448) 1425 / 1501.
+// MiB) 352 / 332, 20000 x 8 x 8 KiB (156) 533 / 510, 20000 x 6 x 8 KiB 438 / 408, 14000 x 8 x 12 KiB (164) 544 / 515, 22000 x 8 x 9 KiB (193) 631 / 614, 20000 x 10 x
+// 10 KiB (195) 815 / 783, 26000 x 7 x 8 KiB (203) 614 / 597, 26000 x 8 x 8208 B 744 / 714, 28600 x 8 x 8 KiB (223) 726 / 725; 30000 x 8 x 8 KiB (234) 766 / 764, 24000 x 8
+// x 14 KiB (328) 1059 / 1092, 32768 x 8 x 14 KiB (448) 1428 / 1520.
 constexpr size_t kSourceWholeBytes = (size_t)224 << 20;
 static bool source_in_chunks(const fusco_layout *L, size_t row, bool wire)
 {
