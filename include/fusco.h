@@ -193,7 +193,8 @@ int fusco_dispatch(const fusco_layout *L, const void *d_x, size_t row_bytes, con
  * tensor of more than 128 MiB comes with k >= 8, or with k >= 5 and rows that need no column segments.  Calls that
  * write the receive tensors as well have it on top of that with k >= 8, at most 8 devices and rows of at least 8 KiB,
  * or with at most 2 devices and rows that need no column segments (of at least 4 KiB for k < 8); with at least 4 devices and
- * 72 to 128 MiB of source rows in whole 64-byte units (112 to 128 MiB for rows of 8 KiB, of 12 KiB and, with up to 5 devices, between 10 and 12 KiB) the receive
+ * 72 to 128 MiB of source rows in whole 64-byte units (112 to 128 MiB for rows that fill the lanes of their workgroups, as those of 8 and 12 KiB do and, with up to
+ * 5 devices, those of 10 to 12 and 13.4 to 15 KiB) the receive
  * tensors are then written by a token walk of their own.  All ways write
  * the same bytes.
  */

@@ -385,28 +385,29 @@ static bool both_in_transfer_order(const fusco_layout *L, size_t row, int segs)
 
 // Both tensors in two calls, the pairs tile by tile and the receive tensors by the token walk: source tensors of 72 MiB and more that are taken in one
 // piece, rows in whole 64-byte units.  They do not stay in the memory-side cache next to what is written for both, and the walk that reads them once
-// more, writing a third of the bytes, is the faster one.  In one launch / two, us, 4 to 8 devices: 9024 tokens x 8 x 8704 B 226 / 202, 
+// more, writing a third of the bytes, is the faster one.  In one launch / two, us, 4 to 8 devices: 9024 tokens x 8 x 8704 B 226 / 202,
 // 8192 x 8 x 14 KiB 305 / 293 (every token on 4 devices 294 / 267), 6849 x 8 x 17664 B 405 / 338, 11597 x 16 x 11 KiB 568 / 498, with a combine behind it
 // 8454 x 8 x 10432 B 395 / 381, 5579 x 10 x 20 KiB 544 / 514; even 6052 x 16 x 14016 B 332 / 338.  Less source 4096 x 8 x 14 KiB 135 / 137, 8192 x 8 x 8 KiB 148 / 157,
 // 6000 x 10 x 10 KiB 160 / 164; more 9796 x 10 x 13760 B 327 / 365, 20012 x 8 x 8704 B 466 / 450, 14701 x 10 x 13376 B 592 / 636; other rows 8092 x 8 x 14880 B 350 /
 // 393, 9780 x 10 x 10016 B 278 / 309; two devices 8659 x 8 x 12800 B 220 / 248; three, whose send rows of up to 85 MiB of source would fit the memory-side
 // cache and be written plain, 9216 x 8 x 8 KiB with the plan 148 / 185 (161 past the cache), 9300 x 8 x 14 KiB 287 / 297.  With four (and 8 or more
 // entries) there is room for at least 288 MiB of send rows, which the walk writes past that cache as the tiles do.
-// In one launch every (token, device) costs a workgroup, with a row or without, and costs the more the more of its lanes are idle.  Rows of up to 12 KiB that fill
-// their workgroups, to 5/6 with up to 5 devices, whole with more, are in two launches only from kSeparateFullBytes on.  Plan and both tensors, one launch / two, 8
+// In one launch every (token, device) costs a workgroup, with a row or without, and costs the more the more of its lanes are idle.  Rows without column segments
+// that fill their workgroups, to 5/6 with up to 5 devices, whole with more, are in two launches only from kSeparateFullBytes on.  Plan and both tensors, one launch / two, 8
 // entries, on 4, 5 and 8 devices: 8 KiB (128 threads, full) 76 MiB of source 164 / 177, 172 / 184, 200 / 208, 104 MiB 225 / 239, 240 / 253, 274 / 280, 127 MiB
 // 296 / 287, 311 / 302, 342 / 334; 10 KiB (192 threads, 5/6) 76 MiB 168 / 178, 176 / 184, 206 / 205, 104 MiB 236 / 245, 253 / 258, 295 / 286, 127 MiB 309 / 299, 318 /
 // 315, 378 / 346; 12 KiB 76 MiB 184 / 188, 192 / 194, 220 / 215, 127 MiB 306 / 300, 326 / 317, 358 / 347 (dispatch alone of 94 MiB on 8 devices 196 / 184 in another
-// series); two planes 76 MiB on 4 and 8 devices 8128 + 64 B 169 / 180, 213 / 216, 8192 + 256 B 192 / 177, 250 / 212.  One plane of 8256 B (192 threads, 2/3) 178 /
-// 179, 190 / 188, 226 / 210, of 9216 B 186 / 185, 197 / 191, 237 / 214; longer rows, filled, of 16 KiB 197 / 195, 207 / 203, 236 / 224.
+// series); 14 KiB (256 threads, 7/8) 76 MiB 171 / 177, 180 / 185, 211 / 205, 104 MiB 224 / 233, 238 / 245, 277 / 271, 127 MiB 301 / 296, 317 / 313, 364 / 343; 14912 B 104
+// MiB 231 / 239, 246 / 253, 286 / 282; two planes 76 MiB on 4 and 8 devices 8128 + 64 B 169 / 180, 213 / 216, 8192 + 256 B 192 / 177, 250 / 212.  One plane of 8256 B (192 threads, 2/3) 178 /
+// 179, 190 / 188, 226 / 210, of 9216 B 186 / 185, 197 / 191, 237 / 214, of 12800 B
+// (256 threads, 0.78) 176 / 179, 186 / 185, 221 / 208; in column segments, filled, 16 KiB 197 / 195, 207 / 203, 236 / 224.
 constexpr size_t kSeparateWireBytes = (size_t)72 << 20, kSeparateFullBytes = (size_t)112 << 20;
-constexpr int kSeparateFullChunks = 768;
 static bool wire_separately(const fusco_layout *L, size_t row, bool whole)
 {
     int threads, cpt, segs, per;
     const int Ct = (int)(row / 16);
     if (!whole || L->D < 4 || !tiled_shape(L, Ct, threads, cpt, segs, per)) return false;
-    const bool full = Ct <= kSeparateFullChunks && 6 * Ct >= (L->D <= 5 ? 5 : 6) * threads * cpt;
+    const bool full = segs == 1 && 6 * Ct >= (L->D <= 5 ? 5 : 6) * threads * cpt;
     const size_t source = (size_t)L->N * row;
     return source >= (full ? kSeparateFullBytes : kSeparateWireBytes) && source <= g_source_chunk_bytes.load(std::memory_order_relaxed);
 }

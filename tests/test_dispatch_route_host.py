@@ -97,14 +97,14 @@ def test_both_tensors_in_two_launches_from_four_devices_on(route):
 
 def test_both_tensors_of_rows_that_fill_their_workgroups_in_two_launches_from_112_mib_on(route):
     flags = EXPERT | WIRE
-    for row, devices in ((8192, (4, 5, 6, 8)), (10240, (4, 5)), (11264, (4, 5)), (12288, (4, 5, 6, 8))):
+    for row, devices in ((8192, (4, 5, 6, 8)), (10240, (4, 5)), (11264, (4, 5)), (12288, (4, 5, 6, 8)), (13696, (4, 5)), (14336, (4, 5)), (15360, (4, 5))):
         first = -(-(112 * MIB) // row)
         for D in devices:
             E = D * 16
             assert route(first - 1, 8, E, D, row, 0, flags) == route(73 * MIB // row, 8, E, D, row, 0, flags) == BOTH
             assert route(first, 8, E, D, row, 0, flags) == route(128 * MIB // row, 8, E, D, row, 0, flags) == SEPARATE | NONTEMPORAL
             assert route(first - 1, 8, E, D, row - 64, 64, flags) == BOTH            # both planes together
-    for row, devices in ((8256, (4, 8)), (9216, (4, 8)), (10176, (4, 8)), (10240, (6, 8)), (12224, (6, 8)), (12352, (4, 8)), (14336, (4, 8)), (16384, (4, 8))):
+    for row, devices in ((8256, (4, 8)), (9216, (4, 8)), (10176, (4, 8)), (10240, (6, 8)), (12224, (6, 8)), (12352, (4, 8)), (13632, (4, 8)), (13696, (6, 8)), (14336, (6, 8)), (15424, (4, 8)), (16384, (4, 8))):
         for D in devices:
             assert route(73 * MIB // row, 8, D * 16, D, row, 0, flags) == SEPARATE | NONTEMPORAL
 
